@@ -101,10 +101,11 @@ l2kv_status l2kv_norms(const void* K, l2kv_dtype dt, int64_t n_heads, int64_t T,
  *   kept_count out: [n_heads] int32, every entry = k; may be NULL
  *   workspace     : l2kv_select_workspace_bytes(n_heads, T) bytes, 16-aligned;
  *                   contents need not be initialised and are undefined after.
- *                   This version keeps all selection state in registers and
- *                   LDS and never touches the buffer; the size query returns
- *                   a small constant (256).  The argument is part of the
- *                   signature for versions that select across workgroups.
+ *                   For a few long heads several workgroups share a head
+ *                   through it (256 bytes otherwise); calls that use it must
+ *                   then not overlap in time.  Any size from 256 bytes on is
+ *                   accepted: below the queried size every head is selected
+ *                   by one workgroup, which does not touch the buffer.
  * Errors: NULL, SHAPE, RATIO, WORKSPACE, ALIGN, LAUNCH.
  */
 l2kv_status l2kv_select(const float* norms, int64_t n_heads, int64_t T,

@@ -38,6 +38,9 @@ inline bool dim_ok(int32_t D, l2kv_dtype dt) { return D == 64 || D == 128 || (D 
 inline int32_t max_group(int32_t D) { return D == 256 ? 4 : 8; }
 constexpr int64_t kMaxTokens = 0x7fffffffLL;          // token indices are int32
 constexpr int64_t kMaxHeads = 0x7fffffffLL;
+// smallest selection workspace the calls accept; the size query returns more where several
+// workgroups share a head, and a caller that passes less gets one workgroup per head
+constexpr size_t kSelectMinWorkspace = 256;
 
 // Shared checks of a strided [n_heads][T][D] tensor description.
 l2kv_status check_cache(l2kv_dtype dt, int64_t n_heads, int64_t T, int32_t D, int64_t head_stride) {
@@ -76,12 +79,8 @@ l2kv_status l2kv_norms(const void* K, l2kv_dtype dt, int64_t n_heads, int64_t T,
 }
 
 size_t l2kv_select_workspace_bytes(int64_t n_heads, int64_t T) {
-    // The kernels keep all selection state in registers and LDS and never touch
-    // the workspace; the header says so.  A small fixed size keeps callers'
-    // allocation code valid for a version that does need scratch.
-    (void)n_heads;
-    (void)T;
-    return 256;
+    if (n_heads <= 0 || n_heads > kMaxHeads || T <= 0 || T > kMaxTokens) return kSelectMinWorkspace;
+    return select_workspace_bytes(n_heads, T);
 }
 
 l2kv_status l2kv_select_k(const float* norms, int64_t n_heads, int64_t T, int64_t k, l2kv_mode mode,
@@ -91,11 +90,11 @@ l2kv_status l2kv_select_k(const float* norms, int64_t n_heads, int64_t T, int64_
     if (n_heads <= 0 || n_heads > kMaxHeads || T <= 0 || T > kMaxTokens) return L2KV_ERR_SHAPE;
     if (k <= 0 || k > T) return L2KV_ERR_SHAPE;
     if (mode != L2KV_KEEP_LOWEST && mode != L2KV_KEEP_HIGHEST) return L2KV_ERR_SHAPE;
-    if (workspace == nullptr || workspace_bytes < l2kv_select_workspace_bytes(n_heads, T))
+    if (workspace == nullptr || workspace_bytes < kSelectMinWorkspace)
         return L2KV_ERR_WORKSPACE;
     if (!aligned(norms, 4) || !aligned(kept_idx, 4) || !aligned(kept_count, 4) || !aligned(workspace, 16))
         return L2KV_ERR_ALIGN;
-    return select_dispatch(norms, n_heads, T, k, mode, kept_idx, kept_count, workspace,
+    return select_dispatch(norms, n_heads, T, k, mode, kept_idx, kept_count, workspace, workspace_bytes,
                            static_cast<hipStream_t>(stream));
 }
 
@@ -131,7 +130,7 @@ l2kv_status l2kv_compress(const void* K, const void* V, l2kv_dtype dt, int64_t n
     if (l2kv_status st = check_cache(dt, n_heads, T, D, head_stride); st != L2KV_OK) return st;
     if (!(keep_ratio > 0.0) || !(keep_ratio <= 1.0)) return L2KV_ERR_RATIO;
     if (slab_heads < 0) return L2KV_ERR_SHAPE;
-    if (workspace == nullptr || workspace_bytes < l2kv_select_workspace_bytes(n_heads, T)) return L2KV_ERR_WORKSPACE;
+    if (workspace == nullptr || workspace_bytes < kSelectMinWorkspace) return L2KV_ERR_WORKSPACE;
     if (!aligned(K, 16) || !aligned(V, 16) || !aligned(Kc, 16) || !aligned(Vc, 16) || !aligned(norms, 4) ||
         !aligned(kept_idx, 4) || !aligned(workspace, 16))
         return L2KV_ERR_ALIGN;
@@ -148,7 +147,7 @@ l2kv_status l2kv_compress(const void* K, const void* V, l2kv_dtype dt, int64_t n
         int32_t* is = kept_idx + h0 * k;
         const size_t dense = static_cast<size_t>(h0) * static_cast<size_t>(k) * static_cast<size_t>(D) * es;
         l2kv_status st = norms_dispatch(Ks, dt, nh, T, D, head_stride, ns, keep_in_cache, s);
-        if (st == L2KV_OK) st = select_dispatch(ns, nh, T, k, L2KV_KEEP_LOWEST, is, nullptr, workspace, s);
+        if (st == L2KV_OK) st = select_dispatch(ns, nh, T, k, L2KV_KEEP_LOWEST, is, nullptr, workspace, workspace_bytes, s);
         if (st == L2KV_OK)
             st = compact_dispatch(Ks, Vs, dt, is, nh, T, k, D, head_stride, static_cast<char*>(Kc) + dense,
                                   static_cast<char*>(Vc) + dense, s);

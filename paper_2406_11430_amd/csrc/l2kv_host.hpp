@@ -22,7 +22,8 @@ l2kv_status norms_dispatch(const void* K, l2kv_dtype dt, int64_t n_heads, int64_
 
 l2kv_status select_dispatch(const float* norms, int64_t n_heads, int64_t T, int64_t k,
                             l2kv_mode mode, int32_t* kept_idx, int32_t* kept_count,
-                            void* workspace, hipStream_t stream);
+                            void* workspace, size_t workspace_bytes, hipStream_t stream);
+size_t select_workspace_bytes(int64_t n_heads, int64_t T);
 
 l2kv_status random_keys_dispatch(int64_t n_heads, int64_t T, uint32_t seed, float* keys, hipStream_t stream);
 

@@ -4,23 +4,23 @@
 // the lowest-norm keys; Eq. 5: exactly m pairs dropped per layer and head)
 // with ties resolved towards the lower token index.
 //
-// One workgroup of 1024 lanes per head (512 for the packed variant below).
-// The keys (norm bits, complemented for the keep-highest control) sit in
-// registers -- 32 per lane covers 32k tokens -- so nothing is re-read from
-// memory.  The k-th smallest key tau is found
-// exactly by a 32-step binary search on its bits: step b counts the keys below
-// (prefix | 1<<b) with wave ballots + popcounts (scalar unit), one LDS atomic
-// per wave and one barrier.  No histogram, no data-dependent contention.
-// Heads of up to 131072 tokens use the same search on packed halves: the upper
-// 16 bits of all keys fit the registers two to a word (16 steps), then the
-// lower 16 bits of the keys that tie on the upper half are packed the same way
-// (16 more steps); the keys are read three more times from L2 (repack, count,
-// emit) instead of 32.  Longer heads fall back to re-reading the keys in every
-// step.
-// The emit is ordered: every wave owns a contiguous token range, so a prefix
-// over the 16 wave totals plus a running ballot prefix gives each kept token
-// its output slot; keys equal to tau are admitted in token order until the
-// budget k is met.
+// The k-th smallest key tau (key = norm bits, complemented for the keep-highest
+// control) is found exactly, digit by digit from the top: 12, 10 and 10 bits.
+// Each step counts the keys that agree with tau so far in an LDS histogram of
+// their next digit and walks its prefix sums to the digit that holds the k-th
+// key.  (A binary search over the 32 bits, one barrier and one compare per key
+// and bit, was what this replaces: 40 us for 256 heads of 32k tokens against 18 us,
+// 306 us for 8 heads of 131k against 18 us.)  The emit is ordered: every wave owns a contiguous token
+// range, so a prefix over the wave totals plus a running ballot prefix gives
+// each kept token its output slot; keys equal to tau are admitted in token order
+// until the budget k is met.
+//
+// Two launch shapes:
+//  - one workgroup of 1024 lanes per head, its keys in registers (up to 32 per
+//    lane) or, for longer heads, re-read from the L2 in every step;
+//  - few heads, or long ones: each head is cut into chunks and three kernels
+//    with one workgroup per chunk share the work through the caller's workspace
+//    (select_plan below has the rule).
 #include "l2kv_device.hpp"
 #include "l2kv_host.hpp"
 
@@ -29,19 +29,162 @@ namespace l2kv {
 constexpr int kSelThreads = 1024;
 constexpr int kSelWaves = kSelThreads / kWaveSize;   // 16
 constexpr int kSelMaxRegKeys = 32;                   // keys per lane held in registers
+constexpr int kSelBatch = 8;                         // keys per lane fetched together when they are re-read
+
+// Digits of the search, from the top.
+constexpr int kTopBits = 12, kMidBits = 10, kLowBits = 10;
+static_assert(kTopBits + kMidBits + kLowBits == 32, "digits cover the key");
+constexpr int kTopBins = 1 << kTopBits, kMidBins = 1 << kMidBits, kLowBins = 1 << kLowBits;
 
 __device__ __forceinline__ uint32_t lanes_below(uint64_t mask) {
     return __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
 }
 
-// The packed variant runs 512 lanes with twice the register budget per lane:
-// 128 words of two 16-bit halves = 256 keys per lane, 131072 per workgroup.
-constexpr int kSelPackedThreads = 512;
-constexpr int kSelPackedRegs = 128;
+// Inclusive prefix sum over the 64 lanes of a wave.
+__device__ __forceinline__ uint32_t wave_inclusive_sum(uint32_t v) {
+    const int lane = threadIdx.x % kWaveSize;
+#pragma unroll
+    for (int off = 1; off < kWaveSize; off <<= 1) {
+        const uint32_t up = __shfl_up(v, off);
+        if (lane >= off) v += up;
+    }
+    return v;
+}
 
+// LDS histogram of kCopies interleaved counters per digit; lane l counts in copy l % kCopies.  LDS
+// atomics on one address are served one lane at a time, so the copies bound what tied or padded
+// rows (all keys in one digit) cost: 32k equal keys per head take 35 us with 4 copies, 94 us with
+// one, and ordinary norms the same either way.
+constexpr int kCopies = 4;
+__device__ __forceinline__ void count_digit(uint32_t* hist, uint32_t digit) {
+    atomicAdd(&hist[digit * kCopies + threadIdx.x % kCopies], 1u);
+}
+__device__ __forceinline__ uint32_t digit_count(const uint32_t* hist, uint32_t digit) {
+    const uint4 c = reinterpret_cast<const uint4*>(hist)[digit];
+    static_assert(kCopies == 4, "one 16-byte read per digit");
+    return c.x + c.y + c.z + c.w;
+}
+// Clears `words` counters, a multiple of 4 * 1024.
+__device__ __forceinline__ void clear_counts(uint32_t* hist, int words) {
+    for (int i = threadIdx.x; i < words / 4; i += kSelThreads) reinterpret_cast<uint4*>(hist)[i] = make_uint4(0, 0, 0, 0);
+}
+
+// Where the k-th key lies in a histogram: its digit and the number of keys in lower digits.
+struct Found { uint32_t digit, below; };
+
+struct FindShared {
+    uint32_t wave_total[kSelWaves];
+    Found found;
+};
+
+// Called by all 1024 lanes, hist complete (the caller's barrier); ends with a barrier.  `want`
+// is 1-based and at most the sum of the histogram.
+template <int BINS>
+__device__ __forceinline__ Found find_digit(const uint32_t* hist, uint32_t want, FindShared& sh) {
+    constexpr int kPer = BINS / kSelThreads;
+    static_assert(kPer >= 1 && BINS % kSelThreads == 0, "whole bins per lane");
+    const int lane = threadIdx.x % kWaveSize;
+    const int wave = threadIdx.x / kWaveSize;
+    uint32_t c[kPer], sum = 0;
+#pragma unroll
+    for (int i = 0; i < kPer; ++i) {
+        c[i] = digit_count(hist, threadIdx.x * kPer + i);
+        sum += c[i];
+    }
+    const uint32_t incl = wave_inclusive_sum(sum);
+    if (lane == kWaveSize - 1) sh.wave_total[wave] = incl;
+    __syncthreads();
+    uint32_t before = incl - sum;
+#pragma unroll
+    for (int w = 0; w < kSelWaves; ++w) before += w < wave ? sh.wave_total[w] : 0u;
+    if (before < want && want <= before + sum) {          // exactly one lane
+#pragma unroll
+        for (int i = 0; i < kPer; ++i) {
+            if (before < want && want <= before + c[i]) {
+                sh.found.digit = (uint32_t)(threadIdx.x * kPer + i);
+                sh.found.below = before;
+            }
+            before += c[i];
+        }
+    }
+    __syncthreads();
+    return sh.found;
+}
+
+// Ordered emit shared by both launch shapes.  Every wave of the workgroup owns `iters` * 64
+// consecutive positions of [t0, ...); fetch(e) is this lane's key of iteration e (positions past
+// the end read as the largest key and come after every real one).  lt_before / eq_before: keys
+// below / equal to tau ahead of this workgroup's range.
+struct EmitShared { uint32_t lt[kSelWaves], eq[kSelWaves]; };
+
+template <int kUnroll, typename Fetch>
+__device__ __forceinline__ void emit_ordered(Fetch fetch, int64_t iters, uint32_t t0, uint32_t tau, uint32_t need_eq,
+                                             uint32_t lt_before, uint32_t eq_before, int32_t* __restrict__ out,
+                                             EmitShared& sh) {
+    const int lane = threadIdx.x % kWaveSize;
+    const int wave = threadIdx.x / kWaveSize;
+    uint32_t lt_w = 0, eq_w = 0;
+    for (int64_t e0 = 0; e0 < iters; e0 += kUnroll) {
+        uint32_t key[kUnroll];
+#pragma unroll
+        for (int u = 0; u < kUnroll; ++u) key[u] = fetch(e0 + u);
+#pragma unroll
+        for (int u = 0; u < kUnroll; ++u) {
+            lt_w += __popcll(__ballot(key[u] < tau));
+            eq_w += __popcll(__ballot(key[u] == tau));
+        }
+    }
+    if (lane == 0) {
+        sh.lt[wave] = lt_w;
+        sh.eq[wave] = eq_w;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int w = 0; w < kSelWaves; ++w) {
+        lt_before += w < wave ? sh.lt[w] : 0u;
+        eq_before += w < wave ? sh.eq[w] : 0u;
+    }
+    uint32_t out_base = lt_before + (eq_before < need_eq ? eq_before : need_eq);
+    auto for_iters = [&](auto&& body) {
+        for (int64_t e0 = 0; e0 < iters; e0 += kUnroll) {
+            uint32_t key[kUnroll];
+#pragma unroll
+            for (int u = 0; u < kUnroll; ++u) key[u] = fetch(e0 + u);
+#pragma unroll
+            for (int u = 0; u < kUnroll; ++u) body(key[u], (int32_t)(t0 + (uint32_t)(e0 + u) * kWaveSize + lane));
+        }
+    };
+    const bool all_eq = eq_w != 0 && eq_before + eq_w <= need_eq;         // every tie of this wave's range is kept
+    if (all_eq || eq_w == 0 || eq_before >= need_eq) {
+        // ... or none is: one comparison per key.  (Padding equals tau only if tau is the largest
+        // key; a range with padding then never has all its ties kept, need_eq counts real keys.)
+        if (lt_w == 0 && !all_eq) return;
+        uint32_t limit = all_eq ? tau : tau - 1;         // tau > 0 where some key is below it
+        asm volatile("" : "+v"(limit));                  // compare afresh: the masks of the tally would not stay in registers
+        for_iters([&](uint32_t key, int32_t t) {
+            const bool keep = key <= limit;
+            const uint64_t keep_mask = __ballot(keep);
+            if (keep) out[out_base + lanes_below(keep_mask)] = t;
+            out_base += __popcll(keep_mask);
+        });
+    } else {
+        // the wave in whose range the last kept tie lies
+        uint32_t eq_base = eq_before;
+        for_iters([&](uint32_t key, int32_t t) {
+            const bool is_eq = key == tau;
+            const uint64_t eq_mask = __ballot(is_eq);
+            const bool keep = key < tau || (is_eq && (eq_base + lanes_below(eq_mask)) < need_eq);
+            const uint64_t keep_mask = __ballot(keep);
+            if (keep) out[out_base + lanes_below(keep_mask)] = t;
+            out_base += __popcll(keep_mask);
+            eq_base += __popcll(eq_mask);
+        });
+    }
+}
+
+// ---- one workgroup per head ---------------------------------------------------------------
 // E > 0 : keys of the head fit E per lane and are cached in registers.
 // E == 0: streaming variant, keys are re-read from memory (L2) in every pass.
-// E == -1: packed variant, 256 keys per lane as 16-bit halves (T <= 131072).
 // Ragged batches: [n_planes][total_in] norms, sequence s at in_off[s]..in_off[s+1];
 // its kept positions (relative to the sequence start) go to
 // [n_planes][total_out] at out_off[s]..out_off[s+1].  in_off == NULL: uniform.
@@ -52,16 +195,15 @@ struct RaggedSelect {
 };
 
 template <int E>
-__global__ __launch_bounds__(E == -1 ? kSelPackedThreads : kSelThreads)
+__global__ __launch_bounds__(kSelThreads)
 void select_kernel(const uint32_t* __restrict__ norm_bits, int64_t T, uint32_t k, uint32_t flip,
                    int32_t* __restrict__ kept_idx, int32_t* __restrict__ kept_count,
                    RaggedSelect rag) {
     constexpr bool kInRegs = E > 0;
-    constexpr bool kPacked = E == -1;
-    constexpr int kWaves = (kPacked ? kSelPackedThreads : kSelThreads) / kWaveSize;
-    __shared__ uint32_t s_count[32];
-    __shared__ uint32_t s_lt[kSelWaves];
-    __shared__ uint32_t s_eq[kSelWaves];
+    // the counters of the lowest digit reuse those of the top one: 80 KB, two workgroups per compute unit
+    __shared__ __attribute__((aligned(16))) uint32_t s_hist[(kTopBins + kMidBins) * kCopies];
+    __shared__ FindShared s_find;
+    __shared__ EmitShared s_emit;
 
     const int64_t head = blockIdx.x;
     const int lane = threadIdx.x % kWaveSize;
@@ -75,6 +217,8 @@ void select_kernel(const uint32_t* __restrict__ norm_bits, int64_t T, uint32_t k
         const Range in = clamped_range(rag.in_off, seq, rag.total_in);
         const Range outr = clamped_range(rag.out_off, seq, rag.total_out);
         T = in.count;
+        // the register variants see the first 1024 * E tokens (the caller's bound on the lengths)
+        if (kInRegs && T > (int64_t)E * kSelThreads) T = (int64_t)E * kSelThreads;
         const int64_t kk = outr.count;
         if (T <= 0 || kk <= 0) return;                       // whole workgroup: nothing to select
         k = (uint32_t)(kk < T ? kk : T);                     // never more than there are
@@ -85,175 +229,343 @@ void select_kernel(const uint32_t* __restrict__ norm_bits, int64_t T, uint32_t k
     // Wave w owns tokens [w*span, (w+1)*span), span a multiple of 64; iteration
     // e of lane l looks at token w*span + e*64 + l.
     const int64_t iters = kInRegs ? E
-                          : kPacked ? 2 * kSelPackedRegs
-                                    : (((T + kWaves - 1) / kWaves + kWaveSize - 1) / kWaveSize);
-    const int64_t span = iters * kWaveSize;
-    // Token positions fit 32 bits: T < 2^31 and the padded range ends below T + 2^17.
-    const uint32_t t0 = (uint32_t)(wave * span + lane);
+                                  : ((T + (int64_t)kSelThreads * kSelBatch - 1) / ((int64_t)kSelThreads * kSelBatch) * kSelBatch);
+    const uint32_t t0 = (uint32_t)(wave * iters * kWaveSize);     // T < 2^31 and the padded range ends below T + 2^14
     const uint32_t T32 = (uint32_t)T;
 
     // Branch-free: positions past the end re-read the last key (in bounds) and
     // are replaced by the largest key, which is never "below" anything.  Such
     // padding sits after every real token, so in the ordered emit it is reached
     // only after all real keys equal to tau, when the budget is already met.
-    // `base` is this lane's first position, passed through launder() by every
-    // pass that re-reads the keys: otherwise the compiler keeps all addresses
-    // and bounds predicates of one pass alive for the next and spills them.
-    auto launder = [](uint32_t x) -> uint32_t {
-        asm volatile("" : "+v"(x));
-        return x;
-    };
-    auto fetch_at = [&](uint32_t base, int64_t e) -> uint32_t {
-        const uint32_t t = base + (uint32_t)e * kWaveSize;
+    auto fetch_mem = [&](int64_t e) -> uint32_t {
+        const uint32_t t = t0 + (uint32_t)e * kWaveSize + lane;
         const uint32_t v = src[t < T32 ? t : T32 - 1] ^ flip;
         return t < T32 ? v : 0xffffffffu;
     };
-    auto fetch = [&](int64_t e) -> uint32_t { return fetch_at(t0, e); };
-
     uint32_t regs[kInRegs ? E : 1];
     if constexpr (kInRegs) {
 #pragma unroll
-        for (int e = 0; e < E; ++e) regs[e] = fetch(e);
+        for (int e = 0; e < E; ++e) regs[e] = fetch_mem(e);
     }
-    if (threadIdx.x < 32) s_count[threadIdx.x] = 0;
+    clear_counts(s_hist, (kTopBins + kMidBins) * kCopies);
     __syncthreads();
 
-    // ---- k-th smallest key by binary search on its bits (MSB first) -------
-    uint32_t prefix = 0;     // tau so far
-    uint32_t less = 0;       // number of keys < prefix
-    if constexpr (kPacked) {
-        uint32_t pk[kSelPackedRegs];
-        // one 16-step search over the packed halves in pk; `want` keys are sought
-        auto search16 = [&](int count_slot, uint32_t want, uint32_t& found, uint32_t& below_found) {
-            uint32_t pre = 0, lo = 0;
-            for (int bit = 15; bit >= 0; --bit) {
-                const uint32_t cand = pre | (1u << bit);
-                // per-lane counters here (compare + add-with-carry): 128 wave ballots
-                // per step would need more scalar registers than there are
-                uint32_t mine = 0;
+    // every key once, in batches whose loads are issued together
+    auto for_keys = [&](auto&& body) {
+        if constexpr (kInRegs) {
 #pragma unroll
-                for (int r = 0; r < kSelPackedRegs; ++r) {
-                    mine += (pk[r] & 0xffffu) < cand ? 1u : 0u;
-                    mine += (pk[r] >> 16) < cand ? 1u : 0u;
-                }
-                uint32_t cnt = mine;
+            for (int e = 0; e < E; ++e) body(regs[e]);
+        } else {
+            for (int64_t e0 = 0; e0 < iters; e0 += kSelBatch) {
+                uint32_t key[kSelBatch];
 #pragma unroll
-                for (int off = kWaveSize / 2; off > 0; off >>= 1) cnt += __shfl_xor(cnt, off);
-                if (lane == 0 && cnt) atomicAdd(&s_count[count_slot + bit], cnt);
-                __syncthreads();
-                const uint32_t below = s_count[count_slot + bit];
-                if (below < want) {
-                    pre = cand;
-                    lo = below;
-                }
-            }
-            found = pre;
-            below_found = lo;
-        };
-        // upper halves of all keys (padding reads as 0xffff and is never "below")
-        // (batches of 4 words, fenced for the scheduler: issuing all 128 loads and
-        // their bounds predicates at once would not fit the register files)
-        const uint32_t base1 = launder(t0);
+                for (int u = 0; u < kSelBatch; ++u) key[u] = fetch_mem(e0 + u);
 #pragma unroll
-        for (int r0 = 0; r0 < kSelPackedRegs; r0 += 4) {
-#pragma unroll
-            for (int r = r0; r < r0 + 4; ++r)
-                pk[r] = (fetch_at(base1, 2 * r) >> 16) | (fetch_at(base1, 2 * r + 1) & 0xffff0000u);
-            __builtin_amdgcn_sched_barrier(0);
-        }
-        uint32_t tau_hi, less_hi;
-        search16(16, k, tau_hi, less_hi);
-        // lower halves of the keys that tie on the upper half; every other key
-        // is parked at 0xffff, which no candidate value exceeds
-        const uint32_t base2 = launder(t0);
-#pragma unroll
-        for (int r0 = 0; r0 < kSelPackedRegs; r0 += 4) {
-#pragma unroll
-            for (int r = r0; r < r0 + 4; ++r) {
-                const uint32_t a = fetch_at(base2, 2 * r), b = fetch_at(base2, 2 * r + 1);
-                const uint32_t la = (a >> 16) == tau_hi ? (a & 0xffffu) : 0xffffu;
-                const uint32_t lb = (b >> 16) == tau_hi ? (b & 0xffffu) : 0xffffu;
-                pk[r] = la | (lb << 16);
-            }
-            __builtin_amdgcn_sched_barrier(0);
-        }
-        uint32_t tau_lo, less_lo;
-        search16(0, k - less_hi, tau_lo, less_lo);
-        prefix = (tau_hi << 16) | tau_lo;
-        less = less_hi + less_lo;
-    } else {
-        for (int bit = 31; bit >= 0; --bit) {
-            const uint32_t cand = prefix | (1u << bit);
-            uint32_t cnt = 0;
-            if constexpr (kInRegs) {
-#pragma unroll
-                for (int e = 0; e < E; ++e) cnt += __popcll(__ballot(regs[e] < cand));
-            } else {
-                for (int64_t e = 0; e < iters; ++e) cnt += __popcll(__ballot(fetch(e) < cand));
-            }
-            if (lane == 0 && cnt) atomicAdd(&s_count[bit], cnt);
-            __syncthreads();
-            const uint32_t below = s_count[bit];
-            if (below < k) {     // the k-th smallest is >= cand
-                prefix = cand;
-                less = below;
+                for (int u = 0; u < kSelBatch; ++u) body(key[u]);
             }
         }
-    }
-    const uint32_t tau = prefix;
-    const uint32_t need_eq = k - less;   // >= 1 keys equal to tau are kept, lowest tokens first
-
-    // ---- per-wave totals, then ordered emit ---------------------------------
-    uint32_t lt_w = 0, eq_w = 0;
-    auto tally = [&](uint32_t key, int64_t) {
-        lt_w += __popcll(__ballot(key < tau));
-        eq_w += __popcll(__ballot(key == tau));
     };
-    if constexpr (kInRegs) {
-#pragma unroll
-        for (int e = 0; e < E; ++e) tally(regs[e], e);
-    } else {
-        for (int64_t e = 0; e < iters; ++e) tally(fetch(e), e);
-    }
-    if (lane == 0) {
-        s_lt[wave] = lt_w;
-        s_eq[wave] = eq_w;
-    }
+    uint32_t* const h_top = s_hist;
+    uint32_t* const h_mid = s_hist + kTopBins * kCopies;
+    uint32_t* const h_low = s_hist;
+    // (the padding is counted too: it comes after all real keys and k is at most their number)
+    for_keys([&](uint32_t key) { count_digit(h_top, key >> (32 - kTopBits)); });
     __syncthreads();
-    uint32_t lt_before = 0, eq_before = 0;
-    for (int w = 0; w < wave; ++w) {
-        lt_before += s_lt[w];
-        eq_before += s_eq[w];
-    }
-    uint32_t out_base = lt_before + (eq_before < need_eq ? eq_before : need_eq);
-    uint32_t eq_base = eq_before;
+    const Found top = find_digit<kTopBins>(h_top, k, s_find);
+    clear_counts(h_low, kLowBins * kCopies);         // in use again two barriers from here
+    for_keys([&](uint32_t key) {
+        if (key >> (32 - kTopBits) == top.digit) count_digit(h_mid, (key >> kLowBits) & (kMidBins - 1));
+    });
+    __syncthreads();
+    const Found mid = find_digit<kMidBins>(h_mid, k - top.below, s_find);
+    const uint32_t prefix = (top.digit << kMidBits) | mid.digit;
+    for_keys([&](uint32_t key) {
+        if (key >> kLowBits == prefix) count_digit(h_low, key & (kLowBins - 1));
+    });
+    __syncthreads();
+    const Found low = find_digit<kLowBins>(h_low, k - top.below - mid.below, s_find);
+    const uint32_t tau = (prefix << kLowBits) | low.digit;
+    const uint32_t need_eq = k - top.below - mid.below - low.below;   // >= 1 keys equal to tau are kept, lowest tokens first
 
-    auto emit = [&](uint32_t key, int64_t e) {
-        const uint32_t t = t0 + (uint32_t)e * kWaveSize;
-        const bool is_lt = key < tau;
-        const bool is_eq = key == tau;
-        const uint64_t eq_mask = __ballot(is_eq);
-        const bool keep = is_lt || (is_eq && (eq_base + lanes_below(eq_mask)) < need_eq);
-        const uint64_t keep_mask = __ballot(keep);
-        if (keep) out[out_base + lanes_below(keep_mask)] = (int32_t)t;
-        out_base += __popcll(keep_mask);
-        eq_base += __popcll(eq_mask);
-    };
-    if constexpr (kInRegs) {
-#pragma unroll
-        for (int e = 0; e < E; ++e) emit(regs[e], e);
-    } else {
-        for (int64_t e = 0; e < iters; ++e) emit(fetch(e), e);
-    }
+    if constexpr (kInRegs) emit_ordered<E>([&](int64_t e) { return regs[e]; }, E, t0, tau, need_eq, 0u, 0u, out, s_emit);
+    else emit_ordered<kSelBatch>(fetch_mem, iters, t0, tau, need_eq, 0u, 0u, out, s_emit);
     if (kept_count != nullptr && threadIdx.x == 0) kept_count[head] = (int32_t)k;
+}
+
+// ---- several workgroups per head -------------------------------------------------------------
+// chunk c of a head = tokens [c * chunk, (c+1) * chunk).  Three kernels, ordered by the stream:
+//   select_count_kernel   histogram of the top digit per chunk (64 coarse counts beside the 4096)
+//   select_gather_kernel  the digit of tau; keys of that digit go to the candidate list of the
+//                         head, in chunk order; per chunk the counts below it and in it
+//   select_emit_kernel    every workgroup finishes the search over the candidates by itself (a few
+//                         per cent of the keys; all of them in the worst case), counts what lies
+//                         ahead of its chunk and emits its kept tokens
+constexpr int kCoarse = 64;                          // coarse counts per chunk, of kTopBins / 64 digits each
+constexpr int kFinePerCoarse = kTopBins / kCoarse;   // 64
+constexpr int kChunkUnit = kSelThreads * 4;          // chunks are multiples of 4096 tokens
+constexpr int64_t kChunkMax = 8 * kChunkUnit;        // counts per chunk stay below 2^16
+
+struct SelectSplit {
+    uint16_t* fine;       // [heads][chunks][kTopBins]
+    uint32_t* coarse;     // [heads][chunks][kCoarse]
+    uint2* info;          // [heads][chunks]: keys below the digit of tau, keys in it
+    uint32_t* head_info;  // [heads][2]: digit of tau, keys below it in the head
+    uint32_t* cand;       // [heads][T]
+    int64_t chunk;        // tokens per chunk
+    int32_t chunks;       // per head
+};
+
+struct SelectPlan {
+    int64_t chunk = 0;    // 0: one workgroup per head
+    int32_t chunks = 0;
+    size_t bytes = 256;
+};
+
+static size_t round256(size_t n) { return (n + 255) / 256 * 256; }
+
+// Heads that fit the registers of one workgroup (32k tokens) are never split: 8 heads of 32k take
+// 15.5 us either way, more heads are faster whole.  Longer ones are split while the heads alone
+// leave most of the chip idle.  Measured, one workgroup per head / split, us: 8 heads of 40k 22.9 /
+// 16.1, 64 of 40k 23.9 / 28.6; 8 of 131k 59.6 / 17.7, 64 of 131k 66.8 / 46.0, 128 of 131k 80 / 69
+// (and 112 / 199 for 64 heads of equal keys, where every key is a candidate of every workgroup,
+// hence no further than 64).
+static SelectPlan select_plan(int64_t n_heads, int64_t T) {
+    SelectPlan p;
+    constexpr int64_t kWorkgroups = 512;             // two per compute unit
+    if (T <= (int64_t)kSelThreads * kSelMaxRegKeys || T > (int64_t{1} << 22)) return p;
+    if (n_heads > 64 || n_heads > T / 2048) return p;
+    const int64_t want = (kWorkgroups + n_heads - 1) / n_heads;
+    int64_t chunk = (T + want - 1) / want;
+    chunk = (chunk + kChunkUnit - 1) / kChunkUnit * kChunkUnit;
+    if (chunk > kChunkMax) chunk = kChunkMax;
+    p.chunk = chunk;
+    p.chunks = (int32_t)((T + chunk - 1) / chunk);
+    const size_t n = (size_t)n_heads * (size_t)p.chunks;
+    p.bytes = round256(n * kTopBins * sizeof(uint16_t)) + round256(n * kCoarse * sizeof(uint32_t)) +
+              round256(n * sizeof(uint2)) + round256((size_t)n_heads * 2 * sizeof(uint32_t)) +
+              round256((size_t)n_heads * (size_t)T * sizeof(uint32_t));
+    return p;
+}
+
+__global__ __launch_bounds__(kSelThreads)
+void select_count_kernel(const uint32_t* __restrict__ norm_bits, int64_t T, uint32_t flip, SelectSplit sp) {
+    __shared__ __attribute__((aligned(16))) uint32_t s_hist[kTopBins * kCopies];
+    const int64_t head = blockIdx.y;
+    const int64_t slot = head * sp.chunks + blockIdx.x;
+    const uint32_t* src = norm_bits + head * T;
+    const int64_t first = blockIdx.x * sp.chunk;
+    const int64_t last = first + sp.chunk < T ? first + sp.chunk : T;
+    clear_counts(s_hist, kTopBins * kCopies);
+    __syncthreads();
+    for (int64_t base = first; base < last; base += kChunkUnit) {
+        uint32_t key[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int64_t t = base + u * kSelThreads + threadIdx.x;
+            key[u] = src[t < last ? t : last - 1] ^ flip;
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            if (base + u * kSelThreads + threadIdx.x < last) count_digit(s_hist, key[u] >> (32 - kTopBits));
+    }
+    __syncthreads();
+    // lane i: digits 4i .. 4i+3; 16 lanes make up one coarse count
+    uint4 c;
+    c.x = digit_count(s_hist, 4 * threadIdx.x);
+    c.y = digit_count(s_hist, 4 * threadIdx.x + 1);
+    c.z = digit_count(s_hist, 4 * threadIdx.x + 2);
+    c.w = digit_count(s_hist, 4 * threadIdx.x + 3);
+    reinterpret_cast<uint2*>(sp.fine + slot * kTopBins)[threadIdx.x] = make_uint2(c.x | (c.y << 16), c.z | (c.w << 16));
+    uint32_t sum = c.x + c.y + c.z + c.w;
+#pragma unroll
+    for (int off = kFinePerCoarse / 8; off > 0; off >>= 1) sum += __shfl_xor(sum, off);
+    if (threadIdx.x % (kFinePerCoarse / 4) == 0) sp.coarse[slot * kCoarse + threadIdx.x / (kFinePerCoarse / 4)] = sum;
+}
+
+// One wave: the lane whose bin holds the want-th key (bins = the lanes' counts in order).
+__device__ __forceinline__ Found find_lane(uint32_t count, uint32_t want) {
+    const uint32_t incl = wave_inclusive_sum(count);
+    const uint64_t past = __ballot(incl >= want);
+    const int at = (int)__builtin_ctzll(past);               // want <= total: some lane qualifies
+    return Found{(uint32_t)at, __shfl(incl - count, at)};
+}
+
+__global__ __launch_bounds__(kSelThreads)
+void select_gather_kernel(const uint32_t* __restrict__ norm_bits, int64_t T, uint32_t k, uint32_t flip, SelectSplit sp) {
+    __shared__ uint32_t s_sum[2][kSelWaves][kCoarse], s_part[kSelWaves][kFinePerCoarse];
+    __shared__ uint32_t s_lt, s_n;
+    const int64_t head = blockIdx.y;
+    const int64_t slot0 = head * sp.chunks;
+    const int64_t slot = slot0 + blockIdx.x;
+    const int lane = threadIdx.x % kWaveSize;
+    const int wave = threadIdx.x / kWaveSize;
+    // the digit of tau: coarse counts of all chunks, then the 64 digits of the coarse count that
+    // holds the k-th key; the waves share the chunks and every wave ends with the same result
+    uint32_t n = 0;
+#pragma unroll 4
+    for (int c = wave; c < sp.chunks; c += kSelWaves) n += sp.coarse[(slot0 + c) * kCoarse + lane];
+    s_sum[0][wave][lane] = n;
+    if (threadIdx.x == 0) {
+        s_lt = 0;
+        s_n = 0;
+    }
+    __syncthreads();
+    n = 0;
+#pragma unroll
+    for (int w = 0; w < kSelWaves; ++w) n += s_sum[0][w][lane];
+    const Found g = find_lane(n, k);
+    uint32_t m = 0, part = 0;
+#pragma unroll 4
+    for (int c = wave; c < sp.chunks; c += kSelWaves) {
+        const uint32_t v = sp.fine[(slot0 + c) * kTopBins + g.digit * kFinePerCoarse + lane];
+        m += v;
+        part += c < (int)blockIdx.x ? v : 0u;
+    }
+    s_sum[1][wave][lane] = m;
+    s_part[wave][lane] = part;
+    __syncthreads();
+    m = part = 0;
+#pragma unroll
+    for (int w = 0; w < kSelWaves; ++w) {
+        m += s_sum[1][w][lane];
+        part += s_part[w][lane];
+    }
+    const Found f = find_lane(m, k - g.below);
+    const uint32_t ahead = __shfl(part, (int)f.digit);
+    const uint32_t digit = g.digit * kFinePerCoarse + f.digit;
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        sp.head_info[2 * head] = digit;
+        sp.head_info[2 * head + 1] = g.below + f.below;
+    }
+    uint32_t* cand = sp.cand + head * T + ahead;           // the candidates of earlier chunks come first
+    const uint32_t* src = norm_bits + head * T;
+    const int64_t first = blockIdx.x * sp.chunk;
+    const int64_t last = first + sp.chunk < T ? first + sp.chunk : T;
+    uint32_t lt = 0;
+    for (int64_t base = first; base < last; base += kChunkUnit) {
+        uint32_t key[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int64_t t = base + u * kSelThreads + threadIdx.x;
+            key[u] = src[t < last ? t : last - 1] ^ flip;
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const bool real = base + u * kSelThreads + threadIdx.x < last;
+            const uint32_t d = key[u] >> (32 - kTopBits);
+            lt += __popcll(__ballot(real && d < digit));
+            const uint64_t in = __ballot(real && d == digit);
+            uint32_t at = 0;
+            if (in != 0 && lane == 0) at = atomicAdd(&s_n, (uint32_t)__popcll(in));
+            at = __builtin_amdgcn_readfirstlane(at);
+            // order inside the chunk's stretch of the list does not matter: only counts are taken from it
+            if (real && d == digit) cand[at + lanes_below(in)] = key[u];
+        }
+    }
+    if (lane == 0) atomicAdd(&s_lt, lt);
+    __syncthreads();
+    if (threadIdx.x == 0) sp.info[slot] = make_uint2(s_lt, s_n);
+}
+
+__global__ __launch_bounds__(kSelThreads)
+void select_emit_kernel(const uint32_t* __restrict__ norm_bits, int64_t T, uint32_t k, uint32_t flip,
+                        int32_t* __restrict__ kept_idx, int32_t* __restrict__ kept_count, SelectSplit sp) {
+    __shared__ __attribute__((aligned(16))) uint32_t s_hist[(kMidBins + kLowBins) * kCopies];
+    __shared__ FindShared s_find;
+    __shared__ EmitShared s_emit;
+    __shared__ uint32_t s_lt_ahead, s_cand_ahead, s_cands, s_cand_lt, s_cand_eq;
+    const int64_t head = blockIdx.y;
+    const int64_t slot0 = head * sp.chunks;
+    const int lane = threadIdx.x % kWaveSize;
+    const int wave = threadIdx.x / kWaveSize;
+    uint32_t* const h_mid = s_hist;
+    uint32_t* const h_low = s_hist + kMidBins * kCopies;
+    clear_counts(s_hist, (kMidBins + kLowBins) * kCopies);
+    if (threadIdx.x < kWaveSize) {
+        uint32_t lt = 0, ahead = 0, all = 0;
+        for (int c = lane; c < sp.chunks; c += kWaveSize) {
+            const uint2 v = sp.info[slot0 + c];
+            all += v.y;
+            lt += c < (int)blockIdx.x ? v.x : 0u;
+            ahead += c < (int)blockIdx.x ? v.y : 0u;
+        }
+#pragma unroll
+        for (int off = kWaveSize / 2; off > 0; off >>= 1) {
+            lt += __shfl_xor(lt, off);
+            ahead += __shfl_xor(ahead, off);
+            all += __shfl_xor(all, off);
+        }
+        if (lane == 0) {
+            s_lt_ahead = lt;
+            s_cand_ahead = ahead;
+            s_cands = all;
+            s_cand_lt = 0;
+            s_cand_eq = 0;
+        }
+    }
+    const uint32_t top_digit = sp.head_info[2 * head];
+    const uint32_t want = k - sp.head_info[2 * head + 1];
+    __syncthreads();
+    const uint32_t n = s_cands, ahead = s_cand_ahead;
+    const uint32_t* cand = sp.cand + head * T;
+    constexpr int kCandBatch = 4;
+    auto for_cands = [&](uint32_t end, auto&& body) {
+        for (uint32_t i0 = 0; i0 < end; i0 += kSelThreads * kCandBatch) {
+            uint32_t key[kCandBatch];
+#pragma unroll
+            for (int u = 0; u < kCandBatch; ++u) {
+                const uint32_t i = i0 + u * kSelThreads + threadIdx.x;
+                key[u] = cand[i < end ? i : end - 1];
+            }
+#pragma unroll
+            for (int u = 0; u < kCandBatch; ++u) body(key[u], i0 + u * kSelThreads + threadIdx.x < end);
+        }
+    };
+    for_cands(n, [&](uint32_t key, bool real) {
+        if (real) count_digit(h_mid, (key >> kLowBits) & (kMidBins - 1));
+    });
+    __syncthreads();
+    const Found mid = find_digit<kMidBins>(h_mid, want, s_find);
+    const uint32_t prefix = (top_digit << kMidBits) | mid.digit;
+    for_cands(n, [&](uint32_t key, bool real) {
+        if (real && key >> kLowBits == prefix) count_digit(h_low, key & (kLowBins - 1));
+    });
+    __syncthreads();
+    const Found low = find_digit<kLowBins>(h_low, want - mid.below, s_find);
+    const uint32_t tau = (prefix << kLowBits) | low.digit;
+    const uint32_t need_eq = want - mid.below - low.below;
+
+    uint32_t lt = 0, eq = 0;
+    for_cands(ahead, [&](uint32_t key, bool real) {
+        lt += __popcll(__ballot(real && key < tau));
+        eq += __popcll(__ballot(real && key == tau));
+    });
+    if (lane == 0 && (lt | eq)) {
+        atomicAdd(&s_cand_lt, lt);
+        atomicAdd(&s_cand_eq, eq);
+    }
+    __syncthreads();
+    const uint32_t* src = norm_bits + head * T;
+    const int64_t first = blockIdx.x * sp.chunk;
+    const int64_t last = first + sp.chunk < T ? first + sp.chunk : T;
+    const int64_t iters = sp.chunk / kSelThreads;
+    const uint32_t t0 = (uint32_t)(first + wave * iters * kWaveSize);
+    const uint32_t end = (uint32_t)last;
+    emit_ordered<4>(
+        [&](int64_t e) -> uint32_t {
+            const uint32_t t = t0 + (uint32_t)e * kWaveSize + lane;
+            const uint32_t v = src[t < end ? t : end - 1] ^ flip;
+            return t < end ? v : 0xffffffffu;
+        },
+        iters, t0, tau, need_eq, s_lt_ahead + s_cand_lt, s_cand_eq, kept_idx + head * (int64_t)k, s_emit);
+    if (kept_count != nullptr && blockIdx.x == 0 && threadIdx.x == 0) kept_count[head] = (int32_t)k;
 }
 
 template <int E>
 static void launch_select(const float* norms, int64_t n_heads, int64_t T, int64_t k, uint32_t flip,
                           int32_t* kept_idx, int32_t* kept_count, hipStream_t stream,
                           RaggedSelect rag = RaggedSelect{nullptr, nullptr, 0, 0, 0}) {
-    hipLaunchKernelGGL((select_kernel<E>), dim3((unsigned)n_heads),
-                       dim3(E == -1 ? kSelPackedThreads : kSelThreads), 0, stream,
+    hipLaunchKernelGGL((select_kernel<E>), dim3((unsigned)n_heads), dim3(kSelThreads), 0, stream,
                        reinterpret_cast<const uint32_t*>(norms), T, (uint32_t)k, flip, kept_idx,
                        kept_count, rag);
 }
@@ -270,8 +582,6 @@ static void launch_select_for_length(int64_t longest, const float* norms, int64_
     else if (per_lane <= 16) launch_select<16>(norms, n_heads, T, k, flip, kept_idx, kept_count, stream, rag);
     else if (per_lane <= kSelMaxRegKeys)
         launch_select<32>(norms, n_heads, T, k, flip, kept_idx, kept_count, stream, rag);
-    else if (longest <= (int64_t)kSelPackedThreads * 2 * kSelPackedRegs)
-        launch_select<-1>(norms, n_heads, T, k, flip, kept_idx, kept_count, stream, rag);
     else
         launch_select<0>(norms, n_heads, T, k, flip, kept_idx, kept_count, stream, rag);
 }
@@ -304,14 +614,39 @@ l2kv_status random_keys_dispatch(int64_t n_heads, int64_t T, uint32_t seed, floa
     return launch_status();
 }
 
+size_t select_workspace_bytes(int64_t n_heads, int64_t T) { return select_plan(n_heads, T).bytes; }
+
 l2kv_status select_dispatch(const float* norms, int64_t n_heads, int64_t T, int64_t k,
                             l2kv_mode mode, int32_t* kept_idx, int32_t* kept_count,
-                            void* workspace, hipStream_t stream) {
-    (void)workspace;
+                            void* workspace, size_t workspace_bytes, hipStream_t stream) {
     if (n_heads > 0x7fffffffLL) return L2KV_ERR_SHAPE;
     const uint32_t flip = mode == L2KV_KEEP_HIGHEST ? 0xffffffffu : 0u;
-    launch_select_for_length(T, norms, n_heads, T, k, flip, kept_idx, kept_count, stream,
-                             RaggedSelect{nullptr, nullptr, 0, 0, 0});
+    const SelectPlan plan = select_plan(n_heads, T);
+    if (plan.chunk == 0 || workspace_bytes < plan.bytes) {
+        launch_select_for_length(T, norms, n_heads, T, k, flip, kept_idx, kept_count, stream,
+                                 RaggedSelect{nullptr, nullptr, 0, 0, 0});
+        return launch_status();
+    }
+    SelectSplit sp;
+    const size_t n = (size_t)n_heads * (size_t)plan.chunks;
+    char* ws = static_cast<char*>(workspace);
+    sp.fine = reinterpret_cast<uint16_t*>(ws);
+    ws += round256(n * kTopBins * sizeof(uint16_t));
+    sp.coarse = reinterpret_cast<uint32_t*>(ws);
+    ws += round256(n * kCoarse * sizeof(uint32_t));
+    sp.info = reinterpret_cast<uint2*>(ws);
+    ws += round256(n * sizeof(uint2));
+    sp.head_info = reinterpret_cast<uint32_t*>(ws);
+    ws += round256((size_t)n_heads * 2 * sizeof(uint32_t));
+    sp.cand = reinterpret_cast<uint32_t*>(ws);
+    sp.chunk = plan.chunk;
+    sp.chunks = plan.chunks;
+    const dim3 grid((unsigned)plan.chunks, (unsigned)n_heads);
+    const uint32_t* bits = reinterpret_cast<const uint32_t*>(norms);
+    hipLaunchKernelGGL(select_count_kernel, grid, dim3(kSelThreads), 0, stream, bits, T, flip, sp);
+    hipLaunchKernelGGL(select_gather_kernel, grid, dim3(kSelThreads), 0, stream, bits, T, (uint32_t)k, flip, sp);
+    hipLaunchKernelGGL(select_emit_kernel, grid, dim3(kSelThreads), 0, stream, bits, T, (uint32_t)k, flip, kept_idx,
+                       kept_count, sp);
     return launch_status();
 }
 
