@@ -13,8 +13,23 @@
 // second term is then a dot product; the first needs the scores of one query in
 // ascending order, i.e. one sort of T positive floats per query head.
 //
-// Both sorts are least-significant-digit radix sorts (4 passes of 8 bits) run by
-// one 1024-lane workgroup per head.  Each wavefront owns a contiguous chunk of
+// Both need the rank of every element among the n of its head, not the sorted array.
+// A head is shared by several workgroups (share_plan has the rule), each of which ranks a
+// range of VALUES holding about n / shares elements: it counts all keys of the head in
+// 4096 bins of equal width between the smallest and the largest key (the few hundred KB of
+// a head come from the L2), takes the bins whose first element falls into its range of
+// ranks, and ranks those few thousand elements in LDS: counted again in 8192 finer bins,
+// put into bin order, each then compared with the one or two others of its bin.
+// What bounds it is the passes of every workgroup over all keys of its head (fetch, LDS counting,
+// gathering: two thirds of the time) and the LDS round trips of the comparisons, so the
+// shares are as few as the LDS list allows until they fill the chip.  (One workgroup per
+// head and four counting passes of 8 bits over global memory, which this replaces, took
+// 196 us for 32 heads of 32k norms and 221 us for 128 heads of scores; now 22 and 43 us.
+// 131k norms of 8 heads: 671 -> 50 us.)  The counting passes are kept for what the bins cannot separate: more than 1024
+// elements in one of the 4096 bins (masses of equal keys), and heads beyond 8M elements.
+//
+// The counting passes are a least-significant-digit radix sort (4 passes of 8 bits) by
+// one 1024-lane workgroup.  Each wavefront owns a contiguous chunk of
 // the input; a pass counts digits per wavefront in LDS, turns the 16 x 256 counts
 // into start offsets (digit-major, wavefront-minor, which keeps the pass stable)
 // and scatters in input order, ranking the 64 keys of a step against each other
@@ -22,11 +37,13 @@
 // L2; all waves of a workgroup share one vector L1, so a workgroup barrier is all
 // the ordering the passes need.
 //
-// Unnormalised scores e_p = 2^(s_p - max) are sorted and summed (double
+// Unnormalised scores e_p = 2^(s_p - max) are ranked by their logits and summed (double
 // accumulators, fixed order), and the three results are divided by sum_p e_p at
 // the end.
 #include "l2kv_device.hpp"
 #include "l2kv_host.hpp"
+
+#include <type_traits>
 
 namespace l2kv {
 namespace {
@@ -41,10 +58,6 @@ struct SortShared {
     uint32_t hist[kSortWaves][kBins];   // per-wave digit counts, then running output offsets
     uint32_t digit_base[kBins];         // first output position of each digit
 };
-
-__device__ __forceinline__ uint32_t lanes_below(uint64_t mask) {
-    return __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
-}
 
 // What a pass reads as payload and what it writes.
 enum PassKind {
@@ -164,35 +177,464 @@ __device__ void radix_pass(const uint32_t* in_key, const uint32_t* in_val, uint3
     __syncthreads();
 }
 
+// ---- ranking by value ranges ------------------------------------------------------------------
+constexpr int kBinBits = 12;
+constexpr int kRankBins = 1 << kBinBits;             // 4 per lane
+static_assert(kRankBins == 4 * kSortLanes, "prefix sums take four bins per lane");
+constexpr int kListPer = 20;                         // 4-byte words of the LDS list per lane
+constexpr int kListWords = kListPer * kSortLanes;    // 80 KB
+constexpr int kListAhead = 4;                        // words read past the last element of a share
+constexpr uint32_t kMaxBin = 1024;                   // elements of one bin; bounds the comparisons inside a bin
+
+constexpr int kFinePer = 8;                          // finer bins per lane
+constexpr int kFineBins = kFinePer * kSortLanes;
+
+struct __attribute__((aligned(16))) BinShared {
+    uint32_t bin[kRankBins + 4];                     // of the head; one word more than bins
+    uint32_t fine[kFineBins];                        // of the share
+    uint32_t wave[2][kSortWaves];
+    uint32_t first, end, base, stop, crowded;
+    uint32_t ticket;
+};
+
+// A workgroup's part of a head: `share` of `shares`.
+struct Part { int64_t head; int share; };
+
+// Workgroups go to the 8 compute dies round-robin.  With a multiple of 8 heads, the shares of a
+// head are 8 apart, so that the keys of a head are read through one die's L2 and the ranks, which
+// are scattered over the whole head, meet in it.  Otherwise head and share in plain order.
+__device__ __forceinline__ Part part_of_block(uint32_t block, uint32_t n_heads, uint32_t shares) {
+    if (n_heads % 8 == 0) {
+        const uint32_t y = block / 8;
+        return Part{(int64_t)(y / shares) * 8 + block % 8, (int)(y % shares)};
+    }
+    return Part{block / shares, (int)(block % shares)};
+}
+
+// How n elements are cut into shares: the first `rest` of them take one more than n / shares.
+struct Cut {
+    uint32_t shares, quotient, rest;
+    __host__ __device__ Cut(uint32_t n, uint32_t count) : shares(count), quotient(n / count), rest(n % count) {}
+    __device__ __forceinline__ uint32_t start(uint32_t s) const { return s * quotient + (s < rest ? s : rest); }
+};
+
+// Bins of a range of keys, monotone in the key.  Norms spread over octaves: equal widths in their bit
+// patterns (about the logarithm).  Logits lie on both sides of zero: equal widths in the value.  (One fused
+// multiply-add is monotone whatever its rounding, and the clamp keeps every input inside; NaN goes to bin 0.)
+struct BitBins {
+    using Key = uint32_t;
+    static constexpr uint32_t kLowest = 0u, kHighest = 0xffffffffu;
+    uint32_t lo;
+    int shift;
+    static __device__ __forceinline__ uint32_t key(uint32_t bits) { return bits; }
+    static __device__ __forceinline__ uint32_t lower(uint32_t a, uint32_t b) { return a < b ? a : b; }
+    static __device__ __forceinline__ uint32_t higher(uint32_t a, uint32_t b) { return a > b ? a : b; }
+    static __device__ __forceinline__ int width_shift(uint32_t span) {
+        const int bits = span == 0 ? 0 : 32 - __builtin_clz(span);
+        return bits > kBinBits ? bits - kBinBits : 0;
+    }
+    static __device__ __forceinline__ BitBins over(uint32_t kmin, uint32_t kmax) { return BitBins{kmin, width_shift(kmax - kmin)}; }
+    __device__ __forceinline__ uint32_t operator()(uint32_t key) const { return (key - lo) >> shift; }
+    // how far into its bin `b` a key lies, 0 .. 1
+    __device__ __forceinline__ float within(uint32_t key, uint32_t b) const {
+        return __builtin_ldexpf((float)(key - lo - (b << shift)), -shift);
+    }
+};
+struct ValueBins {
+    using Key = float;
+    static constexpr float kLowest = -INFINITY, kHighest = INFINITY;
+    float offset, scale;
+    static __device__ __forceinline__ float key(uint32_t bits) { return __builtin_bit_cast(float, bits); }
+    static __device__ __forceinline__ float lower(float a, float b) { return fminf(a, b); }
+    static __device__ __forceinline__ float higher(float a, float b) { return fmaxf(a, b); }
+    static __device__ __forceinline__ ValueBins over(float kmin, float kmax) {
+        const float scale = (float)kRankBins / (kmax - kmin);
+        return ValueBins{-kmin * scale, scale};
+    }
+    __device__ __forceinline__ uint32_t operator()(float key) const {
+        return (uint32_t)fminf(fmaxf(fmaf(key, scale, offset), 0.f), (float)(kRankBins - 1));
+    }
+    __device__ __forceinline__ float within(float key, uint32_t b) const {
+        return fminf(fmaxf(fmaf(key, scale, offset) - (float)b, 0.f), 1.f);
+    }
+};
+// Bit patterns that order like the floats (other than NaN) they are made from, for the counting passes.
+__device__ __forceinline__ uint32_t ordered_bits(uint32_t bits) { return bits ^ ((int32_t)bits < 0 ? 0xffffffffu : 0x80000000u); }
+__device__ __forceinline__ float float_of_ordered(uint32_t v) {
+    return __builtin_bit_cast(float, v ^ ((int32_t)v < 0 ? 0x80000000u : 0xffffffffu));
+}
+
+// The keys of a head: E > 0: at most 1024 * E, kept in registers; E == 0: re-read in every pass.
+template <int E, typename B> struct HeadKeys {
+    using Bins = B;
+    using Key = typename B::Key;
+    const uint32_t* src;
+    uint32_t n;
+    Key reg[E > 0 ? E : 1];
+    __device__ __forceinline__ HeadKeys(const uint32_t* s, uint32_t count) : src(s), n(count) {
+        if constexpr (E > 0) {
+#pragma unroll
+            for (int e = 0; e < E; ++e) {
+                const uint32_t t = e * kSortLanes + threadIdx.x;
+                reg[e] = B::key(src[t < n ? t : n - 1]);
+            }
+        }
+    }
+    // body(keys, position(u), valid(u)) for batches of keys, called by all lanes of the workgroup alike
+    template <typename F> __device__ __forceinline__ void each_batch(F&& body) const {
+        if constexpr (E > 0) {
+            uint32_t left = n - threadIdx.x;
+            asm volatile("" : "+v"(left));
+            body(reg, [](int u) { return (uint32_t)(u * kSortLanes) + threadIdx.x; }, [&](int u) { return (int32_t)left > u * kSortLanes; });
+        } else {
+            for (uint32_t base = 0; base < n; base += kBatch * kSortLanes) {
+                Key key[kBatch];
+                load_batch(key, base);
+                body(key, [&](int u) { return base + u * kSortLanes + threadIdx.x; },
+                     [&](int u) { return base + u * kSortLanes + threadIdx.x < n; });
+            }
+        }
+    }
+    __device__ __forceinline__ void load_batch(Key (&key)[kBatch], uint32_t base) const {
+#pragma unroll
+        for (int u = 0; u < kBatch; ++u) {
+            const uint32_t t = base + u * kSortLanes + threadIdx.x;
+            key[u] = B::key(src[t < n ? t : n - 1]);
+        }
+    }
+    // body(key, position) for every key of the head once
+    template <typename F> __device__ __forceinline__ void each(F&& body) const {
+        if constexpr (E > 0) {
+            uint32_t left = n - threadIdx.x;                          // negative past the end
+            asm volatile("" : "+v"(left));                            // the lane masks are not worth keeping between passes
+#pragma unroll
+            for (int e = 0; e < E; ++e)
+                if ((int32_t)left > e * kSortLanes) body(reg[e], (uint32_t)(e * kSortLanes) + threadIdx.x);
+        } else {
+            for (uint32_t base = 0; base < n; base += kBatch * kSortLanes) {
+                Key key[kBatch];
+                load_batch(key, base);
+#pragma unroll
+                for (int u = 0; u < kBatch; ++u) {
+                    const uint32_t t = base + u * kSortLanes + threadIdx.x;
+                    if (t < n) body(key[u], t);
+                }
+            }
+        }
+    }
+};
+
+// Turns kPer counters per lane into the sums of all lower ones (and returns this lane's counters).  One
+// barrier inside; the caller's barriers order the counting before and the use after.
+template <int kPer> struct Counts { uint32_t v[kPer]; uint32_t before; };
+template <int kPer>
+__device__ __forceinline__ Counts<kPer> bins_to_starts(uint32_t* bins, uint32_t* wave_total) {
+    static_assert(kPer % 4 == 0, "16-byte accesses");
+    const int lane = threadIdx.x % kWaveSize;
+    const int wave = threadIdx.x / kWaveSize;
+    uint4* const mine = reinterpret_cast<uint4*>(bins) + threadIdx.x * (kPer / 4);
+    Counts<kPer> c;
+    uint32_t sum = 0;
+#pragma unroll
+    for (int i = 0; i < kPer / 4; ++i) {
+        const uint4 v = mine[i];
+        c.v[4 * i] = v.x; c.v[4 * i + 1] = v.y; c.v[4 * i + 2] = v.z; c.v[4 * i + 3] = v.w;
+        sum += v.x + v.y + v.z + v.w;
+    }
+    const uint32_t incl = wave_inclusive_sum(sum);
+    if (lane == kWaveSize - 1) wave_total[wave] = incl;
+    __syncthreads();
+    uint32_t before = incl - sum;
+#pragma unroll
+    for (int w = 0; w < kSortWaves; ++w) before += w < wave ? wave_total[w] : 0u;
+    c.before = before;
+#pragma unroll
+    for (int i = 0; i < kPer / 4; ++i) {
+        uint4 v;
+        v.x = before; before += c.v[4 * i];
+        v.y = before; before += c.v[4 * i + 1];
+        v.z = before; before += c.v[4 * i + 2];
+        v.w = before; before += c.v[4 * i + 3];
+        mine[i] = v;
+    }
+    return c;
+}
+
+template <typename Bins> struct Share {
+    typename Bins::Key kmin, kmax;      // over the head
+    Bins bins;                          // of the head
+    uint32_t first, end;                // bins of this share
+    uint32_t base, count;               // rank of its first element, number of elements
+    bool crowded;                       // some bin of the head holds more than max_bin elements
+};
+
+// Called by all lanes; ends with a barrier.  All shares of a head see the same bins, so they agree
+// on kmin, kmax and crowded, and every bin belongs to exactly one of them.  count is at most
+// ceil(n / shares) + max_bin - 1 unless the head is crowded.  sh.bin then holds the rank of the first
+// element of every bin.
+template <typename Keys>
+__device__ __forceinline__ Share<typename Keys::Bins> find_share(const Keys& keys, uint32_t n, uint32_t s, const Cut& cut,
+                                                                 uint32_t max_bin, BinShared& sh) {
+    using Bins = typename Keys::Bins;
+    using Key = typename Bins::Key;
+    const int lane = threadIdx.x % kWaveSize;
+    const int wave = threadIdx.x / kWaveSize;
+    Share<Bins> r;
+    Key lo = Bins::kHighest, hi = Bins::kLowest;
+    keys.each([&](Key key, uint32_t) {
+        lo = Bins::lower(lo, key);
+        hi = Bins::higher(hi, key);
+    });
+#pragma unroll
+    for (int off = kWaveSize / 2; off > 0; off >>= 1) {
+        lo = Bins::lower(lo, __shfl_xor(lo, off));
+        hi = Bins::higher(hi, __shfl_xor(hi, off));
+    }
+    if (lane == 0) {
+        sh.wave[0][wave] = __builtin_bit_cast(uint32_t, lo);
+        sh.wave[1][wave] = __builtin_bit_cast(uint32_t, hi);
+    }
+    reinterpret_cast<uint4*>(sh.bin)[threadIdx.x] = make_uint4(0, 0, 0, 0);
+    if (threadIdx.x == 0) {
+        sh.first = sh.base = 0;               // what share 0 starts with
+        sh.crowded = 0;
+        sh.bin[kRankBins] = n;                // where a bin behind the last would start
+    }
+    __syncthreads();
+#pragma unroll
+    for (int w = 0; w < kSortWaves; ++w) {
+        lo = Bins::lower(lo, __builtin_bit_cast(Key, sh.wave[0][w]));
+        hi = Bins::higher(hi, __builtin_bit_cast(Key, sh.wave[1][w]));
+    }
+    r.kmin = lo;
+    r.kmax = hi;
+    r.bins = Bins::over(lo, hi);
+    keys.each([&](Key key, uint32_t) { atomicAdd(&sh.bin[r.bins(key)], 1u); });
+    __syncthreads();
+    const Counts<4> c = bins_to_starts<4>(sh.bin, sh.wave[0]);
+    uint32_t before = c.before;
+    // The share starts with the first bin that starts at or past its first rank, i.e. behind the
+    // bin that holds the rank before; it stops behind the bin that holds its last rank.
+    const uint32_t r0 = cut.start(s), r1 = cut.start(s + 1);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const uint32_t after = before + c.v[i];
+        if (r0 > 0 && before <= r0 - 1 && r0 - 1 < after) {
+            sh.first = 4 * threadIdx.x + i + 1;
+            sh.base = after;
+        }
+        if (r1 > 0 && before <= r1 - 1 && r1 - 1 < after) {
+            sh.end = 4 * threadIdx.x + i + 1;
+            sh.stop = after;
+        }
+        if (c.v[i] > max_bin) sh.crowded = 1;
+        before = after;
+    }
+    if (r1 == 0 && threadIdx.x == 0) sh.end = sh.stop = 0;       // no rank falls to it
+    __syncthreads();
+    r.first = sh.first;
+    r.end = sh.end;
+    r.base = sh.base;
+    r.count = sh.stop - sh.base;
+    r.crowded = sh.crowded != 0;
+    return r;
+}
+
+// The elements of a share (at most kPer per lane), each with its rank inside the share: key[u], pos[u]
+// and rank[u] where u * 1024 + lane < count.  One pass over the head gathers them into the list.  They are then
+// counted in finer bins, put into the order of those, and every element compares itself with the others
+// of its bin.  A finer bin is a range of expected ranks: the rank of the first element of the head's bin
+// plus the way into that bin times its elements, so that dense and sparse stretches of values
+// fill the finer bins alike (8192 bins for up to 20k elements).  With finer bins of equal width the
+// tails of the logits left a few hundred elements in each of the others: 140 us for 128 heads in two shares
+// against 46.  Hits are gathered with one counter update per wave and batch (a ballot and an update per key:
+// 16k cycles of the 48k of a share, now 7k).  Equal keys rank by position (kWithPos), else in any order.  Called by all lanes; the
+// list is free again after the caller's barrier.
+template <int kPer, typename Bins> struct Ranked {
+    typename Bins::Key key[kPer];
+    uint32_t pos[kPer], rank[kPer];
+};
+template <bool kWithPos, int kPer, typename Keys>
+__device__ __forceinline__ void rank_share(const Keys& keys, const Share<typename Keys::Bins>& s, BinShared& sh,
+                                           typename Keys::Key* list_key, uint32_t* list_pos,
+                                           Ranked<kPer, typename Keys::Bins>& out) {
+    using Key = typename Keys::Key;
+    const uint32_t bins = s.end - s.first;
+    typename Keys::Bins coarse = s.bins;
+    if constexpr (std::is_same_v<Key, float>) asm volatile("" : "+v"(coarse.scale));   // computed afresh: the bins of
+    else asm volatile("" : "+v"(coarse.lo));                                           // the count would not stay in registers
+    if (threadIdx.x == 0) sh.wave[1][0] = 0;                          // elements gathered
+    for (int i = 0; i < kFinePer / 4; ++i) reinterpret_cast<uint4*>(sh.fine)[i * kSortLanes + threadIdx.x] = make_uint4(0, 0, 0, 0);
+    __syncthreads();
+    keys.each_batch([&](const auto& key, auto pos, auto valid) {
+        constexpr int kN = sizeof(key) / sizeof(key[0]);
+        // this lane's hits as a bit mask, one counter update per wave
+        uint32_t hits = 0;
+#pragma unroll
+        for (int u = 0; u < kN; ++u) hits |= valid(u) && coarse(key[u]) - s.first < bins ? 1u << u : 0u;
+        const uint32_t incl = wave_inclusive_sum(__popc(hits));
+        uint32_t at = 0;
+        if (threadIdx.x % kWaveSize == kWaveSize - 1) at = atomicAdd(&sh.wave[1][0], incl) + incl;
+        at = __shfl(at, kWaveSize - 1) - __shfl(incl, kWaveSize - 1) + incl - __popc(hits);
+#pragma unroll
+        for (int u = 0; u < kN; ++u) {
+            if (hits >> u & 1u) {
+                list_key[at] = key[u];
+                if constexpr (kWithPos) list_pos[at] = pos(u);
+                ++at;
+            }
+        }
+    });
+    __syncthreads();
+    const float per_rank = (float)kFineBins / (float)(s.count > 0 ? s.count : 1);
+    auto fine_bin = [&](Key key) {
+        const uint32_t b = s.bins(key);
+        const uint32_t start = sh.bin[b], next = sh.bin[b + 1];
+        const float expected = fmaf(s.bins.within(key, b), (float)(next - start), (float)(start - s.base));
+        return (uint32_t)fminf(expected * per_rank, (float)(kFineBins - 1));
+    };
+#pragma unroll
+    for (int u = 0; u < kPer; ++u) {
+        const uint32_t i = u * kSortLanes + threadIdx.x;
+        if (i < s.count) {
+            out.key[u] = list_key[i];
+            if constexpr (kWithPos) out.pos[u] = list_pos[i];
+            out.rank[u] = fine_bin(out.key[u]);
+            atomicAdd(&sh.fine[out.rank[u]], 1u);
+        }
+    }
+    __syncthreads();
+    (void)bins_to_starts<kFinePer>(sh.fine, sh.wave[0]);
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < kPer; ++u) {
+        if (u * kSortLanes + threadIdx.x < s.count) {
+            const uint32_t at = atomicAdd(&sh.fine[out.rank[u]], 1u);
+            list_key[at] = out.key[u];
+            if constexpr (kWithPos) list_pos[at] = out.pos[u];
+        }
+    }
+    __syncthreads();
+    // A bin now ends at its counter and starts where the bin before it ends.  The lanes take the elements
+    // in the order of the bins, so that a large bin keeps few waves busy, four at a time and the
+    // first kListAhead elements of their bins at once, so that the LDS round trips overlap; longer
+    // bins go on in steps of as many.  (The list has room for kListAhead words behind any share.)
+    constexpr int kTogether = 4;
+#pragma unroll
+    for (int u0 = 0; u0 < kPer; u0 += kTogether) {
+        if (u0 * kSortLanes >= (int)s.count) break;
+        uint32_t start[kTogether], end[kTogether];
+#pragma unroll
+        for (int v = 0; v < kTogether && u0 + v < kPer; ++v) {
+            const uint32_t i = (u0 + v) * kSortLanes + threadIdx.x;
+            const uint32_t at = i < s.count ? i : 0u;
+            out.key[u0 + v] = list_key[at];
+            out.pos[u0 + v] = kWithPos ? list_pos[at] : at;           // ties in the order of the list
+        }
+#pragma unroll
+        for (int v = 0; v < kTogether && u0 + v < kPer; ++v) {
+            const uint32_t f = fine_bin(out.key[u0 + v]);
+            start[v] = f > 0 ? sh.fine[f - 1] : 0u;
+            end[v] = sh.fine[f];
+        }
+        Key other[kTogether][kListAhead];
+        uint32_t order[kTogether][kListAhead];
+#pragma unroll
+        for (int v = 0; v < kTogether && u0 + v < kPer; ++v) {
+#pragma unroll
+            for (int j = 0; j < kListAhead; ++j) {
+                other[v][j] = list_key[start[v] + j];
+                order[v][j] = kWithPos ? list_pos[start[v] + j] : start[v] + j;
+            }
+        }
+#pragma unroll
+        for (int v = 0; v < kTogether && u0 + v < kPer; ++v) {
+            const Key key = out.key[u0 + v];
+            const uint32_t pos = out.pos[u0 + v];
+            uint32_t r = start[v];
+#pragma unroll
+            for (int j = 0; j < kListAhead; ++j)
+                r += start[v] + j < end[v] && (other[v][j] < key || (other[v][j] == key && order[v][j] < pos)) ? 1u : 0u;
+            for (uint32_t j0 = start[v] + kListAhead; j0 < end[v]; j0 += kListAhead) {
+                Key o[kListAhead];
+                uint32_t p[kListAhead];
+#pragma unroll
+                for (int j = 0; j < kListAhead; ++j) {
+                    o[j] = list_key[j0 + j];
+                    p[j] = kWithPos ? list_pos[j0 + j] : j0 + j;
+                }
+#pragma unroll
+                for (int j = 0; j < kListAhead; ++j) r += j0 + j < end[v] && (o[j] < key || (o[j] == key && p[j] < pos)) ? 1u : 0u;
+            }
+            out.rank[u0 + v] = r;
+        }
+    }
+}
+
 // drop_rank[h][t] = T - 1 - (rank of (norm bits, t) in ascending order).
+template <int E>
 __global__ __launch_bounds__(kSortLanes)
-void norm_ranks_kernel(const float* __restrict__ norms, int64_t T, uint32_t* __restrict__ scratch,
-                       int32_t* __restrict__ drop_rank) {
-    __shared__ SortShared sh;
-    const int64_t h = blockIdx.x;
-    const uint32_t* keys = reinterpret_cast<const uint32_t*>(norms) + h * T;
-    uint32_t* a_key = scratch + h * 4 * T;
-    uint32_t* a_val = a_key + T;
-    uint32_t* b_key = a_val + T;
-    uint32_t* b_val = b_key + T;
-    uint32_t* rank = reinterpret_cast<uint32_t*>(drop_rank) + h * T;
-    radix_pass<kIotaIn>(keys, nullptr, a_key, a_val, T, 0, sh);
-    radix_pass<kPairs>(a_key, a_val, b_key, b_val, T, 8, sh);
-    radix_pass<kPairs>(b_key, b_val, a_key, a_val, T, 16, sh);
-    radix_pass<kRankOut>(a_key, a_val, nullptr, rank, T, 24, sh);
+void norm_ranks_kernel(const float* __restrict__ norms, int64_t T, uint32_t n_heads, Cut cut, uint32_t max_bin,
+                       uint32_t* __restrict__ scratch, int32_t* __restrict__ drop_rank) {
+    __shared__ BinShared sh;
+    __shared__ __attribute__((aligned(16))) uint32_t s_list[kListWords];
+    static_assert(sizeof(SortShared) <= sizeof(s_list), "the counting passes share the list's memory");
+    const Part part = part_of_block(blockIdx.x, n_heads, cut.shares);
+    const uint32_t n = (uint32_t)T;
+    const uint32_t* src = reinterpret_cast<const uint32_t*>(norms) + part.head * T;
+    uint32_t* rank = reinterpret_cast<uint32_t*>(drop_rank) + part.head * T;
+    const HeadKeys<E, BitBins> keys(src, n);
+    const auto s = find_share(keys, n, part.share, cut, max_bin, sh);
+    if (s.kmin == s.kmax) {                                          // equal norms: the order of the positions
+        const uint32_t end = cut.start(part.share + 1);
+        for (uint32_t t = cut.start(part.share) + threadIdx.x; t < end; t += kSortLanes) rank[t] = n - 1 - t;
+        return;
+    }
+    if (s.crowded) {
+        if (part.share != 0) return;
+        SortShared& sort = *reinterpret_cast<SortShared*>(s_list);
+        uint32_t* a_key = scratch + part.head * 4 * T;
+        uint32_t* a_val = a_key + T;
+        uint32_t* b_key = a_val + T;
+        uint32_t* b_val = b_key + T;
+        radix_pass<kIotaIn>(src, nullptr, a_key, a_val, T, 0, sort);
+        radix_pass<kPairs>(a_key, a_val, b_key, b_val, T, 8, sort);
+        radix_pass<kPairs>(b_key, b_val, a_key, a_val, T, 16, sort);
+        radix_pass<kRankOut>(a_key, a_val, nullptr, rank, T, 24, sort);
+        return;
+    }
+    constexpr int kPer = kListPer / 2;                               // keys and positions share the list
+    Ranked<kPer, BitBins> mine;
+    rank_share<true, kPer>(keys, s, sh, s_list, s_list + kPer * kSortLanes, mine);
+#pragma unroll
+    for (int u = 0; u < kPer; ++u)
+        if (u * kSortLanes + threadIdx.x < s.count) rank[mine.pos[u]] = n - 1 - (s.base + mine.rank[u]);
+}
+
+// Where the shares of a query head leave their sums: at the start of the head's second scratch array,
+// which only the counting passes use otherwise.  One counter, then a record per share.
+constexpr int kRecordHeader = 4;                     // words in front of the records
+constexpr int kRecordSums = 5;                       // sum e, sum e * rank, dropped sum, sum e_(j) * j, sum of the m lowest
+constexpr int kRecordWords = 2 * kRecordSums;        // doubles
+__device__ __forceinline__ uint32_t* record_base(uint32_t* second, int64_t head, int64_t T) {
+    return reinterpret_cast<uint32_t*>((reinterpret_cast<uintptr_t>(second + head * T) + 15) & ~(uintptr_t)15);
 }
 
 // Scaled logits of all G query heads of one KV head over a block of rows:
 // scores[b*Hq + hkv*G + g][t] = (q_g . K_t) * scale * log2(e).
 constexpr int kScoreWaves = 4;
-constexpr int kScoreLoads = 8;                                        // row loads in flight per lane
-constexpr int kScoreRowsPerWave = kScoreLoads * kRowsPerWaveLoad;     // 32
-constexpr int kScoreRowsPerBlock = kScoreWaves * kScoreRowsPerWave;   // 128
+// 4 loads in flight per lane: 43.5 us for 32 heads of 32k rows and 4 query heads each (6.2 TB/s); 8 loads 44.8, 2 loads
+// 47.5.  Scores stored straight from the row loop, 16 bytes per row group, instead of one run per wave
+// and head: 46.7 (8 loads).
+constexpr int kScoreLoads = 4;                                        // row loads in flight per lane
+constexpr int kScoreRowsPerWave = kScoreLoads * kRowsPerWaveLoad;     // 16
+constexpr int kScoreRowsPerBlock = kScoreWaves * kScoreRowsPerWave;   // 64
 
 template <typename E, int D, int G>
 __global__ __launch_bounds__(kScoreWaves * kWaveSize)
 void alr_scores_kernel(const void* __restrict__ Q, const void* __restrict__ K, int64_t T,
-                       int64_t k_head_stride, float scale_log2e, float* __restrict__ scores) {
+                       int64_t k_head_stride, float scale_log2e, float* __restrict__ scores,
+                       uint32_t* __restrict__ records) {
     using S = Slice<E, D>;
     const int lane = threadIdx.x % kWaveSize;
     const int wave = threadIdx.x / kWaveSize;
@@ -200,6 +642,8 @@ void alr_scores_kernel(const void* __restrict__ Q, const void* __restrict__ K, i
     const int r = lane / kRowLanes;
     const int64_t head = blockIdx.y;                                   // b * Hkv + hkv
     const int64_t q_head0 = head * G;                                  // b * Hq + hkv * G
+    // the arrival counters of the ranking launch that follows
+    if (records != nullptr && blockIdx.x == 0 && threadIdx.x < G) *record_base(records, q_head0 + threadIdx.x, T) = 0u;
     // q and K rows are shared among the 16 lanes in the same 16-byte pieces (the dot product
     // does not care which lane holds which element)
     using P = Pieces<S::kWords>;
@@ -210,6 +654,7 @@ void alr_scores_kernel(const void* __restrict__ Q, const void* __restrict__ K, i
 #pragma unroll
     for (int g = 0; g < G; ++g) widen<E, D>(load_words<S::kWords, P::kStride>(qbase + (size_t)g * S::kRowBytes), q[g]);
 
+    __shared__ float s_scores[kScoreWaves][G][kScoreRowsPerWave];      // every wave uses its own part
     const int64_t row0 = (int64_t)blockIdx.x * kScoreRowsPerBlock + wave * kScoreRowsPerWave + r;
     Words<S::kWords> tile[kScoreLoads];
 #pragma unroll
@@ -231,105 +676,218 @@ void alr_scores_kernel(const void* __restrict__ Q, const void* __restrict__ K, i
             p = row16_tree_sum(p);
             mine = c == g ? p : mine;
         }
-        const int64_t t = row0 + u * kRowsPerWaveLoad;
-        if (c < G && t < T) scores[(q_head0 + c) * T + t] = mine * scale_log2e;
+        if (c < G) s_scores[wave][c][u * kRowsPerWaveLoad + r] = mine * scale_log2e;
+    }
+    // the wave's scores of consecutive rows leave as one run per head
+    __builtin_amdgcn_wave_barrier();
+    const int64_t first = (int64_t)blockIdx.x * kScoreRowsPerBlock + wave * kScoreRowsPerWave;
+    constexpr int kHeadsPerStore = kWaveSize / kScoreRowsPerWave;
+    const int row = lane % kScoreRowsPerWave;
+#pragma unroll
+    for (int g0 = 0; g0 < G; g0 += kHeadsPerStore) {
+        const int g = g0 + lane / kScoreRowsPerWave;
+        if (g < G && first + row < T) scores[(q_head0 + g) * T + first + row] = s_scores[wave][g][row];
     }
 }
 
-// Fixed-order sum of one double per lane over the workgroup; result valid in thread 0.
+// Sum of one double per lane over the wave, in a fixed order; the same in all lanes.
+template <int CTRL> __device__ __forceinline__ double dpp_read(double v) {
+    const uint64_t u = __builtin_bit_cast(uint64_t, v);
+    const uint32_t lo = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)u, CTRL, 0xf, 0xf, true);
+    const uint32_t hi = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)(u >> 32), CTRL, 0xf, 0xf, true);
+    return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
+__device__ __forceinline__ double read_lane(double v, int lane) {
+    const uint64_t u = __builtin_bit_cast(uint64_t, v);
+    const uint32_t lo = __builtin_amdgcn_readlane((int)(uint32_t)u, lane);
+    const uint32_t hi = __builtin_amdgcn_readlane((int)(uint32_t)(u >> 32), lane);
+    return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
+__device__ __forceinline__ double wave_sum(double v) {
+    v += dpp_read<kDppXor1>(v);
+    v += dpp_read<kDppXor2>(v);
+    v += dpp_read<kDppHalfMirror>(v);
+    v += dpp_read<kDppMirror>(v);
+    return (read_lane(v, 0) + read_lane(v, 16)) + (read_lane(v, 32) + read_lane(v, 48));
+}
+
+// Fixed-order sums of N doubles per lane over the workgroup; results valid in thread 0.
 template <int N>
 __device__ void block_sum(double (&v)[N], double (*stage)[N]) {
     const int lane = threadIdx.x % kWaveSize;
     const int wave = threadIdx.x / kWaveSize;
 #pragma unroll
     for (int i = 0; i < N; ++i) {
-#pragma unroll
-        for (int off = kWaveSize / 2; off > 0; off >>= 1) v[i] += __shfl_down(v[i], off);
-    }
-    if (lane == 0) {
-#pragma unroll
-        for (int i = 0; i < N; ++i) stage[wave][i] = v[i];
+        const double s = wave_sum(v[i]);
+        if (lane == 0) stage[wave][i] = s;
     }
     __syncthreads();
-    if (threadIdx.x == 0) {
+    if (wave == 0) {                      // lane w holds wave w's sum
 #pragma unroll
-        for (int i = 0; i < N; ++i) {
-            double s = stage[0][i];
-            for (int w = 1; w < kSortWaves; ++w) s += stage[w][i];
-            v[i] = s;
-        }
+        for (int i = 0; i < N; ++i) v[i] = wave_sum(lane < kSortWaves ? stage[lane][i] : 0.0);
     }
     __syncthreads();
 }
 
-// One workgroup per query head: softmax statistics, rank-weighted sums, sort of
-// the scores, and the three outputs.
+// Softmax statistics, rank-weighted sums, ranks of the scores by value ranges, and the three
+// outputs.  Every share adds up its stretch of positions and its range of ranks; with several
+// shares the sums meet in the head's records and the share that finishes last (arrival counter)
+// adds them in order of the shares, so the result does not depend on timing.  Records and counter
+// travel with device scope; a share waits until its record has been acknowledged before it
+// takes its ticket, and nobody waits for anybody.
+template <int E>
 __global__ __launch_bounds__(kSortLanes)
 void alr_head_kernel(uint32_t* __restrict__ scratch, const int32_t* __restrict__ drop_rank, int64_t T,
-                     int32_t G, int64_t m, double* __restrict__ alr, double* __restrict__ loss,
-                     double* __restrict__ loss_ref) {
-    __shared__ SortShared sh;
-    __shared__ double stage[kSortWaves][3];
-    __shared__ float wave_max[kSortWaves];
-    const int64_t head = blockIdx.x;                                   // b * Hq + hq
-    const int lane = threadIdx.x % kWaveSize;
-    const int wave = threadIdx.x / kWaveSize;
+                     uint32_t n_heads, int32_t G, Cut cut, uint32_t max_bin, int64_t m, double* __restrict__ alr,
+                     double* __restrict__ loss, double* __restrict__ loss_ref) {
+    __shared__ BinShared sh;
+    __shared__ __attribute__((aligned(16))) uint32_t s_list[kListWords];
+    __shared__ double stage[kSortWaves][kRecordSums];
+    const Part part = part_of_block(blockIdx.x, n_heads, cut.shares);     // head = b * Hq + hq
+    const int64_t head = part.head;
+    const uint32_t n = (uint32_t)T;
     // scratch: two arrays [n_heads][T]; the first holds the logits on entry
     uint32_t* buf0 = scratch + head * T;
-    uint32_t* buf1 = scratch + ((int64_t)gridDim.x + head) * T;
+    uint32_t* second = scratch + (int64_t)n_heads * T;
     const int32_t* rank = drop_rank + (head / G) * T;
 
-    float mx = -INFINITY;
-    for (int64_t t = threadIdx.x; t < T; t += kSortLanes) mx = fmaxf(mx, __builtin_bit_cast(float, buf0[t]));
-#pragma unroll
-    for (int off = kWaveSize / 2; off > 0; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off));
-    if (lane == 0) wave_max[wave] = mx;
-    __syncthreads();
-    mx = wave_max[0];
-    for (int w = 1; w < kSortWaves; ++w) mx = fmaxf(mx, wave_max[w]);
+    const HeadKeys<E, ValueBins> keys(buf0, n);
+    const auto s = find_share(keys, n, part.share, cut, max_bin, sh);
+    const float mx = s.kmax;
+    auto score = [&](float logit) { return (double)__builtin_amdgcn_exp2f(logit - mx); };
 
     // e_p, their sum, the rank-weighted sum and the mass of the m pairs dropped by norm
-    double acc[3] = {0.0, 0.0, 0.0};
-    for (int64_t t = threadIdx.x; t < T; t += kSortLanes) {
-        const float e = __builtin_amdgcn_exp2f(__builtin_bit_cast(float, buf0[t]) - mx);
-        buf0[t] = __builtin_bit_cast(uint32_t, e);
-        const int32_t rk = rank[t];
-        acc[0] += (double)e;
-        acc[1] += (double)e * (double)rk;
-        acc[2] += rk < m ? (double)e : 0.0;
+    double acc[kRecordSums] = {0.0, 0.0, 0.0, 0.0, 0.0};
+    const uint32_t p1 = cut.start(part.share + 1);
+    for (uint32_t base = cut.start(part.share); base < p1; base += kBatch * kSortLanes) {
+        float logit[kBatch];
+        int32_t rk[kBatch];
+#pragma unroll
+        for (int u = 0; u < kBatch; ++u) {
+            const uint32_t t = base + u * kSortLanes + threadIdx.x;
+            logit[u] = __builtin_bit_cast(float, buf0[t < p1 ? t : p1 - 1]);
+            rk[u] = rank[t < p1 ? t : p1 - 1];
+        }
+#pragma unroll
+        for (int u = 0; u < kBatch; ++u) {
+            const uint32_t t = base + u * kSortLanes + threadIdx.x;
+            const double e = t < p1 ? score(logit[u]) : 0.0;
+            acc[0] += e;
+            acc[1] += e * (double)rk[u];
+            acc[2] += rk[u] < m ? e : 0.0;
+            if (s.kmin == s.kmax) {                                   // equal scores: any order
+                acc[3] += e * (double)t;
+                acc[4] += t < m ? e : 0.0;
+            }
+        }
     }
-    block_sum<3>(acc, stage);           // also orders the e_p stores before the sort
-    const double l = acc[0], by_norm = acc[1], lost = acc[2];
-
-    // ascending sort of the e_p (non-negative floats order like their bit patterns)
-    radix_pass<kKeysOnly>(buf0, nullptr, buf1, nullptr, T, 0, sh);
-    radix_pass<kKeysOnly>(buf1, nullptr, buf0, nullptr, T, 8, sh);
-    radix_pass<kKeysOnly>(buf0, nullptr, buf1, nullptr, T, 16, sh);
-    radix_pass<kKeysOnly>(buf1, nullptr, buf0, nullptr, T, 24, sh);
-
-    double ref[3] = {0.0, 0.0, 0.0};
-    for (int64_t j = threadIdx.x; j < T; j += kSortLanes) {
-        const double e = (double)__builtin_bit_cast(float, buf0[j]);
-        ref[0] += e * (double)j;
-        ref[1] += j < m ? e : 0.0;
+    const bool crowded = s.crowded && s.kmin != s.kmax;
+    if (!s.crowded && s.kmin != s.kmax) {
+        // ranks inside the share, then the sums in order of rank
+        float* list = reinterpret_cast<float*>(s_list);
+        Ranked<kListPer, ValueBins> mine;
+        rank_share<false, kListPer>(keys, s, sh, list, nullptr, mine);
+        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < kListPer; ++u)
+            if (u * kSortLanes + threadIdx.x < s.count) list[mine.rank[u]] = mine.key[u];
+        __syncthreads();
+        for (uint32_t i = threadIdx.x; i < s.count; i += kSortLanes) {
+            const double e = score(list[i]);
+            const uint32_t j = s.base + i;
+            acc[3] += e * (double)j;
+            acc[4] += (int64_t)j < m ? e : 0.0;
+        }
     }
-    block_sum<3>(ref, stage);
+    block_sum<kRecordSums>(acc, stage);                               // valid in thread 0
+
+    if (cut.shares > 1) {
+        uint32_t* counter = record_base(second, head, T);
+        uint32_t* records = counter + kRecordHeader;
+        if (threadIdx.x == 0) {
+            auto* out = reinterpret_cast<unsigned long long*>(records + part.share * kRecordWords);
+#pragma unroll
+            for (int i = 0; i < kRecordSums; ++i)
+                __hip_atomic_store(out + i, __builtin_bit_cast(unsigned long long, acc[i]), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);
+            sh.ticket = __hip_atomic_fetch_add(counter, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        __syncthreads();
+        if (sh.ticket != cut.shares - 1) return;
+        // the records into LDS with independent loads, then added in order
+        uint32_t* copy = s_list;
+        for (uint32_t i = threadIdx.x; i < cut.shares * kRecordWords; i += kSortLanes)
+            copy[i] = __hip_atomic_load(records + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __syncthreads();
+        if (threadIdx.x == 0) {
+#pragma unroll
+            for (int i = 0; i < kRecordSums; ++i) acc[i] = 0.0;
+            for (uint32_t w = 0; w < cut.shares; ++w) {
+#pragma unroll
+                for (int i = 0; i < kRecordSums; ++i) acc[i] += reinterpret_cast<const double*>(copy + w * kRecordWords)[i];
+            }
+        }
+        __syncthreads();
+    }
+    if (crowded) {
+        // ascending sort by the counting passes; every share has read the logits by now
+        SortShared& sort = *reinterpret_cast<SortShared*>(s_list);
+        uint32_t* buf1 = second + head * T;
+        for (uint32_t t = threadIdx.x; t < n; t += kSortLanes) buf0[t] = ordered_bits(buf0[t]);
+        __syncthreads();
+        radix_pass<kKeysOnly>(buf0, nullptr, buf1, nullptr, T, 0, sort);
+        radix_pass<kKeysOnly>(buf1, nullptr, buf0, nullptr, T, 8, sort);
+        radix_pass<kKeysOnly>(buf0, nullptr, buf1, nullptr, T, 16, sort);
+        radix_pass<kKeysOnly>(buf1, nullptr, buf0, nullptr, T, 24, sort);
+        double ref[2] = {0.0, 0.0};
+        for (uint32_t j = threadIdx.x; j < n; j += kSortLanes) {
+            const double e = score(float_of_ordered(buf0[j]));
+            ref[0] += e * (double)j;
+            ref[1] += (int64_t)j < m ? e : 0.0;
+        }
+        block_sum<2>(ref, reinterpret_cast<double(*)[2]>(stage));
+        acc[3] = ref[0];
+        acc[4] = ref[1];
+    }
     if (threadIdx.x == 0) {
-        alr[head] = (ref[0] - by_norm) / l;
-        if (loss != nullptr) loss[head] = lost / l;
-        if (loss_ref != nullptr) loss_ref[head] = ref[1] / l;
+        alr[head] = (acc[3] - acc[1]) / acc[0];
+        if (loss != nullptr) loss[head] = acc[2] / acc[0];
+        if (loss_ref != nullptr) loss_ref[head] = acc[4] / acc[0];
     }
+}
+
+// How many workgroups share a head, and the largest bin they accept (0: one workgroup per head and
+// the counting passes).  `list` = elements a share may hold.
+//  - as many as the list needs, less what the last bin of a share may bring with it;
+//  - more while the launch has fewer workgroups than compute units, down to 2048 elements each;
+//  - every share goes over all keys of its head, 50 us per 131k keys and 256 shares at a time, the
+//    counting passes take 670 us per 131k keys and 256 heads at a time (512 heads of 131k: 1.5 ms in 15
+//    shares each, 6.4 ms by the passes): the passes cost less from about 64 shares on, where
+//    the heads are many enough to fill the chip.
+struct SharePlan { uint32_t shares, max_bin; };
+SharePlan share_plan(int64_t n_heads, int64_t T, int64_t list) {
+    constexpr int64_t kLongest = int64_t{1} << 23;     // the records of all shares of a head fit the LDS list
+    const SharePlan passes{1, 0};
+    if (T > kLongest) return passes;
+    const int64_t full = list - kMaxBin;
+    int64_t shares = (T + full - 1) / full;
+    if (shares > 64 && n_heads * shares > 4096) return passes;
+    const int64_t fill = (256 + n_heads - 1) / n_heads, most = (T + 2047) / 2048;
+    const int64_t want = fill < most ? fill : most;
+    if (want > shares) shares = want;
+    if (n_heads * shares > 0x7fffffffLL) return passes;
+    return SharePlan{(uint32_t)shares, kMaxBin};              // ceil(T / shares) + kMaxBin <= list
 }
 
 template <typename E, int D>
 l2kv_status launch_scores(const void* Q, const void* K, int32_t B, int32_t Hkv, int32_t G, int64_t T,
-                          int64_t k_head_stride, float scale_log2e, float* scores, hipStream_t stream) {
+                          int64_t k_head_stride, float scale_log2e, float* scores, uint32_t* records, hipStream_t stream) {
     const dim3 grid((unsigned)((T + kScoreRowsPerBlock - 1) / kScoreRowsPerBlock), (unsigned)(B * Hkv));
     const dim3 block(kScoreWaves * kWaveSize);
 #define L2KV_SCORES(GG)                                                                             \
     case GG:                                                                                        \
         hipLaunchKernelGGL((alr_scores_kernel<E, D, GG>), grid, block, 0, stream, Q, K, T,          \
-                           k_head_stride, scale_log2e, scores);                                     \
+                           k_head_stride, scale_log2e, scores, records);                            \
         break;
     switch (G) {
         L2KV_SCORES(1) L2KV_SCORES(2) L2KV_SCORES(3) L2KV_SCORES(4)
@@ -354,8 +912,10 @@ size_t alr_workspace_bytes(int32_t B, int32_t Hq, int64_t T) {
 
 l2kv_status norm_ranks_dispatch(const float* norms, int64_t n_heads, int64_t T, int32_t* drop_rank,
                                 void* workspace, hipStream_t stream) {
-    hipLaunchKernelGGL(norm_ranks_kernel, dim3((unsigned)n_heads), dim3(kSortLanes), 0, stream, norms, T,
-                       static_cast<uint32_t*>(workspace), drop_rank);
+    const SharePlan plan = share_plan(n_heads, T, kListWords / 2 - kListAhead);
+    auto kernel = T <= 8 * kSortLanes ? norm_ranks_kernel<8> : T <= 32 * kSortLanes ? norm_ranks_kernel<32> : norm_ranks_kernel<0>;
+    hipLaunchKernelGGL(kernel, dim3((unsigned)n_heads * plan.shares), dim3(kSortLanes), 0, stream, norms, T,
+                       (uint32_t)n_heads, Cut((uint32_t)T, plan.shares), plan.max_bin, static_cast<uint32_t*>(workspace), drop_rank);
     return launch_status();
 }
 
@@ -367,18 +927,22 @@ l2kv_status alr_dispatch(const void* Q, const void* K, l2kv_dtype dt, const int3
     const float s = scale > 0.f ? scale : 1.0f / sqrtf((float)D);
     const float scale_log2e = s * 1.44269504088896340736f;
     float* scores = static_cast<float*>(workspace);
+    const SharePlan plan = share_plan((int64_t)B * Hq, T, kListWords - kListAhead);
+    uint32_t* records = plan.shares > 1 ? static_cast<uint32_t*>(workspace) + (int64_t)B * Hq * T : nullptr;
     l2kv_status st;
     if (dt == L2KV_BF16 && D == 256)
-        st = launch_scores<BF16, 256>(Q, K, B, Hkv, G, T, k_head_stride, scale_log2e, scores, stream);
+        st = launch_scores<BF16, 256>(Q, K, B, Hkv, G, T, k_head_stride, scale_log2e, scores, records, stream);
     else if (dt == L2KV_BF16)
-        st = D == 128 ? launch_scores<BF16, 128>(Q, K, B, Hkv, G, T, k_head_stride, scale_log2e, scores, stream)
-                      : launch_scores<BF16, 64>(Q, K, B, Hkv, G, T, k_head_stride, scale_log2e, scores, stream);
+        st = D == 128 ? launch_scores<BF16, 128>(Q, K, B, Hkv, G, T, k_head_stride, scale_log2e, scores, records, stream)
+                      : launch_scores<BF16, 64>(Q, K, B, Hkv, G, T, k_head_stride, scale_log2e, scores, records, stream);
     else
-        st = D == 128 ? launch_scores<F32, 128>(Q, K, B, Hkv, G, T, k_head_stride, scale_log2e, scores, stream)
-                      : launch_scores<F32, 64>(Q, K, B, Hkv, G, T, k_head_stride, scale_log2e, scores, stream);
+        st = D == 128 ? launch_scores<F32, 128>(Q, K, B, Hkv, G, T, k_head_stride, scale_log2e, scores, records, stream)
+                      : launch_scores<F32, 64>(Q, K, B, Hkv, G, T, k_head_stride, scale_log2e, scores, records, stream);
     if (st != L2KV_OK) return st;
-    hipLaunchKernelGGL(alr_head_kernel, dim3((unsigned)(B * Hq)), dim3(kSortLanes), 0, stream,
-                       static_cast<uint32_t*>(workspace), drop_rank, T, G, m, alr, loss, loss_ref);
+    auto kernel = T <= 8 * kSortLanes ? alr_head_kernel<8> : alr_head_kernel<0>;    // registers for 32: 43 us, re-read: 41 us for 128 heads of 32k
+    hipLaunchKernelGGL(kernel, dim3((unsigned)(B * Hq) * plan.shares), dim3(kSortLanes), 0, stream,
+                       static_cast<uint32_t*>(workspace), drop_rank, T, (uint32_t)(B * Hq), G, Cut((uint32_t)T, plan.shares), plan.max_bin, m,
+                       alr, loss, loss_ref);
     return launch_status();
 }
 

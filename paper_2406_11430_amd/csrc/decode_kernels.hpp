@@ -62,11 +62,6 @@ static_assert(kDecWaves * kDecRowsPerStep == kDecodeRowTile, "row tile mismatch"
 
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 
-typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
-__device__ __forceinline__ float dot2_bf16(uint32_t a, uint32_t b, float c) {
-    return __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2_t, a), __builtin_bit_cast(bf16x2_t, b), c, false);
-}
-
 // Row element held in fp32 slot e of the slice of lane c (slots in the order of widen()), with
 // the row shared among the lanes in 16-byte pieces (Pieces in l2kv_device.hpp).
 template <typename E, int W>
@@ -87,13 +82,6 @@ template <int W>
 __device__ __forceinline__ Words<W> cached_words(const char* p) {
     return load_words<W, Pieces<W>::kStride>(p);
 }
-
-// s_waitcnt immediate for "vmcnt(0)" alone in the gfx9-family encoding that gfx950 uses: vmcnt
-// in bits [3:0] and [15:14] = 0, expcnt [6:4] and lgkmcnt [11:8] left at their maxima.
-constexpr int kWaitVmcnt0 = 0x0F70;
-#if defined(__HIP_DEVICE_COMPILE__) && !defined(__gfx950__)
-#error "the s_waitcnt immediate above is the gfx950 encoding: this file is written for gfx950 only"
-#endif
 
 // Device-scope (agent) relaxed store of one float.
 __device__ __forceinline__ void publish(float* p, float v) {

@@ -16,6 +16,13 @@ constexpr int kWaveSize = 64;
 constexpr int kRowLanes = 16;   // lanes cooperating on one cache row
 constexpr int kRowsPerWaveLoad = kWaveSize / kRowLanes;
 
+// s_waitcnt immediate for "vmcnt(0)" alone in the gfx9-family encoding that gfx950 uses: vmcnt
+// in bits [3:0] and [15:14] = 0, expcnt [6:4] and lgkmcnt [11:8] left at their maxima.
+constexpr int kWaitVmcnt0 = 0x0F70;
+#if defined(__HIP_DEVICE_COMPILE__) && !defined(__gfx950__)
+#error "the s_waitcnt immediate above is the gfx950 encoding: this file is written for gfx950 only"
+#endif
+
 // DPP control words (cross-lane operand swizzles inside a 16-lane row).
 constexpr int kDppXor1 = 0xB1;        // quad_perm [1,0,3,2]
 constexpr int kDppXor2 = 0x4E;        // quad_perm [2,3,0,1]
@@ -45,9 +52,38 @@ __device__ __forceinline__ float row16_tree_sum(float p) {
     return p;
 }
 
+// Inclusive prefix sum over the 64 lanes of a wave: within the DPP rows by shifts of 1, 2, 4 and 8 lanes,
+// then the last lane of each row is added to the row after it (rows 1 and 3), and lane 31 to rows 2
+// and 3.  Lanes without a source add 0.  All 64 lanes must be active.  (Shuffles go through the LDS
+// crossbar, one round trip per step.)
+template <int CTRL, int ROWS>
+__device__ __forceinline__ uint32_t dpp_or_zero(uint32_t v) {
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, ROWS, 0xf, false);
+}
+__device__ __forceinline__ uint32_t wave_inclusive_sum(uint32_t v) {
+    v += dpp_or_zero<0x111, 0xf>(v);      // row_shr:1
+    v += dpp_or_zero<0x112, 0xf>(v);      // row_shr:2
+    v += dpp_or_zero<0x114, 0xf>(v);      // row_shr:4
+    v += dpp_or_zero<0x118, 0xf>(v);      // row_shr:8
+    v += dpp_or_zero<0x142, 0xa>(v);      // row_bcast:15
+    v += dpp_or_zero<0x143, 0xc>(v);      // row_bcast:31
+    return v;
+}
+
+// Number of lanes below this one whose bit is set.
+__device__ __forceinline__ uint32_t lanes_below(uint64_t mask) {
+    return __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
+}
+
 // bf16 -> fp32 widening is a 16-bit shift (exact).
 __device__ __forceinline__ float bf16_lo(uint32_t w) { return __builtin_bit_cast(float, w << 16); }
 __device__ __forceinline__ float bf16_hi(uint32_t w) { return __builtin_bit_cast(float, w & 0xffff0000u); }
+
+// Dot product of two pairs of bf16 values, added to c (exact products, fp32 sum).
+typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ float dot2_bf16(uint32_t a, uint32_t b, float c) {
+    return __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2_t, a), __builtin_bit_cast(bf16x2_t, b), c, false);
+}
 
 // A lane's slice of a row as W 32-bit words (W = 2, 4 or 8).
 template <int W> struct Words { uint32_t w[W]; };

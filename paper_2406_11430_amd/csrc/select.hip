@@ -36,21 +36,6 @@ constexpr int kTopBits = 12, kMidBits = 10, kLowBits = 10;
 static_assert(kTopBits + kMidBits + kLowBits == 32, "digits cover the key");
 constexpr int kTopBins = 1 << kTopBits, kMidBins = 1 << kMidBits, kLowBins = 1 << kLowBits;
 
-__device__ __forceinline__ uint32_t lanes_below(uint64_t mask) {
-    return __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
-}
-
-// Inclusive prefix sum over the 64 lanes of a wave.
-__device__ __forceinline__ uint32_t wave_inclusive_sum(uint32_t v) {
-    const int lane = threadIdx.x % kWaveSize;
-#pragma unroll
-    for (int off = 1; off < kWaveSize; off <<= 1) {
-        const uint32_t up = __shfl_up(v, off);
-        if (lane >= off) v += up;
-    }
-    return v;
-}
-
 // LDS histogram of kCopies interleaved counters per digit; lane l counts in copy l % kCopies.  LDS
 // atomics on one address are served one lane at a time, so the copies bound what tied or padded
 // rows (all keys in one digit) cost: 32k equal keys per head take 35 us with 4 copies, 94 us with
