@@ -75,7 +75,7 @@ l2kv_status l2kv_norms(const void* K, l2kv_dtype dt, int64_t n_heads, int64_t T,
     if (K == nullptr || norms == nullptr) return L2KV_ERR_NULL;
     if (l2kv_status st = check_cache(dt, n_heads, T, D, head_stride); st != L2KV_OK) return st;
     if (!aligned(K, 16) || !aligned(norms, 4)) return L2KV_ERR_ALIGN;
-    return norms_dispatch(K, dt, n_heads, T, D, head_stride, norms, false, static_cast<hipStream_t>(stream));
+    return norms_dispatch(K, dt, n_heads, T, D, head_stride, norms, kReadAgainBytes, static_cast<hipStream_t>(stream));
 }
 
 size_t l2kv_select_workspace_bytes(int64_t n_heads, int64_t T) {
@@ -135,8 +135,8 @@ l2kv_status l2kv_compress(const void* K, const void* V, l2kv_dtype dt, int64_t n
         !aligned(kept_idx, 4) || !aligned(workspace, 16))
         return L2KV_ERR_ALIGN;
     const int64_t k = l2kv_keep_count(T, keep_ratio);
+    const int64_t read_again = 3 * k >= T ? kReadAgainBytes : 0;
     const int64_t slab = slab_heads == 0 || slab_heads > n_heads ? n_heads : slab_heads;
-    const bool keep_in_cache = slab < n_heads;       // the slab's K rows are read again two launches later
     const size_t es = static_cast<size_t>(elem_bytes(dt));
     hipStream_t s = static_cast<hipStream_t>(stream);
     for (int64_t h0 = 0; h0 < n_heads; h0 += slab) {
@@ -146,7 +146,7 @@ l2kv_status l2kv_compress(const void* K, const void* V, l2kv_dtype dt, int64_t n
         float* ns = norms + h0 * T;
         int32_t* is = kept_idx + h0 * k;
         const size_t dense = static_cast<size_t>(h0) * static_cast<size_t>(k) * static_cast<size_t>(D) * es;
-        l2kv_status st = norms_dispatch(Ks, dt, nh, T, D, head_stride, ns, keep_in_cache, s);
+        l2kv_status st = norms_dispatch(Ks, dt, nh, T, D, head_stride, ns, read_again, s);
         if (st == L2KV_OK) st = select_dispatch(ns, nh, T, k, L2KV_KEEP_LOWEST, is, nullptr, workspace, workspace_bytes, s);
         if (st == L2KV_OK)
             st = compact_dispatch(Ks, Vs, dt, is, nh, T, k, D, head_stride, static_cast<char*>(Kc) + dense,

@@ -3,10 +3,14 @@
 //
 // A byte copy of whole rows: 16 lanes move one row (16 bytes per lane and
 // instruction: one piece of a 256-byte row, pieces c and c + 16 of a 512-byte
-// row), a wavefront moves 4 rows per instruction, and each row group handles kUnroll consecutive output rows so
-// all index loads, then all row loads of K and V, are in flight before the
-// first store.  Loads and stores carry the non-temporal hint (every byte is
+// row; 8 lanes share a 128-byte row), a wavefront moves 4 rows (8 short ones) per instruction.  Loads and stores carry the non-temporal hint (every byte is
 // touched once).  Dropped rows are never read.
+//
+// Memory-bound: half of the rows of 256 heads of 32k (4.3 GB in and out) move at 6.2 TB/s (690 us; a plain copy
+// of 4 GiB through the runtime reaches 4.8).  K and V go through workgroups of their own, which alternate in
+// the launch: one read and one write stream per workgroup, and one row in flight per row group, disturb
+// each other less than two of each and four rows (732 us).  Ordinary loads or stores instead of
+// non-temporal ones: 768 and 772 us; every compute die on a range of its own: 771 us.
 #include "l2kv_device.hpp"
 #include "l2kv_host.hpp"
 
@@ -15,76 +19,72 @@ namespace l2kv {
 constexpr int kCompactThreads = 256;
 constexpr int kCompactWaves = kCompactThreads / kWaveSize;
 #ifndef L2KV_COMPACT_UNROLL
-#define L2KV_COMPACT_UNROLL 4
+#define L2KV_COMPACT_UNROLL 1
 #endif
 constexpr int kCompactUnroll = L2KV_COMPACT_UNROLL;
-constexpr int kCompactRowsPerBlock = kCompactWaves * kRowsPerWaveLoad * kCompactUnroll;  // 64
+template <int kRowBytes>
+constexpr int kCompactRowsPerBlock = kCompactWaves * RowCopy<kRowBytes>::kRowsPerWave * kCompactUnroll;   // 16, or 32 short ones
 
-// W = 32-bit words per lane slice (row bytes = 16 lanes * 4W).
-template <int W, bool HAS_V>
+// kTensors = 2: odd workgroups are V's.
+template <int kRowBytes, int kTensors>
 __global__ __launch_bounds__(kCompactThreads)
 void compact_kernel(const char* __restrict__ K, const char* __restrict__ V,
                     const int32_t* __restrict__ kept_idx, int64_t T, int64_t k, int64_t head_stride_bytes,
-                    int64_t blocks_per_head, char* __restrict__ Kc, char* __restrict__ Vc) {
-    using P = Pieces<W>;
-    constexpr int64_t kRowBytes = kRowLanes * 4 * W;
-    const int64_t head = blockIdx.x / blocks_per_head;
-    const int64_t chunk = blockIdx.x % blocks_per_head;
+                    uint32_t first_block, char* __restrict__ Kc, char* __restrict__ Vc) {
+    using P = RowCopy<kRowBytes>;
+    constexpr int W = P::kWords;
+    // from the end: the norm pass has left the last rows of K in the caches (kReadAgainBytes)
+    const int64_t head = gridDim.y - 1 - blockIdx.y;
+    const uint32_t block = first_block + gridDim.x - 1 - blockIdx.x;
+    const uint32_t chunk = block / kTensors;
+    const bool is_v = kTensors == 2 && block % 2 != 0;
     const int lane = threadIdx.x % kWaveSize;
     const int wave = threadIdx.x / kWaveSize;
-    const int c = lane % kRowLanes;
-    const int rg = lane / kRowLanes;
+    const int c = lane % P::kLanes;
+    const int rg = lane / P::kLanes;
 
-    const int64_t first = chunk * kCompactRowsPerBlock + (wave * kRowsPerWaveLoad + rg) * kCompactUnroll;
+    const int64_t first = (int64_t)chunk * kCompactRowsPerBlock<kRowBytes> + (wave * P::kRowsPerWave + rg) * kCompactUnroll;
     const int32_t* idx = kept_idx + head * k;
-    const int64_t src_head = head * head_stride_bytes;
-    const int64_t dst_head = head * k * kRowBytes;
+    const char* src = (is_v ? V : K) + head * head_stride_bytes + c * 16;
+    char* dst = (is_v ? Vc : Kc) + head * k * kRowBytes + c * 16;
 
-    int64_t src[kCompactUnroll];
-#pragma unroll
-    for (int u = 0; u < kCompactUnroll; ++u) {
-        int64_t j = first + u;
-        j = j < k ? j : k - 1;            // tail: duplicate the last row, store skipped
-        int64_t t = idx[j];
-        t = t < 0 ? 0 : (t < T ? t : T - 1);          // an index outside [0, T) cannot lead out of the head
-        src[u] = src_head + t * kRowBytes + c * P::kBytes;
-    }
-    Words<W> kr[kCompactUnroll], vr[kCompactUnroll];
-#pragma unroll
-    for (int u = 0; u < kCompactUnroll; ++u) kr[u] = load_words_stream<W, P::kStride>(K + src[u]);
-    if constexpr (HAS_V) {
-#pragma unroll
-        for (int u = 0; u < kCompactUnroll; ++u) vr[u] = load_words_stream<W, P::kStride>(V + src[u]);
-    }
+    int64_t t[kCompactUnroll];
 #pragma unroll
     for (int u = 0; u < kCompactUnroll; ++u) {
         const int64_t j = first + u;
-        if (j < k) {
-            const int64_t dst = dst_head + j * kRowBytes + c * P::kBytes;
-            store_words_stream<W, P::kStride>(Kc + dst, kr[u]);
-            if constexpr (HAS_V) store_words_stream<W, P::kStride>(Vc + dst, vr[u]);
-        }
+        const int64_t row = idx[j < k ? j : k - 1];   // tail: duplicate the last row, store skipped
+        t[u] = row < 0 ? 0 : (row < T ? row : T - 1);  // an index outside [0, T) cannot lead out of the head
     }
+    Words<W> rows[kCompactUnroll];
+#pragma unroll
+    for (int u = 0; u < kCompactUnroll; ++u) rows[u] = load_words_stream<W, P::kStride>(src + t[u] * (int64_t)kRowBytes);
+#pragma unroll
+    for (int u = 0; u < kCompactUnroll; ++u)
+        if (first + u < k) store_words_stream<W, P::kStride>(dst + (first + u) * kRowBytes, rows[u]);
 }
 
-template <int W>
+template <int kRowBytes>
 static l2kv_status launch_compact(const void* K, const void* V, const int32_t* kept_idx,
                                   int64_t n_heads, int64_t T, int64_t k, int64_t head_stride_bytes,
                                   void* Kc, void* Vc, hipStream_t stream) {
-    const int64_t bph = (k + kCompactRowsPerBlock - 1) / kCompactRowsPerBlock;
-    const int64_t blocks = bph * n_heads;
-    if (blocks > 0x7fffffffLL) return L2KV_ERR_SHAPE;
-    if (V != nullptr) {
-        hipLaunchKernelGGL((compact_kernel<W, true>), dim3((unsigned)blocks), dim3(kCompactThreads), 0,
-                           stream, static_cast<const char*>(K), static_cast<const char*>(V), kept_idx,
-                           T, k, head_stride_bytes, bph, static_cast<char*>(Kc), static_cast<char*>(Vc));
-    } else {
-        hipLaunchKernelGGL((compact_kernel<W, false>), dim3((unsigned)blocks), dim3(kCompactThreads), 0,
-                           stream, static_cast<const char*>(K), static_cast<const char*>(nullptr),
-                           kept_idx, T, k, head_stride_bytes, bph, static_cast<char*>(Kc),
-                           static_cast<char*>(nullptr));
+    if ((k + 63) / 64 * n_heads > 0x7fffffffLL) return L2KV_ERR_SHAPE;
+    const int64_t bph = (k + kCompactRowsPerBlock<kRowBytes> - 1) / kCompactRowsPerBlock<kRowBytes> * (V != nullptr ? 2 : 1);
+    auto kernel = V != nullptr ? compact_kernel<kRowBytes, 2> : compact_kernel<kRowBytes, 1>;
+    constexpr int64_t kMaxX = 1 << 23, kMaxY = 65535;      // a launch has fewer than 2^32 lanes in x, 2^16 workgroups in y
+    for (int64_t h1 = n_heads; h1 > 0; h1 -= kMaxY) {
+        const int64_t nh = h1 < kMaxY ? h1 : kMaxY, h0 = h1 - nh;
+        const int64_t dense = h0 * k * kRowBytes;
+        for (int64_t b0 = 0; b0 < bph; b0 += kMaxX) {
+            const int64_t nb = bph - b0 < kMaxX ? bph - b0 : kMaxX;
+            hipLaunchKernelGGL(kernel, dim3((unsigned)nb, (unsigned)nh), dim3(kCompactThreads), 0, stream,
+                               static_cast<const char*>(K) + h0 * head_stride_bytes,
+                               V != nullptr ? static_cast<const char*>(V) + h0 * head_stride_bytes : nullptr,
+                               kept_idx + h0 * k, T, k, head_stride_bytes, (uint32_t)b0, static_cast<char*>(Kc) + dense,
+                               V != nullptr ? static_cast<char*>(Vc) + dense : nullptr);
+            if (l2kv_status st = launch_status(); st != L2KV_OK) return st;
+        }
     }
-    return launch_status();
+    return L2KV_OK;
 }
 
 l2kv_status compact_dispatch(const void* K, const void* V, l2kv_dtype dt, const int32_t* kept_idx,
@@ -94,9 +94,9 @@ l2kv_status compact_dispatch(const void* K, const void* V, l2kv_dtype dt, const 
     const int row_bytes = D * es;                      // 128, 256 or 512
     const int64_t hs_bytes = head_stride * es;
     switch (row_bytes) {
-        case 128: return launch_compact<2>(K, V, kept_idx, n_heads, T, k, hs_bytes, Kc, Vc, stream);
-        case 256: return launch_compact<4>(K, V, kept_idx, n_heads, T, k, hs_bytes, Kc, Vc, stream);
-        case 512: return launch_compact<8>(K, V, kept_idx, n_heads, T, k, hs_bytes, Kc, Vc, stream);
+        case 128: return launch_compact<128>(K, V, kept_idx, n_heads, T, k, hs_bytes, Kc, Vc, stream);
+        case 256: return launch_compact<256>(K, V, kept_idx, n_heads, T, k, hs_bytes, Kc, Vc, stream);
+        case 512: return launch_compact<512>(K, V, kept_idx, n_heads, T, k, hs_bytes, Kc, Vc, stream);
     }
     return L2KV_ERR_SHAPE;
 }

@@ -18,7 +18,14 @@ int device_compute_units();
 
 l2kv_status read_probe_dispatch(const void* data, size_t bytes, uint32_t* sink, hipStream_t stream);
 l2kv_status norms_dispatch(const void* K, l2kv_dtype dt, int64_t n_heads, int64_t T, int32_t D,
-                           int64_t head_stride, float* norms, bool keep_in_cache, hipStream_t stream);
+                           int64_t head_stride, float* norms, int64_t read_again_bytes, hipStream_t stream);
+// What the norm pass reads last, up to this much, it leaves in the caches for the compaction, which reads the kept
+// rows again and starts from the end.  Half of what the memory-side cache holds: V and the outputs pass
+// through it meanwhile (224 MB gave the same).  32 heads of 4k, half kept: 25.6 us against 26.7 for the whole
+// compression, 8 heads of 294k: 339 against 348, 256 heads of 32k: 1038 against 1039.  Ordinary loads stream
+// a little slower than non-temporal ones, so it only pays where a good part is read again: 8 heads
+// of 131k, a tenth kept: 81.4 against 79.6.
+constexpr int64_t kReadAgainBytes = int64_t{128} << 20;
 
 l2kv_status select_dispatch(const float* norms, int64_t n_heads, int64_t T, int64_t k,
                             l2kv_mode mode, int32_t* kept_idx, int32_t* kept_count,

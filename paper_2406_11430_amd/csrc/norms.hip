@@ -34,18 +34,23 @@ constexpr int kNormRowsPerBlock = kNormWaves * kRowsPerWaveLoad * kNormUnroll;  
 // The results leave with the non-temporal hint as well: the few stores then disturb the read
 // stream less (1.290 against 1.314 ms for the 8 GiB of the 32k-context workload; the selection
 // that reads the norms next takes the same 0.150 ms either way).
-template <bool kKeep>
-__device__ __forceinline__ void store_norm(float* p, float v) {
-    if constexpr (kKeep) *p = v;
+__device__ __forceinline__ void store_norm(float* p, float v, bool keep) {
+    if (keep) *p = v;
     else __builtin_nontemporal_store(v, p);
 }
 
-// kKeep: ordinary loads and stores instead of non-temporal ones, for callers that read the same
-// rows again soon (the slab mode of l2kv_compress), so the rows may stay in the caches.
-template <typename E, int D, bool kKeep>
+// Position of a workgroup in the launch, head by head (both grid shapes of the kernels below).
+__device__ __forceinline__ int64_t in_launch(int64_t blocks_per_head, int64_t head, int64_t chunk) {
+    return blocks_per_head == 0 ? head * gridDim.x + chunk : (int64_t)blockIdx.x;
+}
+
+// Workgroups from keep_from on (counted over the launch, head by head) use ordinary loads and stores
+// instead of non-temporal ones: the rows that were read last then stay in the 256 MB memory-side cache for the
+// compaction, which reads the kept ones again (kReadAgainBytes).
+template <typename E, int D>
 __global__ __launch_bounds__(kNormThreads)
 void norms_kernel(const char* __restrict__ K, int64_t T, int64_t head_stride_bytes,
-                  int64_t blocks_per_head, float* __restrict__ norms) {
+                  int64_t blocks_per_head, int64_t keep_from, float* __restrict__ norms) {
 #pragma clang fp contract(off)
     using S = Slice<E, D>;
     using P = Pieces<S::kWords>;
@@ -72,11 +77,17 @@ void norms_kernel(const char* __restrict__ K, int64_t T, int64_t head_stride_byt
     const __amdgpu_buffer_rsrc_t rows = __builtin_amdgcn_make_buffer_rsrc(
         const_cast<char*>(K + head * head_stride_bytes + chunk * (int64_t)(kNormRowsPerBlock * S::kRowBytes)), 0,
         rows_here * S::kRowBytes, kRawBufferWord3);
+    const bool keep = in_launch(blocks_per_head, head, chunk) >= keep_from;
     Words<S::kWords> raw[kNormUnroll];
+    if (keep) {
 #pragma unroll
-    for (int u = 0; u < kNormUnroll; ++u)
-        raw[u] = buffer_load_words<S::kWords, P::kStride, kKeep ? kBufferPolicyPlain : kBufferPolicyStream>(
-            rows, (local + u) * S::kRowBytes + c * P::kBytes);
+        for (int u = 0; u < kNormUnroll; ++u)
+            raw[u] = buffer_load_words<S::kWords, P::kStride, kBufferPolicyPlain>(rows, (local + u) * S::kRowBytes + c * P::kBytes);
+    } else {
+#pragma unroll
+        for (int u = 0; u < kNormUnroll; ++u)
+            raw[u] = buffer_load_words<S::kWords, P::kStride, kBufferPolicyStream>(rows, (local + u) * S::kRowBytes + c * P::kBytes);
+    }
 
     float mine = 0.f;
 #pragma unroll
@@ -127,7 +138,7 @@ void norms_kernel(const char* __restrict__ K, int64_t T, int64_t head_stride_byt
         mine = (c == u) ? total : mine;   // lane c keeps the sum of row u
     }
     const int64_t row = first + c;
-    if (c < kNormUnroll && row < T) store_norm<kKeep>(norms + head * T + row, mine);
+    if (c < kNormUnroll && row < T) store_norm(norms + head * T + row, mine, keep);
 }
 
 // 128-byte rows (bf16, 64 elements): two consecutive rows are 256 contiguous bytes, so the 16
@@ -136,10 +147,9 @@ void norms_kernel(const char* __restrict__ K, int64_t T, int64_t head_stride_byt
 // 16 chunks of the fixed summation order (chunk = 4 elements): it sums each left to right, adds
 // the two (first level of the tree), and the remaining three levels run over the 8 lanes of
 // its row.  Bit-identical to the one-row-per-row-group kernel above.
-template <bool kKeep>
 __global__ __launch_bounds__(kNormThreads)
 void norms_row_pairs_kernel(const char* __restrict__ K, int64_t T, int64_t head_stride_bytes,
-                            int64_t blocks_per_head, float* __restrict__ norms) {
+                            int64_t blocks_per_head, int64_t keep_from, float* __restrict__ norms) {
 #pragma clang fp contract(off)
     constexpr int kRowBytes = 128;
     // grid (chunks, heads) when the head count fits the y dimension; else one long x dimension
@@ -157,13 +167,14 @@ void norms_row_pairs_kernel(const char* __restrict__ K, int64_t T, int64_t head_
     const int64_t first = chunk * kNormRowsPerBlock + (wave * kRowsPerWaveLoad + rg) * kNormUnroll;   // in pairs
     const char* head_base = K + head * head_stride_bytes;
 
+    const bool keep = in_launch(blocks_per_head, head, chunk) >= keep_from;
     Words<4> raw[kNormUnroll];
 #pragma unroll
     for (int u = 0; u < kNormUnroll; ++u) {
         int64_t row = 2 * (first + u) + half;
         row = row < T ? row : T - 1;      // tail: re-read the last row, result unused
         const char* p = head_base + row * kRowBytes + j * 16;
-        if constexpr (kKeep) raw[u] = load_words<4>(p);
+        if (keep) raw[u] = load_words<4>(p);
         else raw[u] = load_words_stream<4>(p);
     }
 
@@ -188,23 +199,24 @@ void norms_row_pairs_kernel(const char* __restrict__ K, int64_t T, int64_t head_
         mine = (j == u) ? v : mine;       // lane j of each half keeps the sum of pair u's row
     }
     const int64_t row = 2 * (first + j) + half;
-    if (j < kNormUnroll && row < T) store_norm<kKeep>(norms + head * T + row, mine);
+    if (j < kNormUnroll && row < T) store_norm(norms + head * T + row, mine, keep);
 }
 
 template <typename E, int D>
 static l2kv_status launch_norms(const void* K, int64_t n_heads, int64_t T, int64_t head_stride,
-                                float* norms, bool keep_in_cache, hipStream_t stream) {
+                                float* norms, int64_t read_again_bytes, hipStream_t stream) {
     constexpr bool kPairs = Slice<E, D>::kRowBytes == 128;                    // a block takes twice the rows then
     const int64_t rows_per_block = kNormRowsPerBlock * (kPairs ? 2 : 1);
     const int64_t bph = (T + rows_per_block - 1) / rows_per_block;
     const int64_t blocks = bph * n_heads;
     if (blocks > 0x7fffffffLL) return L2KV_ERR_SHAPE;
-    auto kernel = keep_in_cache ? norms_kernel<E, D, true> : norms_kernel<E, D, false>;
-    if constexpr (kPairs) kernel = keep_in_cache ? norms_row_pairs_kernel<true> : norms_row_pairs_kernel<false>;
+    auto kernel = norms_kernel<E, D>;
+    if constexpr (kPairs) kernel = norms_row_pairs_kernel;
+    const int64_t kept_blocks = read_again_bytes / (rows_per_block * Slice<E, D>::kRowBytes);
     const bool grid2d = n_heads <= 65535;
     hipLaunchKernelGGL(kernel, grid2d ? dim3((unsigned)bph, (unsigned)n_heads) : dim3((unsigned)blocks),
                        dim3(kNormThreads), 0, stream, static_cast<const char*>(K), T,
-                       head_stride * (int64_t)E::kBytes, grid2d ? (int64_t)0 : bph, norms);
+                       head_stride * (int64_t)E::kBytes, grid2d ? (int64_t)0 : bph, blocks > kept_blocks ? blocks - kept_blocks : 0, norms);
     return launch_status();
 }
 
@@ -233,14 +245,14 @@ l2kv_status read_probe_dispatch(const void* data, size_t bytes, uint32_t* sink, 
 }
 
 l2kv_status norms_dispatch(const void* K, l2kv_dtype dt, int64_t n_heads, int64_t T, int32_t D,
-                           int64_t head_stride, float* norms, bool keep_in_cache, hipStream_t stream) {
+                           int64_t head_stride, float* norms, int64_t read_again_bytes, hipStream_t stream) {
     if (dt == L2KV_F32) {
-        return D == 64 ? launch_norms<F32, 64>(K, n_heads, T, head_stride, norms, keep_in_cache, stream)
-                       : launch_norms<F32, 128>(K, n_heads, T, head_stride, norms, keep_in_cache, stream);
+        return D == 64 ? launch_norms<F32, 64>(K, n_heads, T, head_stride, norms, read_again_bytes, stream)
+                       : launch_norms<F32, 128>(K, n_heads, T, head_stride, norms, read_again_bytes, stream);
     }
-    if (D == 256) return launch_norms<BF16, 256>(K, n_heads, T, head_stride, norms, keep_in_cache, stream);
-    return D == 64 ? launch_norms<BF16, 64>(K, n_heads, T, head_stride, norms, keep_in_cache, stream)
-                   : launch_norms<BF16, 128>(K, n_heads, T, head_stride, norms, keep_in_cache, stream);
+    if (D == 256) return launch_norms<BF16, 256>(K, n_heads, T, head_stride, norms, read_again_bytes, stream);
+    return D == 64 ? launch_norms<BF16, 64>(K, n_heads, T, head_stride, norms, read_again_bytes, stream)
+                   : launch_norms<BF16, 128>(K, n_heads, T, head_stride, norms, read_again_bytes, stream);
 }
 
 }  // namespace l2kv
