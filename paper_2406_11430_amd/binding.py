@@ -133,12 +133,15 @@ def _dev(*tensors: Optional[torch.Tensor]) -> None:
 
 
 def _ptr(t: Optional[torch.Tensor]):
-    return None if t is None else C.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()      # the argument types turn plain integers into pointers
 
 
 def _stream(stream: Optional[torch.cuda.Stream]):
-    s = torch.cuda.current_stream() if stream is None else stream
-    return C.c_void_p(s.cuda_stream)
+    # The current stream of the current device by its raw handle: building the stream object of
+    # torch.cuda.current_stream() only to ask it for the handle takes longer than the launch.
+    if stream is None:
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    return stream.cuda_stream
 
 
 # ------------------------------------------------------------ host helpers
