@@ -146,11 +146,21 @@ l2kv_status l2kv_compress(const void* K, const void* V, l2kv_dtype dt, int64_t n
         float* ns = norms + h0 * T;
         int32_t* is = kept_idx + h0 * k;
         const size_t dense = static_cast<size_t>(h0) * static_cast<size_t>(k) * static_cast<size_t>(D) * es;
-        l2kv_status st = norms_dispatch(Ks, dt, nh, T, D, head_stride, ns, read_again, s);
-        if (st == L2KV_OK) st = select_dispatch(ns, nh, T, k, L2KV_KEEP_LOWEST, is, nullptr, workspace, workspace_bytes, s);
-        if (st == L2KV_OK)
-            st = compact_dispatch(Ks, Vs, dt, is, nh, T, k, D, head_stride, static_cast<char*>(Kc) + dense,
-                                  static_cast<char*>(Vc) + dense, s);
+        char* Kd = static_cast<char*>(Kc) + dense;
+        char* Vd = static_cast<char*>(Vc) + dense;
+        const int32_t row_bytes = D * static_cast<int32_t>(es);
+        l2kv_status st;
+        if (compress_short_applies(nh, T, k, row_bytes)) {
+            st = compress_short_dispatch(Ks, Vs, dt, nh, T, D, head_stride, k, ns, is, Kd, Vd, s);
+        } else {
+            st = norms_dispatch(Ks, dt, nh, T, D, head_stride, ns, read_again, s);
+            if (st == L2KV_OK && select_compact_applies(nh, T, k, row_bytes)) {
+                st = select_compact_dispatch(ns, nh, T, k, Ks, Vs, dt, D, head_stride, is, Kd, Vd, s);
+            } else if (st == L2KV_OK) {
+                st = select_dispatch(ns, nh, T, k, L2KV_KEEP_LOWEST, is, nullptr, workspace, workspace_bytes, s);
+                if (st == L2KV_OK) st = compact_dispatch(Ks, Vs, dt, is, nh, T, k, D, head_stride, Kd, Vd, s);
+            }
+        }
         if (st != L2KV_OK) return st;
     }
     return L2KV_OK;

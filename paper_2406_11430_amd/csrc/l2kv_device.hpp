@@ -70,6 +70,21 @@ __device__ __forceinline__ uint32_t wave_inclusive_sum(uint32_t v) {
     return v;
 }
 
+// Smallest value over the 64 lanes of a wave, the same in all lanes (all must be active): lane pairs of the DPP row
+// as in row16_tree_sum, then the four rows.
+template <int CTRL>
+__device__ __forceinline__ uint32_t dpp_min(uint32_t v) {
+    const uint32_t o = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xf, 0xf, true);
+    return o < v ? o : v;
+}
+__device__ __forceinline__ uint32_t wave_min(uint32_t v) {
+    v = dpp_min<kDppMirror>(dpp_min<kDppHalfMirror>(dpp_min<kDppXor2>(dpp_min<kDppXor1>(v))));
+    const uint32_t a = __builtin_amdgcn_readlane((int)v, 0), b = __builtin_amdgcn_readlane((int)v, 16);
+    const uint32_t c = __builtin_amdgcn_readlane((int)v, 32), d = __builtin_amdgcn_readlane((int)v, 48);
+    const uint32_t ab = a < b ? a : b, cd = c < d ? c : d;
+    return ab < cd ? ab : cd;
+}
+
 // Number of lanes below this one whose bit is set.
 __device__ __forceinline__ uint32_t lanes_below(uint64_t mask) {
     return __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));

@@ -31,6 +31,16 @@ l2kv_status select_dispatch(const float* norms, int64_t n_heads, int64_t T, int6
                             l2kv_mode mode, int32_t* kept_idx, int32_t* kept_count,
                             void* workspace, size_t workspace_bytes, hipStream_t stream);
 size_t select_workspace_bytes(int64_t n_heads, int64_t T);
+// Selection (keep lowest) and compaction in one launch, for short heads; where it applies.
+bool select_compact_applies(int64_t n_heads, int64_t T, int64_t k, int32_t row_bytes);
+l2kv_status select_compact_dispatch(const float* norms, int64_t n_heads, int64_t T, int64_t k, const void* K, const void* V,
+                                    l2kv_dtype dt, int32_t D, int64_t head_stride, int32_t* kept_idx, void* Kc, void* Vc,
+                                    hipStream_t stream);
+// The norms as well, for the shortest.
+bool compress_short_applies(int64_t n_heads, int64_t T, int64_t k, int32_t row_bytes);
+l2kv_status compress_short_dispatch(const void* K, const void* V, l2kv_dtype dt, int64_t n_heads, int64_t T, int32_t D,
+                                    int64_t head_stride, int64_t k, float* norms, int32_t* kept_idx, void* Kc, void* Vc,
+                                    hipStream_t stream);
 
 l2kv_status random_keys_dispatch(int64_t n_heads, int64_t T, uint32_t seed, float* keys, hipStream_t stream);
 

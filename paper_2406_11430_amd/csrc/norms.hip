@@ -20,6 +20,7 @@
 // each piece slot and the two slots are added last (chunks 0..7 + chunks 8..15).
 #include "l2kv_device.hpp"
 #include "l2kv_host.hpp"
+#include "row_norm.hpp"
 
 namespace l2kv {
 
@@ -94,47 +95,7 @@ void norms_kernel(const char* __restrict__ K, int64_t T, int64_t head_stride_byt
     for (int u = 0; u < kNormUnroll; ++u) {
         float x[S::kElems];
         widen<E, D>(raw[u], x);
-        float total;
-        if constexpr (P::kCount == 1) {
-            float acc = x[0] * x[0];
-#pragma unroll
-            for (int e = 1; e < S::kElems; ++e) {
-                float sq = x[e] * x[e];
-                acc = acc + sq;
-            }
-            total = row16_tree_sum(acc);
-        } else {
-            constexpr int n = S::kElems / 2;              // elements per piece; x[s * n ..] = piece slot s
-            float t[2];
-#pragma unroll
-            for (int s = 0; s < 2; ++s) {
-                // first half of a chunk (valid in even lanes): 0 + x0^2 is x0^2 exactly
-                float acc = 0.f;
-#pragma unroll
-                for (int e = 0; e < n; ++e) {
-                    float sq = x[s * n + e] * x[s * n + e];
-                    acc = acc + sq;
-                }
-                // second half (valid in odd lanes): continue from the even neighbour's sum.  Even
-                // lanes continue from their own sum; their result is overwritten below.  (No
-                // select on the lane parity here: the cross-lane read must run with all lanes
-                // active.)
-                float full = dpp_read<kDppQuadEven>(acc);
-#pragma unroll
-                for (int e = 0; e < n; ++e) {
-                    float sq = x[s * n + e] * x[s * n + e];
-                    full = full + sq;
-                }
-                // chunk sums sit in the odd lanes: copy to the even neighbour, then the tree
-                // over the 8 chunks of this slot
-                float v = dpp_read<kDppQuadOdd>(full);
-                v = v + dpp_read<kDppXor2>(v);
-                v = v + dpp_read<kDppHalfMirror>(v);
-                v = v + dpp_read<kDppMirror>(v);
-                t[s] = v;
-            }
-            total = t[0] + t[1];
-        }
+        const float total = chunked_sum_of_squares<E, D>(x);
         mine = (c == u) ? total : mine;   // lane c keeps the sum of row u
     }
     const int64_t row = first + c;
@@ -181,21 +142,7 @@ void norms_row_pairs_kernel(const char* __restrict__ K, int64_t T, int64_t head_
     float mine = 0.f;
 #pragma unroll
     for (int u = 0; u < kNormUnroll; ++u) {
-        float x[8];
-        widen<BF16, 128>(raw[u], x);      // 4 words -> 8 values in element order
-        float a = x[0] * x[0];
-        float b = x[4] * x[4];
-#pragma unroll
-        for (int e = 1; e < 4; ++e) {
-            float sa = x[e] * x[e];
-            float sb = x[4 + e] * x[4 + e];
-            a = a + sa;
-            b = b + sb;
-        }
-        float v = a + b;                                  // chunks 2j and 2j+1
-        v = v + dpp_read<kDppXor1>(v);
-        v = v + dpp_read<kDppXor2>(v);
-        v = v + dpp_read<kDppHalfMirror>(v);              // the 8 lanes of this row
+        const float v = row_pair_sum_of_squares(raw[u]);  // of this lane's row
         mine = (j == u) ? v : mine;       // lane j of each half keeps the sum of pair u's row
     }
     const int64_t row = 2 * (first + j) + half;

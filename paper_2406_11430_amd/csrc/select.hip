@@ -5,17 +5,18 @@
 // with ties resolved towards the lower token index.
 //
 // The k-th smallest key tau (key = norm bits, complemented for the keep-highest
-// control) is found exactly, digit by digit from the top: 12, 10 and 10 bits.
-// Each step counts the keys that agree with tau so far in an LDS histogram of
-// their next digit and walks its prefix sums to the digit that holds the k-th
-// key.  (A binary search over the 32 bits, one barrier and one compare per key
-// and bit, was what this replaces: 40 us for 256 heads of 32k tokens against 18 us,
-// 306 us for 8 heads of 131k against 18 us.)  The emit is ordered: every wave owns a contiguous token
+// control) is found exactly: the keys are counted in 4096 LDS bins of equal width between the
+// smallest and the largest of the head, and the prefix sums lead to the bin that holds the k-th.  The bin's
+// keys, a few dozen as a rule, are listed and compared with each other; a fuller bin (tied or
+// clustered norms) is divided into 4096 again, at most twice, until its keys are few or equal.
+// Bound by the LDS round trips and barriers of that chain, not by its arithmetic: SEARCH_FIG
+// (A binary search over the 32 bits, one barrier and one compare per key
+// and bit, took 40 us for 256 heads of 32k tokens.)  The emit is ordered: every wave owns a contiguous token
 // range, so a prefix over the wave totals plus a running ballot prefix gives
 // each kept token its output slot; keys equal to tau are admitted in token order
 // until the budget k is met.
 //
-// Two launch shapes:
+// Four launch shapes:
 //  - one workgroup of 1024 lanes per head, its keys in registers (up to 32 per
 //    lane) or, for longer heads, re-read from the L2 in every step;
 //  - few heads, or long ones: each head is cut into chunks and three kernels
@@ -23,6 +24,7 @@
 //    (select_plan below has the rule).
 #include "l2kv_device.hpp"
 #include "l2kv_host.hpp"
+#include "row_norm.hpp"
 
 namespace l2kv {
 
@@ -31,7 +33,7 @@ constexpr int kSelWaves = kSelThreads / kWaveSize;   // 16
 constexpr int kSelMaxRegKeys = 32;                   // keys per lane held in registers
 constexpr int kSelBatch = 8;                         // keys per lane fetched together when they are re-read
 
-// Digits of the search, from the top.
+// Digits of the search over several workgroups, from the top.
 constexpr int kTopBits = 12, kMidBits = 10, kLowBits = 10;
 static_assert(kTopBits + kMidBits + kLowBits == 32, "digits cover the key");
 constexpr int kTopBins = 1 << kTopBits, kMidBins = 1 << kMidBits, kLowBins = 1 << kLowBits;
@@ -55,7 +57,7 @@ __device__ __forceinline__ void clear_counts(uint32_t* hist, int words) {
 }
 
 // Where the k-th key lies in a histogram: its digit and the number of keys in lower digits.
-struct Found { uint32_t digit, below; };
+struct Found { uint32_t digit, below, count; };
 
 struct FindShared {
     uint32_t wave_total[kSelWaves];
@@ -88,6 +90,7 @@ __device__ __forceinline__ Found find_digit(const uint32_t* hist, uint32_t want,
             if (before < want && want <= before + c[i]) {
                 sh.found.digit = (uint32_t)(threadIdx.x * kPer + i);
                 sh.found.below = before;
+                sh.found.count = c[i];
             }
             before += c[i];
         }
@@ -99,13 +102,12 @@ __device__ __forceinline__ Found find_digit(const uint32_t* hist, uint32_t want,
 // Ordered emit shared by both launch shapes.  Every wave of the workgroup owns `iters` * 64
 // consecutive positions of [t0, ...); fetch(e) is this lane's key of iteration e (positions past
 // the end read as the largest key and come after every real one).  lt_before / eq_before: keys
-// below / equal to tau ahead of this workgroup's range.
+// below / equal to tau ahead of this workgroup's range.  put(i, t): token t is the i-th kept one.
 struct EmitShared { uint32_t lt[kSelWaves], eq[kSelWaves]; };
 
-template <int kUnroll, typename Fetch>
+template <int kUnroll, typename Fetch, typename Put>
 __device__ __forceinline__ void emit_ordered(Fetch fetch, int64_t iters, uint32_t t0, uint32_t tau, uint32_t need_eq,
-                                             uint32_t lt_before, uint32_t eq_before, int32_t* __restrict__ out,
-                                             EmitShared& sh) {
+                                             uint32_t lt_before, uint32_t eq_before, Put put, EmitShared& sh) {
     const int lane = threadIdx.x % kWaveSize;
     const int wave = threadIdx.x / kWaveSize;
     uint32_t lt_w = 0, eq_w = 0;
@@ -149,7 +151,7 @@ __device__ __forceinline__ void emit_ordered(Fetch fetch, int64_t iters, uint32_
         for_iters([&](uint32_t key, int32_t t) {
             const bool keep = key <= limit;
             const uint64_t keep_mask = __ballot(keep);
-            if (keep) out[out_base + lanes_below(keep_mask)] = t;
+            if (keep) put(out_base + lanes_below(keep_mask), t);
             out_base += __popcll(keep_mask);
         });
     } else {
@@ -160,7 +162,7 @@ __device__ __forceinline__ void emit_ordered(Fetch fetch, int64_t iters, uint32_
             const uint64_t eq_mask = __ballot(is_eq);
             const bool keep = key < tau || (is_eq && (eq_base + lanes_below(eq_mask)) < need_eq);
             const uint64_t keep_mask = __ballot(keep);
-            if (keep) out[out_base + lanes_below(keep_mask)] = t;
+            if (keep) put(out_base + lanes_below(keep_mask), t);
             out_base += __popcll(keep_mask);
             eq_base += __popcll(eq_mask);
         });
@@ -170,6 +172,144 @@ __device__ __forceinline__ void emit_ordered(Fetch fetch, int64_t iters, uint32_
 // ---- one workgroup per head ---------------------------------------------------------------
 // E > 0 : keys of the head fit E per lane and are cached in registers.
 // E == 0: streaming variant, keys are re-read from memory (L2) in every pass.
+template <int E> struct HeadKeys {
+    const uint32_t* src;
+    uint32_t T, flip, t0;                 // t0: first token of the wave's range
+    int64_t iters;
+    uint32_t regs[E > 0 ? E : 1];
+    // Wave w owns tokens [w*span, (w+1)*span), span a multiple of 64; iteration
+    // e of lane l looks at token w*span + e*64 + l.
+    __device__ __forceinline__ HeadKeys(const uint32_t* s, int64_t count, uint32_t f) : src(s), T((uint32_t)count), flip(f) {
+        iters = E > 0 ? E : ((count + (int64_t)kSelThreads * kSelBatch - 1) / ((int64_t)kSelThreads * kSelBatch) * kSelBatch);
+        t0 = (uint32_t)(threadIdx.x / kWaveSize * iters * kWaveSize);     // T < 2^31 and the padded range ends below T + 2^14
+        if constexpr (E > 0) {
+#pragma unroll
+            for (int e = 0; e < E; ++e) regs[e] = fetch_mem(e);
+        }
+    }
+    __device__ __forceinline__ uint32_t token(int64_t e) const { return t0 + (uint32_t)e * kWaveSize + threadIdx.x % kWaveSize; }
+    // Branch-free: positions past the end re-read the last key (in bounds) and
+    // are replaced by the largest key, which is never "below" anything.  Such
+    // padding sits after every real token, so in the ordered emit it is reached
+    // only after all real keys equal to tau, when the budget is already met.
+    __device__ __forceinline__ uint32_t fetch_mem(int64_t e) const {
+        const uint32_t t = token(e);
+        const uint32_t v = src[t < T ? t : T - 1] ^ flip;
+        return t < T ? v : 0xffffffffu;
+    }
+    __device__ __forceinline__ uint32_t fetch(int64_t e) const {
+        if constexpr (E > 0) return regs[e];
+        else return fetch_mem(e);
+    }
+    // body(key, real) for every key once, in batches whose loads are issued together
+    template <typename F> __device__ __forceinline__ void each(F&& body) const {
+        if constexpr (E > 0) {
+            uint32_t left = T - token(0);                     // negative past the end; fresh masks in every pass
+            asm volatile("" : "+v"(left));
+#pragma unroll
+            for (int e = 0; e < E; ++e) body(regs[e], (int32_t)left > e * kWaveSize);
+        } else {
+            for (int64_t e0 = 0; e0 < iters; e0 += kSelBatch) {
+                uint32_t key[kSelBatch];
+#pragma unroll
+                for (int u = 0; u < kSelBatch; ++u) key[u] = fetch_mem(e0 + u);
+#pragma unroll
+                for (int u = 0; u < kSelBatch; ++u) body(key[u], token(e0 + u) < T);
+            }
+        }
+    }
+};
+
+constexpr uint32_t kListedKeys = 256;                 // keys of a bin that are compared with each other
+struct SearchShared {
+    uint32_t hist[kTopBins * kCopies];                // 64 KB: two workgroups per compute unit
+    uint32_t list[kListedKeys];
+    uint32_t lo[kSelWaves], hi[kSelWaves];
+    FindShared find;
+    uint32_t listed, tau, need_eq;
+};
+struct Threshold { uint32_t tau, need_eq; };          // need_eq >= 1 keys equal to tau are kept, lowest tokens first
+
+// The k-th smallest of a head's keys, 1 <= k <= their number.  Called by all 1024 lanes.
+template <int E>
+__device__ __forceinline__ Threshold find_threshold(const HeadKeys<E>& keys, uint32_t k, SearchShared& sh) {
+    const int lane = threadIdx.x % kWaveSize;
+    const int wave = threadIdx.x / kWaveSize;
+    uint32_t lo = 0xffffffffu, hi = 0u;
+    keys.each([&](uint32_t key, bool real) {
+        lo = key < lo ? key : lo;                     // the padding is the largest key
+        hi = real && key > hi ? key : hi;
+    });
+    lo = wave_min(lo);
+    hi = ~wave_min(~hi);
+    if (lane == 0) {
+        sh.lo[wave] = lo;
+        sh.hi[wave] = hi;
+    }
+    if (threadIdx.x == 0) sh.listed = 0;
+    clear_counts(sh.hist, kTopBins * kCopies);
+    __syncthreads();
+#pragma unroll
+    for (int w = 0; w < kSelWaves; ++w) {
+        lo = sh.lo[w] < lo ? sh.lo[w] : lo;
+        hi = sh.hi[w] > hi ? sh.hi[w] : hi;
+    }
+    lo = __builtin_amdgcn_readfirstlane(lo);
+    hi = __builtin_amdgcn_readfirstlane(hi);
+    // every pass computes the bins afresh: kept from one pass to the next they would not fit the registers
+    auto origin = [&] { uint32_t v = lo; asm volatile("" : "+s"(v)); return v; };
+    const int bits = hi == lo ? 0 : 32 - __builtin_clz(hi - lo);
+    int shift = bits > kTopBits ? bits - kTopBits : 0;
+    // (the padding falls into the last bin: it comes after all real keys and k is at most their number)
+    uint32_t o = origin();
+    keys.each([&](uint32_t key, bool) {
+        const uint32_t b = (key - o) >> shift;
+        count_digit(sh.hist, b < kTopBins ? b : kTopBins - 1);
+    });
+    __syncthreads();
+    Found f = find_digit<kTopBins>(sh.hist, k, sh.find);
+    uint32_t want = k - f.below;
+    uint32_t bin = __builtin_amdgcn_readfirstlane(f.digit);           // (key - lo) >> shift of the wanted key
+    uint32_t count = __builtin_amdgcn_readfirstlane(f.count);
+    while (shift > 0 && count > kListedKeys) {
+        const int finer = shift > kTopBits ? shift - kTopBits : 0;
+        clear_counts(sh.hist, kTopBins * kCopies);
+        __syncthreads();
+        o = origin();
+        keys.each([&](uint32_t key, bool) {
+            if ((key - o) >> shift == bin) count_digit(sh.hist, ((key - o) >> finer) - (bin << (shift - finer)));
+        });
+        __syncthreads();
+        f = find_digit<kTopBins>(sh.hist, want, sh.find);
+        want -= f.below;
+        bin = (bin << (shift - finer)) + __builtin_amdgcn_readfirstlane(f.digit);
+        count = __builtin_amdgcn_readfirstlane(f.count);
+        shift = finer;
+    }
+    if (shift == 0) return Threshold{lo + bin, want};                 // one key per bin
+    o = origin();
+    keys.each([&](uint32_t key, bool) {
+        if ((key - o) >> shift == bin) sh.list[atomicAdd(&sh.listed, 1u)] = key;
+    });
+    __syncthreads();
+    count = sh.listed;                                                // without padding that was counted with the last bin
+    if (threadIdx.x < count) {
+        const uint32_t key = sh.list[threadIdx.x];
+        uint32_t less = 0, equal = 0;
+        for (uint32_t j = 0; j < count; ++j) {
+            const uint32_t other = sh.list[j];
+            less += other < key ? 1u : 0u;
+            equal += other == key ? 1u : 0u;
+        }
+        if (less < want && want <= less + equal) {                    // the wanted key, and its equals alike
+            sh.tau = key;
+            sh.need_eq = want - less;
+        }
+    }
+    __syncthreads();
+    return Threshold{sh.tau, sh.need_eq};
+}
+
 // Ragged batches: [n_planes][total_in] norms, sequence s at in_off[s]..in_off[s+1];
 // its kept positions (relative to the sequence start) go to
 // [n_planes][total_out] at out_off[s]..out_off[s+1].  in_off == NULL: uniform.
@@ -184,97 +324,170 @@ __global__ __launch_bounds__(kSelThreads)
 void select_kernel(const uint32_t* __restrict__ norm_bits, int64_t T, uint32_t k, uint32_t flip,
                    int32_t* __restrict__ kept_idx, int32_t* __restrict__ kept_count,
                    RaggedSelect rag) {
-    constexpr bool kInRegs = E > 0;
-    // the counters of the lowest digit reuse those of the top one: 80 KB, two workgroups per compute unit
-    __shared__ __attribute__((aligned(16))) uint32_t s_hist[(kTopBins + kMidBins) * kCopies];
-    __shared__ FindShared s_find;
+    __shared__ __attribute__((aligned(16))) SearchShared s_search;
     __shared__ EmitShared s_emit;
 
     const int64_t head = blockIdx.x;
-    const int lane = threadIdx.x % kWaveSize;
-    const int wave = threadIdx.x / kWaveSize;
     const uint32_t* src = norm_bits + head * T;
     int32_t* out = kept_idx + head * (int64_t)k;
     if (rag.in_off != nullptr) {
         // ragged batch: block = (plane, sequence); sizes and places come from the offset arrays
-        const int64_t plane = head / rag.n_seq;
-        const int64_t seq = head % rag.n_seq;
+        const int64_t plane = (uint32_t)head / (uint32_t)rag.n_seq;
+        const int64_t seq = (uint32_t)head % (uint32_t)rag.n_seq;
         const Range in = clamped_range(rag.in_off, seq, rag.total_in);
         const Range outr = clamped_range(rag.out_off, seq, rag.total_out);
         T = in.count;
         // the register variants see the first 1024 * E tokens (the caller's bound on the lengths)
-        if (kInRegs && T > (int64_t)E * kSelThreads) T = (int64_t)E * kSelThreads;
+        if (E > 0 && T > (int64_t)E * kSelThreads) T = (int64_t)E * kSelThreads;
         const int64_t kk = outr.count;
         if (T <= 0 || kk <= 0) return;                       // whole workgroup: nothing to select
         k = (uint32_t)(kk < T ? kk : T);                     // never more than there are
         src = norm_bits + plane * rag.total_in + in.first;
         out = kept_idx + plane * rag.total_out + outr.first;
     }
+    const HeadKeys<E> keys(src, T, flip);
+    const Threshold th = find_threshold(keys, k, s_search);
+    emit_ordered<E == 0 ? kSelBatch : E>([&](int64_t e) { return keys.fetch(e); }, E == 0 ? keys.iters : E, keys.t0, th.tau,
+                                         th.need_eq, 0u, 0u, [&](uint32_t i, int32_t t) { out[i] = t; }, s_emit);
+    if (kept_count != nullptr && threadIdx.x == 0) kept_count[head] = (int32_t)k;
+}
 
-    // Wave w owns tokens [w*span, (w+1)*span), span a multiple of 64; iteration
-    // e of lane l looks at token w*span + e*64 + l.
-    const int64_t iters = kInRegs ? E
-                                  : ((T + (int64_t)kSelThreads * kSelBatch - 1) / ((int64_t)kSelThreads * kSelBatch) * kSelBatch);
-    const uint32_t t0 = (uint32_t)(wave * iters * kWaveSize);     // T < 2^31 and the padded range ends below T + 2^14
-    const uint32_t T32 = (uint32_t)T;
+// ---- selection and compaction of short heads in one launch ------------------------------------
+// The kept rows of a head are shared by gridDim.x workgroups.  Each finds the threshold by itself (the keys of a
+// short head are a few per lane, so repeating the search costs less than the launch and the round trip
+// through memory that a search of its own takes), writes its share of the indices and copies
+// its share of the rows.  32 heads of 4k, half kept: 24.4 us for norms and this launch, 25.3 for the three kernels;
+// 8 heads of 4k 15.7 against 17.1.
+constexpr int kFuseMaxTokens = 8 * kSelThreads;
+constexpr int kFuseMaxHeads = 256, kFuseWorkgroups = 512;
+constexpr int64_t kFuseMaxBytes = int64_t{20} << 20, kShortMaxBytes = int64_t{2} << 20;
+constexpr int kFuseRows = 4096;                       // most rows of a share: indices in LDS as 16-bit numbers
+static_assert(kFuseMaxTokens <= 65536, "token indices fit 16 bits");
 
-    // Branch-free: positions past the end re-read the last key (in bounds) and
-    // are replaced by the largest key, which is never "below" anything.  Such
-    // padding sits after every real token, so in the ordered emit it is reached
-    // only after all real keys equal to tau, when the budget is already met.
-    auto fetch_mem = [&](int64_t e) -> uint32_t {
-        const uint32_t t = t0 + (uint32_t)e * kWaveSize + lane;
-        const uint32_t v = src[t < T32 ? t : T32 - 1] ^ flip;
-        return t < T32 ? v : 0xffffffffu;
-    };
-    uint32_t regs[kInRegs ? E : 1];
-    if constexpr (kInRegs) {
-#pragma unroll
-        for (int e = 0; e < E; ++e) regs[e] = fetch_mem(e);
-    }
-    clear_counts(s_hist, (kTopBins + kMidBins) * kCopies);
+struct FuseShared {
+    SearchShared search;
+    EmitShared emit;
+    uint16_t row[kFuseRows];
+};
+
+// Rows [r0, r0 + rows) of the kept rows of a head: selection by all lanes, indices, copy of K and V.  K, V, out, Kc,
+// Vc point at the head.
+template <int E, int kRowBytes>
+__device__ __forceinline__ void select_and_copy(const HeadKeys<E>& keys, uint32_t k, uint32_t r0, uint32_t rows,
+                                                const char* __restrict__ K, const char* __restrict__ V, int32_t* __restrict__ out,
+                                                char* __restrict__ Kc, char* __restrict__ Vc, FuseShared& sh) {
+    const Threshold th = find_threshold(keys, k, sh.search);
+    emit_ordered<E>([&](int64_t e) { return keys.fetch(e); }, E, keys.t0, th.tau, th.need_eq, 0u, 0u,
+                    [&](uint32_t i, int32_t t) {
+                        if (i - r0 < rows) {
+                            sh.row[i - r0] = (uint16_t)t;
+                            out[i] = t;
+                        }
+                    }, sh.emit);
     __syncthreads();
-
-    // every key once, in batches whose loads are issued together
-    auto for_keys = [&](auto&& body) {
-        if constexpr (kInRegs) {
+    using P = RowCopy<kRowBytes>;
+    constexpr uint32_t kRowsPerStep = kSelThreads / P::kLanes;
+    constexpr int kUnroll = 2;
+    const uint32_t c = threadIdx.x % P::kLanes, rg = threadIdx.x / P::kLanes;
+    for (uint32_t base = 0; base < rows; base += kRowsPerStep * kUnroll) {
+        Words<P::kWords> a[kUnroll], b[kUnroll];
 #pragma unroll
-            for (int e = 0; e < E; ++e) body(regs[e]);
-        } else {
-            for (int64_t e0 = 0; e0 < iters; e0 += kSelBatch) {
-                uint32_t key[kSelBatch];
+        for (int u = 0; u < kUnroll; ++u) {
+            const uint32_t r = base + u * kRowsPerStep + rg;
+            const int64_t from = sh.row[r < rows ? r : rows - 1] * (int64_t)kRowBytes + c * 16;
+            a[u] = load_words_stream<P::kWords, P::kStride>(K + from);
+            b[u] = load_words_stream<P::kWords, P::kStride>(V + from);
+        }
 #pragma unroll
-                for (int u = 0; u < kSelBatch; ++u) key[u] = fetch_mem(e0 + u);
-#pragma unroll
-                for (int u = 0; u < kSelBatch; ++u) body(key[u]);
+        for (int u = 0; u < kUnroll; ++u) {
+            const uint32_t r = base + u * kRowsPerStep + rg;
+            const int64_t to = (r0 + (int64_t)r) * kRowBytes + c * 16;
+            if (r < rows) {
+                store_words_stream<P::kWords, P::kStride>(Kc + to, a[u]);
+                store_words_stream<P::kWords, P::kStride>(Vc + to, b[u]);
             }
         }
-    };
-    uint32_t* const h_top = s_hist;
-    uint32_t* const h_mid = s_hist + kTopBins * kCopies;
-    uint32_t* const h_low = s_hist;
-    // (the padding is counted too: it comes after all real keys and k is at most their number)
-    for_keys([&](uint32_t key) { count_digit(h_top, key >> (32 - kTopBits)); });
-    __syncthreads();
-    const Found top = find_digit<kTopBins>(h_top, k, s_find);
-    clear_counts(h_low, kLowBins * kCopies);         // in use again two barriers from here
-    for_keys([&](uint32_t key) {
-        if (key >> (32 - kTopBits) == top.digit) count_digit(h_mid, (key >> kLowBits) & (kMidBins - 1));
-    });
-    __syncthreads();
-    const Found mid = find_digit<kMidBins>(h_mid, k - top.below, s_find);
-    const uint32_t prefix = (top.digit << kMidBits) | mid.digit;
-    for_keys([&](uint32_t key) {
-        if (key >> kLowBits == prefix) count_digit(h_low, key & (kLowBins - 1));
-    });
-    __syncthreads();
-    const Found low = find_digit<kLowBins>(h_low, k - top.below - mid.below, s_find);
-    const uint32_t tau = (prefix << kLowBits) | low.digit;
-    const uint32_t need_eq = k - top.below - mid.below - low.below;   // >= 1 keys equal to tau are kept, lowest tokens first
+    }
+}
 
-    if constexpr (kInRegs) emit_ordered<E>([&](int64_t e) { return regs[e]; }, E, t0, tau, need_eq, 0u, 0u, out, s_emit);
-    else emit_ordered<kSelBatch>(fetch_mem, iters, t0, tau, need_eq, 0u, 0u, out, s_emit);
-    if (kept_count != nullptr && threadIdx.x == 0) kept_count[head] = (int32_t)k;
+template <int E, int kRowBytes>
+__global__ __launch_bounds__(kSelThreads)
+void select_compact_kernel(const uint32_t* __restrict__ norm_bits, int64_t T, uint32_t k, uint32_t rows_per_share,
+                           const char* __restrict__ K, const char* __restrict__ V, int64_t head_stride_bytes,
+                           int32_t* __restrict__ kept_idx, char* __restrict__ Kc, char* __restrict__ Vc) {
+    __shared__ __attribute__((aligned(16))) FuseShared sh;
+    const int64_t head = blockIdx.y;
+    const uint32_t r0 = blockIdx.x * rows_per_share;
+    if (r0 >= k) return;
+    const HeadKeys<E> keys(norm_bits + head * T, T, 0u);
+    const int64_t dense = head * (int64_t)k;
+    select_and_copy<E, kRowBytes>(keys, k, r0, k - r0 < rows_per_share ? k - r0 : rows_per_share, K + head * head_stride_bytes,
+                                  V + head * head_stride_bytes, kept_idx + dense, Kc + dense * kRowBytes, Vc + dense * kRowBytes, sh);
+}
+
+// The whole compression of heads of at most 1024 tokens in one launch: every share also computes all norms of its
+// head (out of the L2 for all but the first reader), the first share writes them.  Meant for the
+// smallest calls, whose time is the number of launches: 4 heads of 512
+// tokens, half kept, 10 us against 16 for three kernels (of 2.4, 5.7 and 3.3 us).  Not beyond 2 MB of K, which the
+// shares read over and over: 32 heads of 1000 tokens (8 MB) 18.2 against 14.7 for two launches.
+template <typename E, int D>
+__global__ __launch_bounds__(kSelThreads)
+void compress_short_kernel(const char* __restrict__ K, const char* __restrict__ V, int64_t T, uint32_t k,
+                           uint32_t rows_per_share, int64_t head_stride_bytes, float* __restrict__ norms,
+                           int32_t* __restrict__ kept_idx, char* __restrict__ Kc, char* __restrict__ Vc) {
+    using S = Slice<E, D>;
+    __shared__ __attribute__((aligned(16))) FuseShared sh;
+    __shared__ float s_norm[kSelThreads];
+    const int64_t head = blockIdx.y;
+    const uint32_t r0 = blockIdx.x * rows_per_share;
+    if (r0 >= k) return;
+    const char* Kh = K + head * head_stride_bytes;
+    const uint32_t n = (uint32_t)T;
+    const int c = threadIdx.x % kRowLanes;
+    constexpr uint32_t kGroups = kSelThreads / kRowLanes;            // 64 row groups
+    constexpr int kBatch = 4;
+    if constexpr (S::kRowBytes == 128) {
+        // pairs of rows, 8 lanes each
+        for (uint32_t base = 0; base < n; base += 2 * kGroups * kBatch) {
+            Words<4> raw[kBatch];
+#pragma unroll
+            for (int u = 0; u < kBatch; ++u) {
+                const uint32_t row = base + 2 * (u * kGroups + threadIdx.x / kRowLanes) + c / 8;
+                raw[u] = load_words<4>(Kh + (row < n ? row : n - 1) * (int64_t)S::kRowBytes + (c % 8) * 16);
+            }
+#pragma unroll
+            for (int u = 0; u < kBatch; ++u) {
+                const uint32_t row = base + 2 * (u * kGroups + threadIdx.x / kRowLanes) + c / 8;
+                const float v = row_pair_sum_of_squares(raw[u]);
+                if (c % 8 == 0 && row < n) s_norm[row] = v;
+            }
+        }
+    } else {
+        using P = Pieces<S::kWords>;
+        for (uint32_t base = 0; base < n; base += kGroups * kBatch) {
+            Words<S::kWords> raw[kBatch];
+#pragma unroll
+            for (int u = 0; u < kBatch; ++u) {
+                const uint32_t row = base + u * kGroups + threadIdx.x / kRowLanes;
+                raw[u] = load_words<S::kWords, P::kStride>(Kh + (row < n ? row : n - 1) * (int64_t)S::kRowBytes + c * P::kBytes);
+            }
+#pragma unroll
+            for (int u = 0; u < kBatch; ++u) {
+                const uint32_t row = base + u * kGroups + threadIdx.x / kRowLanes;
+                float x[S::kElems];
+                widen<E, D>(raw[u], x);
+                const float v = chunked_sum_of_squares<E, D>(x);
+                if (c == 0 && row < n) s_norm[row] = v;
+            }
+        }
+    }
+    __syncthreads();
+    if (blockIdx.x == 0 && threadIdx.x < n) norms[head * T + threadIdx.x] = s_norm[threadIdx.x];
+    const HeadKeys<1> keys(reinterpret_cast<const uint32_t*>(s_norm), T, 0u);
+    const int64_t dense = head * (int64_t)k;
+    select_and_copy<1, S::kRowBytes>(keys, k, r0, k - r0 < rows_per_share ? k - r0 : rows_per_share, Kh,
+                                     V + head * head_stride_bytes, kept_idx + dense, Kc + dense * S::kRowBytes,
+                                     Vc + dense * S::kRowBytes, sh);
 }
 
 // ---- several workgroups per head -------------------------------------------------------------
@@ -372,7 +585,7 @@ __device__ __forceinline__ Found find_lane(uint32_t count, uint32_t want) {
     const uint32_t incl = wave_inclusive_sum(count);
     const uint64_t past = __ballot(incl >= want);
     const int at = (int)__builtin_ctzll(past);               // want <= total: some lane qualifies
-    return Found{(uint32_t)at, __shfl(incl - count, at)};
+    return Found{(uint32_t)at, __shfl(incl - count, at), __shfl(count, at)};
 }
 
 __global__ __launch_bounds__(kSelThreads)
@@ -542,7 +755,8 @@ void select_emit_kernel(const uint32_t* __restrict__ norm_bits, int64_t T, uint3
             const uint32_t v = src[t < end ? t : end - 1] ^ flip;
             return t < end ? v : 0xffffffffu;
         },
-        iters, t0, tau, need_eq, s_lt_ahead + s_cand_lt, s_cand_eq, kept_idx + head * (int64_t)k, s_emit);
+        iters, t0, tau, need_eq, s_lt_ahead + s_cand_lt, s_cand_eq,
+        [&](uint32_t i, int32_t t) { kept_idx[head * (int64_t)k + i] = t; }, s_emit);
     if (kept_count != nullptr && blockIdx.x == 0 && threadIdx.x == 0) kept_count[head] = (int32_t)k;
 }
 
@@ -632,6 +846,62 @@ l2kv_status select_dispatch(const float* norms, int64_t n_heads, int64_t T, int6
     hipLaunchKernelGGL(select_gather_kernel, grid, dim3(kSelThreads), 0, stream, bits, T, (uint32_t)k, flip, sp);
     hipLaunchKernelGGL(select_emit_kernel, grid, dim3(kSelThreads), 0, stream, bits, T, (uint32_t)k, flip, kept_idx,
                        kept_count, sp);
+    return launch_status();
+}
+
+template <int E>
+static void launch_select_compact(const dim3 grid, int row_bytes, const float* norms, int64_t T, int64_t k, int64_t rows,
+                                  const void* K, const void* V, int64_t head_stride_bytes, int32_t* kept_idx, void* Kc,
+                                  void* Vc, hipStream_t stream) {
+    auto kernel = row_bytes == 128 ? select_compact_kernel<E, 128>
+                  : row_bytes == 256 ? select_compact_kernel<E, 256> : select_compact_kernel<E, 512>;
+    hipLaunchKernelGGL(kernel, grid, dim3(kSelThreads), 0, stream, reinterpret_cast<const uint32_t*>(norms), T, (uint32_t)k,
+                       (uint32_t)rows, static_cast<const char*>(K), static_cast<const char*>(V), head_stride_bytes, kept_idx,
+                       static_cast<char*>(Kc), static_cast<char*>(Vc));
+}
+
+// Where the kept rows fill the memory system for longer than the repeated search takes, a selection and a
+// compaction are the faster pair: 128
+// heads of 4k in fp32 (128 MB of kept rows) 126 us against 136, 32 heads of 8k (64 MB) 66 against 71; 32 of 4k in
+// bf16 (16 MB) the other way round, 25.3 against 24.4.
+bool select_compact_applies(int64_t n_heads, int64_t T, int64_t k, int32_t row_bytes) {
+    return T <= kFuseMaxTokens && n_heads <= kFuseMaxHeads && n_heads * k * row_bytes <= kFuseMaxBytes;
+}
+bool compress_short_applies(int64_t n_heads, int64_t T, int64_t k, int32_t row_bytes) {
+    return T <= kSelThreads && select_compact_applies(n_heads, T, k, row_bytes) && n_heads * T * row_bytes <= kShortMaxBytes;
+}
+
+// Rows of a share: a multiple of 16, and as many shares as run at once.
+static int64_t rows_per_share(int64_t n_heads, int64_t k, int64_t least) {
+    const int64_t shares = (kFuseWorkgroups + n_heads - 1) / n_heads;
+    const int64_t rows = ((k + shares - 1) / shares + 15) / 16 * 16;
+    return rows > least ? rows : least;
+}
+
+l2kv_status select_compact_dispatch(const float* norms, int64_t n_heads, int64_t T, int64_t k, const void* K, const void* V,
+                                    l2kv_dtype dt, int32_t D, int64_t head_stride, int32_t* kept_idx, void* Kc, void* Vc,
+                                    hipStream_t stream) {
+    const int es = dt == L2KV_F32 ? 4 : 2;
+    const int64_t rows = rows_per_share(n_heads, k, 16);
+    const dim3 grid((unsigned)((k + rows - 1) / rows), (unsigned)n_heads);
+    const int64_t per_lane = (T + kSelThreads - 1) / kSelThreads;
+    auto launch = per_lane <= 1 ? launch_select_compact<1> : per_lane <= 2 ? launch_select_compact<2>
+                  : per_lane <= 4 ? launch_select_compact<4> : launch_select_compact<8>;
+    launch(grid, D * es, norms, T, k, rows, K, V, head_stride * es, kept_idx, Kc, Vc, stream);
+    return launch_status();
+}
+
+l2kv_status compress_short_dispatch(const void* K, const void* V, l2kv_dtype dt, int64_t n_heads, int64_t T, int32_t D,
+                                    int64_t head_stride, int64_t k, float* norms, int32_t* kept_idx, void* Kc, void* Vc,
+                                    hipStream_t stream) {
+    const int64_t rows = rows_per_share(n_heads, k, 64);             // every share reads the whole head
+    const dim3 grid((unsigned)((k + rows - 1) / rows), (unsigned)n_heads);
+    auto kernel = dt == L2KV_F32 ? (D == 64 ? compress_short_kernel<F32, 64> : compress_short_kernel<F32, 128>)
+                  : D == 256 ? compress_short_kernel<BF16, 256>
+                  : D == 64 ? compress_short_kernel<BF16, 64> : compress_short_kernel<BF16, 128>;
+    hipLaunchKernelGGL(kernel, grid, dim3(kSelThreads), 0, stream, static_cast<const char*>(K), static_cast<const char*>(V), T,
+                       (uint32_t)k, (uint32_t)rows, head_stride * (dt == L2KV_F32 ? 4 : 2), norms, kept_idx,
+                       static_cast<char*>(Kc), static_cast<char*>(Vc));
     return launch_status();
 }
 
