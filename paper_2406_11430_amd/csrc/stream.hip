@@ -187,6 +187,17 @@ l2kv_status compact_ragged_dispatch(const void* K, const void* V, const float* n
     return L2KV_OK;
 }
 
+// a / b and a % b for 0 <= a <= bound, 0 < b < 2^32: in 32 bits wherever the launch's bound fits (a 64-bit division is
+// a hundred instructions at the start of kernels that last five microseconds).
+struct DivMod { int64_t quotient, rest; };
+__device__ __forceinline__ DivMod divided(int64_t a, int64_t b, int64_t bound) {
+    if (bound <= 0xffffffffLL) {
+        const uint32_t q = (uint32_t)a / (uint32_t)b;
+        return DivMod{q, (uint32_t)a - q * (uint32_t)b};
+    }
+    return DivMod{a / b, a % b};
+}
+
 // -------------------------------------------------------------- stream_append
 // One 16-lane row group per (layer, sequence, KV head).  Knew, Vnew are
 // [n_layers][n_seq][Hkv][D]; the plane of (layer, head) is layer*Hkv + head.
@@ -204,9 +215,9 @@ void stream_append_kernel(const char* __restrict__ Knew, const char* __restrict_
     int64_t r = (int64_t)blockIdx.x * (256 / kRowLanes) + threadIdx.x / kRowLanes;   // (layer, seq, head) row
     const bool live = r < n_rows;
     r = live ? r : n_rows - 1;                    // idle groups shadow the last row, stores skipped
-    const int64_t head = r % Hkv;
-    const int64_t seq = (r / Hkv) % n_seq;
-    const int64_t layer = r / (Hkv * n_seq);
+    const DivMod row = divided(r, Hkv, n_rows);
+    const DivMod of = divided(row.quotient, n_seq, n_rows);
+    const int64_t head = row.rest, seq = of.rest, layer = of.quotient;
     const int64_t plane = layer * Hkv + head;
 
     const int32_t len = lens_in[seq];
@@ -263,14 +274,21 @@ l2kv_status stream_append_dispatch(const void* Knew, const void* Vnew, l2kv_dtyp
 // --------------------------------------------------------------- stream_evict
 constexpr int kEvictThreads = 256;
 constexpr int kEvictWaves = kEvictThreads / kWaveSize;
+// From here on one wave per team: 8192 teams 13.3 us (workgroups 14.4), 16384 teams 24 (33); 1024 teams 229 us for
+// a streaming step of two layers against 242 the other way.
+constexpr int64_t kEvictWaveTeams = 4096;
 
 // One team of lanes per (plane, sequence): a whole workgroup (kTeam = 256), or one wave of a
-// workgroup that serves four of them (kTeam = 64, for batches whose sequences are short: the
-// work of a team is a chain of dependent loads, so more and smaller teams keep more of them in
-// flight; no LDS and no barrier then).  Every eviction is one arg-max over the occupied slots
-// of key = (norm bits << 32 | token id): per-lane scan, wave reduction with shuffles, and for
-// workgroup teams 4 wave results through LDS.  In the steady state of a growing budget at most
-// one slot goes per step.
+// workgroup that serves four of them (kTeam = 64; no LDS and no barrier then).  The work of a team is a chain of
+// dependent memory round trips -- lengths, scan, move -- so what counts is how short the chain is
+// while the teams are few, and how many of them are in flight when they are many (the dispatch
+// has the line).  Every eviction is one arg-max over the occupied slots
+// of key = (norm bits, token id): per-lane scan of the norms, wave maximum by lane swaps, and for
+// workgroup teams 4 wave results through LDS.  Token ids are read only where two norms tie.  The
+// row that would move into the hole is known before the scan (the last one) and requested ahead of
+// it.  In the steady state of a growing budget at most one slot goes per step.  One of
+// 512 to 4096 slots from each of 64 sequences in 16 planes: 12.1 -> 7.2 us, in 256 planes 36 -> 24 (ids read and
+// merged for every lane, the row requested after the scan, one wave per team in both).
 template <int W, int kTeam>
 __global__ __launch_bounds__(kEvictThreads)
 void stream_evict_kernel(int64_t n_seq, int64_t n_teams, const int64_t* __restrict__ slot_off, int64_t total_slots,
@@ -279,13 +297,13 @@ void stream_evict_kernel(int64_t n_seq, int64_t n_teams, const int64_t* __restri
                          float* __restrict__ norms_c, int32_t* __restrict__ pos_c) {
     constexpr int64_t kSliceBytes = 4 * W;
     constexpr int64_t kRowBytes = kRowLanes * kSliceBytes;
-    __shared__ unsigned long long s_key[kEvictWaves];
+    __shared__ uint32_t s_norm[kEvictWaves];
     __shared__ int32_t s_slot[kEvictWaves];
     const int64_t team = (int64_t)blockIdx.x * (kEvictThreads / kTeam) + threadIdx.x / kTeam;
     if (team >= n_teams) return;                   // a whole wave (teams are waves or workgroups)
     const int tid = threadIdx.x % kTeam;           // position in the team
-    const int64_t seq = team % n_seq;
-    const int64_t plane = team / n_seq;
+    const DivMod at = divided(team, n_seq, n_teams);
+    const int64_t seq = at.rest, plane = at.quotient;
     const int lane = threadIdx.x % kWaveSize;
     [[maybe_unused]] const int wave = threadIdx.x / kWaveSize;
 
@@ -300,14 +318,28 @@ void stream_evict_kernel(int64_t n_seq, int64_t n_teams, const int64_t* __restri
     float* nw = norms_c + base;
     int32_t* pw = pos_c + base;
 
-    while (len > budget) {                         // uniform over the workgroup
-        // Per-lane scan over the NORMS only (half of the bytes a scan of norms and token ids would
+    // of two slots with equal norms the one with the larger token id goes first
+    auto later = [&](int32_t a, int32_t b) { return (uint32_t)pw[a] > (uint32_t)pw[b]; };
+    while (len > budget) {                         // uniform over the team
+        const int32_t last = len - 1;
+        // first 16 lanes K, next 16 lanes V, one lane norm and id of the last slot
+        char* const buf = tid < kRowLanes ? Kc : Vc;
+        const int c = tid % kRowLanes;
+        Words<W> row;
+        float last_norm = 0.f;
+        int32_t last_id = 0;
+        if (tid < 2 * kRowLanes) {
+            row = load_words<W>(buf + (base + last) * kRowBytes + c * kSliceBytes);
+        } else if (tid == 2 * kRowLanes) {
+            last_norm = nw[last];
+            last_id = pw[last];
+        }
+        // Per-lane scan over the norms only (half of the bytes a scan of norms and token ids would
         // read): eight slots per lane and step, their loads issued before the first compare
-        // (positions past the end re-read the last slot, which cannot beat itself).  Token ids
-        // are fetched only where they decide: when two norms tie, and once per lane at the end.
+        // (positions past the end re-read the last slot, which cannot beat itself).
         uint32_t best_norm = 0;
         int32_t best_slot = -1, best_id = 0;
-        bool have_id = false;
+        bool have_id = false;                                             // best_id is that of best_slot
         constexpr int kScan = 8;
         for (int32_t j0 = tid; j0 < len; j0 += kScan * kTeam) {
             uint32_t nv[kScan];
@@ -335,45 +367,42 @@ void stream_evict_kernel(int64_t n_seq, int64_t n_teams, const int64_t* __restri
                 }
             }
         }
-        if (best_slot >= 0 && !have_id) best_id = pw[best_slot];
-        unsigned long long best = ((unsigned long long)best_norm << 32) | (uint32_t)best_id;
-        // keys are distinct (token ids are), so "larger key" is a total order; -1 marks "none"
-#pragma unroll
-        for (int off = kWaveSize / 2; off > 0; off >>= 1) {
-            const unsigned long long ok = __shfl_xor(best, off);
-            const int32_t os = __shfl_xor(best_slot, off);
-            if (os >= 0 && (best_slot < 0 || ok > best)) {
-                best = ok;
-                best_slot = os;
+        // wave maximum (lanes without a slot hold norm 0), then the lanes that reach it; one as a rule
+        const uint32_t top = ~wave_min(~best_norm);
+        uint64_t reach = __ballot(best_slot >= 0 && best_norm == top);
+        int32_t slot = -1;
+        if (reach != 0) {
+            if ((reach & (reach - 1)) != 0) {                                 // rare: the largest id among them
+                const bool mine = best_slot >= 0 && best_norm == top;
+                if (mine && !have_id) best_id = pw[best_slot];
+                const uint32_t id = ~wave_min(mine ? ~(uint32_t)best_id : 0xffffffffu);
+                reach = __ballot(mine && (uint32_t)best_id == id);
             }
+            slot = __builtin_amdgcn_readlane(best_slot, (int)__builtin_ctzll(reach));
         }
         if constexpr (kTeam == kEvictThreads) {
             if (lane == 0) {
-                s_key[wave] = best;
-                s_slot[wave] = best_slot;
+                s_norm[wave] = top;
+                s_slot[wave] = slot;
             }
             __syncthreads();
-            best = s_key[0];
-            best_slot = s_slot[0];
+            uint32_t norm = s_norm[0];
+            slot = s_slot[0];
 #pragma unroll
             for (int w = 1; w < kEvictWaves; ++w) {
-                if (s_slot[w] >= 0 && (best_slot < 0 || s_key[w] > best)) {
-                    best = s_key[w];
-                    best_slot = s_slot[w];
+                const int32_t other = s_slot[w];
+                if (other >= 0 && (slot < 0 || s_norm[w] > norm || (s_norm[w] == norm && other != slot && later(other, slot)))) {
+                    norm = s_norm[w];
+                    slot = other;
                 }
             }
         }
-        const int32_t last = len - 1;
-        if (best_slot != last) {
-            // move the last slot into the hole: first 16 lanes K, next 16 lanes V
+        if (slot != last) {
             if (tid < 2 * kRowLanes) {
-                char* buf = tid < kRowLanes ? Kc : Vc;
-                const int c = tid % kRowLanes;
-                const Words<W> row = load_words<W>(buf + (base + last) * kRowBytes + c * kSliceBytes);
-                store_words<W>(buf + (base + best_slot) * kRowBytes + c * kSliceBytes, row);
+                store_words<W>(buf + (base + slot) * kRowBytes + c * kSliceBytes, row);
             } else if (tid == 2 * kRowLanes) {
-                nw[best_slot] = nw[last];
-                pw[best_slot] = pw[last];
+                nw[slot] = last_norm;
+                pw[slot] = last_id;
             }
         }
         len = last;
@@ -390,8 +419,8 @@ l2kv_status stream_evict_dispatch(l2kv_dtype dt, int32_t n_planes, int32_t n_seq
                                   float* norms_c, int32_t* pos_c, hipStream_t stream) {
     const int row_bytes = D * (dt == L2KV_F32 ? 4 : 2);
     const int64_t teams = (int64_t)n_planes * n_seq;
-    // sequences of a few thousand slots on average: one wave per (plane, sequence)
-    const bool waves = total_slots / n_seq <= 8192;
+    // many sequences of a few thousand slots on average: one wave per (plane, sequence)
+    const bool waves = total_slots / n_seq <= 8192 && teams >= kEvictWaveTeams;
     const int64_t blocks = waves ? (teams + kEvictWaves - 1) / kEvictWaves : teams;
     if (blocks <= 0 || blocks > 0x7fffffffLL) return L2KV_ERR_SHAPE;
 #define L2KV_EV(WW)                                                                               \

@@ -1,0 +1,69 @@
+"""Eviction by one wave and by one workgroup per (plane, sequence): lengths around the lanes of a team
+and its scan step, several evictions per call, tied and special norms."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2406_11430_amd as l2kv
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def dev():
+    if not torch.cuda.is_available():
+        pytest.fail("no HIP device visible: the gpu tests need a real MI355X")
+    l2kv.lib()
+    return torch.device("cuda:0")
+
+
+def evict(bits, ids, length, budget):
+    """Slots of one sequence after the eviction, as indices into the slots before it."""
+    slots = list(range(len(bits)))
+    while length > budget:
+        worst = max(range(length), key=lambda j: (int(bits[slots[j]]), int(ids[slots[j]])))
+        length -= 1
+        slots[worst] = slots[length]
+    return slots, length
+
+
+# teams = planes x sequences: a workgroup each below 4096, else a wave each
+@pytest.mark.parametrize("planes", [1, 3, 300, 412])
+@pytest.mark.parametrize("norms", ["distinct", "ties", "special"])
+def test_evict(dev, planes, norms):
+    rng = np.random.default_rng(planes)
+    D, dtype = 64, torch.float32
+    cap = np.array([1, 2, 64, 65, 257, 512, 513, 700, 70, 5])
+    length = np.array([1, 2, 64, 65, 257, 512, 513, 699, 0, 5])
+    budget = np.array([0, 1, 60, 65, 256, 511, 510, 699, 3, 1])
+    off = np.concatenate([[0], np.cumsum(cap)]).astype(np.int64)
+    total = int(off[-1])
+    nb = rng.random((planes, total)).astype(np.float32)
+    if norms == "ties":
+        nb = rng.integers(0, 3, (planes, total)).astype(np.float32)
+    if norms == "special":
+        nb[:, rng.permutation(total)[:total // 3]] = np.inf
+        nb[:, rng.permutation(total)[:20]] = np.nan
+        nb[:, rng.permutation(total)[:total // 3]] = 0.0
+    ids = np.stack([rng.permutation(total) for _ in range(planes)]).astype(np.int32)
+    g = torch.Generator(device=dev).manual_seed(planes)
+    Kc, Vc = (torch.randn((planes, total, D), generator=g, device=dev).to(dtype) for _ in range(2))
+    norms_c, pos_c = torch.from_numpy(nb).to(dev), torch.from_numpy(ids).to(dev)
+    K0, V0, N0, P0 = (x.clone() for x in (Kc, Vc, norms_c, pos_c))
+    as_i32 = [torch.from_numpy(x.astype(np.int32)).to(dev) for x in (length, budget)]
+    lens_out = torch.full((len(cap),), -1, dtype=torch.int32, device=dev)
+    l2kv.l2kv_stream_evict(torch.from_numpy(off).to(dev), as_i32[0], as_i32[1], lens_out, Kc, Vc, norms_c, pos_c)
+    bits = nb.view(np.uint32)
+    source = np.tile(np.arange(total), (planes, 1))
+    for p in {0, planes // 2, planes - 1}:
+        for s in range(len(cap)):
+            a, b = off[s], off[s + 1]
+            slots, n = evict(bits[p, a:b], ids[p, a:b], int(length[s]), int(budget[s]))
+            assert int(lens_out[s]) == n
+            source[p, a:a + n] = a + np.array(slots[:n], dtype=np.int64)
+        for s in range(len(cap)):
+            n = int(lens_out[s])
+            live = slice(int(off[s]), int(off[s]) + n)
+            at = torch.from_numpy(source[p, live]).to(dev)
+            for got, old in ((Kc, K0), (Vc, V0), (norms_c, N0), (pos_c, P0)):
+                assert torch.equal(got[p, live].contiguous().view(torch.int32), old[p][at].view(torch.int32)), (p, s)
