@@ -22,7 +22,8 @@ l2kv_status norms_dispatch(const void* K, l2kv_dtype dt, int64_t n_heads, int64_
 // What the norm pass reads last, up to this much, it leaves in the caches for the compaction, which reads the kept
 // rows again and starts from the end.  Half of what the memory-side cache holds: V and the outputs pass
 // through it meanwhile (224 MB gave the same).  32 heads of 4k, half kept: 25.6 us against 26.7 for the whole
-// compression, 8 heads of 294k: 339 against 348, 256 heads of 32k: 1038 against 1039.  Ordinary loads stream
+// compression, 8 heads of 324k: 339 against 348; no gain from 1 GiB of K on (256 heads of 32k: 1038 against 1039), where it is
+// left out.  Ordinary loads stream
 // a little slower than non-temporal ones, so it only pays where a good part is read again: 8 heads
 // of 131k, a tenth kept: 81.4 against 79.6.
 constexpr int64_t kReadAgainBytes = int64_t{128} << 20;

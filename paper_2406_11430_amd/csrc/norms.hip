@@ -40,18 +40,16 @@ __device__ __forceinline__ void store_norm(float* p, float v, bool keep) {
     else __builtin_nontemporal_store(v, p);
 }
 
-// Position of a workgroup in the launch, head by head (both grid shapes of the kernels below).
-__device__ __forceinline__ int64_t in_launch(int64_t blocks_per_head, int64_t head, int64_t chunk) {
-    return blocks_per_head == 0 ? head * gridDim.x + chunk : (int64_t)blockIdx.x;
-}
-
-// Workgroups from keep_from on (counted over the launch, head by head) use ordinary loads and stores
+// Workgroups from chunk keep_chunk of head keep_head on use ordinary loads and stores
 // instead of non-temporal ones: the rows that were read last then stay in the 256 MB memory-side cache for the
-// compaction, which reads the kept ones again (kReadAgainBytes).
-template <typename E, int D>
+// compaction, which reads the kept ones again (kReadAgainBytes).  (kKeepSome: whether
+// there are any.  The two arguments come last: between the others they split the loads of the arguments,
+// which shows in workgroups as short as these, 1300 against 1285 us for 8 GiB; a position counted over the launch needs
+// the grid size from memory, 1318.)
+template <typename E, int D, bool kKeepSome>
 __global__ __launch_bounds__(kNormThreads)
 void norms_kernel(const char* __restrict__ K, int64_t T, int64_t head_stride_bytes,
-                  int64_t blocks_per_head, int64_t keep_from, float* __restrict__ norms) {
+                  int64_t blocks_per_head, float* __restrict__ norms, int32_t keep_head, int32_t keep_chunk) {
 #pragma clang fp contract(off)
     using S = Slice<E, D>;
     using P = Pieces<S::kWords>;
@@ -78,7 +76,7 @@ void norms_kernel(const char* __restrict__ K, int64_t T, int64_t head_stride_byt
     const __amdgpu_buffer_rsrc_t rows = __builtin_amdgcn_make_buffer_rsrc(
         const_cast<char*>(K + head * head_stride_bytes + chunk * (int64_t)(kNormRowsPerBlock * S::kRowBytes)), 0,
         rows_here * S::kRowBytes, kRawBufferWord3);
-    const bool keep = in_launch(blocks_per_head, head, chunk) >= keep_from;
+    const bool keep = kKeepSome && ((int32_t)head > keep_head || ((int32_t)head == keep_head && (int32_t)chunk >= keep_chunk));
     Words<S::kWords> raw[kNormUnroll];
     if (keep) {
 #pragma unroll
@@ -108,9 +106,10 @@ void norms_kernel(const char* __restrict__ K, int64_t T, int64_t head_stride_byt
 // 16 chunks of the fixed summation order (chunk = 4 elements): it sums each left to right, adds
 // the two (first level of the tree), and the remaining three levels run over the 8 lanes of
 // its row.  Bit-identical to the one-row-per-row-group kernel above.
+template <bool kKeepSome>
 __global__ __launch_bounds__(kNormThreads)
 void norms_row_pairs_kernel(const char* __restrict__ K, int64_t T, int64_t head_stride_bytes,
-                            int64_t blocks_per_head, int64_t keep_from, float* __restrict__ norms) {
+                            int64_t blocks_per_head, float* __restrict__ norms, int32_t keep_head, int32_t keep_chunk) {
 #pragma clang fp contract(off)
     constexpr int kRowBytes = 128;
     // grid (chunks, heads) when the head count fits the y dimension; else one long x dimension
@@ -128,7 +127,7 @@ void norms_row_pairs_kernel(const char* __restrict__ K, int64_t T, int64_t head_
     const int64_t first = chunk * kNormRowsPerBlock + (wave * kRowsPerWaveLoad + rg) * kNormUnroll;   // in pairs
     const char* head_base = K + head * head_stride_bytes;
 
-    const bool keep = in_launch(blocks_per_head, head, chunk) >= keep_from;
+    const bool keep = kKeepSome && ((int32_t)head > keep_head || ((int32_t)head == keep_head && (int32_t)chunk >= keep_chunk));
     Words<4> raw[kNormUnroll];
 #pragma unroll
     for (int u = 0; u < kNormUnroll; ++u) {
@@ -157,13 +156,17 @@ static l2kv_status launch_norms(const void* K, int64_t n_heads, int64_t T, int64
     const int64_t bph = (T + rows_per_block - 1) / rows_per_block;
     const int64_t blocks = bph * n_heads;
     if (blocks > 0x7fffffffLL) return L2KV_ERR_SHAPE;
-    auto kernel = norms_kernel<E, D>;
-    if constexpr (kPairs) kernel = norms_row_pairs_kernel;
-    const int64_t kept_blocks = read_again_bytes / (rows_per_block * Slice<E, D>::kRowBytes);
+    // not where it would be a small part of K
+    const int64_t block_bytes = rows_per_block * Slice<E, D>::kRowBytes;
+    const int64_t kept_blocks = blocks * block_bytes <= 8 * read_again_bytes ? read_again_bytes / block_bytes : 0;
+    auto kernel = kept_blocks > 0 ? norms_kernel<E, D, true> : norms_kernel<E, D, false>;
+    if constexpr (kPairs) kernel = kept_blocks > 0 ? norms_row_pairs_kernel<true> : norms_row_pairs_kernel<false>;
+    const int64_t keep_from = blocks > kept_blocks ? blocks - kept_blocks : 0;     // counted head by head
     const bool grid2d = n_heads <= 65535;
     hipLaunchKernelGGL(kernel, grid2d ? dim3((unsigned)bph, (unsigned)n_heads) : dim3((unsigned)blocks),
                        dim3(kNormThreads), 0, stream, static_cast<const char*>(K), T,
-                       head_stride * (int64_t)E::kBytes, grid2d ? (int64_t)0 : bph, blocks > kept_blocks ? blocks - kept_blocks : 0, norms);
+                       head_stride * (int64_t)E::kBytes, grid2d ? (int64_t)0 : bph, norms, (int32_t)(keep_from / bph),
+                       (int32_t)(keep_from % bph));
     return launch_status();
 }
 
