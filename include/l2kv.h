@@ -156,10 +156,10 @@ l2kv_status l2kv_compact(const void* K, const void* V, l2kv_dtype dt,
  * lowest-norm keys and their values) in one call: l2kv_norms, l2kv_select and
  * l2kv_compact enqueued back to back on `stream`, with the same results as the
  * three separate calls.
- *   slab_heads : 0 = all heads at once (three launches).  > 0 = the three
+ *   slab_heads : 0 = all heads at once (three launches; one or two for short
+ *                heads).  > 0 = the three
  *                steps are enqueued slab by slab of that many consecutive
- *                heads, and the norm pass reads K with ordinary instead of
- *                non-temporal loads, so that the compaction's second read of
+ *                heads, so that the compaction's second read of
  *                the kept K rows of a slab can be served by the caches while
  *                the slab still fits them.  On an MI355X this is SLOWER than
  *                slab_heads = 0 at the shapes measured (selection runs one
