@@ -678,8 +678,11 @@ void alr_scores_kernel(const void* __restrict__ Q, const void* __restrict__ K, i
         }
         if (c < G) s_scores[wave][c][u * kRowsPerWaveLoad + r] = mine * scale_log2e;
     }
-    // the wave's scores of consecutive rows leave as one run per head
+    // the wave's scores of consecutive rows leave as one run per head; other lanes wrote them, so the
+    // compiler must not move the reads past the writes (the wave's LDS accesses themselves stay in order)
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     const int64_t first = (int64_t)blockIdx.x * kScoreRowsPerBlock + wave * kScoreRowsPerWave;
     constexpr int kHeadsPerStore = kWaveSize / kScoreRowsPerWave;
     const int row = lane % kScoreRowsPerWave;
