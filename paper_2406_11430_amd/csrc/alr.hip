@@ -8,10 +8,9 @@
 //     sum_m L^m     = sum_p a_p (T - r(p)),
 //     sum_m L^m,ref = sum_j a_(j) (T - j)       (a_(0) <= a_(1) <= ... ascending),
 //     Y             = sum_j a_(j) j - sum_p a_p r(p).
-// r depends only on the key norms: it comes from one sort of (norm bits,
-// position) per KV head (norm_ranks_kernel) and is shared by all queries.  The
-// second term is then a dot product; the first needs the scores of one query in
-// ascending order, i.e. one sort of T positive floats per query head.
+// r depends only on the key norms: it is the rank of (norm bits, position) in its KV head
+// (norm_ranks_kernel) and is shared by all queries.  The second term is then a dot product; the
+// first needs the scores of one query in ascending order.
 //
 // Both need the rank of every element among the n of its head, not the sorted array.
 // A head is shared by several workgroups (share_plan has the rule), each of which ranks a
@@ -25,8 +24,11 @@
 // shares are as few as the LDS list allows until they fill the chip.  (One workgroup per
 // head and four counting passes of 8 bits over global memory, which this replaces, took
 // 196 us for 32 heads of 32k norms and 221 us for 128 heads of scores; now 22 and 43 us.
-// 131k norms of 8 heads: 671 -> 50 us.)  The counting passes are kept for what the bins cannot separate: more than 1024
-// elements in one of the 4096 bins (masses of equal keys), and heads beyond 8M elements.
+// 131k norms of 8 heads: 671 -> 52 us.)
+// Where the bins do not separate the keys -- more than kMaxBin elements in a bin of the head, more than
+// kMaxFine in a finer one: tied or clustered rows, one outlier that stretches the bins of a long head, heads
+// of a million elements -- a share finds the elements of its ranks exactly and sorts them (sorted_range).
+// The counting passes, one workgroup per head, remain for many long heads.
 //
 // The counting passes are a least-significant-digit radix sort (4 passes of 8 bits) by
 // one 1024-lane workgroup.  Each wavefront owns a contiguous chunk of
@@ -40,6 +42,7 @@
 // Unnormalised scores e_p = 2^(s_p - max) are ranked by their logits and summed (double
 // accumulators, fixed order), and the three results are divided by sum_p e_p at
 // the end.
+#include "digit_search.hpp"
 #include "l2kv_device.hpp"
 #include "l2kv_host.hpp"
 
@@ -184,7 +187,9 @@ static_assert(kRankBins == 4 * kSortLanes, "prefix sums take four bins per lane"
 constexpr int kListPer = 20;                         // 4-byte words of the LDS list per lane
 constexpr int kListWords = kListPer * kSortLanes;    // 80 KB
 constexpr int kListAhead = 4;                        // words read past the last element of a share
-constexpr uint32_t kMaxBin = 1024;                   // elements of one bin; bounds the comparisons inside a bin
+constexpr uint32_t kMaxBin = 1024;                   // elements of one bin of a head that is cut along bins
+constexpr uint32_t kLongHead = 1 << 17;              // keys from which the counters of the bins have copies
+constexpr uint32_t kMaxFine = 64;                    // elements of a finer bin that are compared with each other
 
 constexpr int kFinePer = 8;                          // finer bins per lane
 constexpr int kFineBins = kFinePer * kSortLanes;
@@ -268,6 +273,7 @@ __device__ __forceinline__ float float_of_ordered(uint32_t v) {
 template <int E, typename B> struct HeadKeys {
     using Bins = B;
     using Key = typename B::Key;
+    static constexpr bool kReread = E == 0;
     const uint32_t* src;
     uint32_t n;
     Key reg[E > 0 ? E : 1];
@@ -324,23 +330,27 @@ template <int E, typename B> struct HeadKeys {
     }
 };
 
-// Turns kPer counters per lane into the sums of all lower ones (and returns this lane's counters).  One
+// Turns kPer counters per lane into the sums of all lower ones, written to `starts`.  One
 // barrier inside; the caller's barriers order the counting before and the use after.
-template <int kPer> struct Counts { uint32_t v[kPer]; uint32_t before; };
+template <int kPer> struct Counts {
+    uint32_t v[kPer], before;
+    __device__ __forceinline__ void load(const uint32_t* counters) {
+        const uint4* const mine = reinterpret_cast<const uint4*>(counters) + threadIdx.x * (kPer / 4);
+#pragma unroll
+        for (int i = 0; i < kPer / 4; ++i) {
+            const uint4 q = mine[i];
+            v[4 * i] = q.x; v[4 * i + 1] = q.y; v[4 * i + 2] = q.z; v[4 * i + 3] = q.w;
+        }
+    }
+};
 template <int kPer>
-__device__ __forceinline__ Counts<kPer> bins_to_starts(uint32_t* bins, uint32_t* wave_total) {
+__device__ __forceinline__ void counts_to_starts(Counts<kPer>& c, uint32_t* starts, uint32_t* wave_total) {
     static_assert(kPer % 4 == 0, "16-byte accesses");
     const int lane = threadIdx.x % kWaveSize;
     const int wave = threadIdx.x / kWaveSize;
-    uint4* const mine = reinterpret_cast<uint4*>(bins) + threadIdx.x * (kPer / 4);
-    Counts<kPer> c;
     uint32_t sum = 0;
 #pragma unroll
-    for (int i = 0; i < kPer / 4; ++i) {
-        const uint4 v = mine[i];
-        c.v[4 * i] = v.x; c.v[4 * i + 1] = v.y; c.v[4 * i + 2] = v.z; c.v[4 * i + 3] = v.w;
-        sum += v.x + v.y + v.z + v.w;
-    }
+    for (int i = 0; i < kPer; ++i) sum += c.v[i];
     const uint32_t incl = wave_inclusive_sum(sum);
     if (lane == kWaveSize - 1) wave_total[wave] = incl;
     __syncthreads();
@@ -348,6 +358,7 @@ __device__ __forceinline__ Counts<kPer> bins_to_starts(uint32_t* bins, uint32_t*
 #pragma unroll
     for (int w = 0; w < kSortWaves; ++w) before += w < wave ? wave_total[w] : 0u;
     c.before = before;
+    uint4* const mine = reinterpret_cast<uint4*>(starts) + threadIdx.x * (kPer / 4);
 #pragma unroll
     for (int i = 0; i < kPer / 4; ++i) {
         uint4 v;
@@ -357,7 +368,6 @@ __device__ __forceinline__ Counts<kPer> bins_to_starts(uint32_t* bins, uint32_t*
         v.w = before; before += c.v[4 * i + 3];
         mine[i] = v;
     }
-    return c;
 }
 
 template <typename Bins> struct Share {
@@ -365,16 +375,16 @@ template <typename Bins> struct Share {
     Bins bins;                          // of the head
     uint32_t first, end;                // bins of this share
     uint32_t base, count;               // rank of its first element, number of elements
-    bool crowded;                       // some bin of the head holds more than max_bin elements
+    bool crowded;                       // some bin of the head holds more than kMaxBin elements
 };
 
-// Called by all lanes; ends with a barrier.  All shares of a head see the same bins, so they agree
+// `work`: room for the counters of the bins, the list's.  Called by all lanes; ends with a barrier.  All shares of a head see the same bins, so they agree
 // on kmin, kmax and crowded, and every bin belongs to exactly one of them.  count is at most
-// ceil(n / shares) + max_bin - 1 unless the head is crowded.  sh.bin then holds the rank of the first
+// ceil(n / shares) + kMaxBin - 1 unless the head is crowded.  sh.bin then holds the rank of the first
 // element of every bin.
 template <typename Keys>
 __device__ __forceinline__ Share<typename Keys::Bins> find_share(const Keys& keys, uint32_t n, uint32_t s, const Cut& cut,
-                                                                 uint32_t max_bin, BinShared& sh) {
+                                                                 uint32_t* work, BinShared& sh) {
     using Bins = typename Keys::Bins;
     using Key = typename Bins::Key;
     const int lane = threadIdx.x % kWaveSize;
@@ -394,7 +404,11 @@ __device__ __forceinline__ Share<typename Keys::Bins> find_share(const Keys& key
         sh.wave[0][wave] = __builtin_bit_cast(uint32_t, lo);
         sh.wave[1][wave] = __builtin_bit_cast(uint32_t, hi);
     }
-    reinterpret_cast<uint4*>(sh.bin)[threadIdx.x] = make_uint4(0, 0, 0, 0);
+    // long heads: interleaved counters, which equal keys share (64 heads of 400k norms, 30 % zero: 3.95 ms instead of 4.59);
+    // short ones would notice the clearing (8 heads of 4k: 10.3 us instead of 9.4)
+    const bool copies = Keys::kReread && n > kLongHead;
+    if (copies) clear_counts(work, kRankBins * kCopies);
+    else reinterpret_cast<uint4*>(sh.bin)[threadIdx.x] = make_uint4(0, 0, 0, 0);
     if (threadIdx.x == 0) {
         sh.first = sh.base = 0;               // what share 0 starts with
         sh.crowded = 0;
@@ -409,9 +423,17 @@ __device__ __forceinline__ Share<typename Keys::Bins> find_share(const Keys& key
     r.kmin = lo;
     r.kmax = hi;
     r.bins = Bins::over(lo, hi);
-    keys.each([&](Key key, uint32_t) { atomicAdd(&sh.bin[r.bins(key)], 1u); });
+    if (copies) keys.each([&](Key key, uint32_t) { count_digit(work, r.bins(key)); });
+    else keys.each([&](Key key, uint32_t) { atomicAdd(&sh.bin[r.bins(key)], 1u); });
     __syncthreads();
-    const Counts<4> c = bins_to_starts<4>(sh.bin, sh.wave[0]);
+    Counts<4> c;
+    if (copies) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) c.v[i] = digit_count(work, 4 * threadIdx.x + i);
+    } else {
+        c.load(sh.bin);
+    }
+    counts_to_starts(c, sh.bin, sh.wave[0]);
     uint32_t before = c.before;
     // The share starts with the first bin that starts at or past its first rank, i.e. behind the
     // bin that holds the rank before; it stops behind the bin that holds its last rank.
@@ -427,7 +449,7 @@ __device__ __forceinline__ Share<typename Keys::Bins> find_share(const Keys& key
             sh.end = 4 * threadIdx.x + i + 1;
             sh.stop = after;
         }
-        if (c.v[i] > max_bin) sh.crowded = 1;
+        if (c.v[i] > kMaxBin) sh.crowded = 1;
         before = after;
     }
     if (r1 == 0 && threadIdx.x == 0) sh.end = sh.stop = 0;       // no rank falls to it
@@ -455,7 +477,7 @@ template <int kPer, typename Bins> struct Ranked {
     uint32_t pos[kPer], rank[kPer];
 };
 template <bool kWithPos, int kPer, typename Keys>
-__device__ __forceinline__ void rank_share(const Keys& keys, const Share<typename Keys::Bins>& s, BinShared& sh,
+__device__ __forceinline__ bool rank_share(const Keys& keys, const Share<typename Keys::Bins>& s, BinShared& sh,
                                            typename Keys::Key* list_key, uint32_t* list_pos,
                                            Ranked<kPer, typename Keys::Bins>& out) {
     using Key = typename Keys::Key;
@@ -504,8 +526,14 @@ __device__ __forceinline__ void rank_share(const Keys& keys, const Share<typenam
         }
     }
     __syncthreads();
-    (void)bins_to_starts<kFinePer>(sh.fine, sh.wave[0]);
+    Counts<kFinePer> c;
+    c.load(sh.fine);
+    counts_to_starts(c, sh.fine, sh.wave[0]);
+#pragma unroll
+    for (int i = 0; i < kFinePer; ++i)
+        if (c.v[i] > kMaxFine) sh.crowded = 1;                        // 0 so far: the head is not crowded
     __syncthreads();
+    if (sh.crowded != 0) return false;
 #pragma unroll
     for (int u = 0; u < kPer; ++u) {
         if (u * kSortLanes + threadIdx.x < s.count) {
@@ -520,13 +548,15 @@ __device__ __forceinline__ void rank_share(const Keys& keys, const Share<typenam
     // first kListAhead elements of their bins at once, so that the LDS round trips overlap; longer
     // bins go on in steps of as many.  (The list has room for kListAhead words behind any share.)
     constexpr int kTogether = 4;
+    uint32_t lane_of_all = threadIdx.x;
+    asm volatile("" : "+v"(lane_of_all));                             // the positions of the passes above are not worth registers
 #pragma unroll
     for (int u0 = 0; u0 < kPer; u0 += kTogether) {
         if (u0 * kSortLanes >= (int)s.count) break;
         uint32_t start[kTogether], end[kTogether];
 #pragma unroll
         for (int v = 0; v < kTogether && u0 + v < kPer; ++v) {
-            const uint32_t i = (u0 + v) * kSortLanes + threadIdx.x;
+            const uint32_t i = (u0 + v) * kSortLanes + lane_of_all;
             const uint32_t at = i < s.count ? i : 0u;
             out.key[u0 + v] = list_key[at];
             out.pos[u0 + v] = kWithPos ? list_pos[at] : at;           // ties in the order of the list
@@ -569,46 +599,386 @@ __device__ __forceinline__ void rank_share(const Keys& keys, const Share<typenam
             out.rank[u0 + v] = r;
         }
     }
+    return true;
+}
+
+// ---- ranking by an exact cut and a sort ---------------------------------------------------------
+// For the keys that bins do not separate: tied or clustered ones, and long heads.  The elements of ranks
+// [r0, r1) in the order of (key, position), whatever the keys are.  The cuts are found as in the selection, by
+// three digits for both at once; the elements between them are gathered in the order of their positions
+// and sorted in the list by 8-bit digits of what their keys differ in, every wave a stretch of the list with
+// its elements in registers.  Five passes over the head (re-read from the L2) and up to four over the list:
+//   32 heads of 32k norms, 30 % zero       174 us by one workgroup's counting passes, 63 here
+//   128 heads of 8k norms, 9 values        60 us, 507 by comparing inside the bins, 36 here
+//   128 heads of 32k scores, 36 values     266 us, 1500 by comparing inside the bins, 157 here (with the logits)
+//   4 heads of 1M norms                    7.4 ms, 1.4 here
+struct NormKey {
+    static __device__ __forceinline__ uint32_t of(uint32_t bits) { return bits; }
+};
+struct LogitKey {
+    static __device__ __forceinline__ uint32_t of(uint32_t bits) { return ordered_bits(bits); }
+};
+
+// The first r elements of a head: the keys below tau and the first `need` keys equal to it.
+struct Bound { uint32_t tau, need; };
+
+// Elements x0 .. x0 + count - 1 that lie in [from, to).
+__device__ __forceinline__ uint32_t overlap(uint32_t x0, uint32_t count, uint32_t from, uint32_t to) {
+    const uint32_t a = x0 > from ? x0 : from, b = x0 + count < to ? x0 + count : to;
+    return a < b ? b - a : 0u;
+}
+
+struct CutShared {
+    FindShared find;
+    uint32_t inside[kSortWaves], at_lo[kSortWaves], at_hi[kSortWaves];
+};
+
+// Four consecutive keys of a head, which starts at any word.
+typedef uint32_t KeyQuad __attribute__((ext_vector_type(4), aligned(4)));
+
+// The elements of ranks [r0, r1) into the list, in the order of their positions; returns the keys they lie between.
+// `work`: 16384 words, may be the list's.  Called by all lanes; ends with a barrier.
+struct KeyRange { uint32_t least, most; };
+template <typename KeyOf, bool kWithPos>
+__device__ __forceinline__ KeyRange gather_range(const uint32_t* src, uint32_t n, uint32_t r0, uint32_t r1, uint32_t* work,
+                                                 uint32_t* list_key, uint32_t* list_pos, CutShared& cs) {
+    const uint32_t lane = threadIdx.x % kWaveSize;
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWaveSize);
+    const uint32_t count = r1 - r0;
+    // Every wave takes a stretch of consecutive positions, a lane four at a time in one 16-byte load (four of which in
+    // flight; single words leave the L2's latency exposed: 64 heads of 262k norms, 30 % zero, 2.71 ms
+    // in place of 2.17).
+    // body(four keys, position of the first, is_real(j)), by all lanes, in the order of the positions.
+    constexpr uint32_t kLoads = 4, kStep = 4 * kWaveSize;
+    const uint32_t stretch = (n + kSortWaves * kLoads * kStep - 1) / (kSortWaves * kLoads * kStep) * (kLoads * kStep);
+    auto each = [&](auto&& body) {
+        const uint32_t first = wave * stretch;
+        const uint32_t end = first + stretch < n ? first + stretch : n;
+        uint32_t base = first;
+        for (; base < end && base + kLoads * kStep <= n; base += kLoads * kStep) {
+            uint32_t key[kLoads][4];
+#pragma unroll
+            for (uint32_t u = 0; u < kLoads; ++u) {
+                const KeyQuad q = *reinterpret_cast<const KeyQuad*>(src + base + u * kStep + lane * 4);
+#pragma unroll
+                for (uint32_t j = 0; j < 4; ++j) key[u][j] = q[j];
+            }
+#pragma unroll
+            for (uint32_t u = 0; u < kLoads; ++u) {
+#pragma unroll
+                for (uint32_t j = 0; j < 4; ++j) key[u][j] = KeyOf::of(key[u][j]);
+                body(key[u], base + u * kStep + lane * 4, [](uint32_t) { return true; });
+            }
+        }
+        for (; base < end; base += kStep) {                           // the last steps of the head
+            const uint32_t t = base + lane * 4;
+            uint32_t key[4];
+#pragma unroll
+            for (uint32_t j = 0; j < 4; ++j) key[j] = KeyOf::of(src[t + j < n ? t + j : n - 1]);
+            body(key, t, [&](uint32_t j) { return t + j < n; });
+        }
+    };
+
+    // the key of rank r0, and that of rank r1 (or the largest, all of which then are inside)
+    uint32_t want_lo = r0 + 1, want_hi = r1 < n ? r1 + 1 : n;
+    clear_counts(work, kTopBins * kCopies);
+    __syncthreads();
+    each([&](const uint32_t (&key)[4], uint32_t, auto is_real) {
+#pragma unroll
+        for (uint32_t j = 0; j < 4; ++j)
+            if (is_real(j)) count_digit(work, key[j] >> (32 - kTopBits));
+    });
+    __syncthreads();
+    Found a = find_digit<kTopBins>(work, want_lo, cs.find);
+    Found b = find_digit<kTopBins>(work, want_hi, cs.find);
+    Bound lo{a.digit, want_lo - a.below}, hi{b.digit, want_hi - b.below};
+    static_assert(kMidBits == kLowBits, "two digits of one size");
+    uint32_t* const count_lo = work;
+    uint32_t* const count_hi = work + kMidBins * kCopies;
+#pragma unroll
+    for (int shift = kLowBits; shift >= 0; shift -= kLowBits) {
+        clear_counts(work, 2 * kMidBins * kCopies);
+        __syncthreads();
+        each([&](const uint32_t (&key)[4], uint32_t, auto is_real) {
+#pragma unroll
+            for (uint32_t j = 0; j < 4; ++j) {
+                const uint32_t in_lo = (key[j] >> shift) - (lo.tau << kMidBits), in_hi = (key[j] >> shift) - (hi.tau << kMidBits);
+                if (is_real(j) && in_lo < kMidBins) count_digit(count_lo, in_lo);
+                if (is_real(j) && in_hi < kMidBins) count_digit(count_hi, in_hi);
+            }
+        });
+        __syncthreads();
+        a = find_digit<kMidBins>(count_lo, lo.need, cs.find);
+        b = find_digit<kMidBins>(count_hi, hi.need, cs.find);
+        lo = Bound{lo.tau << kMidBits | a.digit, lo.need - a.below};
+        hi = Bound{hi.tau << kMidBits | b.digit, hi.need - b.below};
+    }
+    [[maybe_unused]] const uint32_t lo_count = a.count, hi_count = b.count;      // keys equal to the bounds
+    lo.need -= 1;                                                     // the element of rank r0 itself is inside
+    hi.need = r1 < n ? hi.need - 1 : 0xffffffffu;
+
+    // of the keys equal to a bound, those inside: positions [lo.need, lo_end) and [0, hi_end) among their equals
+    const bool one_key = lo.tau == hi.tau;
+    [[maybe_unused]] const uint32_t lo_end = one_key ? hi.need : 0xffffffffu, hi_end = one_key ? 0u : hi.need;
+    const uint32_t between = one_key ? 0u : hi.tau - lo.tau - 1;
+    auto is_inside = [&](uint32_t key) { return key - (lo.tau + 1) < between; };
+    if constexpr (!kWithPos) {
+        // equal keys are alike: copies of the bounds, and what lies between them in any order
+        const uint32_t equal_lo = one_key ? count : (lo_count - lo.need < count ? lo_count - lo.need : count);
+        const uint32_t equal_hi = one_key ? 0u : (r1 < n ? hi.need : hi_count);
+        for (uint32_t i = threadIdx.x; i < equal_lo; i += kSortLanes) list_key[i] = lo.tau;
+        for (uint32_t i = threadIdx.x; i < equal_hi; i += kSortLanes) list_key[count - 1 - i] = hi.tau;
+        if (threadIdx.x == 0) cs.inside[0] = equal_lo;
+        __syncthreads();
+        each([&](const uint32_t (&key)[4], uint32_t, auto is_real) {
+            uint32_t take = 0;
+#pragma unroll
+            for (uint32_t j = 0; j < 4; ++j) take |= is_real(j) && is_inside(key[j]) ? 1u << j : 0u;
+            if (__ballot(take != 0) == 0) return;                     // the same for all lanes
+            const uint32_t incl = wave_inclusive_sum(__popc(take));
+            uint32_t at = 0;
+            if (lane == kWaveSize - 1) at = atomicAdd(&cs.inside[0], incl);
+            at = (uint32_t)__builtin_amdgcn_readlane((int)at, kWaveSize - 1) + incl - __popc(take);
+#pragma unroll
+            for (uint32_t j = 0; j < 4; ++j) {
+                if ((take >> j & 1u) && at < count) list_key[at++] = key[j];      // counts add up, so `at` always is
+            }
+        });
+        __syncthreads();
+        return KeyRange{lo.tau, hi.tau};
+    }
+    uint32_t inside = 0, at_lo = 0, at_hi = 0;
+    each([&](const uint32_t (&key)[4], uint32_t, auto is_real) {
+#pragma unroll
+        for (uint32_t j = 0; j < 4; ++j) {
+            inside += is_real(j) && is_inside(key[j]) ? 1u : 0u;
+            at_lo += is_real(j) && key[j] == lo.tau ? 1u : 0u;
+            at_hi += is_real(j) && key[j] == hi.tau ? 1u : 0u;
+        }
+    });
+    inside = wave_inclusive_sum(inside);
+    at_lo = wave_inclusive_sum(at_lo);
+    at_hi = wave_inclusive_sum(at_hi);
+    if (lane == kWaveSize - 1) {
+        cs.inside[wave] = inside;
+        cs.at_lo[wave] = at_lo;
+        cs.at_hi[wave] = at_hi;
+    }
+    __syncthreads();
+    uint32_t out = 0;
+    at_lo = at_hi = 0;
+#pragma unroll
+    for (uint32_t w = 0; w < (uint32_t)kSortWaves; ++w) {
+        if (w < wave) {
+            out += cs.inside[w] + overlap(at_lo, cs.at_lo[w], lo.need, lo_end) + overlap(at_hi, cs.at_hi[w], 0u, hi_end);
+            at_lo += cs.at_lo[w];
+            at_hi += cs.at_hi[w];
+        }
+    }
+    // numbers the set bits of all lanes in order, from `from` on; `from` moves behind the last
+    auto numbered = [&](uint32_t bits, uint32_t& from) {
+        const uint32_t incl = wave_inclusive_sum(__popc(bits));
+        const uint32_t mine = from + incl - __popc(bits);
+        from += (uint32_t)__builtin_amdgcn_readlane((int)incl, kWaveSize - 1);
+        return mine;
+    };
+    each([&](const uint32_t (&key)[4], uint32_t t, auto is_real) {
+        uint32_t take = 0, is_lo = 0, is_hi = 0;
+#pragma unroll
+        for (uint32_t j = 0; j < 4; ++j) {
+            take |= is_real(j) && is_inside(key[j]) ? 1u << j : 0u;
+            is_lo |= is_real(j) && key[j] == lo.tau ? 1u << j : 0u;
+            is_hi |= is_real(j) && key[j] == hi.tau ? 1u << j : 0u;
+        }
+        if (__ballot((is_lo | is_hi) != 0) != 0) {                    // the same for all lanes
+            uint32_t lo_at = numbered(is_lo, at_lo), hi_at = numbered(is_hi, at_hi);
+#pragma unroll
+            for (uint32_t j = 0; j < 4; ++j) {
+                if (is_lo >> j & 1u) take |= lo_at >= lo.need && lo_at < lo_end ? 1u << j : 0u, ++lo_at;
+                if (is_hi >> j & 1u) take |= hi_at < hi_end ? 1u << j : 0u, ++hi_at;
+            }
+        }
+        if (__ballot(take != 0) != 0) {
+            uint32_t at = numbered(take, out);
+#pragma unroll
+            for (uint32_t j = 0; j < 4; ++j) {
+                if ((take >> j & 1u) && at < count) {                 // counts add up, so `at` always is
+                    list_key[at] = key[j];
+                    if constexpr (kWithPos) list_pos[at] = t + j;
+                    ++at;
+                }
+            }
+        }
+    });
+    __syncthreads();
+    return KeyRange{lo.tau, hi.tau};
+}
+
+// Sorts the list by key, equal keys in the order in which they stand.  Eight of the bits in which the keys may differ at
+// a time.  count <= kPer * 1024.  Called by all lanes; ends with a barrier.
+template <bool kWithPos, int kPer>
+__device__ __forceinline__ void sort_list(uint32_t* list_key, uint32_t* list_pos, uint32_t count, KeyRange range, BinShared& sh) {
+    const uint32_t lane = threadIdx.x % kWaveSize;
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWaveSize);
+    const uint32_t span = range.most - range.least;
+    const int bits = span == 0 ? 0 : 32 - __builtin_clz(span);
+    const uint32_t chunk = ((count + kSortWaves - 1) / kSortWaves + kWaveSize - 1) / kWaveSize * kWaveSize;
+    const uint32_t first = wave * chunk;                              // of this wave; chunk <= kPer * 64
+    const uint32_t mine = first >= count ? 0u : (count - first < chunk ? count - first : chunk);
+    static_assert(kSortWaves * kBins <= kFineBins && kBins <= kRankBins && kBins % kWaveSize == 0, "counters fit the bins");
+    volatile uint32_t* const counts = sh.fine + wave * kBins;         // of this wave: its elements of every digit so far
+    for (int shift = 0; shift < bits; shift += kRadixBits) {
+        uint32_t key[kPer], pos[kPer], place[(kPer + 1) / 2];          // places below 2^16, two to a word
+        for (uint32_t i = lane; i < kBins; i += kWaveSize) counts[i] = 0u;
+#pragma unroll
+        for (int u = 0; u < kPer; ++u) {
+            const uint32_t i = u * kWaveSize + lane;
+            key[u] = list_key[first + (i < mine ? i : 0u)];
+            pos[u] = kWithPos ? list_pos[first + (i < mine ? i : 0u)] : 0u;
+        }
+#pragma unroll
+        for (int u = 0; u < kPer; ++u) {
+            if ((uint32_t)(u * kWaveSize) >= mine) break;             // same for all lanes of the wave
+            const bool valid = u * kWaveSize + lane < mine;
+            const uint32_t d = (key[u] - range.least) >> shift & (kBins - 1);
+            uint64_t same = __ballot(valid);                          // lanes holding my digit
+#pragma unroll
+            for (int bit = 0; bit < kRadixBits; ++bit) {
+                const bool set = d >> bit & 1u;
+                const uint64_t has = __ballot(set);
+                same &= set ? has : ~has;
+            }
+            const uint32_t before = lanes_below(same), together = (uint32_t)__popcll(same);
+            const uint32_t so_far = counts[d];
+            if (u % 2 == 0) place[u / 2] = so_far + before;
+            else place[u / 2] |= (so_far + before) << 16;
+            __builtin_amdgcn_wave_barrier();
+            if (valid && before + 1 == together) counts[d] = so_far + together;      // last lane of the digit
+            __builtin_amdgcn_wave_barrier();
+        }
+        __syncthreads();
+        // digits follow each other in value order, the waves of a digit in the order of the list
+        if (threadIdx.x < kBins) {
+            uint32_t run = 0;
+#pragma unroll
+            for (int w = 0; w < kSortWaves; ++w) {
+                const uint32_t c = sh.fine[w * kBins + threadIdx.x];
+                sh.fine[w * kBins + threadIdx.x] = run;
+                run += c;
+            }
+            const uint32_t incl = wave_inclusive_sum(run);
+            sh.bin[threadIdx.x] = incl - run;
+            if (lane == kWaveSize - 1) sh.wave[0][wave] = incl;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < kPer; ++u) {
+            if (u % 4 == 0) __builtin_amdgcn_sched_barrier(0);        // not the reads of all steps at once: the registers are full
+            if (u * kWaveSize + lane < mine) {
+                const uint32_t d = (key[u] - range.least) >> shift & (kBins - 1);
+                uint32_t at = sh.bin[d] + counts[d] + (place[u / 2] >> (u % 2 * 16) & 0xffffu);
+#pragma unroll
+                for (uint32_t w = 0; w + 1 < (uint32_t)(kBins / kWaveSize); ++w) at += w < d / kWaveSize ? sh.wave[0][w] : 0u;
+                if (at < count) {
+                    list_key[at] = key[u];
+                    if constexpr (kWithPos) list_pos[at] = pos[u];
+                }
+            }
+        }
+        __syncthreads();
+    }
+}
+
+// The elements of ranks [r0, r1) in order; returns where in the list they start.  A head that fits the list is sorted
+// whole (8 heads of 4k, 30 % zero: 24 us instead of 28).
+template <typename KeyOf, bool kWithPos, int kPer>
+__device__ __forceinline__ uint32_t sorted_range(const uint32_t* src, uint32_t n, uint32_t r0, uint32_t r1, uint32_t* list_key,
+                                                 uint32_t* list_pos, BinShared& sh, CutShared& cs) {
+    __syncthreads();                                                  // the list is free
+    if (n <= (uint32_t)(kPer * kSortLanes)) {
+        uint32_t least = 0xffffffffu, most = 0u;
+#pragma unroll
+        for (int u = 0; u < kPer; ++u) {
+            const uint32_t t = u * kSortLanes + threadIdx.x;
+            if (t < n) {
+                const uint32_t key = KeyOf::of(src[t]);
+                list_key[t] = key;
+                if constexpr (kWithPos) list_pos[t] = t;
+                least = key < least ? key : least;
+                most = key > most ? key : most;
+            }
+        }
+        least = wave_min(least);
+        most = ~wave_min(~most);
+        if (threadIdx.x % kWaveSize == 0) {
+            cs.at_lo[threadIdx.x / kWaveSize] = least;
+            cs.at_hi[threadIdx.x / kWaveSize] = most;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int w = 0; w < kSortWaves; ++w) {
+            least = cs.at_lo[w] < least ? cs.at_lo[w] : least;
+            most = cs.at_hi[w] > most ? cs.at_hi[w] : most;
+        }
+        sort_list<kWithPos, kPer>(list_key, list_pos, n, KeyRange{least, most}, sh);
+        return r0;
+    }
+    if (r0 == r1) return 0;                                           // the same for all lanes
+    const KeyRange range = gather_range<KeyOf, kWithPos>(src, n, r0, r1, list_key, list_key, list_pos, cs);
+    sort_list<kWithPos, kPer>(list_key, list_pos, r1 - r0, range, sh);
+    return 0;
 }
 
 // drop_rank[h][t] = T - 1 - (rank of (norm bits, t) in ascending order).
 template <int E>
 __global__ __launch_bounds__(kSortLanes)
-void norm_ranks_kernel(const float* __restrict__ norms, int64_t T, uint32_t n_heads, Cut cut, uint32_t max_bin,
-                       uint32_t* __restrict__ scratch, int32_t* __restrict__ drop_rank) {
+void norm_ranks_kernel(const float* __restrict__ norms, int64_t T, uint32_t n_heads, Cut cut, int32_t* __restrict__ drop_rank) {
     __shared__ BinShared sh;
+    __shared__ CutShared s_cut;
     __shared__ __attribute__((aligned(16))) uint32_t s_list[kListWords];
-    static_assert(sizeof(SortShared) <= sizeof(s_list), "the counting passes share the list's memory");
     const Part part = part_of_block(blockIdx.x, n_heads, cut.shares);
     const uint32_t n = (uint32_t)T;
     const uint32_t* src = reinterpret_cast<const uint32_t*>(norms) + part.head * T;
     uint32_t* rank = reinterpret_cast<uint32_t*>(drop_rank) + part.head * T;
     const HeadKeys<E, BitBins> keys(src, n);
-    const auto s = find_share(keys, n, part.share, cut, max_bin, sh);
+    const auto s = find_share(keys, n, part.share, cut, s_list, sh);
     if (s.kmin == s.kmax) {                                          // equal norms: the order of the positions
         const uint32_t end = cut.start(part.share + 1);
         for (uint32_t t = cut.start(part.share) + threadIdx.x; t < end; t += kSortLanes) rank[t] = n - 1 - t;
         return;
     }
-    if (s.crowded) {
-        if (part.share != 0) return;
-        SortShared& sort = *reinterpret_cast<SortShared*>(s_list);
-        uint32_t* a_key = scratch + part.head * 4 * T;
-        uint32_t* a_val = a_key + T;
-        uint32_t* b_key = a_val + T;
-        uint32_t* b_val = b_key + T;
-        radix_pass<kIotaIn>(src, nullptr, a_key, a_val, T, 0, sort);
-        radix_pass<kPairs>(a_key, a_val, b_key, b_val, T, 8, sort);
-        radix_pass<kPairs>(b_key, b_val, a_key, a_val, T, 16, sort);
-        radix_pass<kRankOut>(a_key, a_val, nullptr, rank, T, 24, sort);
-        return;
-    }
     constexpr int kPer = kListPer / 2;                               // keys and positions share the list
-    Ranked<kPer, BitBins> mine;
-    rank_share<true, kPer>(keys, s, sh, s_list, s_list + kPer * kSortLanes, mine);
+    uint32_t* const list_pos = s_list + kPer * kSortLanes;
+    if (!s.crowded) {
+        Ranked<kPer, BitBins> mine;
+        if (rank_share<true, kPer>(keys, s, sh, s_list, list_pos, mine)) {
 #pragma unroll
-    for (int u = 0; u < kPer; ++u)
-        if (u * kSortLanes + threadIdx.x < s.count) rank[mine.pos[u]] = n - 1 - (s.base + mine.rank[u]);
+            for (int u = 0; u < kPer; ++u)
+                if (u * kSortLanes + threadIdx.x < s.count) rank[mine.pos[u]] = n - 1 - (s.base + mine.rank[u]);
+            return;
+        }
+    }
+    const uint32_t r0 = s.crowded ? cut.start(part.share) : s.base;
+    const uint32_t r1 = s.crowded ? cut.start(part.share + 1) : s.base + s.count;
+    const uint32_t at = sorted_range<NormKey, true, kPer>(src, n, r0, r1, s_list, list_pos, sh, s_cut);
+    for (uint32_t i = threadIdx.x; i < r1 - r0; i += kSortLanes) rank[list_pos[at + i]] = n - 1 - (r0 + i);
+}
+
+// The same by the counting passes, one workgroup per head (share_plan has the line).
+__global__ __launch_bounds__(kSortLanes)
+void norm_ranks_passes_kernel(const float* __restrict__ norms, int64_t T, uint32_t* __restrict__ scratch,
+                              int32_t* __restrict__ drop_rank) {
+    __shared__ SortShared sort;
+    const int64_t head = blockIdx.x;
+    const uint32_t* src = reinterpret_cast<const uint32_t*>(norms) + head * T;
+    uint32_t* a_key = scratch + head * 4 * T;
+    uint32_t* a_val = a_key + T;
+    uint32_t* b_key = a_val + T;
+    uint32_t* b_val = b_key + T;
+    radix_pass<kIotaIn>(src, nullptr, a_key, a_val, T, 0, sort);
+    radix_pass<kPairs>(a_key, a_val, b_key, b_val, T, 8, sort);
+    radix_pass<kPairs>(b_key, b_val, a_key, a_val, T, 16, sort);
+    radix_pass<kRankOut>(a_key, a_val, nullptr, reinterpret_cast<uint32_t*>(drop_rank) + head * T, T, 24, sort);
 }
 
 // Where the shares of a query head leave their sums: at the start of the head's second scratch array,
@@ -716,7 +1086,7 @@ __device__ __forceinline__ double wave_sum(double v) {
 
 // Fixed-order sums of N doubles per lane over the workgroup; results valid in thread 0.
 template <int N>
-__device__ void block_sum(double (&v)[N], double (*stage)[N]) {
+__device__ __forceinline__ void block_sum(double (&v)[N], double (*stage)[N]) {
     const int lane = threadIdx.x % kWaveSize;
     const int wave = threadIdx.x / kWaveSize;
 #pragma unroll
@@ -732,6 +1102,52 @@ __device__ void block_sum(double (&v)[N], double (*stage)[N]) {
     __syncthreads();
 }
 
+__device__ __forceinline__ double score(float logit, float mx) { return (double)__builtin_amdgcn_exp2f(logit - mx); }
+
+// What the element of rank j in ascending order of the scores adds to the reference of Eq. 6 and 7.
+struct RankedSums { double weighted = 0.0, lowest = 0.0; };
+__device__ __forceinline__ void add_ranked(RankedSums& sums, double e, uint32_t j, int64_t m) {
+    sums.weighted += e * (double)j;
+    sums.lowest += (int64_t)j < m ? e : 0.0;
+}
+
+// e_p = 2^(logit - mx) of positions [p0, p1): their sum, the rank-weighted sum and the mass of the m pairs dropped by
+// norm.  equal: all scores are, so that positions do for ranks.  kToBits: the logits are replaced by their ordered bits.
+struct PositionSums { double all = 0.0, weighted = 0.0, dropped = 0.0; };
+template <bool kToBits>
+__device__ __forceinline__ PositionSums position_sums(uint32_t* logits, const int32_t* __restrict__ rank, uint32_t p0, uint32_t p1,
+                                                      int64_t m, float mx, bool equal, RankedSums& ranked) {
+    PositionSums sums;
+    for (uint32_t base = p0; base < p1; base += kBatch * kSortLanes) {
+        uint32_t bits[kBatch];
+        int32_t rk[kBatch];
+#pragma unroll
+        for (int u = 0; u < kBatch; ++u) {
+            const uint32_t t = base + u * kSortLanes + threadIdx.x;
+            bits[u] = logits[t < p1 ? t : p1 - 1];
+            rk[u] = rank[t < p1 ? t : p1 - 1];
+        }
+#pragma unroll
+        for (int u = 0; u < kBatch; ++u) {
+            const uint32_t t = base + u * kSortLanes + threadIdx.x;
+            const double e = t < p1 ? score(__builtin_bit_cast(float, bits[u]), mx) : 0.0;
+            sums.all += e;
+            sums.weighted += e * (double)rk[u];
+            sums.dropped += rk[u] < m ? e : 0.0;
+            if (equal) add_ranked(ranked, e, t, m);
+            if (kToBits && t < p1) logits[t] = ordered_bits(bits[u]);
+        }
+    }
+    return sums;
+}
+
+__device__ __forceinline__ void write_losses(const double (&acc)[kRecordSums], int64_t head, double* __restrict__ alr,
+                                             double* __restrict__ loss, double* __restrict__ loss_ref) {
+    alr[head] = (acc[3] - acc[1]) / acc[0];
+    if (loss != nullptr) loss[head] = acc[2] / acc[0];
+    if (loss_ref != nullptr) loss_ref[head] = acc[4] / acc[0];
+}
+
 // Softmax statistics, rank-weighted sums, ranks of the scores by value ranges, and the three
 // outputs.  Every share adds up its stretch of positions and its range of ranks; with several
 // shares the sums meet in the head's records and the share that finishes last (arrival counter)
@@ -741,67 +1157,52 @@ __device__ void block_sum(double (&v)[N], double (*stage)[N]) {
 template <int E>
 __global__ __launch_bounds__(kSortLanes)
 void alr_head_kernel(uint32_t* __restrict__ scratch, const int32_t* __restrict__ drop_rank, int64_t T,
-                     uint32_t n_heads, int32_t G, Cut cut, uint32_t max_bin, int64_t m, double* __restrict__ alr,
+                     uint32_t n_heads, int32_t G, Cut cut, int64_t m, double* __restrict__ alr,
                      double* __restrict__ loss, double* __restrict__ loss_ref) {
     __shared__ BinShared sh;
+    __shared__ CutShared s_cut;
     __shared__ __attribute__((aligned(16))) uint32_t s_list[kListWords];
     __shared__ double stage[kSortWaves][kRecordSums];
     const Part part = part_of_block(blockIdx.x, n_heads, cut.shares);     // head = b * Hq + hq
     const int64_t head = part.head;
     const uint32_t n = (uint32_t)T;
-    // scratch: two arrays [n_heads][T]; the first holds the logits on entry
-    uint32_t* buf0 = scratch + head * T;
+    // scratch: two arrays [n_heads][T]; the first holds the logits
+    uint32_t* logits = scratch + head * T;
     uint32_t* second = scratch + (int64_t)n_heads * T;
     const int32_t* rank = drop_rank + (head / G) * T;
 
-    const HeadKeys<E, ValueBins> keys(buf0, n);
-    const auto s = find_share(keys, n, part.share, cut, max_bin, sh);
+    const HeadKeys<E, ValueBins> keys(logits, n);
+    const auto s = find_share(keys, n, part.share, cut, s_list, sh);
     const float mx = s.kmax;
-    auto score = [&](float logit) { return (double)__builtin_amdgcn_exp2f(logit - mx); };
+    const bool equal = s.kmin == s.kmax;                                  // equal scores: any order
 
-    // e_p, their sum, the rank-weighted sum and the mass of the m pairs dropped by norm
-    double acc[kRecordSums] = {0.0, 0.0, 0.0, 0.0, 0.0};
-    const uint32_t p1 = cut.start(part.share + 1);
-    for (uint32_t base = cut.start(part.share); base < p1; base += kBatch * kSortLanes) {
-        float logit[kBatch];
-        int32_t rk[kBatch];
+    RankedSums ranked;
+    if (!equal) {
+        bool done = false;
+        if (!s.crowded) {
+            // ranks inside the share, then the sums in order of rank
+            float* list = reinterpret_cast<float*>(s_list);
+            Ranked<kListPer, ValueBins> mine;
+            done = rank_share<false, kListPer>(keys, s, sh, list, nullptr, mine);
+            if (done) {
+                __syncthreads();
 #pragma unroll
-        for (int u = 0; u < kBatch; ++u) {
-            const uint32_t t = base + u * kSortLanes + threadIdx.x;
-            logit[u] = __builtin_bit_cast(float, buf0[t < p1 ? t : p1 - 1]);
-            rk[u] = rank[t < p1 ? t : p1 - 1];
-        }
-#pragma unroll
-        for (int u = 0; u < kBatch; ++u) {
-            const uint32_t t = base + u * kSortLanes + threadIdx.x;
-            const double e = t < p1 ? score(logit[u]) : 0.0;
-            acc[0] += e;
-            acc[1] += e * (double)rk[u];
-            acc[2] += rk[u] < m ? e : 0.0;
-            if (s.kmin == s.kmax) {                                   // equal scores: any order
-                acc[3] += e * (double)t;
-                acc[4] += t < m ? e : 0.0;
+                for (int u = 0; u < kListPer; ++u)
+                    if (u * kSortLanes + threadIdx.x < s.count) list[mine.rank[u]] = mine.key[u];
+                __syncthreads();
+                for (uint32_t i = threadIdx.x; i < s.count; i += kSortLanes) add_ranked(ranked, score(list[i], mx), s.base + i, m);
             }
         }
-    }
-    const bool crowded = s.crowded && s.kmin != s.kmax;
-    if (!s.crowded && s.kmin != s.kmax) {
-        // ranks inside the share, then the sums in order of rank
-        float* list = reinterpret_cast<float*>(s_list);
-        Ranked<kListPer, ValueBins> mine;
-        rank_share<false, kListPer>(keys, s, sh, list, nullptr, mine);
-        __syncthreads();
-#pragma unroll
-        for (int u = 0; u < kListPer; ++u)
-            if (u * kSortLanes + threadIdx.x < s.count) list[mine.rank[u]] = mine.key[u];
-        __syncthreads();
-        for (uint32_t i = threadIdx.x; i < s.count; i += kSortLanes) {
-            const double e = score(list[i]);
-            const uint32_t j = s.base + i;
-            acc[3] += e * (double)j;
-            acc[4] += (int64_t)j < m ? e : 0.0;
+        if (!done) {
+            const uint32_t r0 = s.crowded ? cut.start(part.share) : s.base;
+            const uint32_t r1 = s.crowded ? cut.start(part.share + 1) : s.base + s.count;
+            const uint32_t at = sorted_range<LogitKey, false, kListPer>(logits, n, r0, r1, s_list, nullptr, sh, s_cut);
+            for (uint32_t i = threadIdx.x; i < r1 - r0; i += kSortLanes)
+                add_ranked(ranked, score(float_of_ordered(s_list[at + i]), mx), r0 + i, m);
         }
     }
+    const PositionSums sums = position_sums<false>(logits, rank, cut.start(part.share), cut.start(part.share + 1), m, mx, equal, ranked);
+    double acc[kRecordSums] = {sums.all, sums.weighted, sums.dropped, ranked.weighted, ranked.lowest};
     block_sum<kRecordSums>(acc, stage);                               // valid in thread 0
 
     if (cut.shares > 1) {
@@ -830,56 +1231,65 @@ void alr_head_kernel(uint32_t* __restrict__ scratch, const int32_t* __restrict__
                 for (int i = 0; i < kRecordSums; ++i) acc[i] += reinterpret_cast<const double*>(copy + w * kRecordWords)[i];
             }
         }
-        __syncthreads();
     }
-    if (crowded) {
-        // ascending sort by the counting passes; every share has read the logits by now
-        SortShared& sort = *reinterpret_cast<SortShared*>(s_list);
-        uint32_t* buf1 = second + head * T;
-        for (uint32_t t = threadIdx.x; t < n; t += kSortLanes) buf0[t] = ordered_bits(buf0[t]);
-        __syncthreads();
-        radix_pass<kKeysOnly>(buf0, nullptr, buf1, nullptr, T, 0, sort);
-        radix_pass<kKeysOnly>(buf1, nullptr, buf0, nullptr, T, 8, sort);
-        radix_pass<kKeysOnly>(buf0, nullptr, buf1, nullptr, T, 16, sort);
-        radix_pass<kKeysOnly>(buf1, nullptr, buf0, nullptr, T, 24, sort);
-        double ref[2] = {0.0, 0.0};
-        for (uint32_t j = threadIdx.x; j < n; j += kSortLanes) {
-            const double e = score(float_of_ordered(buf0[j]));
-            ref[0] += e * (double)j;
-            ref[1] += (int64_t)j < m ? e : 0.0;
-        }
-        block_sum<2>(ref, reinterpret_cast<double(*)[2]>(stage));
-        acc[3] = ref[0];
-        acc[4] = ref[1];
-    }
-    if (threadIdx.x == 0) {
-        alr[head] = (acc[3] - acc[1]) / acc[0];
-        if (loss != nullptr) loss[head] = acc[2] / acc[0];
-        if (loss_ref != nullptr) loss_ref[head] = acc[4] / acc[0];
-    }
+    if (threadIdx.x == 0) write_losses(acc, head, alr, loss, loss_ref);
 }
 
-// How many workgroups share a head, and the largest bin they accept (0: one workgroup per head and
-// the counting passes).  `list` = elements a share may hold.
+// The same by the counting passes, one workgroup per head.  Both scratch arrays are the passes'.
+__global__ __launch_bounds__(kSortLanes)
+void alr_head_passes_kernel(uint32_t* __restrict__ scratch, const int32_t* __restrict__ drop_rank, int64_t T, int32_t G, int64_t m,
+                            double* __restrict__ alr, double* __restrict__ loss, double* __restrict__ loss_ref) {
+    __shared__ SortShared sort;
+    __shared__ double stage[kSortWaves][kRecordSums];
+    __shared__ float s_max[kSortWaves];
+    const int64_t head = blockIdx.x;
+    const uint32_t n = (uint32_t)T;
+    uint32_t* buf0 = scratch + head * T;
+    uint32_t* buf1 = scratch + ((int64_t)gridDim.x + head) * T;
+    const int32_t* rank = drop_rank + (head / G) * T;
+
+    float mx = -INFINITY;
+    for (uint32_t t = threadIdx.x; t < n; t += kSortLanes) mx = fmaxf(mx, __builtin_bit_cast(float, buf0[t]));
+#pragma unroll
+    for (int off = kWaveSize / 2; off > 0; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off));
+    if (threadIdx.x % kWaveSize == 0) s_max[threadIdx.x / kWaveSize] = mx;
+    __syncthreads();
+#pragma unroll
+    for (int w = 0; w < kSortWaves; ++w) mx = fmaxf(mx, s_max[w]);
+
+    RankedSums ranked;
+    const PositionSums sums = position_sums<true>(buf0, rank, 0, n, m, mx, false, ranked);
+    __syncthreads();                                                  // the stores before the sort
+    radix_pass<kKeysOnly>(buf0, nullptr, buf1, nullptr, T, 0, sort);
+    radix_pass<kKeysOnly>(buf1, nullptr, buf0, nullptr, T, 8, sort);
+    radix_pass<kKeysOnly>(buf0, nullptr, buf1, nullptr, T, 16, sort);
+    radix_pass<kKeysOnly>(buf1, nullptr, buf0, nullptr, T, 24, sort);
+    for (uint32_t j = threadIdx.x; j < n; j += kSortLanes) add_ranked(ranked, score(float_of_ordered(buf0[j]), mx), j, m);
+    double acc[kRecordSums] = {sums.all, sums.weighted, sums.dropped, ranked.weighted, ranked.lowest};
+    block_sum<kRecordSums>(acc, stage);
+    if (threadIdx.x == 0) write_losses(acc, head, alr, loss, loss_ref);
+}
+
+// How many workgroups share a head; 0: one workgroup per head and the counting passes.  `list` = elements
+// a share may hold.
 //  - as many as the list needs, less what the last bin of a share may bring with it;
 //  - more while the launch has fewer workgroups than compute units, down to 2048 elements each;
-//  - every share goes over all keys of its head, 50 us per 131k keys and 256 shares at a time, the
-//    counting passes take 670 us per 131k keys and 256 heads at a time (512 heads of 131k: 1.5 ms in 15
-//    shares each, 6.4 ms by the passes): the passes cost less from about 64 shares on, where
-//    the heads are many enough to fill the chip.
-struct SharePlan { uint32_t shares, max_bin; };
-SharePlan share_plan(int64_t n_heads, int64_t T, int64_t list) {
+//  - every share goes over all keys of its head, one head by the passes is one workgroup's, so many long heads
+//    are the passes'.  Norms, ms by shares (distinct norms, 30 % zero) and by the passes: 16 heads of 1M 5.2, 6.4
+//    and 8.4, 7.6; 32 of 1M 9.7, 11.9 and 11.5, 10.0; 64 of 1M 18.2, 23.2 and 16.4, 13.2; 64 of 400k 1.5, 3.9 and 5.9, 4.6;
+//    512 of 131k 1.6, 4.1 and 6.4, 4.7.  Scores: 32 heads of 1M 5.0, 5.9 and 6.0, 6.5; 64 of 1M 10.2, 11.8 and 9.1, 8.7.
+//    Heads of more than kCrowded elements cannot do without the sort of their shares, shorter ones mostly can.
+int64_t share_plan(int64_t n_heads, int64_t T, int64_t list) {
     constexpr int64_t kLongest = int64_t{1} << 23;     // the records of all shares of a head fit the LDS list
-    const SharePlan passes{1, 0};
-    if (T > kLongest) return passes;
+    constexpr int64_t kCrowded = 3 << 18;
+    if (T > kLongest) return 0;
     const int64_t full = list - kMaxBin;
     int64_t shares = (T + full - 1) / full;
-    if (shares > 64 && n_heads * shares > 4096) return passes;
+    if (T > kCrowded ? n_heads * shares > 2048 : shares > 64 && n_heads * shares > 4096) return 0;
     const int64_t fill = (256 + n_heads - 1) / n_heads, most = (T + 2047) / 2048;
     const int64_t want = fill < most ? fill : most;
     if (want > shares) shares = want;
-    if (n_heads * shares > 0x7fffffffLL) return passes;
-    return SharePlan{(uint32_t)shares, kMaxBin};              // ceil(T / shares) + kMaxBin <= list
+    return n_heads * shares <= 0x7fffffffLL ? shares : 0;      // ceil(T / shares) + kMaxBin <= list
 }
 
 template <typename E, int D>
@@ -915,10 +1325,15 @@ size_t alr_workspace_bytes(int32_t B, int32_t Hq, int64_t T) {
 
 l2kv_status norm_ranks_dispatch(const float* norms, int64_t n_heads, int64_t T, int32_t* drop_rank,
                                 void* workspace, hipStream_t stream) {
-    const SharePlan plan = share_plan(n_heads, T, kListWords / 2 - kListAhead);
+    const int64_t shares = share_plan(n_heads, T, kListWords / 2 - kListAhead);
+    if (shares == 0) {
+        hipLaunchKernelGGL(norm_ranks_passes_kernel, dim3((unsigned)n_heads), dim3(kSortLanes), 0, stream, norms, T,
+                           static_cast<uint32_t*>(workspace), drop_rank);
+        return launch_status();
+    }
     auto kernel = T <= 8 * kSortLanes ? norm_ranks_kernel<8> : T <= 32 * kSortLanes ? norm_ranks_kernel<32> : norm_ranks_kernel<0>;
-    hipLaunchKernelGGL(kernel, dim3((unsigned)n_heads * plan.shares), dim3(kSortLanes), 0, stream, norms, T,
-                       (uint32_t)n_heads, Cut((uint32_t)T, plan.shares), plan.max_bin, static_cast<uint32_t*>(workspace), drop_rank);
+    hipLaunchKernelGGL(kernel, dim3((unsigned)(n_heads * shares)), dim3(kSortLanes), 0, stream, norms, T,
+                       (uint32_t)n_heads, Cut((uint32_t)T, (uint32_t)shares), drop_rank);
     return launch_status();
 }
 
@@ -930,8 +1345,9 @@ l2kv_status alr_dispatch(const void* Q, const void* K, l2kv_dtype dt, const int3
     const float s = scale > 0.f ? scale : 1.0f / sqrtf((float)D);
     const float scale_log2e = s * 1.44269504088896340736f;
     float* scores = static_cast<float*>(workspace);
-    const SharePlan plan = share_plan((int64_t)B * Hq, T, kListWords - kListAhead);
-    uint32_t* records = plan.shares > 1 ? static_cast<uint32_t*>(workspace) + (int64_t)B * Hq * T : nullptr;
+    const int64_t n_heads = (int64_t)B * Hq;
+    const int64_t shares = share_plan(n_heads, T, kListWords - kListAhead);
+    uint32_t* records = shares > 1 ? static_cast<uint32_t*>(workspace) + n_heads * T : nullptr;
     l2kv_status st;
     if (dt == L2KV_BF16 && D == 256)
         st = launch_scores<BF16, 256>(Q, K, B, Hkv, G, T, k_head_stride, scale_log2e, scores, records, stream);
@@ -942,9 +1358,14 @@ l2kv_status alr_dispatch(const void* Q, const void* K, l2kv_dtype dt, const int3
         st = D == 128 ? launch_scores<F32, 128>(Q, K, B, Hkv, G, T, k_head_stride, scale_log2e, scores, records, stream)
                       : launch_scores<F32, 64>(Q, K, B, Hkv, G, T, k_head_stride, scale_log2e, scores, records, stream);
     if (st != L2KV_OK) return st;
+    if (shares == 0) {
+        hipLaunchKernelGGL(alr_head_passes_kernel, dim3((unsigned)n_heads), dim3(kSortLanes), 0, stream,
+                           static_cast<uint32_t*>(workspace), drop_rank, T, G, m, alr, loss, loss_ref);
+        return launch_status();
+    }
     auto kernel = T <= 8 * kSortLanes ? alr_head_kernel<8> : alr_head_kernel<0>;    // registers for 32: 43 us, re-read: 41 us for 128 heads of 32k
-    hipLaunchKernelGGL(kernel, dim3((unsigned)(B * Hq) * plan.shares), dim3(kSortLanes), 0, stream,
-                       static_cast<uint32_t*>(workspace), drop_rank, T, (uint32_t)(B * Hq), G, Cut((uint32_t)T, plan.shares), plan.max_bin, m,
+    hipLaunchKernelGGL(kernel, dim3((unsigned)(n_heads * shares)), dim3(kSortLanes), 0, stream,
+                       static_cast<uint32_t*>(workspace), drop_rank, T, (uint32_t)n_heads, G, Cut((uint32_t)T, (uint32_t)shares), m,
                        alr, loss, loss_ref);
     return launch_status();
 }
