@@ -22,6 +22,8 @@
 #include "l2kv_host.hpp"
 #include "row_norm.hpp"
 
+#include <type_traits>
+
 namespace l2kv {
 
 constexpr int kNormThreads = 256;
@@ -32,21 +34,26 @@ constexpr int kNormWaves = kNormThreads / kWaveSize;
 constexpr int kNormUnroll = L2KV_NORM_UNROLL;                    // rows per row group
 constexpr int kNormRowsPerBlock = kNormWaves * kRowsPerWaveLoad * kNormUnroll;  // 32
 
-// The results leave with the non-temporal hint as well: the few stores then disturb the read
-// stream less (1.290 against 1.314 ms for the 8 GiB of the 32k-context workload; the selection
-// that reads the norms next takes the same 0.150 ms either way).
-__device__ __forceinline__ void store_norm(float* p, float v, bool keep) {
-    if (keep) *p = v;
-    else __builtin_nontemporal_store(v, p);
+// How a pass treats the caches.
+//  kStream  rows and results are non-temporal
+//  kResults rows are, results are ordinary stores: better up to 1 GiB of K and 16 MB of norms (half of the L2s).  Heads of
+//           32k rows: 8 of 128 elements in bf16 12.1 against 12.4 us, 64 of them 78.1 against 80.4, 120 (1 GiB) 148.7 against
+//           149.5; the other way round 200 of them 251.4 against 249.2, 1024 1314 against 1284, 200 of 64 elements (0.8 GiB,
+//           26 MB of norms) 131.6 against 128.1, 100 of 128 elements in fp32 (1.7 GB, 13 MB) 251.3 against 244.9
+//  kTail    as kResults, and workgroups from chunk keep_chunk of head keep_head on read with ordinary loads: the rows
+//           that were read last then stay in the 256 MB memory-side cache for the compaction, which reads the kept ones
+//           again (kReadAgainBytes)
+// A template argument and no condition at run time: two stores that differ in the hint alone are merged into one
+// without it.
+enum class NormCaching { kStream, kResults, kTail };
+template <NormCaching C>
+__device__ __forceinline__ void store_norm(float* p, float v) {
+    if constexpr (C == NormCaching::kStream) __builtin_nontemporal_store(v, p);
+    else *p = v;
 }
+constexpr int64_t kPlainResultBytes = int64_t{16} << 20, kPlainResultKeys = int64_t{1} << 30;
 
-// Workgroups from chunk keep_chunk of head keep_head on use ordinary loads and stores
-// instead of non-temporal ones: the rows that were read last then stay in the 256 MB memory-side cache for the
-// compaction, which reads the kept ones again (kReadAgainBytes).  (kKeepSome: whether
-// there are any.  The two arguments come last: between the others they split the loads of the arguments,
-// which shows in workgroups as short as these, 1300 against 1285 us for 8 GiB; a position counted over the launch needs
-// the grid size from memory, 1318.)
-template <typename E, int D, bool kKeepSome>
+template <typename E, int D, NormCaching C>
 __global__ __launch_bounds__(kNormThreads)
 void norms_kernel(const char* __restrict__ K, int64_t T, int64_t head_stride_bytes,
                   int64_t blocks_per_head, float* __restrict__ norms, int32_t keep_head, int32_t keep_chunk) {
@@ -76,7 +83,7 @@ void norms_kernel(const char* __restrict__ K, int64_t T, int64_t head_stride_byt
     const __amdgpu_buffer_rsrc_t rows = __builtin_amdgcn_make_buffer_rsrc(
         const_cast<char*>(K + head * head_stride_bytes + chunk * (int64_t)(kNormRowsPerBlock * S::kRowBytes)), 0,
         rows_here * S::kRowBytes, kRawBufferWord3);
-    const bool keep = kKeepSome && ((int32_t)head > keep_head || ((int32_t)head == keep_head && (int32_t)chunk >= keep_chunk));
+    const bool keep = C == NormCaching::kTail && ((int32_t)head > keep_head || ((int32_t)head == keep_head && (int32_t)chunk >= keep_chunk));
     Words<S::kWords> raw[kNormUnroll];
     if (keep) {
 #pragma unroll
@@ -97,7 +104,7 @@ void norms_kernel(const char* __restrict__ K, int64_t T, int64_t head_stride_byt
         mine = (c == u) ? total : mine;   // lane c keeps the sum of row u
     }
     const int64_t row = first + c;
-    if (c < kNormUnroll && row < T) store_norm(norms + head * T + row, mine, keep);
+    if (c < kNormUnroll && row < T) store_norm<C>(norms + head * T + row, mine);
 }
 
 // 128-byte rows (bf16, 64 elements): two consecutive rows are 256 contiguous bytes, so the 16
@@ -106,7 +113,7 @@ void norms_kernel(const char* __restrict__ K, int64_t T, int64_t head_stride_byt
 // 16 chunks of the fixed summation order (chunk = 4 elements): it sums each left to right, adds
 // the two (first level of the tree), and the remaining three levels run over the 8 lanes of
 // its row.  Bit-identical to the one-row-per-row-group kernel above.
-template <bool kKeepSome>
+template <NormCaching C>
 __global__ __launch_bounds__(kNormThreads)
 void norms_row_pairs_kernel(const char* __restrict__ K, int64_t T, int64_t head_stride_bytes,
                             int64_t blocks_per_head, float* __restrict__ norms, int32_t keep_head, int32_t keep_chunk) {
@@ -127,7 +134,7 @@ void norms_row_pairs_kernel(const char* __restrict__ K, int64_t T, int64_t head_
     const int64_t first = chunk * kNormRowsPerBlock + (wave * kRowsPerWaveLoad + rg) * kNormUnroll;   // in pairs
     const char* head_base = K + head * head_stride_bytes;
 
-    const bool keep = kKeepSome && ((int32_t)head > keep_head || ((int32_t)head == keep_head && (int32_t)chunk >= keep_chunk));
+    const bool keep = C == NormCaching::kTail && ((int32_t)head > keep_head || ((int32_t)head == keep_head && (int32_t)chunk >= keep_chunk));
     Words<4> raw[kNormUnroll];
 #pragma unroll
     for (int u = 0; u < kNormUnroll; ++u) {
@@ -145,7 +152,7 @@ void norms_row_pairs_kernel(const char* __restrict__ K, int64_t T, int64_t head_
         mine = (j == u) ? v : mine;       // lane j of each half keeps the sum of pair u's row
     }
     const int64_t row = 2 * (first + j) + half;
-    if (j < kNormUnroll && row < T) store_norm(norms + head * T + row, mine, keep);
+    if (j < kNormUnroll && row < T) store_norm<C>(norms + head * T + row, mine);
 }
 
 template <typename E, int D>
@@ -159,8 +166,15 @@ static l2kv_status launch_norms(const void* K, int64_t n_heads, int64_t T, int64
     // not where it would be a small part of K
     const int64_t block_bytes = rows_per_block * Slice<E, D>::kRowBytes;
     const int64_t kept_blocks = blocks * block_bytes <= 8 * read_again_bytes ? read_again_bytes / block_bytes : 0;
-    auto kernel = kept_blocks > 0 ? norms_kernel<E, D, true> : norms_kernel<E, D, false>;
-    if constexpr (kPairs) kernel = kept_blocks > 0 ? norms_row_pairs_kernel<true> : norms_row_pairs_kernel<false>;
+    auto pick = [](auto caching) {
+        constexpr NormCaching kC = decltype(caching)::value;
+        if constexpr (kPairs) return norms_row_pairs_kernel<kC>;
+        else return norms_kernel<E, D, kC>;
+    };
+    auto kernel = kept_blocks > 0 ? pick(std::integral_constant<NormCaching, NormCaching::kTail>{})
+                  : n_heads * T * (int64_t)sizeof(float) <= kPlainResultBytes && blocks * block_bytes <= kPlainResultKeys
+                      ? pick(std::integral_constant<NormCaching, NormCaching::kResults>{})
+                      : pick(std::integral_constant<NormCaching, NormCaching::kStream>{});
     const int64_t keep_from = blocks > kept_blocks ? blocks - kept_blocks : 0;     // counted head by head
     const bool grid2d = n_heads <= 65535;
     hipLaunchKernelGGL(kernel, grid2d ? dim3((unsigned)bph, (unsigned)n_heads) : dim3((unsigned)blocks),
