@@ -75,7 +75,7 @@ l2kv_status l2kv_norms(const void* K, l2kv_dtype dt, int64_t n_heads, int64_t T,
     if (K == nullptr || norms == nullptr) return L2KV_ERR_NULL;
     if (l2kv_status st = check_cache(dt, n_heads, T, D, head_stride); st != L2KV_OK) return st;
     if (!aligned(K, 16) || !aligned(norms, 4)) return L2KV_ERR_ALIGN;
-    return norms_dispatch(K, dt, n_heads, T, D, head_stride, norms, kReadAgainBytes, static_cast<hipStream_t>(stream));
+    return norms_dispatch(K, dt, n_heads, T, D, head_stride, norms, 0, static_cast<hipStream_t>(stream));
 }
 
 size_t l2kv_select_workspace_bytes(int64_t n_heads, int64_t T) {

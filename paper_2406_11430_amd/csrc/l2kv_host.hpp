@@ -19,13 +19,13 @@ int device_compute_units();
 l2kv_status read_probe_dispatch(const void* data, size_t bytes, uint32_t* sink, hipStream_t stream);
 l2kv_status norms_dispatch(const void* K, l2kv_dtype dt, int64_t n_heads, int64_t T, int32_t D,
                            int64_t head_stride, float* norms, int64_t read_again_bytes, hipStream_t stream);
-// What the norm pass reads last, up to this much, it leaves in the caches for the compaction, which reads the kept
-// rows again and starts from the end.  Half of what the memory-side cache holds: V and the outputs pass
-// through it meanwhile (224 MB gave the same).  32 heads of 4k, half kept: 25.6 us against 26.7 for the whole
-// compression, 8 heads of 324k: 339 against 348; no gain from 1 GiB of K on (256 heads of 32k: 1038 against 1039), where it is
-// left out.  Ordinary loads stream
-// a little slower than non-temporal ones, so it only pays where a good part is read again: 8 heads
-// of 131k, a tenth kept: 81.4 against 79.6.
+// What the norm pass of l2kv_compress reads last, up to this much, it leaves in the caches for the compaction, which reads the
+// kept rows again and starts from the end.  Half of what the memory-side cache holds: V and the outputs pass
+// through it meanwhile (224 MB gave the same).  Ordinary loads stream a little slower than non-temporal ones (8 heads of
+// 131k: 43.3 against 40.5 us for the norms), so it pays only where a good part is read again.  Compression with and without,
+// other inputs in every call: 32 heads of 4k, half kept, 24.6 against 26.1 us; 32 fp32 heads of 32k 257 against 267;
+// 8 heads of 131k, 0.9 kept, 207 against 213, half 146 and 146, 0.3 114 and 115.  From 1 GiB of K on
+// it is left out (120 heads of 32k 485 and 485).  l2kv_norms by itself does without: its caller may not compact.
 constexpr int64_t kReadAgainBytes = int64_t{128} << 20;
 
 l2kv_status select_dispatch(const float* norms, int64_t n_heads, int64_t T, int64_t k,
