@@ -274,9 +274,12 @@ l2kv_status stream_append_dispatch(const void* Knew, const void* Vnew, l2kv_dtyp
 // --------------------------------------------------------------- stream_evict
 constexpr int kEvictThreads = 256;
 constexpr int kEvictWaves = kEvictThreads / kWaveSize;
-// From here on one wave per team: 8192 teams 13.3 us (workgroups 14.4), 16384 teams 24 (33); 1024 teams 229 us for
-// a streaming step of two layers against 242 the other way.
-constexpr int64_t kEvictWaveTeams = 4096;
+// One wave per team from 2048 teams on, and from two for every slot of a sequence: as many waves as the chip holds at
+// once hide each other's round trips, while a long scan is the faster for every lane that shares it.  Waves and
+// workgroups, us, by teams and slots: 1536 of 512 7.0, 7.1; 2048 of 512 7.0, 8.8; 3072 of 512 7.0, 10.2; 2048 of 1024 7.0, 8.5;
+// 3072 of 2048 17.7, 14.4; 4032 of 2048 18.7, 18.0; 6144 of 2048 20.9, 24.3; 1024 of 4096 26, 8; 4032 of 4096 31, 23;
+// 8192 of 4096 43, 35; 16384 of 4096 75, 75; 16384 of 1024 29, 51.
+constexpr int64_t kEvictWaveTeams = 2048;
 
 // One team of lanes per (plane, sequence): a whole workgroup (kTeam = 256), or one wave of a
 // workgroup that serves four of them (kTeam = 64; no LDS and no barrier then).  The work of a team is a chain of
@@ -419,8 +422,7 @@ l2kv_status stream_evict_dispatch(l2kv_dtype dt, int32_t n_planes, int32_t n_seq
                                   float* norms_c, int32_t* pos_c, hipStream_t stream) {
     const int row_bytes = D * (dt == L2KV_F32 ? 4 : 2);
     const int64_t teams = (int64_t)n_planes * n_seq;
-    // many sequences of a few thousand slots on average: one wave per (plane, sequence)
-    const bool waves = total_slots / n_seq <= 8192 && teams >= kEvictWaveTeams;
+    const bool waves = teams >= kEvictWaveTeams && teams >= 2 * (total_slots / n_seq);
     const int64_t blocks = waves ? (teams + kEvictWaves - 1) / kEvictWaves : teams;
     if (blocks <= 0 || blocks > 0x7fffffffLL) return L2KV_ERR_SHAPE;
 #define L2KV_EV(WW)                                                                               \
