@@ -30,7 +30,9 @@ def same(a, b):
 
 
 @pytest.mark.parametrize("dtype,D", ROWS)
-@pytest.mark.parametrize("heads,T,k", [(1, 1, 1), (3, 40, 15), (3, 40, 16), (2, 70, 33), (70001, 2, 1)])
+# 64 (short rows 128) rows of K and V to a workgroup from that many rows on, up to 1024 workgroups; else 16 (32) of either
+@pytest.mark.parametrize("heads,T,k", [(1, 1, 1), (3, 40, 15), (3, 40, 16), (2, 70, 33), (70001, 2, 1), (3, 70, 64), (2, 140, 65),
+                                       (1, 200, 127), (5, 200, 129), (1024, 130, 64), (1025, 130, 64), (512, 130, 128), (513, 260, 129)])
 @pytest.mark.parametrize("with_v", [True, False])
 def test_compact(dev, dtype, D, heads, T, k, with_v):
     g = torch.Generator().manual_seed(heads + T + k)
