@@ -47,12 +47,18 @@ def test_compact(dev, dtype, D, heads, T, k, with_v):
     assert not with_v or same(Vc, torch.gather(V, 1, at))
 
 
-# 1, 2, 64, 65 and 4097 sequences: one, two and three steps of the owner search
+# 1, 2, 64, 65 and 4097 sequences: one, two and three steps of the owner search; runs of empty sequences around
+# the 64 that a row looks through at once
 @pytest.mark.parametrize("dtype,D", ROWS)
-@pytest.mark.parametrize("n_seq,longest,planes", [(1, 200, 2), (2, 9, 1), (64, 6, 3), (65, 40, 2), (4097, 5, 2), (3, 4, 65539)])
-def test_compact_ragged(dev, dtype, D, n_seq, longest, planes):
+@pytest.mark.parametrize("n_seq,longest,planes,empty", [(1, 200, 2, 0), (2, 9, 1, 0), (64, 6, 3, 0), (65, 40, 2, 0), (4097, 5, 2, 0),
+                                                        (3, 4, 65539, 0), (600, 5, 2, 62), (600, 5, 2, 64), (600, 9, 1, 131),
+                                                        (300, 3, 1, 290)])
+def test_compact_ragged(dev, dtype, D, n_seq, longest, planes, empty):
     rng = np.random.default_rng(n_seq)
     kept = rng.integers(0, longest + 1, n_seq)                       # empty sequences too
+    if empty:
+        for first in range(3, n_seq, empty + 5):
+            kept[first:first + empty] = 0
     kept[0] = longest
     length = kept + rng.integers(0, 4, n_seq)
     room = kept + rng.integers(0, 3, n_seq)
