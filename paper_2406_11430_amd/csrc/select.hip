@@ -434,16 +434,16 @@ void compress_short_kernel(const char* __restrict__ K, const char* __restrict__ 
 //   select_count_kernel   histogram of the top digit per chunk (64 coarse counts beside the 4096)
 //   select_gather_kernel  the digit of tau; keys of that digit go to the candidate list of the
 //                         head, in chunk order; per chunk the counts below it and in it
-//   select_emit_kernel    every workgroup finishes the search over the candidates by itself (a few
-//                         per cent of the keys; all of them in the worst case), counts what lies
-//                         ahead of its chunk and emits its kept tokens
+//   select_emit_kernel    every workgroup finishes the search over the candidates by itself (3 % of log-normal
+//                         norms, a third of the norms of rows without a scale of their own; all of them in the
+//                         worst case), counts what lies ahead of its chunk and emits its kept tokens
 constexpr int kCoarse = 64;                          // coarse counts per chunk, of kTopBins / 64 digits each
 constexpr int kFinePerCoarse = kTopBins / kCoarse;   // 64
 constexpr int kChunkUnit = kSelThreads * 4;          // chunks are multiples of 4096 tokens
-constexpr int64_t kChunkMax = 8 * kChunkUnit;        // counts per chunk stay below 2^16
+constexpr int64_t kChunk16 = 8 * kChunkUnit;         // up to here the counts of a chunk are 16-bit numbers
 
 struct SelectSplit {
-    uint16_t* fine;       // [heads][chunks][kTopBins]
+    void* fine;           // [heads][chunks][kTopBins], 16-bit numbers while the chunks are short, else 32-bit ones
     uint32_t* coarse;     // [heads][chunks][kCoarse]
     uint2* info;          // [heads][chunks]: keys below the digit of tau, keys in it
     uint32_t* head_info;  // [heads][2]: digit of tau, keys below it in the head
@@ -459,31 +459,39 @@ struct SelectPlan {
 };
 
 static size_t round256(size_t n) { return (n + 255) / 256 * 256; }
+static size_t count_bytes(int64_t chunk) { return chunk <= kChunk16 ? sizeof(uint16_t) : sizeof(uint32_t); }
 
 // Heads that fit the registers of one workgroup (32k tokens) are never split: 8 heads of 32k take
 // 15.5 us either way, more heads are faster whole.  Longer ones are split while the heads alone
-// leave most of the chip idle.  Measured, one workgroup per head / split, us: 8 heads of 40k 22.9 /
-// 16.1, 64 of 40k 23.9 / 28.6; 8 of 131k 59.6 / 17.7, 64 of 131k 66.8 / 46.0, 128 of 131k 80 / 69
-// (and 112 / 199 for 64 heads of equal keys, where every key is a candidate of every workgroup,
-// hence no further than 64).
+// leave most of the chip idle, into as many chunks as run at once in all: every one goes over the candidates of the
+// whole head, which are all keys where all are equal, so that their number must not grow with the length
+// (with chunks of at most 32k keys 64 heads of 4M took 1.8 ms, 58 for equal keys).  us, one workgroup per head / split:
+//                  log-normal norms   normal, no scale   30 % zero, 30 % kept   all equal
+//   8 of 131k           59 / 17           59 / 22             87 / 38            64 / 92
+//   64 of 131k          65 / 39           64 / 51             90 / 72            68 / 177
+//   64 of 262k         158 / 68          156 / 91            183 / 132          136 / 344
+//   8 of 1M            549 / 54          546 / 108           674 / 339          488 / 1102
+//   64 of 1M           654 / 267         656 / 354           722 / 500          551 / 1352
+//   4 of 4M           2396 / 126        2438 / 331          2790 / 796         2095 / 4206
+//   64 of 4M          3285 / 1117       3296 / 1483         3450 / 2054        2562 / 5447
+// and log-normal 8 of 40k 22.9 / 16.1, 64 of 40k 23.9 / 28.6, 128 of 131k 80 / 69 (not split: 112 / 199 for equal keys).
 static SelectPlan select_plan(int64_t n_heads, int64_t T) {
     SelectPlan p;
     constexpr int64_t kWorkgroups = 512;             // two per compute unit
     if (T <= (int64_t)kSelThreads * kSelMaxRegKeys || T > (int64_t{1} << 22)) return p;
     if (n_heads > 64 || n_heads > T / 2048) return p;
     const int64_t want = (kWorkgroups + n_heads - 1) / n_heads;
-    int64_t chunk = (T + want - 1) / want;
-    chunk = (chunk + kChunkUnit - 1) / kChunkUnit * kChunkUnit;
-    if (chunk > kChunkMax) chunk = kChunkMax;
+    const int64_t chunk = ((T + want - 1) / want + kChunkUnit - 1) / kChunkUnit * kChunkUnit;
     p.chunk = chunk;
     p.chunks = (int32_t)((T + chunk - 1) / chunk);
     const size_t n = (size_t)n_heads * (size_t)p.chunks;
-    p.bytes = round256(n * kTopBins * sizeof(uint16_t)) + round256(n * kCoarse * sizeof(uint32_t)) +
+    p.bytes = round256(n * kTopBins * count_bytes(chunk)) + round256(n * kCoarse * sizeof(uint32_t)) +
               round256(n * sizeof(uint2)) + round256((size_t)n_heads * 2 * sizeof(uint32_t)) +
               round256((size_t)n_heads * (size_t)T * sizeof(uint32_t));
     return p;
 }
 
+template <typename Count>
 __global__ __launch_bounds__(kSelThreads)
 void select_count_kernel(const uint32_t* __restrict__ norm_bits, int64_t T, uint32_t flip, SelectSplit sp) {
     __shared__ __attribute__((aligned(16))) uint32_t s_hist[kTopBins * kCopies];
@@ -512,7 +520,9 @@ void select_count_kernel(const uint32_t* __restrict__ norm_bits, int64_t T, uint
     c.y = digit_count(s_hist, 4 * threadIdx.x + 1);
     c.z = digit_count(s_hist, 4 * threadIdx.x + 2);
     c.w = digit_count(s_hist, 4 * threadIdx.x + 3);
-    reinterpret_cast<uint2*>(sp.fine + slot * kTopBins)[threadIdx.x] = make_uint2(c.x | (c.y << 16), c.z | (c.w << 16));
+    Count* const fine = static_cast<Count*>(sp.fine) + slot * kTopBins;
+    if constexpr (sizeof(Count) == 2) reinterpret_cast<uint2*>(fine)[threadIdx.x] = make_uint2(c.x | (c.y << 16), c.z | (c.w << 16));
+    else reinterpret_cast<uint4*>(fine)[threadIdx.x] = c;
     uint32_t sum = c.x + c.y + c.z + c.w;
 #pragma unroll
     for (int off = kFinePerCoarse / 8; off > 0; off >>= 1) sum += __shfl_xor(sum, off);
@@ -527,6 +537,7 @@ __device__ __forceinline__ Found find_lane(uint32_t count, uint32_t want) {
     return Found{(uint32_t)at, __shfl(incl - count, at), __shfl(count, at)};
 }
 
+template <typename Count>
 __global__ __launch_bounds__(kSelThreads)
 void select_gather_kernel(const uint32_t* __restrict__ norm_bits, int64_t T, uint32_t k, uint32_t flip, SelectSplit sp) {
     __shared__ uint32_t s_sum[2][kSelWaves][kCoarse], s_part[kSelWaves][kFinePerCoarse];
@@ -554,7 +565,7 @@ void select_gather_kernel(const uint32_t* __restrict__ norm_bits, int64_t T, uin
     uint32_t m = 0, part = 0;
 #pragma unroll 4
     for (int c = wave; c < sp.chunks; c += kSelWaves) {
-        const uint32_t v = sp.fine[(slot0 + c) * kTopBins + g.digit * kFinePerCoarse + lane];
+        const uint32_t v = static_cast<const Count*>(sp.fine)[(slot0 + c) * kTopBins + g.digit * kFinePerCoarse + lane];
         m += v;
         part += c < (int)blockIdx.x ? v : 0u;
     }
@@ -768,8 +779,8 @@ l2kv_status select_dispatch(const float* norms, int64_t n_heads, int64_t T, int6
     SelectSplit sp;
     const size_t n = (size_t)n_heads * (size_t)plan.chunks;
     char* ws = static_cast<char*>(workspace);
-    sp.fine = reinterpret_cast<uint16_t*>(ws);
-    ws += round256(n * kTopBins * sizeof(uint16_t));
+    sp.fine = ws;
+    ws += round256(n * kTopBins * count_bytes(plan.chunk));
     sp.coarse = reinterpret_cast<uint32_t*>(ws);
     ws += round256(n * kCoarse * sizeof(uint32_t));
     sp.info = reinterpret_cast<uint2*>(ws);
@@ -781,8 +792,11 @@ l2kv_status select_dispatch(const float* norms, int64_t n_heads, int64_t T, int6
     sp.chunks = plan.chunks;
     const dim3 grid((unsigned)plan.chunks, (unsigned)n_heads);
     const uint32_t* bits = reinterpret_cast<const uint32_t*>(norms);
-    hipLaunchKernelGGL(select_count_kernel, grid, dim3(kSelThreads), 0, stream, bits, T, flip, sp);
-    hipLaunchKernelGGL(select_gather_kernel, grid, dim3(kSelThreads), 0, stream, bits, T, (uint32_t)k, flip, sp);
+    const bool short_counts = count_bytes(plan.chunk) == sizeof(uint16_t);
+    hipLaunchKernelGGL((short_counts ? select_count_kernel<uint16_t> : select_count_kernel<uint32_t>), grid, dim3(kSelThreads), 0,
+                       stream, bits, T, flip, sp);
+    hipLaunchKernelGGL((short_counts ? select_gather_kernel<uint16_t> : select_gather_kernel<uint32_t>), grid, dim3(kSelThreads), 0,
+                       stream, bits, T, (uint32_t)k, flip, sp);
     hipLaunchKernelGGL(select_emit_kernel, grid, dim3(kSelThreads), 0, stream, bits, T, (uint32_t)k, flip, kept_idx,
                        kept_count, sp);
     return launch_status();
