@@ -41,12 +41,13 @@ constexpr int kSelBatch = 8;                         // keys per lane fetched to
 // Ordered emit shared by both launch shapes.  Every wave of the workgroup owns `iters` * 64
 // consecutive positions of [t0, ...); fetch(e) is this lane's key of iteration e (positions past
 // the end read as the largest key and come after every real one).  lt_before / eq_before: keys
-// below / equal to tau ahead of this workgroup's range.  put(i, t): token t is the i-th kept one.
+// below / equal to tau ahead of this workgroup's range.  put(i, t): token t is the i-th kept one.  A wave whose tokens
+// would go beyond `limit` of them emits none (kLimited: the counts come from the caller's memory).
 struct EmitShared { uint32_t lt[kSelWaves], eq[kSelWaves]; };
 
-template <int kUnroll, typename Fetch, typename Put>
+template <int kUnroll, bool kLimited, typename Fetch, typename Put>
 __device__ __forceinline__ void emit_ordered(Fetch fetch, int64_t iters, uint32_t t0, uint32_t tau, uint32_t need_eq,
-                                             uint32_t lt_before, uint32_t eq_before, Put put, EmitShared& sh) {
+                                             uint32_t lt_before, uint32_t eq_before, Put put, uint32_t limit, EmitShared& sh) {
     const int lane = threadIdx.x % kWaveSize;
     const int wave = threadIdx.x / kWaveSize;
     uint32_t lt_w = 0, eq_w = 0;
@@ -81,14 +82,18 @@ __device__ __forceinline__ void emit_ordered(Fetch fetch, int64_t iters, uint32_
         }
     };
     const bool all_eq = eq_w != 0 && eq_before + eq_w <= need_eq;         // every tie of this wave's range is kept
+    if constexpr (kLimited) {
+        const uint32_t left = eq_before < need_eq ? need_eq - eq_before : 0u;
+        if ((uint64_t)out_base + lt_w + (eq_w < left ? eq_w : left) > limit) return;
+    }
     if (all_eq || eq_w == 0 || eq_before >= need_eq) {
         // ... or none is: one comparison per key.  (Padding equals tau only if tau is the largest
         // key; a range with padding then never has all its ties kept, need_eq counts real keys.)
         if (lt_w == 0 && !all_eq) return;
-        uint32_t limit = all_eq ? tau : tau - 1;         // tau > 0 where some key is below it
-        asm volatile("" : "+v"(limit));                  // compare afresh: the masks of the tally would not stay in registers
+        uint32_t highest = all_eq ? tau : tau - 1;       // tau > 0 where some key is below it
+        asm volatile("" : "+v"(highest));                  // compare afresh: the masks of the tally would not stay in registers
         for_iters([&](uint32_t key, int32_t t) {
-            const bool keep = key <= limit;
+            const bool keep = key <= highest;
             const uint64_t keep_mask = __ballot(keep);
             if (keep) put(out_base + lanes_below(keep_mask), t);
             out_base += __popcll(keep_mask);
@@ -286,8 +291,8 @@ void select_kernel(const uint32_t* __restrict__ norm_bits, int64_t T, uint32_t k
     }
     const HeadKeys<E> keys(src, T, flip);
     const Threshold th = find_threshold(keys, k, s_search);
-    emit_ordered<E == 0 ? kSelBatch : E>([&](int64_t e) { return keys.fetch(e); }, E == 0 ? keys.iters : E, keys.t0, th.tau,
-                                         th.need_eq, 0u, 0u, [&](uint32_t i, int32_t t) { out[i] = t; }, s_emit);
+    emit_ordered<E == 0 ? kSelBatch : E, false>([&](int64_t e) { return keys.fetch(e); }, E == 0 ? keys.iters : E, keys.t0, th.tau,
+                                         th.need_eq, 0u, 0u, [&](uint32_t i, int32_t t) { out[i] = t; }, k, s_emit);
     if (kept_count != nullptr && threadIdx.x == 0) kept_count[head] = (int32_t)k;
 }
 
@@ -316,13 +321,13 @@ __device__ __forceinline__ void select_and_copy(const HeadKeys<E>& keys, uint32_
                                                 const char* __restrict__ K, const char* __restrict__ V, int32_t* __restrict__ out,
                                                 char* __restrict__ Kc, char* __restrict__ Vc, FuseShared& sh) {
     const Threshold th = find_threshold(keys, k, sh.search);
-    emit_ordered<E>([&](int64_t e) { return keys.fetch(e); }, E, keys.t0, th.tau, th.need_eq, 0u, 0u,
+    emit_ordered<E, false>([&](int64_t e) { return keys.fetch(e); }, E, keys.t0, th.tau, th.need_eq, 0u, 0u,
                     [&](uint32_t i, int32_t t) {
                         if (i - r0 < rows) {
                             sh.row[i - r0] = (uint16_t)t;
                             out[i] = t;
                         }
-                    }, sh.emit);
+                    }, k, sh.emit);
     __syncthreads();
     using P = RowCopy<kRowBytes>;
     constexpr uint32_t kRowsPerStep = kSelThreads / P::kLanes;
@@ -437,6 +442,8 @@ void compress_short_kernel(const char* __restrict__ K, const char* __restrict__ 
 //   select_emit_kernel    every workgroup finishes the search over the candidates by itself (3 % of log-normal
 //                         norms, a third of the norms of rows without a scale of their own; all of them in the
 //                         worst case), counts what lies ahead of its chunk and emits its kept tokens
+// Counts and lists pass from kernel to kernel through the caller's memory.  No access is bounded by what is read there
+// alone: if two calls overlap on one workspace, against the contract, they select wrong rows and nothing worse.
 constexpr int kCoarse = 64;                          // coarse counts per chunk, of kTopBins / 64 digits each
 constexpr int kFinePerCoarse = kTopBins / kCoarse;   // 64
 constexpr int kChunkUnit = kSelThreads * 4;          // chunks are multiples of 4096 tokens
@@ -533,7 +540,7 @@ void select_count_kernel(const uint32_t* __restrict__ norm_bits, int64_t T, uint
 __device__ __forceinline__ Found find_lane(uint32_t count, uint32_t want) {
     const uint32_t incl = wave_inclusive_sum(count);
     const uint64_t past = __ballot(incl >= want);
-    const int at = (int)__builtin_ctzll(past);               // want <= total: some lane qualifies
+    const int at = past != 0 ? (int)__builtin_ctzll(past) : kWaveSize - 1;       // want <= total: some lane qualifies
     return Found{(uint32_t)at, __shfl(incl - count, at), __shfl(count, at)};
 }
 
@@ -579,13 +586,15 @@ void select_gather_kernel(const uint32_t* __restrict__ norm_bits, int64_t T, uin
         part += s_part[w][lane];
     }
     const Found f = find_lane(m, k - g.below);
-    const uint32_t ahead = __shfl(part, (int)f.digit);
+    // candidates of earlier chunks, which come first: no more than those chunks have keys
+    const uint32_t before = (uint32_t)(blockIdx.x * sp.chunk), listed = __shfl(part, (int)f.digit);
+    const uint32_t ahead = listed < before ? listed : before;
     const uint32_t digit = g.digit * kFinePerCoarse + f.digit;
     if (blockIdx.x == 0 && threadIdx.x == 0) {
         sp.head_info[2 * head] = digit;
         sp.head_info[2 * head + 1] = g.below + f.below;
     }
-    uint32_t* cand = sp.cand + head * T + ahead;           // the candidates of earlier chunks come first
+    uint32_t* cand = sp.cand + head * T + ahead;
     const uint32_t* src = norm_bits + head * T;
     const int64_t first = blockIdx.x * sp.chunk;
     const int64_t last = first + sp.chunk < T ? first + sp.chunk : T;
@@ -654,7 +663,7 @@ void select_emit_kernel(const uint32_t* __restrict__ norm_bits, int64_t T, uint3
     const uint32_t top_digit = sp.head_info[2 * head];
     const uint32_t want = k - sp.head_info[2 * head + 1];
     __syncthreads();
-    const uint32_t n = s_cands, ahead = s_cand_ahead;
+    const uint32_t n = s_cands < (uint32_t)T ? s_cands : (uint32_t)T, ahead = s_cand_ahead < n ? s_cand_ahead : n;
     const uint32_t* cand = sp.cand + head * T;
     constexpr int kCandBatch = 4;
     auto for_cands = [&](uint32_t end, auto&& body) {
@@ -699,14 +708,14 @@ void select_emit_kernel(const uint32_t* __restrict__ norm_bits, int64_t T, uint3
     const int64_t iters = sp.chunk / kSelThreads;
     const uint32_t t0 = (uint32_t)(first + wave * iters * kWaveSize);
     const uint32_t end = (uint32_t)last;
-    emit_ordered<4>(
+    emit_ordered<4, true>(
         [&](int64_t e) -> uint32_t {
             const uint32_t t = t0 + (uint32_t)e * kWaveSize + lane;
             const uint32_t v = src[t < end ? t : end - 1] ^ flip;
             return t < end ? v : 0xffffffffu;
         },
         iters, t0, tau, need_eq, s_lt_ahead + s_cand_lt, s_cand_eq,
-        [&](uint32_t i, int32_t t) { kept_idx[head * (int64_t)k + i] = t; }, s_emit);
+        [&](uint32_t i, int32_t t) { kept_idx[head * (int64_t)k + i] = t; }, k, s_emit);
     if (kept_count != nullptr && blockIdx.x == 0 && threadIdx.x == 0) kept_count[head] = (int32_t)k;
 }
 
