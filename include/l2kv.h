@@ -101,11 +101,13 @@ l2kv_status l2kv_norms(const void* K, l2kv_dtype dt, int64_t n_heads, int64_t T,
  *   kept_count out: [n_heads] int32, every entry = k; may be NULL
  *   workspace     : l2kv_select_workspace_bytes(n_heads, T) bytes, 16-aligned;
  *                   contents need not be initialised and are undefined after.
- *                   For a few long heads several workgroups share a head
- *                   through it (256 bytes otherwise); calls that use it must
- *                   then not overlap in time.  Any size from 256 bytes on is
- *                   accepted: below the queried size every head is selected
- *                   by one workgroup, which does not touch the buffer.
+ *                   For a few long heads (at most 64, beyond 32768 tokens)
+ *                   several workgroups share a head through it; two calls
+ *                   whose queried size is above 256 must therefore not use one
+ *                   workspace at the same time, on other streams either.  Any
+ *                   size from 256 bytes on is accepted: below the queried size
+ *                   every head is selected by one workgroup, which does not
+ *                   touch the buffer.
  * Errors: NULL, SHAPE, RATIO, WORKSPACE, ALIGN, LAUNCH.
  */
 l2kv_status l2kv_select(const float* norms, int64_t n_heads, int64_t T,
@@ -162,14 +164,16 @@ l2kv_status l2kv_compact(const void* K, const void* V, l2kv_dtype dt,
  *                heads, so that the compaction's second read of
  *                the kept K rows of a slab can be served by the caches while
  *                the slab still fits them.  On an MI355X this is SLOWER than
- *                slab_heads = 0 at the shapes measured (selection runs one
- *                workgroup per head, so a slab of a few heads leaves most of
- *                the chip idle during its selection); the mode exists so that
- *                the trade can be measured.
+ *                slab_heads = 0 at the shapes measured (a slab of a few heads
+ *                leaves most of the chip idle during its selection, and every
+ *                launch costs); the mode exists so that the trade can be
+ *                measured.
  *   norms      out: [n_heads][T] fp32 (needed as scratch; left filled)
  *   kept_idx   out: [n_heads][k], k = l2kv_keep_count(T, keep_ratio)
- *   Kc, Vc     out: [n_heads][k][D]
- *   workspace     : as l2kv_select
+ *   Kc, Vc     out: [n_heads][k][D] (scratch memory of the selection before
+ *                they are filled)
+ *   workspace     : at least 256 bytes, 16-aligned, as for l2kv_select of the
+ *                same heads; not touched, so calls may share it
  * Errors: NULL, SHAPE, DTYPE, RATIO, WORKSPACE, ALIGN, LAUNCH (a launch failure
  * part-way leaves the earlier slabs done).
  */

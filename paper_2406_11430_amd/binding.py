@@ -208,7 +208,9 @@ def l2kv_norms(K: torch.Tensor, norms: torch.Tensor, stream=None) -> None:
 
 def l2kv_select(norms: torch.Tensor, keep_ratio: float, kept_idx: torch.Tensor,
                 kept_count: Optional[torch.Tensor], workspace: torch.Tensor, stream=None) -> None:
-    """norms ``[..., T]`` -> kept_idx ``[..., k]`` int32, k = l2kv_keep_count(T, keep_ratio)."""
+    """norms ``[..., T]`` -> kept_idx ``[..., k]`` int32, k = l2kv_keep_count(T, keep_ratio).
+
+    A workspace of more than 256 bytes (a few long heads) is used: one per call that may run at the same time."""
     _dev(norms, kept_idx, kept_count, workspace)
     T = norms.shape[-1]
     n = norms.numel() // T
@@ -257,7 +259,8 @@ def l2kv_compact(K: torch.Tensor, V: Optional[torch.Tensor], kept_idx: torch.Ten
 def l2kv_compress(K: torch.Tensor, V: torch.Tensor, keep_ratio: float, norms: torch.Tensor,
                   kept_idx: torch.Tensor, Kc: torch.Tensor, Vc: torch.Tensor, workspace: torch.Tensor,
                   slab_heads: int = 0, stream=None) -> None:
-    """norms -> select -> compact in one call (optionally slab by slab of ``slab_heads`` heads)."""
+    """norms -> select -> compact in one call (optionally slab by slab of ``slab_heads`` heads).  The workspace is not
+    touched; the outputs are scratch memory before they are filled."""
     _dev(K, V, norms, kept_idx, Kc, Vc, workspace)
     n, T, D = _heads(K)
     k = kept_idx.shape[-1]

@@ -94,7 +94,7 @@ l2kv_status l2kv_select_k(const float* norms, int64_t n_heads, int64_t T, int64_
         return L2KV_ERR_WORKSPACE;
     if (!aligned(norms, 4) || !aligned(kept_idx, 4) || !aligned(kept_count, 4) || !aligned(workspace, 16))
         return L2KV_ERR_ALIGN;
-    return select_dispatch(norms, n_heads, T, k, mode, kept_idx, kept_count, workspace, workspace_bytes,
+    return select_dispatch(norms, n_heads, T, k, mode, kept_idx, kept_count, select_scratch(workspace, workspace_bytes, n_heads, T),
                            static_cast<hipStream_t>(stream));
 }
 
@@ -157,7 +157,10 @@ l2kv_status l2kv_compress(const void* K, const void* V, l2kv_dtype dt, int64_t n
             if (st == L2KV_OK && select_compact_applies(nh, T, k, row_bytes)) {
                 st = select_compact_dispatch(ns, nh, T, k, Ks, Vs, dt, D, head_stride, is, Kd, Vd, s);
             } else if (st == L2KV_OK) {
-                st = select_dispatch(ns, nh, T, k, L2KV_KEEP_LOWEST, is, nullptr, workspace, workspace_bytes, s);
+                // The outputs of these heads, which the compaction fills afterwards, are the scratch memory of their
+                // selection: large enough from one kept row of 128 bytes in 32 on, and no other call's.
+                const size_t out = static_cast<size_t>(nh) * static_cast<size_t>(k) * static_cast<size_t>(row_bytes);
+                st = select_dispatch(ns, nh, T, k, L2KV_KEEP_LOWEST, is, nullptr, SelectScratch{Kd, out, Vd, out}, s);
                 if (st == L2KV_OK) st = compact_dispatch(Ks, Vs, dt, is, nh, T, k, D, head_stride, Kd, Vd, s);
             }
         }

@@ -28,10 +28,19 @@ l2kv_status norms_dispatch(const void* K, l2kv_dtype dt, int64_t n_heads, int64_
 // it is left out (120 heads of 32k 485 and 485).  l2kv_norms by itself does without: its caller may not compact.
 constexpr int64_t kReadAgainBytes = int64_t{128} << 20;
 
+// Scratch memory of a selection in which several workgroups share a head, 16-byte aligned; with less than it takes, or
+// none, every head is selected by one workgroup.
+struct SelectScratch {
+    void* counts = nullptr;
+    size_t counts_bytes = 0;
+    void* list = nullptr;
+    size_t list_bytes = 0;
+};
 l2kv_status select_dispatch(const float* norms, int64_t n_heads, int64_t T, int64_t k,
                             l2kv_mode mode, int32_t* kept_idx, int32_t* kept_count,
-                            void* workspace, size_t workspace_bytes, hipStream_t stream);
+                            const SelectScratch& scratch, hipStream_t stream);
 size_t select_workspace_bytes(int64_t n_heads, int64_t T);
+SelectScratch select_scratch(void* workspace, size_t bytes, int64_t n_heads, int64_t T);     // parts of a workspace of that size
 // Selection (keep lowest) and compaction in one launch, for short heads; where it applies.
 bool select_compact_applies(int64_t n_heads, int64_t T, int64_t k, int32_t row_bytes);
 l2kv_status select_compact_dispatch(const float* norms, int64_t n_heads, int64_t T, int64_t k, const void* K, const void* V,

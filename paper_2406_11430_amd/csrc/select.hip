@@ -442,7 +442,7 @@ void compress_short_kernel(const char* __restrict__ K, const char* __restrict__ 
 //   select_emit_kernel    every workgroup finishes the search over the candidates by itself (3 % of log-normal
 //                         norms, a third of the norms of rows without a scale of their own; all of them in the
 //                         worst case), counts what lies ahead of its chunk and emits its kept tokens
-// Counts and lists pass from kernel to kernel through the caller's memory.  No access is bounded by what is read there
+// Counts and lists pass from kernel to kernel through the caller's memory (SelectScratch).  No access is bounded by what is read there
 // alone: if two calls overlap on one workspace, against the contract, they select wrong rows and nothing worse.
 constexpr int kCoarse = 64;                          // coarse counts per chunk, of kTopBins / 64 digits each
 constexpr int kFinePerCoarse = kTopBins / kCoarse;   // 64
@@ -462,7 +462,7 @@ struct SelectSplit {
 struct SelectPlan {
     int64_t chunk = 0;    // 0: one workgroup per head
     int32_t chunks = 0;
-    size_t bytes = 256;
+    size_t counts = 256, list = 0;    // bytes of scratch memory
 };
 
 static size_t round256(size_t n) { return (n + 255) / 256 * 256; }
@@ -492,9 +492,9 @@ static SelectPlan select_plan(int64_t n_heads, int64_t T) {
     p.chunk = chunk;
     p.chunks = (int32_t)((T + chunk - 1) / chunk);
     const size_t n = (size_t)n_heads * (size_t)p.chunks;
-    p.bytes = round256(n * kTopBins * count_bytes(chunk)) + round256(n * kCoarse * sizeof(uint32_t)) +
-              round256(n * sizeof(uint2)) + round256((size_t)n_heads * 2 * sizeof(uint32_t)) +
-              round256((size_t)n_heads * (size_t)T * sizeof(uint32_t));
+    p.counts = round256(n * kTopBins * count_bytes(chunk)) + round256(n * kCoarse * sizeof(uint32_t)) +
+               round256(n * sizeof(uint2)) + round256((size_t)n_heads * 2 * sizeof(uint32_t));
+    p.list = round256((size_t)n_heads * (size_t)T * sizeof(uint32_t));
     return p;
 }
 
@@ -772,22 +772,31 @@ l2kv_status random_keys_dispatch(int64_t n_heads, int64_t T, uint32_t seed, floa
     return launch_status();
 }
 
-size_t select_workspace_bytes(int64_t n_heads, int64_t T) { return select_plan(n_heads, T).bytes; }
+size_t select_workspace_bytes(int64_t n_heads, int64_t T) {
+    const SelectPlan plan = select_plan(n_heads, T);
+    return plan.counts + plan.list;
+}
+
+SelectScratch select_scratch(void* workspace, size_t bytes, int64_t n_heads, int64_t T) {
+    const SelectPlan plan = select_plan(n_heads, T);
+    if (bytes < plan.counts + plan.list) return SelectScratch{};
+    return SelectScratch{workspace, plan.counts, static_cast<char*>(workspace) + plan.counts, plan.list};
+}
 
 l2kv_status select_dispatch(const float* norms, int64_t n_heads, int64_t T, int64_t k,
                             l2kv_mode mode, int32_t* kept_idx, int32_t* kept_count,
-                            void* workspace, size_t workspace_bytes, hipStream_t stream) {
+                            const SelectScratch& scratch, hipStream_t stream) {
     if (n_heads > 0x7fffffffLL) return L2KV_ERR_SHAPE;
     const uint32_t flip = mode == L2KV_KEEP_HIGHEST ? 0xffffffffu : 0u;
     const SelectPlan plan = select_plan(n_heads, T);
-    if (plan.chunk == 0 || workspace_bytes < plan.bytes) {
+    if (plan.chunk == 0 || scratch.counts_bytes < plan.counts || scratch.list_bytes < plan.list) {
         launch_select_for_length(T, norms, n_heads, T, k, flip, kept_idx, kept_count, stream,
                                  RaggedSelect{nullptr, nullptr, 0, 0, 0});
         return launch_status();
     }
     SelectSplit sp;
     const size_t n = (size_t)n_heads * (size_t)plan.chunks;
-    char* ws = static_cast<char*>(workspace);
+    char* ws = static_cast<char*>(scratch.counts);
     sp.fine = ws;
     ws += round256(n * kTopBins * count_bytes(plan.chunk));
     sp.coarse = reinterpret_cast<uint32_t*>(ws);
@@ -795,8 +804,7 @@ l2kv_status select_dispatch(const float* norms, int64_t n_heads, int64_t T, int6
     sp.info = reinterpret_cast<uint2*>(ws);
     ws += round256(n * sizeof(uint2));
     sp.head_info = reinterpret_cast<uint32_t*>(ws);
-    ws += round256((size_t)n_heads * 2 * sizeof(uint32_t));
-    sp.cand = reinterpret_cast<uint32_t*>(ws);
+    sp.cand = static_cast<uint32_t*>(scratch.list);
     sp.chunk = plan.chunk;
     sp.chunks = plan.chunks;
     const dim3 grid((unsigned)plan.chunks, (unsigned)n_heads);
