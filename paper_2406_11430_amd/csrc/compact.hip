@@ -79,11 +79,12 @@ static l2kv_status launch_compact(const void* K, const void* V, const int32_t* k
     if ((k + 63) / 64 * n_heads > 0x7fffffffLL) return L2KV_ERR_SHAPE;
     constexpr int64_t kFew = kCompactRowsPerBlock<kRowBytes, 4>, kMany = kCompactRowsPerBlock<kRowBytes, 1>;
     const int64_t few = (k + kFew - 1) / kFew, many = (k + kMany - 1) / kMany;
-    // While workgroups of 64 rows (128 short ones) of K and V all run at once, fewer and larger ones are the better: the eight
-    // times as many small ones are bound by how fast they start.  Half of 4k rows, us, together and in turn: 16 heads of
+    // While workgroups of 64 rows (128 short ones) of K and V all run at once, 16 MB of either, fewer and larger ones are the
+    // better: the eight times as many small ones are bound by how fast they start.  Half of 4k rows, us, together and in turn: 16 heads of
     // 256-byte rows (512 workgroups) 7.5, 8.5; 32 heads 13.3, 13.8; 64 heads 24.4, 24.3; 16 heads of 512-byte rows 12.4, 13.9; 32 heads
-    // of 128-byte rows 7.5, 8.4.  With fewer rows than a workgroup takes: 1000 heads of 32 rows 7.7, 7.1.
-    const bool together = V != nullptr && n_heads * few <= 1024 && k >= kFew;
+    // of 128-byte rows 7.5, 8.4; 32 heads of 512-byte rows (32 MB) 24.0, 24.5, but 0.9 of 16 of them within l2kv_compress 33.8,
+    // 31.3.  With fewer rows than a workgroup takes: 1000 heads of 32 rows 7.7, 7.1.
+    const bool together = V != nullptr && n_heads * few * kFew * kRowBytes <= int64_t{16} << 20 && k >= kFew;
     const int64_t bph = together ? few : V != nullptr ? 2 * many : many;
     auto kernel = together ? compact_kernel<kRowBytes, Tensors::kTogether, 4>
                   : V != nullptr ? compact_kernel<kRowBytes, Tensors::kInTurn, 1> : compact_kernel<kRowBytes, Tensors::kKeysOnly, 1>;

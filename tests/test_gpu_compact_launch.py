@@ -30,7 +30,8 @@ def same(a, b):
 
 
 @pytest.mark.parametrize("dtype,D", ROWS)
-# 64 (short rows 128) rows of K and V to a workgroup from that many rows on, up to 1024 workgroups; else 16 (32) of either
+# 64 (short rows 128) rows of K and V to a workgroup from that many rows on, up to 16 MB (1024 workgroups of 256-byte rows);
+# else 16 (32) of either
 @pytest.mark.parametrize("heads,T,k", [(1, 1, 1), (3, 40, 15), (3, 40, 16), (2, 70, 33), (70001, 2, 1), (3, 70, 64), (2, 140, 65),
                                        (1, 200, 127), (5, 200, 129), (1024, 130, 64), (1025, 130, 64), (512, 130, 128), (513, 260, 129)])
 @pytest.mark.parametrize("with_v", [True, False])
