@@ -300,10 +300,10 @@ void select_kernel(const uint32_t* __restrict__ norm_bits, int64_t T, uint32_t k
 // The kept rows of a head are shared by gridDim.x workgroups.  Each finds the threshold by itself (the keys of a
 // short head are a few per lane, so repeating the search costs less than the launch and the round trip
 // through memory that a search of its own takes), writes its share of the indices and copies
-// its share of the rows.  32 heads of 4k, half kept: 24.4 us for norms and this launch, 25.3 for the three kernels;
-// 8 heads of 4k 15.7 against 17.1.
+// its share of the rows.  With the norm pass, against three kernels, other inputs in every call: half of 8 heads of 2k 12.6 us
+// and 14.1, of 32 heads of 4k 25.2 and 26.0, of 8 heads of 8k 16.9 and 18.6.
 constexpr int kFuseMaxTokens = 8 * kSelThreads;
-constexpr int kFuseMaxHeads = 256, kFuseWorkgroups = 512;
+constexpr int kFuseMaxHeads = 256;
 constexpr int64_t kFuseMaxBytes = int64_t{20} << 20, kShortMaxBytes = int64_t{2} << 20;
 constexpr int kFuseRows = 4096;                       // most rows of a share: indices in LDS as 16-bit numbers
 static_assert(kFuseMaxTokens <= 65536, "token indices fit 16 bits");
@@ -831,19 +831,21 @@ static void launch_select_compact(const dim3 grid, int row_bytes, const float* n
 }
 
 // Where the kept rows fill the memory system for longer than the repeated search takes, a selection and a
-// compaction are the faster pair: 128
-// heads of 4k in fp32 (128 MB of kept rows) 126 us against 136, 32 heads of 8k (64 MB) 66 against 71; 32 of 4k in
-// bf16 (16 MB) the other way round, 25.3 against 24.4.
+// compaction do as well or better: half of 200 heads of 1k (26 MB of K) 35.5 us together and 35.0 apart, of 48 heads of 4k
+// (25 MB) 33.9 and 34.4, of 64 heads of 4k (34 MB) 41.4 and 41.9; below 17 MB together is the faster everywhere.
 bool select_compact_applies(int64_t n_heads, int64_t T, int64_t k, int32_t row_bytes) {
-    return T <= kFuseMaxTokens && n_heads <= kFuseMaxHeads && n_heads * k * row_bytes <= kFuseMaxBytes;
+    return T <= kFuseMaxTokens && n_heads <= (T <= 4 * kSelThreads ? kFuseMaxHeads : kFuseMaxHeads / 2) &&
+           n_heads * k * row_bytes <= kFuseMaxBytes;
 }
 bool compress_short_applies(int64_t n_heads, int64_t T, int64_t k, int32_t row_bytes) {
     return T <= kSelThreads && select_compact_applies(n_heads, T, k, row_bytes) && n_heads * T * row_bytes <= kShortMaxBytes;
 }
 
-// Rows of a share: a multiple of 16, and as many shares as run at once.
-static int64_t rows_per_share(int64_t n_heads, int64_t k, int64_t least) {
-    const int64_t shares = (kFuseWorkgroups + n_heads - 1) / n_heads;
+// Rows of a share: a multiple of 16, and no more shares than run at once: two on a compute unit, one with eight keys per
+// lane.  (A few workgroups more make a last round of whole searches: half of 100 heads of 1k and 64 elements 18.6 us with 600
+// workgroups, 15.4 with 500; of 8 heads of 8k 22.9 with 512, 16.9 with 256.)
+static int64_t rows_per_share(int64_t n_heads, int64_t T, int64_t k, int64_t least) {
+    const int64_t shares = (T <= 4 * kSelThreads ? 512 : 256) / n_heads;        // at least 1: kFuseMaxHeads
     const int64_t rows = ((k + shares - 1) / shares + 15) / 16 * 16;
     return rows > least ? rows : least;
 }
@@ -852,7 +854,7 @@ l2kv_status select_compact_dispatch(const float* norms, int64_t n_heads, int64_t
                                     l2kv_dtype dt, int32_t D, int64_t head_stride, int32_t* kept_idx, void* Kc, void* Vc,
                                     hipStream_t stream) {
     const int es = dt == L2KV_F32 ? 4 : 2;
-    const int64_t rows = rows_per_share(n_heads, k, 16);
+    const int64_t rows = rows_per_share(n_heads, T, k, 16);
     const dim3 grid((unsigned)((k + rows - 1) / rows), (unsigned)n_heads);
     const int64_t per_lane = (T + kSelThreads - 1) / kSelThreads;
     auto launch = per_lane <= 1 ? launch_select_compact<1> : per_lane <= 2 ? launch_select_compact<2>
@@ -864,7 +866,7 @@ l2kv_status select_compact_dispatch(const float* norms, int64_t n_heads, int64_t
 l2kv_status compress_short_dispatch(const void* K, const void* V, l2kv_dtype dt, int64_t n_heads, int64_t T, int32_t D,
                                     int64_t head_stride, int64_t k, float* norms, int32_t* kept_idx, void* Kc, void* Vc,
                                     hipStream_t stream) {
-    const int64_t rows = rows_per_share(n_heads, k, 64);             // every share reads the whole head
+    const int64_t rows = rows_per_share(n_heads, T, k, 64);             // every share reads the whole head
     const dim3 grid((unsigned)((k + rows - 1) / rows), (unsigned)n_heads);
     auto kernel = dt == L2KV_F32 ? (D == 64 ? compress_short_kernel<F32, 64> : compress_short_kernel<F32, 128>)
                   : D == 256 ? compress_short_kernel<BF16, 256>

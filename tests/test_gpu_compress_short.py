@@ -35,7 +35,8 @@ def separate(K, V, k):
                                      (torch.float32, 64), (torch.float32, 128)])
 @pytest.mark.parametrize("heads,T,ratio", [(1, 1, 1.0), (3, 2, 0.5), (1, 127, 0.3), (2, 1023, 0.51), (5, 1024, 1.0), (40, 1024, 0.01),
                                            (9, 1025, 0.5), (2, 2049, 0.9), (3, 4097, 0.1), (2, 8192, 1.0), (256, 300, 0.7),
-                                           (257, 300, 0.7), (2, 8193, 0.5)])
+                                           (257, 300, 0.7), (2, 8193, 0.5), (200, 130, 0.5), (171, 1100, 0.9), (128, 4097, 0.1),
+                                           (129, 4097, 0.1), (3, 8192, 0.9), (127, 4200, 0.05)])
 def test_compress_equals_the_three_calls(dev, dtype, D, heads, T, ratio):
     g = torch.Generator(device=dev).manual_seed(T + heads)
     K = torch.randn((heads, T, D), generator=g, device=dev) * torch.exp(0.5 * torch.randn((heads, T, 1), generator=g, device=dev))
