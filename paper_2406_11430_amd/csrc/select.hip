@@ -304,7 +304,7 @@ void select_kernel(const uint32_t* __restrict__ norm_bits, int64_t T, uint32_t k
 // and 14.1, of 32 heads of 4k 25.2 and 26.0, of 8 heads of 8k 16.9 and 18.6.
 constexpr int kFuseMaxTokens = 8 * kSelThreads;
 constexpr int kFuseMaxHeads = 256;
-constexpr int64_t kFuseMaxBytes = int64_t{20} << 20, kShortMaxBytes = int64_t{2} << 20;
+constexpr int64_t kFuseMaxBytes = int64_t{20} << 20, kShortMaxBytes = int64_t{2} << 20, kShortHeadBytes = int64_t{256} << 10;
 constexpr int kFuseRows = 4096;                       // most rows of a share: indices in LDS as 16-bit numbers
 static_assert(kFuseMaxTokens <= 65536, "token indices fit 16 bits");
 
@@ -373,7 +373,9 @@ void select_compact_kernel(const uint32_t* __restrict__ norm_bits, int64_t T, ui
 // head (out of the L2 for all but the first reader), the first share writes them.  Meant for the
 // smallest calls, whose time is the number of launches: 4 heads of 512
 // tokens, half kept, 10 us against 16 for three kernels (of 2.4, 5.7 and 3.3 us).  Not beyond 2 MB of K, which the
-// shares read over and over: 32 heads of 1000 tokens (8 MB) 18.2 against 14.7 for two launches.
+// shares read over and over (32 heads of 1024 tokens, 8 MB, 17.2 against 13.6 for two launches), and 256 KB of a head, which
+// one workgroup goes through before anything else: half of 1024 tokens of 2 heads, rows of 128 bytes 8.5 against 10.6, of
+// 256 bytes 10.3 and 10.4, of 512 bytes 15.6 against 11.8.
 template <typename E, int D>
 __global__ __launch_bounds__(kSelThreads)
 void compress_short_kernel(const char* __restrict__ K, const char* __restrict__ V, int64_t T, uint32_t k,
@@ -838,7 +840,8 @@ bool select_compact_applies(int64_t n_heads, int64_t T, int64_t k, int32_t row_b
            n_heads * k * row_bytes <= kFuseMaxBytes;
 }
 bool compress_short_applies(int64_t n_heads, int64_t T, int64_t k, int32_t row_bytes) {
-    return T <= kSelThreads && select_compact_applies(n_heads, T, k, row_bytes) && n_heads * T * row_bytes <= kShortMaxBytes;
+    return T <= kSelThreads && select_compact_applies(n_heads, T, k, row_bytes) && n_heads * T * row_bytes <= kShortMaxBytes &&
+           T * row_bytes <= kShortHeadBytes;
 }
 
 // Rows of a share: a multiple of 16, and no more shares than run at once: two on a compute unit, one with eight keys per
