@@ -383,7 +383,7 @@ void compress_short_kernel(const char* __restrict__ K, const char* __restrict__ 
                            int32_t* __restrict__ kept_idx, char* __restrict__ Kc, char* __restrict__ Vc) {
     using S = Slice<E, D>;
     __shared__ __attribute__((aligned(16))) FuseShared sh;
-    __shared__ float s_norm[kSelThreads];
+    __shared__ uint32_t s_norm[kSelThreads];                          // bit patterns
     const int64_t head = blockIdx.y;
     const uint32_t r0 = blockIdx.x * rows_per_share;
     if (r0 >= k) return;
@@ -405,7 +405,7 @@ void compress_short_kernel(const char* __restrict__ K, const char* __restrict__ 
             for (int u = 0; u < kBatch; ++u) {
                 const uint32_t row = base + 2 * (u * kGroups + threadIdx.x / kRowLanes) + c / 8;
                 const float v = row_pair_sum_of_squares(raw[u]);
-                if (c % 8 == 0 && row < n) s_norm[row] = v;
+                if (c % 8 == 0 && row < n) s_norm[row] = __builtin_bit_cast(uint32_t, v);
             }
         }
     } else {
@@ -423,13 +423,13 @@ void compress_short_kernel(const char* __restrict__ K, const char* __restrict__ 
                 float x[S::kElems];
                 widen<E, D>(raw[u], x);
                 const float v = chunked_sum_of_squares<E, D>(x);
-                if (c == 0 && row < n) s_norm[row] = v;
+                if (c == 0 && row < n) s_norm[row] = __builtin_bit_cast(uint32_t, v);
             }
         }
     }
     __syncthreads();
-    if (blockIdx.x == 0 && threadIdx.x < n) norms[head * T + threadIdx.x] = s_norm[threadIdx.x];
-    const HeadKeys<1> keys(reinterpret_cast<const uint32_t*>(s_norm), T, 0u);
+    if (blockIdx.x == 0 && threadIdx.x < n) norms[head * T + threadIdx.x] = __builtin_bit_cast(float, s_norm[threadIdx.x]);
+    const HeadKeys<1> keys(s_norm, T, 0u);
     const int64_t dense = head * (int64_t)k;
     select_and_copy<1, S::kRowBytes>(keys, k, r0, k - r0 < rows_per_share ? k - r0 : rows_per_share, Kh,
                                      V + head * head_stride_bytes, kept_idx + dense, Kc + dense * S::kRowBytes,
