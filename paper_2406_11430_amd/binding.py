@@ -136,12 +136,19 @@ def _ptr(t: Optional[torch.Tensor]):
     return None if t is None else t.data_ptr()      # the argument types turn plain integers into pointers
 
 
+# Not part of torch's public interface: None where a version does not have them.
+_raw_stream_of = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_device_index = getattr(torch._C, "_cuda_getDevice", None)
+
+
 def _stream(stream: Optional[torch.cuda.Stream]):
     # The current stream of the current device by its raw handle: building the stream object of
     # torch.cuda.current_stream() only to ask it for the handle takes longer than the launch.
-    if stream is None:
-        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
-    return stream.cuda_stream
+    if stream is not None:
+        return stream.cuda_stream
+    if _raw_stream_of is None or _device_index is None:
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream_of(_device_index())
 
 
 # ------------------------------------------------------------ host helpers
