@@ -816,8 +816,8 @@ __device__ __forceinline__ KeyRange gather_range(const uint32_t* src, uint32_t n
 
 // Sorts the list by key, equal keys in the order in which they stand.  Eight of the bits in which the keys may differ at
 // a time.  count <= kPer * 1024.  Called by all lanes; ends with a barrier.
-template <bool kWithPos, int kPer>
-__device__ __forceinline__ void sort_list(uint32_t* list_key, uint32_t* list_pos, uint32_t count, KeyRange range, BinShared& sh) {
+template <bool kWithPos, int kPer, typename Sh>
+__device__ __forceinline__ void sort_list(uint32_t* list_key, uint32_t* list_pos, uint32_t count, KeyRange range, Sh& sh) {
     const uint32_t lane = threadIdx.x % kWaveSize;
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWaveSize);
     const uint32_t span = range.most - range.least;
@@ -889,38 +889,44 @@ __device__ __forceinline__ void sort_list(uint32_t* list_key, uint32_t* list_pos
     }
 }
 
-// The elements of ranks [r0, r1) in order; returns where in the list they start.  A head that fits the list is sorted
-// whole (8 heads of 4k, 30 % zero: 24 us instead of 28).
+// All elements of a head that fits the list, in order (8 heads of 4k, 30 % zero: 24 us, 28 by the cuts).
+template <typename KeyOf, bool kWithPos, int kPer, typename Sh>
+__device__ __forceinline__ void sort_head(const uint32_t* src, uint32_t n, uint32_t* list_key, uint32_t* list_pos, Sh& sh) {
+    uint32_t least = 0xffffffffu, most = 0u;
+#pragma unroll
+    for (int u = 0; u < kPer; ++u) {
+        const uint32_t t = u * kSortLanes + threadIdx.x;
+        if (t < n) {
+            const uint32_t key = KeyOf::of(src[t]);
+            list_key[t] = key;
+            if constexpr (kWithPos) list_pos[t] = t;
+            least = key < least ? key : least;
+            most = key > most ? key : most;
+        }
+    }
+    least = wave_min(least);
+    most = ~wave_min(~most);
+    if (threadIdx.x % kWaveSize == 0) {
+        sh.wave[0][threadIdx.x / kWaveSize] = least;
+        sh.wave[1][threadIdx.x / kWaveSize] = most;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int w = 0; w < kSortWaves; ++w) {
+        least = sh.wave[0][w] < least ? sh.wave[0][w] : least;
+        most = sh.wave[1][w] > most ? sh.wave[1][w] : most;
+    }
+    sort_list<kWithPos, kPer>(list_key, list_pos, n, KeyRange{least, most}, sh);
+}
+
+// The elements of ranks [r0, r1) in order; returns where in the list they start.  Two shares and more would each sort the
+// whole head, which costs less than the cuts while it is short.
 template <typename KeyOf, bool kWithPos, int kPer>
 __device__ __forceinline__ uint32_t sorted_range(const uint32_t* src, uint32_t n, uint32_t r0, uint32_t r1, uint32_t* list_key,
                                                  uint32_t* list_pos, BinShared& sh, CutShared& cs) {
     __syncthreads();                                                  // the list is free
-    if (n <= (uint32_t)(kPer * kSortLanes)) {
-        uint32_t least = 0xffffffffu, most = 0u;
-#pragma unroll
-        for (int u = 0; u < kPer; ++u) {
-            const uint32_t t = u * kSortLanes + threadIdx.x;
-            if (t < n) {
-                const uint32_t key = KeyOf::of(src[t]);
-                list_key[t] = key;
-                if constexpr (kWithPos) list_pos[t] = t;
-                least = key < least ? key : least;
-                most = key > most ? key : most;
-            }
-        }
-        least = wave_min(least);
-        most = ~wave_min(~most);
-        if (threadIdx.x % kWaveSize == 0) {
-            cs.at_lo[threadIdx.x / kWaveSize] = least;
-            cs.at_hi[threadIdx.x / kWaveSize] = most;
-        }
-        __syncthreads();
-#pragma unroll
-        for (int w = 0; w < kSortWaves; ++w) {
-            least = cs.at_lo[w] < least ? cs.at_lo[w] : least;
-            most = cs.at_hi[w] > most ? cs.at_hi[w] : most;
-        }
-        sort_list<kWithPos, kPer>(list_key, list_pos, n, KeyRange{least, most}, sh);
+    if (n <= (uint32_t)(kPer * kSortLanes / 2) || (r0 == 0 && r1 == n && n <= (uint32_t)(kPer * kSortLanes))) {
+        sort_head<KeyOf, kWithPos, kPer>(src, n, list_key, list_pos, sh);
         return r0;
     }
     if (r0 == r1) return 0;                                           // the same for all lanes
@@ -962,6 +968,24 @@ void norm_ranks_kernel(const float* __restrict__ norms, int64_t T, uint32_t n_he
     const uint32_t r1 = s.crowded ? cut.start(part.share + 1) : s.base + s.count;
     const uint32_t at = sorted_range<NormKey, true, kPer>(src, n, r0, r1, s_list, list_pos, sh, s_cut);
     for (uint32_t i = threadIdx.x; i < r1 - r0; i += kSortLanes) rank[list_pos[at + i]] = n - 1 - (r0 + i);
+}
+
+// Short heads: sorted whole by one workgroup each, in so little LDS that two run on a compute unit.
+struct ShortShared {
+    uint32_t fine[kSortWaves * kBins];
+    uint32_t bin[kBins];
+    uint32_t wave[2][kSortWaves];
+};
+template <int kPer>
+__global__ __launch_bounds__(kSortLanes)
+void norm_ranks_short_kernel(const float* __restrict__ norms, int64_t T, int32_t* __restrict__ drop_rank) {
+    __shared__ ShortShared sh;
+    __shared__ uint32_t s_key[kPer * kSortLanes], s_pos[kPer * kSortLanes];
+    const uint32_t n = (uint32_t)T;
+    uint32_t* rank = reinterpret_cast<uint32_t*>(drop_rank) + blockIdx.x * T;
+    sort_head<NormKey, true, kPer>(reinterpret_cast<const uint32_t*>(norms) + blockIdx.x * T, n, s_key, s_pos, sh);
+    __syncthreads();                                                  // one key: no pass, no barrier
+    for (uint32_t i = threadIdx.x; i < n; i += kSortLanes) rank[s_pos[i]] = n - 1 - i;
 }
 
 // The same by the counting passes, one workgroup per head (share_plan has the line).
@@ -1235,6 +1259,28 @@ void alr_head_kernel(uint32_t* __restrict__ scratch, const int32_t* __restrict__
     if (threadIdx.x == 0) write_losses(acc, head, alr, loss, loss_ref);
 }
 
+// The same for short heads, sorted whole by one workgroup each.
+template <int kPer>
+__global__ __launch_bounds__(kSortLanes)
+void alr_head_short_kernel(uint32_t* __restrict__ scratch, const int32_t* __restrict__ drop_rank, int64_t T, int32_t G, int64_t m,
+                           double* __restrict__ alr, double* __restrict__ loss, double* __restrict__ loss_ref) {
+    __shared__ ShortShared sh;
+    __shared__ uint32_t s_key[kPer * kSortLanes];
+    __shared__ double stage[kSortWaves][kRecordSums];
+    const int64_t head = blockIdx.x;
+    const uint32_t n = (uint32_t)T;
+    uint32_t* logits = scratch + head * T;
+    sort_head<LogitKey, false, kPer>(logits, n, s_key, nullptr, sh);
+    __syncthreads();
+    const float mx = float_of_ordered(s_key[n - 1]);
+    RankedSums ranked;
+    for (uint32_t j = threadIdx.x; j < n; j += kSortLanes) add_ranked(ranked, score(float_of_ordered(s_key[j]), mx), j, m);
+    const PositionSums sums = position_sums<false>(logits, drop_rank + (head / G) * T, 0, n, m, mx, false, ranked);
+    double acc[kRecordSums] = {sums.all, sums.weighted, sums.dropped, ranked.weighted, ranked.lowest};
+    block_sum<kRecordSums>(acc, stage);
+    if (threadIdx.x == 0) write_losses(acc, head, alr, loss, loss_ref);
+}
+
 // The same by the counting passes, one workgroup per head.  Both scratch arrays are the passes'.
 __global__ __launch_bounds__(kSortLanes)
 void alr_head_passes_kernel(uint32_t* __restrict__ scratch, const int32_t* __restrict__ drop_rank, int64_t T, int32_t G, int64_t m,
@@ -1292,6 +1338,12 @@ int64_t share_plan(int64_t n_heads, int64_t T, int64_t list) {
     return n_heads * shares <= 0x7fffffffLL ? shares : 0;      // ceil(T / shares) + kMaxBin <= list
 }
 
+// Heads that are sorted whole in a small workgroup.  Binning takes 100 KB more of LDS, so that half as many run at once, and
+// does not gain on a sort of one or two keys per lane.  Norms, us, by bins / by the counting passes / whole: 16 heads of 300
+// 8.3, 11.0, 6.3 (30 % zero 34.8, 11.1, 6.3); 4096 heads of 300 117, 94, 52; 4096 of 1000 122, 152, 81; 1024 of 2000 37.5,
+// 70.9, 38.7 (30 % zero 77, 64, 37); the bins are the better 16 heads of 2000 9.0, 18.3, 12.1 and 1024 of 4096 50, 137, 71.
+bool is_short(int64_t n_heads, int64_t T) { return T <= kSortLanes || (T <= 2 * kSortLanes && n_heads >= 512); }
+
 template <typename E, int D>
 l2kv_status launch_scores(const void* Q, const void* K, int32_t B, int32_t Hkv, int32_t G, int64_t T,
                           int64_t k_head_stride, float scale_log2e, float* scores, uint32_t* records, hipStream_t stream) {
@@ -1325,6 +1377,11 @@ size_t alr_workspace_bytes(int32_t B, int32_t Hq, int64_t T) {
 
 l2kv_status norm_ranks_dispatch(const float* norms, int64_t n_heads, int64_t T, int32_t* drop_rank,
                                 void* workspace, hipStream_t stream) {
+    if (is_short(n_heads, T)) {
+        auto kernel = T <= kSortLanes ? norm_ranks_short_kernel<1> : norm_ranks_short_kernel<2>;
+        hipLaunchKernelGGL(kernel, dim3((unsigned)n_heads), dim3(kSortLanes), 0, stream, norms, T, drop_rank);
+        return launch_status();
+    }
     const int64_t shares = share_plan(n_heads, T, kListWords / 2 - kListAhead);
     if (shares == 0) {
         hipLaunchKernelGGL(norm_ranks_passes_kernel, dim3((unsigned)n_heads), dim3(kSortLanes), 0, stream, norms, T,
@@ -1346,7 +1403,7 @@ l2kv_status alr_dispatch(const void* Q, const void* K, l2kv_dtype dt, const int3
     const float scale_log2e = s * 1.44269504088896340736f;
     float* scores = static_cast<float*>(workspace);
     const int64_t n_heads = (int64_t)B * Hq;
-    const int64_t shares = share_plan(n_heads, T, kListWords - kListAhead);
+    const int64_t shares = is_short(n_heads, T) ? 1 : share_plan(n_heads, T, kListWords - kListAhead);
     uint32_t* records = shares > 1 ? static_cast<uint32_t*>(workspace) + n_heads * T : nullptr;
     l2kv_status st;
     if (dt == L2KV_BF16 && D == 256)
@@ -1358,6 +1415,12 @@ l2kv_status alr_dispatch(const void* Q, const void* K, l2kv_dtype dt, const int3
         st = D == 128 ? launch_scores<F32, 128>(Q, K, B, Hkv, G, T, k_head_stride, scale_log2e, scores, records, stream)
                       : launch_scores<F32, 64>(Q, K, B, Hkv, G, T, k_head_stride, scale_log2e, scores, records, stream);
     if (st != L2KV_OK) return st;
+    if (is_short(n_heads, T)) {
+        auto kernel = T <= kSortLanes ? alr_head_short_kernel<1> : alr_head_short_kernel<2>;
+        hipLaunchKernelGGL(kernel, dim3((unsigned)n_heads), dim3(kSortLanes), 0, stream,
+                           static_cast<uint32_t*>(workspace), drop_rank, T, G, m, alr, loss, loss_ref);
+        return launch_status();
+    }
     if (shares == 0) {
         hipLaunchKernelGGL(alr_head_passes_kernel, dim3((unsigned)n_heads), dim3(kSortLanes), 0, stream,
                            static_cast<uint32_t*>(workspace), drop_rank, T, G, m, alr, loss, loss_ref);

@@ -63,6 +63,15 @@ def test_norm_ranks(dev, T):
     assert np.array_equal(ranks(dev, norms), expected(norms))
 
 
+# one workgroup per head up to 1024 elements, and up to 2048 from 512 heads on
+@pytest.mark.parametrize("T", [1, 64, 65, 1000, 1024, 1025, 2000, 2048, 2049])
+@pytest.mark.parametrize("heads", [9, 513])
+def test_short_heads(dev, heads, T):
+    one = key_sets(np.random.default_rng(T), T)
+    norms = np.ascontiguousarray(one[np.arange(heads) % len(one)])
+    assert np.array_equal(ranks(dev, norms), expected(one)[np.arange(heads) % len(one)])
+
+
 # 65 shares of a head of 600k, all heads by the passes (64 x 66 shares would be too many), 4M elements in a bin's range
 @pytest.mark.parametrize("heads,T", [(1, 599999), (64, 600001), (1, 4194305)])
 def test_long_heads(dev, heads, T):
@@ -75,7 +84,8 @@ def test_long_heads(dev, heads, T):
 
 
 # rows repeated a few hundred times: clusters of equal logits below (300, 900) and above (1100) what a bin may hold
-@pytest.mark.parametrize("T,Hkv,G", [(2049, 1, 1), (4096, 2, 4), (19453, 2, 4), (45000, 1, 2)])
+@pytest.mark.parametrize("T,Hkv,G", [(1, 1, 1), (700, 2, 4), (1024, 1, 3), (1025, 1, 2), (1500, 64, 8), (2049, 1, 1), (4096, 2, 4),
+                                     (10241, 1, 2), (19453, 2, 4), (45000, 1, 2)])
 @pytest.mark.parametrize("each", [100, 300, 900, 1100])
 @pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
 def test_alr(dev, T, Hkv, G, each, dtype):
@@ -121,12 +131,11 @@ def seconds(f):
     return best
 
 
-@pytest.mark.parametrize("each", [100, 300, 900, 3000])
-def test_clusters_do_not_cost_many_times_distinct_keys(dev, each):
+@pytest.mark.parametrize("heads,T,each", [(128, 8192, 100), (128, 8192, 300), (128, 8192, 900), (128, 8192, 3000), (1024, 900, 200)])
+def test_clusters_do_not_cost_many_times_distinct_keys(dev, heads, T, each):
     """The comparisons inside a bin grow with the square of its equal keys: 128 heads of 8192 took 34 times as long
     at 900 equal norms per value.  A sort of the share instead takes a few times as long."""
     rng = np.random.default_rng(each)
-    T, heads = 8192, 128
     sets = [(np.exp(rng.standard_normal((heads, T))) * 128).astype(np.float32), np.stack([levels(rng, T, each) for _ in range(heads)])]
     rank = torch.empty((heads, T), dtype=torch.int32, device=dev)
     ws = torch.empty(l2kv.l2kv_norm_ranks_workspace_bytes(heads, T), dtype=torch.uint8, device=dev)
