@@ -28,7 +28,8 @@
 // Where the bins do not separate the keys -- more than kMaxBin elements in a bin of the head, more than
 // kMaxFine in a finer one: tied or clustered rows, one outlier that stretches the bins of a long head, heads
 // of a million elements -- a share finds the elements of its ranks exactly and sorts them (sorted_range).
-// The counting passes, one workgroup per head, remain for many long heads.
+// Short heads are sorted whole, one small workgroup each (is_short, sort_head).  The counting passes, one workgroup per
+// head, remain for many long heads (share_plan).
 //
 // The counting passes are a least-significant-digit radix sort (4 passes of 8 bits) by
 // one 1024-lane workgroup.  Each wavefront owns a contiguous chunk of

@@ -304,7 +304,7 @@ constexpr int64_t kEvictWaveTeams = 2048;
 // workgroup teams 4 wave results through LDS.  Token ids are read only where two norms tie.  The
 // row that would move into the hole is known before the scan (the last one) and requested ahead of
 // it.  In the steady state of a growing budget at most one slot goes per step.  One of
-// 512 to 4096 slots from each of 64 sequences in 16 planes: 12.1 -> 7.2 us, in 256 planes 36 -> 24 (ids read and
+// 512 to 4096 slots from each of 64 sequences in 16 planes: 12.1 -> 7.2 us, in 256 planes 31 -> 26 (ids read and
 // merged for every lane, the row requested after the scan, one wave per team in both).
 template <int W, int kTeam>
 __global__ __launch_bounds__(kEvictThreads)

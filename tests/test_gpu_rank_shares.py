@@ -1,6 +1,6 @@
 """Ranking by value ranges in the attention-loss analysis: head lengths around the switches between
 launch shapes (keys in registers or re-read, one or several shares per head), key sets that fill
-the bins unevenly, and the counting passes that take over where a bin is too full."""
+the bins unevenly, and the exact cut and sort that take over where a bin is too full."""
 import numpy as np
 import pytest
 import torch
@@ -65,7 +65,7 @@ def test_alr(dev, T, Hkv, G, rows):
     K = (rng.standard_normal((1, Hkv, T, 128)) * np.exp(0.5 * rng.standard_normal((1, Hkv, T, 1)))).astype(np.float32)
     Q = rng.standard_normal((1, Hkv * G, 128)).astype(np.float32)
     if rows == "half zero":
-        K[:, :, rng.permutation(T)[:T // 2]] = 0.0                     # half of the logits equal: counting passes
+        K[:, :, rng.permutation(T)[:T // 2]] = 0.0                     # half of the logits equal: cut and sorted
     if rows == "one large":
         K[:, :, 7] *= 30.0                                             # stretches the bins
     if rows == "zero query":
