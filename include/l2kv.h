@@ -159,7 +159,7 @@ l2kv_status l2kv_compact(const void* K, const void* V, l2kv_dtype dt,
  * l2kv_compact enqueued back to back on `stream`, with the same results as the
  * three separate calls.
  *   slab_heads : 0 = all heads at once (three launches; one or two for short
- *                heads).  > 0 = the three
+ *                heads, five for a few long ones).  > 0 = the three
  *                steps are enqueued slab by slab of that many consecutive
  *                heads, so that the compaction's second read of
  *                the kept K rows of a slab can be served by the caches while
