@@ -23,7 +23,7 @@
 // gathering: two thirds of the time) and the LDS round trips of the comparisons, so the
 // shares are as few as the LDS list allows until they fill the chip.  (One workgroup per
 // head and four counting passes of 8 bits over global memory, which this replaces, took
-// 196 us for 32 heads of 32k norms and 221 us for 128 heads of scores; now 22 and 43 us.
+// 196 us for 32 heads of 32k norms and 221 us for 128 heads of scores; now 22 and 33 us.
 // 131k norms of 8 heads: 671 -> 52 us.)
 // Where the bins do not separate the keys -- more than kMaxBin elements in a bin of the head, more than
 // kMaxFine in a finer one: tied or clustered rows, one outlier that stretches the bins of a long head, heads
@@ -190,6 +190,7 @@ constexpr int kListWords = kListPer * kSortLanes;    // 80 KB
 constexpr int kListAhead = 4;                        // words read past the last element of a share
 constexpr uint32_t kMaxBin = 1024;                   // elements of one bin of a head that is cut along bins
 constexpr uint32_t kLongHead = 1 << 17;              // keys from which the counters of the bins have copies
+constexpr int kDppWaveShl1 = 0x130;                  // lane i <- lane i + 1; the last lane keeps its own
 constexpr uint32_t kMaxFine = 64;                    // elements of a finer bin that are compared with each other
 
 constexpr int kFinePer = 8;                          // finer bins per lane
@@ -197,7 +198,7 @@ constexpr int kFineBins = kFinePer * kSortLanes;
 
 struct __attribute__((aligned(16))) BinShared {
     uint32_t bin[kRankBins + 4];                     // of the head; one word more than bins
-    uint32_t fine[kFineBins];                        // of the share
+    uint32_t fine[kFineBins + kWaveSize];            // of the share; a word per lane for keys of other shares
     uint32_t wave[2][kSortWaves];
     uint32_t first, end, base, stop, crowded;
     uint32_t ticket;
@@ -257,12 +258,10 @@ struct ValueBins {
         const float scale = (float)kRankBins / (kmax - kmin);
         return ValueBins{-kmin * scale, scale};
     }
-    __device__ __forceinline__ uint32_t operator()(float key) const {
-        return (uint32_t)fminf(fmaxf(fmaf(key, scale, offset), 0.f), (float)(kRankBins - 1));
-    }
-    __device__ __forceinline__ float within(float key, uint32_t b) const {
-        return fminf(fmaxf(fmaf(key, scale, offset) - (float)b, 0.f), 1.f);
-    }
+    static constexpr float kTop = (float)kRankBins - 0x1p-12f;       // the largest below the number of bins
+    __device__ __forceinline__ float position(float key) const { return __builtin_amdgcn_fmed3f(fmaf(key, scale, offset), 0.f, kTop); }
+    __device__ __forceinline__ uint32_t operator()(float key) const { return (uint32_t)position(key); }
+    __device__ __forceinline__ float within(float key, uint32_t) const { return __builtin_amdgcn_fractf(position(key)); }
 };
 // Bit patterns that order like the floats (other than NaN) they are made from, for the counting passes.
 __device__ __forceinline__ uint32_t ordered_bits(uint32_t bits) { return bits ^ ((int32_t)bits < 0 ? 0xffffffffu : 0x80000000u); }
@@ -473,6 +472,19 @@ __device__ __forceinline__ Share<typename Keys::Bins> find_share(const Keys& key
 // against 46.  Hits are gathered with one counter update per wave and batch (a ballot and an update per key:
 // 16k cycles of the 48k of a share, now 7k).  Equal keys rank by position (kWithPos), else in any order.  Called by all lanes; the
 // list is free again after the caller's barrier.
+template <typename Bins> struct FineBins {
+    const Share<Bins>& s;
+    const BinShared& sh;
+    const float per_rank;
+    __device__ __forceinline__ FineBins(const Share<Bins>& share, const BinShared& shared)
+        : s(share), sh(shared), per_rank((float)kFineBins / (float)(share.count > 0 ? share.count : 1)) {}
+    __device__ __forceinline__ uint32_t operator()(typename Bins::Key key) const {
+        const uint32_t b = s.bins(key);
+        const uint32_t start = sh.bin[b], next = sh.bin[b + 1];
+        const float expected = fmaf(s.bins.within(key, b), (float)(next - start), (float)(start - s.base));
+        return (uint32_t)fminf(expected * per_rank, (float)(kFineBins - 1));
+    }
+};
 template <int kPer, typename Bins> struct Ranked {
     typename Bins::Key key[kPer];
     uint32_t pos[kPer], rank[kPer];
@@ -509,13 +521,7 @@ __device__ __forceinline__ bool rank_share(const Keys& keys, const Share<typenam
         }
     });
     __syncthreads();
-    const float per_rank = (float)kFineBins / (float)(s.count > 0 ? s.count : 1);
-    auto fine_bin = [&](Key key) {
-        const uint32_t b = s.bins(key);
-        const uint32_t start = sh.bin[b], next = sh.bin[b + 1];
-        const float expected = fmaf(s.bins.within(key, b), (float)(next - start), (float)(start - s.base));
-        return (uint32_t)fminf(expected * per_rank, (float)(kFineBins - 1));
-    };
+    const FineBins<typename Keys::Bins> fine_bin(s, sh);
 #pragma unroll
     for (int u = 0; u < kPer; ++u) {
         const uint32_t i = u * kSortLanes + threadIdx.x;
@@ -601,6 +607,152 @@ __device__ __forceinline__ bool rank_share(const Keys& keys, const Share<typenam
         }
     }
     return true;
+}
+
+// ---- the elements of a share in order, straight from registers ----------------------------------
+// For logits, whose positions do not matter, while the keys of the head stay in registers.  A key of the share is
+// counted in its finer bin as it stands; the number the counter returns is its place in that bin, so that one
+// more store puts it there, and nothing is gathered or read again.  What is then left to do is order inside the finer bins, of
+// two elements on average: a lane sorts 32 neighbours in registers, which does every bin that does not reach over their end, and
+// merges the upper half of them with the lower half of the next lane's, which does the others, as long as
+// no bin has more than 17.  The lane then holds 32 elements of consecutive ranks and adds them up.
+// What bounds it: a key costs 0.2 us per vector instruction and CU (32 keys a lane, four waves a SIMD), and each of its LDS
+// accesses 10 to 15 cycles a wave with its bank conflicts; so a key's way takes a dozen instructions, one atomic and two
+// reads, all lanes doing the same.  128 heads of 32k logits in two shares each, us: fetch and range 6.6, coarse bins 3.9, finer
+// bins 4.0, starts 1.4, scatter 3.9, sort 2.7, merge and sums 4.5, position sums 5.1, records 0.9: 33 in place of 45 with
+// the keys fetched three times, gathered into a list, counted and compared there (6.3 + 3.4 + 3.5 + 10.3 + 3.2).
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+constexpr int kTogetherKeys = 4;                     // keys whose LDS round trips overlap (8: the same time)
+constexpr int kRun = 32;                             // elements a lane sorts
+constexpr uint32_t kMaxRun = kRun / 2 + 1;           // of one finer bin
+constexpr uint32_t kListFront = kRun / 2;            // words of the list in front of the first element
+
+template <int kN, int kSpan, int kStep> __device__ __forceinline__ void merge_step(float (&x)[kN]) {
+#pragma unroll
+    for (int j = kStep % kSpan; j + kStep < kN; j += 2 * kStep) {
+#pragma unroll
+        for (int i = 0; i < kStep; ++i) {
+            const int a = i + j, b = a + kStep;
+            if (b < kN && a / (2 * kSpan) == b / (2 * kSpan)) {
+                const float lo = fminf(x[a], x[b]), hi = fmaxf(x[a], x[b]);
+                x[a] = lo;
+                x[b] = hi;
+            }
+        }
+    }
+    if constexpr (kStep > 1) merge_step<kN, kSpan, kStep / 2>(x);
+}
+// Sorted runs of kSpan become one of kN: Batcher's odd-even merge sort.
+template <int kN, int kSpan> __device__ __forceinline__ void merge_runs(float (&x)[kN]) {
+    merge_step<kN, kSpan, kSpan>(x);
+    if constexpr (2 * kSpan < kN) merge_runs<kN, 2 * kSpan>(x);
+}
+
+// Word of the list for an element: 16-byte pieces of the 32 words of a lane in an order that depends on the lane, so
+// that lanes reading the same piece of theirs hit different banks.
+__device__ __forceinline__ uint32_t run_word(uint32_t at) { return at ^ ((at >> 5 & 7u) << 2); }
+
+enum ShareOrder { kInOrder, kTooManyForRuns, kTooManyForBins };
+// kInOrder: run[] holds the elements of ranks kRun * threadIdx.x .. inside the share, as far as they are below s.count.
+// Otherwise nothing.  Called by all lanes; the list is free again after the caller's barrier.
+template <int E>
+__device__ __forceinline__ ShareOrder order_share(const HeadKeys<E, ValueBins>& keys, const Share<ValueBins>& s, BinShared& sh,
+                                                  float* list, float (&run)[kRun]) {
+    const uint32_t lane = threadIdx.x % kWaveSize;
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWaveSize);
+    const uint32_t bins = s.end - s.first;
+    for (int i = 0; i < kFinePer / 4; ++i) reinterpret_cast<uint4*>(sh.fine)[i * kSortLanes + threadIdx.x] = make_uint4(0, 0, 0, 0);
+    // A bin of the head as a line: the finer bin its first element is expected in, and how many it spans.  Its end does not
+    // reach past the start of the next one, whatever the rounding, so the finer bins are in the order of the keys.
+    f32x2* const line = reinterpret_cast<f32x2*>(list);               // the list is not in use yet
+    const float per_rank = ((float)kFineBins - 0.5f) / (float)(s.count > 0 ? s.count : 1);
+#pragma unroll
+    for (int i = 0; i < kRankBins / kSortLanes; ++i) {
+        const uint32_t b = threadIdx.x + i * kSortLanes;
+        const float here = (float)(int32_t)(sh.bin[b] - s.base) * per_rank, next = (float)(int32_t)(sh.bin[b + 1] - s.base) * per_rank;
+        line[b] = f32x2{here, (next - here) * (1.f - 0x1p-22f)};
+    }
+    __syncthreads();
+    // Keys of other shares are counted in a word of the lane instead of being branched around: nothing stands between one
+    // key's LDS round trips and the next one's.
+    static_assert((kMaxFine + 1) * kFineBins * 8 < 0xffffffffu, "number in the bin and offset of its counter in one word");
+    uint32_t place[E];
+    uint32_t left = keys.n - threadIdx.x;                             // negative past the end
+    asm volatile("" : "+v"(left));
+    const uint32_t aside = (kFineBins + lane) * 4;
+#pragma unroll
+    for (int e0 = 0; e0 < E; e0 += kTogetherKeys) {
+#pragma unroll
+        for (int u = 0; u < kTogetherKeys; ++u) {
+            const float at = s.bins.position(keys.reg[e0 + u]);
+            const uint32_t b = (uint32_t)at;
+            const f32x2 in_bin = line[b];
+            const uint32_t f = (uint32_t)fmaf(__builtin_amdgcn_fractf(at), in_bin.y, in_bin.x) * 4;
+            const bool mine = ((int32_t)left > (e0 + u) * kSortLanes) & (b - s.first < bins);
+            place[e0 + u] = mine ? f : aside;
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int u = 0; u < kTogetherKeys; ++u) {
+            uint32_t* const counter = reinterpret_cast<uint32_t*>(reinterpret_cast<char*>(sh.fine) + place[e0 + u]);
+            place[e0 + u] |= atomicAdd(counter, 1u) * (kFineBins * 8);
+        }
+#pragma unroll
+        for (int u = 0; u < kTogetherKeys; ++u) asm volatile("" : "+v"(place[e0 + u]));       // one register each, not two
+    }
+    __syncthreads();
+    Counts<kFinePer> c;
+    c.load(sh.fine);
+    counts_to_starts(c, sh.fine, sh.wave[0]);
+#pragma unroll
+    for (int i = 0; i < kFinePer; ++i)
+        if (c.v[i] > kMaxRun) atomicOr(&sh.crowded, c.v[i] > kMaxFine ? 2u : 1u);       // 0 so far: the head is not crowded
+    __syncthreads();
+    if (sh.crowded != 0) return sh.crowded < 2 ? kTooManyForRuns : kTooManyForBins;
+    constexpr uint32_t kAside = kListFront + kListWords;              // behind the longest share
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+        const uint32_t f = place[e] % (kFineBins * 8);
+        const uint32_t start = *reinterpret_cast<const uint32_t*>(reinterpret_cast<const char*>(sh.fine) + f);
+        const uint32_t at = run_word(start + place[e] / (kFineBins * 8) + kListFront);
+        list[f < kFineBins * 4 ? at : kAside + lane] = keys.reg[e];
+    }
+    if (threadIdx.x < kListFront) list[run_word(threadIdx.x)] = -INFINITY;
+    __syncthreads();
+    // Lane i: the words 32 i .. 32 i + 31, elements from 16 before its ranks on.
+    const uint32_t words = s.count + kListFront;
+    float x[kRun];
+    if (wave * (kWaveSize * kRun) < words) {
+#pragma unroll
+        for (uint32_t q = 0; q < kRun / 4; ++q) {
+            const uint32_t at = threadIdx.x * kRun + 4 * q;
+            f32x4 v = {INFINITY, INFINITY, INFINITY, INFINITY};
+            if (at < words) v = *reinterpret_cast<const f32x4*>(list + run_word(at));
+#pragma unroll
+            for (uint32_t i = 0; i < 4; ++i) x[4 * q + i] = at + i < words ? v[i] : INFINITY;
+        }
+        merge_runs<kRun, 1>(x);
+    } else {
+#pragma unroll
+        for (int i = 0; i < kRun; ++i) x[i] = INFINITY;
+    }
+    // the lower half of the next lane's; of the next wave's first lane through LDS
+    float* const edge = reinterpret_cast<float*>(sh.fine);
+    if (lane == 0) {
+#pragma unroll
+        for (uint32_t i = 0; i < kRun / 2; ++i) edge[wave * (kRun / 2) + i] = x[i];
+    }
+    __syncthreads();
+#pragma unroll
+    for (uint32_t i = 0; i < kRun / 2; ++i) {
+        const float next = wave + 1 < (uint32_t)kSortWaves ? edge[(wave + 1) * (kRun / 2) + i] : INFINITY;
+        run[kRun / 2 + i] = __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(__builtin_bit_cast(int, next),
+                                                                                 __builtin_bit_cast(int, x[i]), kDppWaveShl1, 0xf, 0xf, false));
+        run[i] = x[kRun / 2 + i];
+    }
+    merge_step<kRun, kRun / 2, kRun / 2>(run);
+    return kInOrder;
 }
 
 // ---- ranking by an exact cut and a sort ---------------------------------------------------------
@@ -827,10 +979,14 @@ __device__ __forceinline__ void sort_list(uint32_t* list_key, uint32_t* list_pos
     const uint32_t first = wave * chunk;                              // of this wave; chunk <= kPer * 64
     const uint32_t mine = first >= count ? 0u : (count - first < chunk ? count - first : chunk);
     static_assert(kSortWaves * kBins <= kFineBins && kBins <= kRankBins && kBins % kWaveSize == 0, "counters fit the bins");
-    volatile uint32_t* const counts = sh.fine + wave * kBins;         // of this wave: its elements of every digit so far
+    // of this wave: its elements of every digit so far.  (Read and written for the other lanes to see, not `volatile`: that would
+    // keep the compiler from learning, in a function of its own, that it points into LDS.)
+    uint32_t* const counts = sh.fine + wave * kBins;
+    auto count_of = [&](uint32_t d) { return __hip_atomic_load(counts + d, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT); };
+    auto set_count = [&](uint32_t d, uint32_t v) { __hip_atomic_store(counts + d, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT); };
     for (int shift = 0; shift < bits; shift += kRadixBits) {
         uint32_t key[kPer], pos[kPer], place[(kPer + 1) / 2];          // places below 2^16, two to a word
-        for (uint32_t i = lane; i < kBins; i += kWaveSize) counts[i] = 0u;
+        for (uint32_t i = lane; i < kBins; i += kWaveSize) set_count(i, 0u);
 #pragma unroll
         for (int u = 0; u < kPer; ++u) {
             const uint32_t i = u * kWaveSize + lane;
@@ -850,11 +1006,11 @@ __device__ __forceinline__ void sort_list(uint32_t* list_key, uint32_t* list_pos
                 same &= set ? has : ~has;
             }
             const uint32_t before = lanes_below(same), together = (uint32_t)__popcll(same);
-            const uint32_t so_far = counts[d];
+            const uint32_t so_far = count_of(d);
             if (u % 2 == 0) place[u / 2] = so_far + before;
             else place[u / 2] |= (so_far + before) << 16;
             __builtin_amdgcn_wave_barrier();
-            if (valid && before + 1 == together) counts[d] = so_far + together;      // last lane of the digit
+            if (valid && before + 1 == together) set_count(d, so_far + together);    // last lane of the digit
             __builtin_amdgcn_wave_barrier();
         }
         __syncthreads();
@@ -877,7 +1033,7 @@ __device__ __forceinline__ void sort_list(uint32_t* list_key, uint32_t* list_pos
             if (u % 4 == 0) __builtin_amdgcn_sched_barrier(0);        // not the reads of all steps at once: the registers are full
             if (u * kWaveSize + lane < mine) {
                 const uint32_t d = (key[u] - range.least) >> shift & (kBins - 1);
-                uint32_t at = sh.bin[d] + counts[d] + (place[u / 2] >> (u % 2 * 16) & 0xffffu);
+                uint32_t at = sh.bin[d] + count_of(d) + (place[u / 2] >> (u % 2 * 16) & 0xffffu);
 #pragma unroll
                 for (uint32_t w = 0; w + 1 < (uint32_t)(kBins / kWaveSize); ++w) at += w < d / kWaveSize ? sh.wave[0][w] : 0u;
                 if (at < count) {
@@ -1166,12 +1322,84 @@ __device__ __forceinline__ PositionSums position_sums(uint32_t* logits, const in
     return sums;
 }
 
+// The elements of ranks r0 .. r0 + kRun - 1, `count` of which are there.
+__device__ __forceinline__ void add_run(RankedSums& sums, const float (&run)[kRun], float mx, uint32_t r0, uint32_t count, int64_t m) {
+    double all = 0.0, above = 0.0;                                    // sum e, sum e * (rank - r0)
+#pragma unroll
+    for (int i = kRun - 1; i >= 0; --i) {
+        if (i < kRun - 1) above += all;
+        all += (uint32_t)i < count ? score(run[i], mx) : 0.0;
+    }
+    sums.weighted += all * (double)r0 + above;
+    if ((int64_t)r0 + kRun <= m) {
+        sums.lowest += all;
+    } else if ((int64_t)r0 < m) {
+#pragma unroll
+        for (int i = 0; i < kRun; ++i) sums.lowest += (uint32_t)i < count && (int64_t)(r0 + i) < m ? score(run[i], mx) : 0.0;
+    }
+}
+
 __device__ __forceinline__ void write_losses(const double (&acc)[kRecordSums], int64_t head, double* __restrict__ alr,
                                              double* __restrict__ loss, double* __restrict__ loss_ref) {
     alr[head] = (acc[3] - acc[1]) / acc[0];
     if (loss != nullptr) loss[head] = acc[2] / acc[0];
     if (loss_ref != nullptr) loss_ref[head] = acc[4] / acc[0];
 }
+
+// What the ranking of a head's scores keeps in LDS, one for the kernel and what it calls.
+struct HeadShared {
+    BinShared sh;
+    CutShared cut;
+    __attribute__((aligned(16))) uint32_t list[kListFront + kListWords + kWaveSize];
+    double stage[kSortWaves][kRecordSums];
+};
+__device__ __forceinline__ HeadShared& head_shared() {
+    __shared__ HeadShared all;
+    return all;
+}
+
+// The sums in order of rank of one share, whose bins are known: by comparing inside the finer bins, or, where there are too
+// many elements in one, by an exact cut and a sort.
+template <typename Keys>
+__device__ __forceinline__ RankedSums ranked_sums(const Keys& keys, const Share<ValueBins>& s, const Cut& cut, uint32_t share,
+                                                  bool compare, int64_t m) {
+    HeadShared& lds = head_shared();
+    RankedSums ranked;
+    if (compare) {
+        // ranks inside the share, then the sums in order of rank
+        float* const list = reinterpret_cast<float*>(lds.list);
+        Ranked<kListPer, ValueBins> mine;
+        if (rank_share<false, kListPer>(keys, s, lds.sh, list, nullptr, mine)) {
+            __syncthreads();
+#pragma unroll
+            for (int u = 0; u < kListPer; ++u)
+                if (u * kSortLanes + threadIdx.x < s.count) list[mine.rank[u]] = mine.key[u];
+            __syncthreads();
+            for (uint32_t i = threadIdx.x; i < s.count; i += kSortLanes) add_ranked(ranked, score(list[i], s.kmax), s.base + i, m);
+            return ranked;
+        }
+    }
+    const uint32_t r0 = s.crowded ? cut.start(share) : s.base;
+    const uint32_t r1 = s.crowded ? cut.start(share + 1) : s.base + s.count;
+    const uint32_t at = sorted_range<LogitKey, false, kListPer>(keys.src, keys.n, r0, r1, lds.list, nullptr, lds.sh, lds.cut);
+    for (uint32_t i = threadIdx.x; i < r1 - r0; i += kSortLanes)
+        add_ranked(ranked, score(float_of_ordered(lds.list[at + i]), s.kmax), r0 + i, m);
+    return ranked;
+}
+// A function of its own: inlined, its registers made the path that nearly all heads take spill (42 us in place of 33).  Half of the logits
+// equal, 128 heads of 32768: 165 us, 155 inlined.
+typedef const uint32_t __attribute__((address_space(1)))* GlobalWords;     // of a plain pointer it would not know that it is not LDS
+__device__ __attribute__((noinline)) RankedSums ranked_sums_apart(GlobalWords logits, uint32_t n, Share<ValueBins> s, Cut cut,
+                                                                  uint32_t share, bool compare, int64_t m) {
+    return ranked_sums(HeadKeys<0, ValueBins>((const uint32_t*)logits, n), s, cut, share, compare, m);
+}
+
+// Heads of more than 8192 tokens whose keys stay in registers.  us for the losses, compared in the list / in runs: 128 heads of 9000
+// 34.1, 31.9; 12000 39.8, 36.6; 16384 47.3, 43.4; 24000 65.1, 58.7; 32768 85.3, 74.4; 256 heads of 17000 72.6, 59.7; few heads
+// and so small shares the same (32 heads of 9000 23.4, 23.6, of 32768 38.3, 36.3).  Up to 8192 tokens a share is so
+// small that runs of 32 leave most lanes idle: 32 heads of 3000 18.4, 19.7; 128 of 3000 20.9, 22.2.
+// Where the finer bins turn out too full the attempt is lost time: 128 heads of 32768 with 20 equal logits each 148, 157.
+template <int E> constexpr bool kInRuns = E > 8;
 
 // Softmax statistics, rank-weighted sums, ranks of the scores by value ranges, and the three
 // outputs.  Every share adds up its stretch of positions and its range of ranks; with several
@@ -1184,10 +1412,10 @@ __global__ __launch_bounds__(kSortLanes)
 void alr_head_kernel(uint32_t* __restrict__ scratch, const int32_t* __restrict__ drop_rank, int64_t T,
                      uint32_t n_heads, int32_t G, Cut cut, int64_t m, double* __restrict__ alr,
                      double* __restrict__ loss, double* __restrict__ loss_ref) {
-    __shared__ BinShared sh;
-    __shared__ CutShared s_cut;
-    __shared__ __attribute__((aligned(16))) uint32_t s_list[kListWords];
-    __shared__ double stage[kSortWaves][kRecordSums];
+    HeadShared& lds = head_shared();
+    BinShared& sh = lds.sh;
+    uint32_t* const s_list = lds.list;
+    double (&stage)[kSortWaves][kRecordSums] = lds.stage;
     const Part part = part_of_block(blockIdx.x, n_heads, cut.shares);     // head = b * Hq + hq
     const int64_t head = part.head;
     const uint32_t n = (uint32_t)T;
@@ -1196,6 +1424,7 @@ void alr_head_kernel(uint32_t* __restrict__ scratch, const int32_t* __restrict__
     uint32_t* second = scratch + (int64_t)n_heads * T;
     const int32_t* rank = drop_rank + (head / G) * T;
 
+    const uint32_t p0 = cut.start(part.share), p1 = cut.start(part.share + 1);
     const HeadKeys<E, ValueBins> keys(logits, n);
     const auto s = find_share(keys, n, part.share, cut, s_list, sh);
     const float mx = s.kmax;
@@ -1203,30 +1432,24 @@ void alr_head_kernel(uint32_t* __restrict__ scratch, const int32_t* __restrict__
 
     RankedSums ranked;
     if (!equal) {
-        bool done = false;
-        if (!s.crowded) {
-            // ranks inside the share, then the sums in order of rank
-            float* list = reinterpret_cast<float*>(s_list);
-            Ranked<kListPer, ValueBins> mine;
-            done = rank_share<false, kListPer>(keys, s, sh, list, nullptr, mine);
-            if (done) {
-                __syncthreads();
-#pragma unroll
-                for (int u = 0; u < kListPer; ++u)
-                    if (u * kSortLanes + threadIdx.x < s.count) list[mine.rank[u]] = mine.key[u];
-                __syncthreads();
-                for (uint32_t i = threadIdx.x; i < s.count; i += kSortLanes) add_ranked(ranked, score(list[i], mx), s.base + i, m);
+        if constexpr (kInRuns<E>) {
+            ShareOrder order = kTooManyForBins;
+            if (!s.crowded) {
+                float run[kRun];
+                order = order_share<E>(keys, s, sh, reinterpret_cast<float*>(s_list), run);
+                const uint32_t at = threadIdx.x * kRun;
+                if (order == kInOrder && at < s.count) add_run(ranked, run, mx, s.base + at, s.count - at, m);
             }
-        }
-        if (!done) {
-            const uint32_t r0 = s.crowded ? cut.start(part.share) : s.base;
-            const uint32_t r1 = s.crowded ? cut.start(part.share + 1) : s.base + s.count;
-            const uint32_t at = sorted_range<LogitKey, false, kListPer>(logits, n, r0, r1, s_list, nullptr, sh, s_cut);
-            for (uint32_t i = threadIdx.x; i < r1 - r0; i += kSortLanes)
-                add_ranked(ranked, score(float_of_ordered(s_list[at + i]), mx), r0 + i, m);
+            if (order != kInOrder) {
+                __syncthreads();
+                if (threadIdx.x == 0) sh.crowded = 0;
+                ranked = ranked_sums_apart((GlobalWords)logits, n, s, cut, (uint32_t)part.share, order == kTooManyForRuns, m);
+            }
+        } else {
+            ranked = ranked_sums(keys, s, cut, (uint32_t)part.share, !s.crowded, m);
         }
     }
-    const PositionSums sums = position_sums<false>(logits, rank, cut.start(part.share), cut.start(part.share + 1), m, mx, equal, ranked);
+    const PositionSums sums = position_sums<false>(logits, rank, p0, p1, m, mx, equal, ranked);
     double acc[kRecordSums] = {sums.all, sums.weighted, sums.dropped, ranked.weighted, ranked.lowest};
     block_sum<kRecordSums>(acc, stage);                               // valid in thread 0
 
@@ -1427,7 +1650,13 @@ l2kv_status alr_dispatch(const void* Q, const void* K, l2kv_dtype dt, const int3
                            static_cast<uint32_t*>(workspace), drop_rank, T, G, m, alr, loss, loss_ref);
         return launch_status();
     }
-    auto kernel = T <= 8 * kSortLanes ? alr_head_kernel<8> : alr_head_kernel<0>;    // registers for 32: 43 us, re-read: 41 us for 128 heads of 32k
+    // keys per lane: every one costs the same whether it is there or not (12000 tokens at 32: 41.3 us, at 16: 36.6)
+    auto kernel = T <= 8 * kSortLanes    ? alr_head_kernel<8>
+                  : T <= 16 * kSortLanes ? alr_head_kernel<16>
+                  : T <= 20 * kSortLanes ? alr_head_kernel<20>
+                  : T <= 24 * kSortLanes ? alr_head_kernel<24>
+                  : T <= 32 * kSortLanes ? alr_head_kernel<32>
+                                         : alr_head_kernel<0>;
     hipLaunchKernelGGL(kernel, dim3((unsigned)(n_heads * shares)), dim3(kSortLanes), 0, stream,
                        static_cast<uint32_t*>(workspace), drop_rank, T, (uint32_t)n_heads, G, Cut((uint32_t)T, (uint32_t)shares), m,
                        alr, loss, loss_ref);
