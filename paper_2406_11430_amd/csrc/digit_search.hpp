@@ -39,6 +39,15 @@ struct FindShared {
     Found found;
 };
 
+// Sum of the entries [0, wave) of a table with one entry per wave: lane i of each DPP row reads entry i.  (All entries in
+// every lane take 16 registers, which kernels that hold rows in flight meanwhile do not have.)
+__device__ __forceinline__ uint32_t sum_before(const uint32_t* per_wave, int wave) {
+    static_assert(kSelWaves == kRowLanes, "one entry per lane of a row");
+    const int i = threadIdx.x % kRowLanes;
+    const uint32_t v = per_wave[i];
+    return __builtin_amdgcn_readfirstlane(row16_sum(i < wave ? v : 0u));
+}
+
 // Called by all 1024 lanes, hist complete (the caller's barrier); ends with a barrier.  `want`
 // is 1-based and at most the sum of the histogram.
 template <int BINS>
@@ -52,13 +61,12 @@ __device__ __forceinline__ Found find_digit(const uint32_t* hist, uint32_t want,
     for (int i = 0; i < kPer; ++i) {
         c[i] = digit_count(hist, threadIdx.x * kPer + i);
         sum += c[i];
+        if (i % 2 == 1) __builtin_amdgcn_sched_barrier(0);            // 8 registers for the copies, not 16, as in sum_before
     }
     const uint32_t incl = wave_inclusive_sum(sum);
     if (lane == kWaveSize - 1) sh.wave_total[wave] = incl;
     __syncthreads();
-    uint32_t before = incl - sum;
-#pragma unroll
-    for (int w = 0; w < kSelWaves; ++w) before += w < wave ? sh.wave_total[w] : 0u;
+    uint32_t before = incl - sum + sum_before(sh.wave_total, wave);
     if (before < want && want <= before + sum) {          // exactly one lane
 #pragma unroll
         for (int i = 0; i < kPer; ++i) {

@@ -77,8 +77,19 @@ __device__ __forceinline__ uint32_t dpp_min(uint32_t v) {
     const uint32_t o = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xf, 0xf, true);
     return o < v ? o : v;
 }
+// Sum and smallest value over the 16 lanes of each DPP row; all lanes must be active.
+template <int CTRL>
+__device__ __forceinline__ uint32_t dpp_add(uint32_t v) {
+    return v + (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xf, 0xf, true);
+}
+__device__ __forceinline__ uint32_t row16_sum(uint32_t v) {
+    return dpp_add<kDppMirror>(dpp_add<kDppHalfMirror>(dpp_add<kDppXor2>(dpp_add<kDppXor1>(v))));
+}
+__device__ __forceinline__ uint32_t row16_min(uint32_t v) {
+    return dpp_min<kDppMirror>(dpp_min<kDppHalfMirror>(dpp_min<kDppXor2>(dpp_min<kDppXor1>(v))));
+}
 __device__ __forceinline__ uint32_t wave_min(uint32_t v) {
-    v = dpp_min<kDppMirror>(dpp_min<kDppHalfMirror>(dpp_min<kDppXor2>(dpp_min<kDppXor1>(v))));
+    v = row16_min(v);
     const uint32_t a = __builtin_amdgcn_readlane((int)v, 0), b = __builtin_amdgcn_readlane((int)v, 16);
     const uint32_t c = __builtin_amdgcn_readlane((int)v, 32), d = __builtin_amdgcn_readlane((int)v, 48);
     const uint32_t ab = a < b ? a : b, cd = c < d ? c : d;

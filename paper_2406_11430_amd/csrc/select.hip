@@ -33,6 +33,8 @@
 #include "l2kv_host.hpp"
 #include "row_norm.hpp"
 
+#include <type_traits>
+
 namespace l2kv {
 
 constexpr int kSelMaxRegKeys = 32;                   // keys per lane held in registers
@@ -66,11 +68,8 @@ __device__ __forceinline__ void emit_ordered(Fetch fetch, int64_t iters, uint32_
         sh.eq[wave] = eq_w;
     }
     __syncthreads();
-#pragma unroll
-    for (int w = 0; w < kSelWaves; ++w) {
-        lt_before += w < wave ? sh.lt[w] : 0u;
-        eq_before += w < wave ? sh.eq[w] : 0u;
-    }
+    lt_before += sum_before(sh.lt, wave);
+    eq_before += sum_before(sh.eq, wave);
     uint32_t out_base = lt_before + (eq_before < need_eq ? eq_before : need_eq);
     auto for_iters = [&](auto&& body) {
         for (int64_t e0 = 0; e0 < iters; e0 += kUnroll) {
@@ -193,13 +192,8 @@ __device__ __forceinline__ Threshold find_threshold(const HeadKeys<E>& keys, uin
     if (threadIdx.x == 0) sh.listed = 0;
     clear_counts(sh.hist, kTopBins * kCopies);
     __syncthreads();
-#pragma unroll
-    for (int w = 0; w < kSelWaves; ++w) {
-        lo = sh.lo[w] < lo ? sh.lo[w] : lo;
-        hi = sh.hi[w] > hi ? sh.hi[w] : hi;
-    }
-    lo = __builtin_amdgcn_readfirstlane(lo);
-    hi = __builtin_amdgcn_readfirstlane(hi);
+    lo = __builtin_amdgcn_readfirstlane(row16_min(sh.lo[lane % kRowLanes]));
+    hi = ~__builtin_amdgcn_readfirstlane(row16_min(~sh.hi[lane % kRowLanes]));
     // every pass computes the bins afresh: kept from one pass to the next they would not fit the registers
     auto origin = [&] { uint32_t v = lo; asm volatile("" : "+s"(v)); return v; };
     const int bits = hi == lo ? 0 : 32 - __builtin_clz(hi - lo);
@@ -297,14 +291,20 @@ void select_kernel(const uint32_t* __restrict__ norm_bits, int64_t T, uint32_t k
 }
 
 // ---- selection and compaction of short heads in one launch ------------------------------------
-// The kept rows of a head are shared by gridDim.x workgroups.  Each finds the threshold by itself (the keys of a
+// The rows of a head are shared by gridDim.x workgroups.  Each finds the threshold by itself (the keys of a
 // short head are a few per lane, so repeating the search costs less than the launch and the round trip
 // through memory that a search of its own takes), writes its share of the indices and copies
-// its share of the rows.  With the norm pass, against three kernels, other inputs in every call: half of 8 heads of 2k 12.6 us
-// and 14.1, of 32 heads of 4k 25.2 and 26.0, of 8 heads of 8k 16.9 and 18.6.
+// its share of the rows.
+// The search (about 6 us with two workgroups on a compute unit) is a chain of LDS round trips during which the memory is idle.
+// So a share is a stretch of tokens where that can be: the rows of V it may need are requested ahead of the search and wait in
+// registers, kept or not, and only the kept rows of K, which the norm pass has just read, are left to fetch.  With the norm
+// pass, other inputs in every call, us, three kernels / shares of kept rows / of tokens: half of 8 heads of 2k 14.1, 12.4,
+// 9.8, of 32 heads of 4k 26.0, 25.3, 21.7 (0.9 of them 34.4 in three kernels, 27.5), of 8 heads of 8k 18.6, 17.4, 16.4, of 100 heads of
+// 1k of 64 elements -, 15.9, 13.4.  Kept tokens all in one stretch, and so all rows of some shares and none of others, 32 heads of 4k: 24.9, 21.2.
 constexpr int kFuseMaxTokens = 8 * kSelThreads;
 constexpr int kFuseMaxHeads = 256;
-constexpr int64_t kFuseMaxBytes = int64_t{20} << 20, kShortMaxBytes = int64_t{2} << 20, kShortHeadBytes = int64_t{256} << 10;
+constexpr int kDies = 8;                               // compute dies, 32 compute units each
+constexpr int64_t kFuseMaxBytes = int64_t{20} << 20, kShortHeadBytes = int64_t{128} << 10;
 constexpr int kFuseRows = 4096;                       // most rows of a share: indices in LDS as 16-bit numbers
 static_assert(kFuseMaxTokens <= 65536, "token indices fit 16 bits");
 
@@ -354,86 +354,165 @@ __device__ __forceinline__ void select_and_copy(const HeadKeys<E>& keys, uint32_
     }
 }
 
+// Rows of V on their way to registers while the search runs.  16 registers: with the keys and what the search takes, 60 of the 64
+// that two workgroups on a compute unit leave a lane.  (Spilled, they are waited for before the search: 28.8 us in place of 21.7.)
+template <int kRowBytes> struct RowsAhead {
+    using P = RowCopy<kRowBytes>;
+    static constexpr uint32_t kRowsPerStep = kSelThreads / P::kLanes;
+    static constexpr int kSteps = kRowBytes > 256 ? 2 : 4;                          // 16 registers
+    static constexpr uint32_t kTokens = kRowsPerStep * kSteps;                      // most tokens of a share
+    Words<P::kWords> row[kSteps];
+    // V points at the first token of the share
+    __device__ __forceinline__ void load(const char* __restrict__ V, uint32_t tokens) {
+        const uint32_t c = threadIdx.x % P::kLanes, rg = threadIdx.x / P::kLanes;
+#pragma unroll
+        for (int u = 0; u < kSteps; ++u) {
+            const uint32_t r = u * kRowsPerStep + rg;
+            row[u] = load_words_stream<P::kWords, P::kStride>(V + (r < tokens ? r : tokens - 1) * (int64_t)kRowBytes + c * 16);
+        }
+    }
+};
+
+constexpr uint16_t kDropped = 0xffff;
+static_assert(kFuseMaxTokens < kDropped && RowsAhead<128>::kTokens <= kSelThreads && RowsAhead<128>::kTokens <= kFuseRows, "places of a share");
+// Tokens [t0, t0 + tokens) of a head, whose rows of V are in `ahead`.  K, out, Kc, Vc point at the head.
 template <int E, int kRowBytes>
-__global__ __launch_bounds__(kSelThreads)
-void select_compact_kernel(const uint32_t* __restrict__ norm_bits, int64_t T, uint32_t k, uint32_t rows_per_share,
+__device__ __forceinline__ void select_and_copy_ahead(const HeadKeys<E>& keys, uint32_t k, uint32_t t0, uint32_t tokens,
+                                                      const RowsAhead<kRowBytes>& ahead, const char* __restrict__ K,
+                                                      int32_t* __restrict__ out, char* __restrict__ Kc, char* __restrict__ Vc,
+                                                      FuseShared& sh) {
+    using A = RowsAhead<kRowBytes>;
+    using P = typename A::P;
+    if (threadIdx.x < A::kTokens) sh.row[threadIdx.x] = kDropped;
+    const Threshold th = find_threshold(keys, k, sh.search);
+    emit_ordered<E, false>([&](int64_t e) { return keys.fetch(e); }, E, keys.t0, th.tau, th.need_eq, 0u, 0u,
+                    [&](uint32_t i, int32_t t) {
+                        if ((uint32_t)t - t0 < tokens) {
+                            sh.row[(uint32_t)t - t0] = (uint16_t)i;
+                            out[i] = t;
+                        }
+                    }, k, sh.emit);
+    __syncthreads();
+    uint32_t at_lane = threadIdx.x;
+    asm volatile("" : "+v"(at_lane));                                // afresh: places kept from the loads on would not fit the registers
+    const uint32_t c = at_lane % P::kLanes, rg = at_lane / P::kLanes;
+    Words<P::kWords> key_row[A::kSteps];
+    uint32_t to[A::kSteps];
+#pragma unroll
+    for (int u = 0; u < A::kSteps; ++u) {
+        if (kRowBytes == 128 && u * A::kRowsPerStep >= tokens) break;                 // four steps of 128 tokens are seldom full
+        const uint32_t r = u * A::kRowsPerStep + rg;
+        to[u] = sh.row[r];                                            // past the share: dropped
+        if (to[u] != kDropped) key_row[u] = load_words_stream<P::kWords, P::kStride>(K + (t0 + r) * (int64_t)kRowBytes + c * 16);
+    }
+#pragma unroll
+    for (int u = 0; u < A::kSteps; ++u) {
+        if (kRowBytes == 128 && u * A::kRowsPerStep >= tokens) break;                 // four steps of 128 tokens are seldom full
+        if (to[u] != kDropped) {
+            const int64_t at = to[u] * (int64_t)kRowBytes + c * 16;
+            store_words_stream<P::kWords, P::kStride>(Vc + at, ahead.row[u]);
+            store_words_stream<P::kWords, P::kStride>(Kc + at, key_row[u]);
+        }
+    }
+}
+
+// kAhead: share = `per_share` tokens of a head, else as many of its kept rows.
+template <int E, int kRowBytes, bool kAhead>
+__global__ __launch_bounds__(kSelThreads, kAhead && E <= 4 ? 8 : 4)
+void select_compact_kernel(const uint32_t* __restrict__ norm_bits, int64_t T, uint32_t k, uint32_t per_share,
                            const char* __restrict__ K, const char* __restrict__ V, int64_t head_stride_bytes,
                            int32_t* __restrict__ kept_idx, char* __restrict__ Kc, char* __restrict__ Vc) {
     __shared__ __attribute__((aligned(16))) FuseShared sh;
     const int64_t head = blockIdx.y;
-    const uint32_t r0 = blockIdx.x * rows_per_share;
-    if (r0 >= k) return;
+    const uint32_t all = kAhead ? (uint32_t)T : k, first = blockIdx.x * per_share;
+    if (first >= all) return;
+    const uint32_t count = all - first < per_share ? all - first : per_share;
     const HeadKeys<E> keys(norm_bits + head * T, T, 0u);
     const int64_t dense = head * (int64_t)k;
-    select_and_copy<E, kRowBytes>(keys, k, r0, k - r0 < rows_per_share ? k - r0 : rows_per_share, K + head * head_stride_bytes,
-                                  V + head * head_stride_bytes, kept_idx + dense, Kc + dense * kRowBytes, Vc + dense * kRowBytes, sh);
+    K += head * head_stride_bytes;
+    V += head * head_stride_bytes;
+    kept_idx += dense;
+    Kc += dense * kRowBytes;
+    Vc += dense * kRowBytes;
+    if constexpr (kAhead) {
+        RowsAhead<kRowBytes> ahead;
+        ahead.load(V + first * (int64_t)kRowBytes, count);
+        __builtin_amdgcn_sched_barrier(0);                            // not next to their use
+        select_and_copy_ahead<E, kRowBytes>(keys, k, first, count, ahead, K, kept_idx, Kc, Vc, sh);
+    } else {
+        select_and_copy<E, kRowBytes>(keys, k, first, count, K, V, kept_idx, Kc, Vc, sh);
+    }
 }
 
-// The whole compression of heads of at most 1024 tokens in one launch: every share also computes all norms of its
-// head (out of the L2 for all but the first reader), the first share writes them.  Meant for the
-// smallest calls, whose time is the number of launches: 4 heads of 512
-// tokens, half kept, 10 us against 16 for three kernels (of 2.4, 5.7 and 3.3 us).  Not beyond 2 MB of K, which the
-// shares read over and over (32 heads of 1024 tokens, 8 MB, 17.2 against 13.6 for two launches), and 256 KB of a head, which
-// one workgroup goes through before anything else: half of 1024 tokens of 2 heads, rows of 128 bytes 8.5 against 10.6, of
-// 256 bytes 10.3 and 10.4, of 512 bytes 15.6 against 11.8.
+// The whole compression of heads of at most 1024 tokens and 128 KB in one launch: every share also computes all norms of its
+// head (out of the L2 for all but the first reader), the first share writes them.  Bound by the chain of load, sums, search
+// and copy of one workgroup.  us, two launches / one: half of 4 heads of 512 tokens 8.2, 7.3, of 64 of 256 9.5, 7.3, of 128 of
+// 512 (16 MB) 13.9, 12.4; of 500 tokens of 17 heads 9.0, 7.7, with the shares of a head on all compute dies 9.6.  Not beyond 128 KB of a head,
+// which one workgroup goes through before anything else: 16 heads of 1024 tokens 9.5, 10.0, one of them 8.0, 9.1, rows of 512 bytes
+// 8.5, 13.8.
 template <typename E, int D>
 __global__ __launch_bounds__(kSelThreads)
-void compress_short_kernel(const char* __restrict__ K, const char* __restrict__ V, int64_t T, uint32_t k,
-                           uint32_t rows_per_share, int64_t head_stride_bytes, float* __restrict__ norms,
+void compress_short_kernel(const char* __restrict__ K, const char* __restrict__ V, uint32_t n_heads, uint32_t shares, int64_t T,
+                           uint32_t k, uint32_t tokens_per_share, int64_t head_stride_bytes, float* __restrict__ norms,
                            int32_t* __restrict__ kept_idx, char* __restrict__ Kc, char* __restrict__ Vc) {
     using S = Slice<E, D>;
     __shared__ __attribute__((aligned(16))) FuseShared sh;
     __shared__ uint32_t s_norm[kSelThreads];                          // bit patterns
-    const int64_t head = blockIdx.y;
-    const uint32_t r0 = blockIdx.x * rows_per_share;
-    if (r0 >= k) return;
+    // Workgroups go to the compute dies round-robin: the shares of a head, which all read the whole of it, to the same one.
+    const uint32_t slot = blockIdx.x / kDies, share = slot % shares;
+    const int64_t head = slot / shares * kDies + blockIdx.x % kDies;
+    const uint32_t n = (uint32_t)T, first = share * tokens_per_share;
+    if (head >= n_heads || first >= n) return;
     const char* Kh = K + head * head_stride_bytes;
-    const uint32_t n = (uint32_t)T;
     const int c = threadIdx.x % kRowLanes;
     constexpr uint32_t kGroups = kSelThreads / kRowLanes;            // 64 row groups
-    constexpr int kBatch = 4;
-    if constexpr (S::kRowBytes == 128) {
-        // pairs of rows, 8 lanes each
-        for (uint32_t base = 0; base < n; base += 2 * kGroups * kBatch) {
-            Words<4> raw[kBatch];
-#pragma unroll
-            for (int u = 0; u < kBatch; ++u) {
-                const uint32_t row = base + 2 * (u * kGroups + threadIdx.x / kRowLanes) + c / 8;
-                raw[u] = load_words<4>(Kh + (row < n ? row : n - 1) * (int64_t)S::kRowBytes + (c % 8) * 16);
-            }
-#pragma unroll
-            for (int u = 0; u < kBatch; ++u) {
-                const uint32_t row = base + 2 * (u * kGroups + threadIdx.x / kRowLanes) + c / 8;
-                const float v = row_pair_sum_of_squares(raw[u]);
-                if (c % 8 == 0 && row < n) s_norm[row] = __builtin_bit_cast(uint32_t, v);
-            }
-        }
-    } else {
+    // kRows rows (pairs of the short ones, 8 lanes each) per row group, all requested before the first is summed
+    auto sums = [&](auto batch) {
+        constexpr int kRows = decltype(batch)::value;
         using P = Pieces<S::kWords>;
-        for (uint32_t base = 0; base < n; base += kGroups * kBatch) {
-            Words<S::kWords> raw[kBatch];
+        constexpr bool kPairs = S::kRowBytes == 128;
+        constexpr uint32_t kStep = kPairs ? 2 * kGroups : kGroups;
+        const uint32_t mine = kPairs ? 2 * (threadIdx.x / kRowLanes) + c / 8 : threadIdx.x / kRowLanes;
+        for (uint32_t base = 0; base < n; base += kStep * kRows) {
+            Words<kPairs ? 4 : S::kWords> raw[kRows];
 #pragma unroll
-            for (int u = 0; u < kBatch; ++u) {
-                const uint32_t row = base + u * kGroups + threadIdx.x / kRowLanes;
-                raw[u] = load_words<S::kWords, P::kStride>(Kh + (row < n ? row : n - 1) * (int64_t)S::kRowBytes + c * P::kBytes);
+            for (int u = 0; u < kRows; ++u) {
+                const uint32_t row = base + u * kStep + mine;
+                const char* const from = Kh + (row < n ? row : n - 1) * (int64_t)S::kRowBytes;
+                if constexpr (kPairs) raw[u] = load_words<4>(from + (c % 8) * 16);
+                else raw[u] = load_words<S::kWords, P::kStride>(from + c * P::kBytes);
             }
 #pragma unroll
-            for (int u = 0; u < kBatch; ++u) {
-                const uint32_t row = base + u * kGroups + threadIdx.x / kRowLanes;
-                float x[S::kElems];
-                widen<E, D>(raw[u], x);
-                const float v = chunked_sum_of_squares<E, D>(x);
-                if (c == 0 && row < n) s_norm[row] = __builtin_bit_cast(uint32_t, v);
+            for (int u = 0; u < kRows; ++u) {
+                const uint32_t row = base + u * kStep + mine;
+                float v;
+                if constexpr (kPairs) {
+                    v = row_pair_sum_of_squares(raw[u]);
+                } else {
+                    float x[S::kElems];
+                    widen<E, D>(raw[u], x);
+                    v = chunked_sum_of_squares<E, D>(x);
+                }
+                if ((kPairs ? c % 8 : c) == 0 && row < n) s_norm[row] = __builtin_bit_cast(uint32_t, v);
             }
         }
-    }
+    };
+    // twice the rows where that saves a round trip, not where it only adds sums of rows that are not there: 512 rows of
+    // 256 bytes 7.6 us, not 8.0, but 80 rows 7.6, not 6.9 (fp32 rows slower throughout: 512 of 256 bytes 7.9, not 7.6)
+    constexpr int kBatch = S::kWords > 4 ? 2 : 4;
+    constexpr uint32_t kBatchRows = kBatch * (S::kRowBytes == 128 ? 2 * kGroups : kGroups);
+    if (E::kBytes == 2 && n > kBatchRows) sums(std::integral_constant<int, 2 * kBatch>());
+    else sums(std::integral_constant<int, kBatch>());
+    const uint32_t count = n - first < tokens_per_share ? n - first : tokens_per_share;
+    RowsAhead<S::kRowBytes> ahead;
+    ahead.load(V + head * head_stride_bytes + first * (int64_t)S::kRowBytes, count);
+    __builtin_amdgcn_sched_barrier(0);                                // not next to their use
     __syncthreads();
-    if (blockIdx.x == 0 && threadIdx.x < n) norms[head * T + threadIdx.x] = __builtin_bit_cast(float, s_norm[threadIdx.x]);
+    if (share == 0 && threadIdx.x < n) norms[head * T + threadIdx.x] = __builtin_bit_cast(float, s_norm[threadIdx.x]);
     const HeadKeys<1> keys(s_norm, T, 0u);
     const int64_t dense = head * (int64_t)k;
-    select_and_copy<1, S::kRowBytes>(keys, k, r0, k - r0 < rows_per_share ? k - r0 : rows_per_share, Kh,
-                                     V + head * head_stride_bytes, kept_idx + dense, Kc + dense * S::kRowBytes,
-                                     Vc + dense * S::kRowBytes, sh);
+    select_and_copy_ahead<1, S::kRowBytes>(keys, k, first, count, ahead, Kh, kept_idx + dense, Kc + dense * S::kRowBytes,
+                                           Vc + dense * S::kRowBytes, sh);
 }
 
 // ---- several workgroups per head -------------------------------------------------------------
@@ -821,27 +900,15 @@ l2kv_status select_dispatch(const float* norms, int64_t n_heads, int64_t T, int6
     return launch_status();
 }
 
-template <int E>
-static void launch_select_compact(const dim3 grid, int row_bytes, const float* norms, int64_t T, int64_t k, int64_t rows,
+template <int E, bool kAhead>
+static void launch_select_compact(const dim3 grid, int row_bytes, const float* norms, int64_t T, int64_t k, int64_t per_share,
                                   const void* K, const void* V, int64_t head_stride_bytes, int32_t* kept_idx, void* Kc,
                                   void* Vc, hipStream_t stream) {
-    auto kernel = row_bytes == 128 ? select_compact_kernel<E, 128>
-                  : row_bytes == 256 ? select_compact_kernel<E, 256> : select_compact_kernel<E, 512>;
+    auto kernel = row_bytes == 128 ? select_compact_kernel<E, 128, kAhead>
+                  : row_bytes == 256 ? select_compact_kernel<E, 256, kAhead> : select_compact_kernel<E, 512, kAhead>;
     hipLaunchKernelGGL(kernel, grid, dim3(kSelThreads), 0, stream, reinterpret_cast<const uint32_t*>(norms), T, (uint32_t)k,
-                       (uint32_t)rows, static_cast<const char*>(K), static_cast<const char*>(V), head_stride_bytes, kept_idx,
+                       (uint32_t)per_share, static_cast<const char*>(K), static_cast<const char*>(V), head_stride_bytes, kept_idx,
                        static_cast<char*>(Kc), static_cast<char*>(Vc));
-}
-
-// Where the kept rows fill the memory system for longer than the repeated search takes, a selection and a
-// compaction do as well or better: half of 200 heads of 1k (26 MB of K) 35.5 us together and 35.0 apart, of 48 heads of 4k
-// (25 MB) 33.9 and 34.4, of 64 heads of 4k (34 MB) 41.4 and 41.9; below 17 MB together is the faster everywhere.
-bool select_compact_applies(int64_t n_heads, int64_t T, int64_t k, int32_t row_bytes) {
-    return T <= kFuseMaxTokens && n_heads <= (T <= 4 * kSelThreads ? kFuseMaxHeads : kFuseMaxHeads / 2) &&
-           n_heads * k * row_bytes <= kFuseMaxBytes;
-}
-bool compress_short_applies(int64_t n_heads, int64_t T, int64_t k, int32_t row_bytes) {
-    return T <= kSelThreads && select_compact_applies(n_heads, T, k, row_bytes) && n_heads * T * row_bytes <= kShortMaxBytes &&
-           T * row_bytes <= kShortHeadBytes;
 }
 
 // Rows of a share: a multiple of 16, and no more shares than run at once: two on a compute unit, one with eight keys per
@@ -853,29 +920,62 @@ static int64_t rows_per_share(int64_t n_heads, int64_t T, int64_t k, int64_t lea
     return rows > least ? rows : least;
 }
 
+static int64_t most_ahead(int32_t row_bytes) {
+    return row_bytes == 128 ? RowsAhead<128>::kTokens : row_bytes == 256 ? RowsAhead<256>::kTokens : RowsAhead<512>::kTokens;
+}
+// Tokens of a share whose rows of V are loaded during the search, 0: shares of kept rows.  While a workgroup holds them, at most
+// 34 MB of V, which the memory brings during the search.  From a third of the tokens on, as for kReadAgainBytes: of 32 heads of 4k
+// 0.1 / 0.3 / 0.4 kept in shares of tokens 20.1, 22.8, 20.5 us, of kept rows 17.5, 21.2, 22.6; of 64 heads of 1k 13.2, 14.3, - and
+// 12.7, 14.4, -; of 8 heads of 8k 0.2 / 1.0 kept 15.6, 19.8 and 14.1, 22.6.  At least 64 tokens: shares of 16 of 2 heads of 3001 11.5 us, of 64 9.6.
+static int64_t tokens_ahead(int64_t n_heads, int64_t T, int64_t k, int32_t row_bytes) {
+    if (T > kFuseMaxTokens || n_heads > (T <= 4 * kSelThreads ? kFuseMaxHeads : kFuseMaxHeads / 2) || 3 * k < T) return 0;
+    const int64_t tokens = rows_per_share(n_heads, T, T, 64);
+    return tokens <= most_ahead(row_bytes) ? tokens : 0;
+}
+
+// Shares of kept rows only while these do not fill the memory system for longer than the repeated search takes; else a selection
+// and a compaction do as well or better: half of 200 heads of 1k (26 MB of K) 35.5 us together and 35.0 apart, of 48 heads of 4k
+// (25 MB) 33.9 and 34.4, of 64 heads of 4k (34 MB) 41.4 and 41.9; below 17 MB together is the faster everywhere.
+bool select_compact_applies(int64_t n_heads, int64_t T, int64_t k, int32_t row_bytes) {
+    return tokens_ahead(n_heads, T, k, row_bytes) != 0 ||
+           (T <= kFuseMaxTokens && n_heads <= (T <= 4 * kSelThreads ? kFuseMaxHeads : kFuseMaxHeads / 2) &&
+            n_heads * k * row_bytes <= kFuseMaxBytes);
+}
+// Tokens of a share of the one-launch compression: at least 64, and at most one workgroup on a compute unit.  0: not that launch.
+static int64_t short_tokens(int64_t n_heads, int64_t T, int32_t row_bytes) {
+    if (T > kSelThreads || n_heads > kFuseMaxHeads || T * row_bytes > kShortHeadBytes) return 0;
+    const int64_t shares = kFuseMaxHeads / n_heads, tokens = ((T + shares - 1) / shares + 15) / 16 * 16;
+    return tokens <= 64 ? 64 : tokens <= most_ahead(row_bytes) ? tokens : 0;
+}
+bool compress_short_applies(int64_t n_heads, int64_t T, int32_t row_bytes) { return short_tokens(n_heads, T, row_bytes) != 0; }
+
 l2kv_status select_compact_dispatch(const float* norms, int64_t n_heads, int64_t T, int64_t k, const void* K, const void* V,
                                     l2kv_dtype dt, int32_t D, int64_t head_stride, int32_t* kept_idx, void* Kc, void* Vc,
                                     hipStream_t stream) {
     const int es = dt == L2KV_F32 ? 4 : 2;
-    const int64_t rows = rows_per_share(n_heads, T, k, 16);
-    const dim3 grid((unsigned)((k + rows - 1) / rows), (unsigned)n_heads);
+    const int64_t tokens = tokens_ahead(n_heads, T, k, D * es);
+    const bool ahead = tokens != 0;
+    const int64_t per_share = ahead ? tokens : rows_per_share(n_heads, T, k, 16), all = ahead ? T : k;
+    const dim3 grid((unsigned)((all + per_share - 1) / per_share), (unsigned)n_heads);
     const int64_t per_lane = (T + kSelThreads - 1) / kSelThreads;
-    auto launch = per_lane <= 1 ? launch_select_compact<1> : per_lane <= 2 ? launch_select_compact<2>
-                  : per_lane <= 4 ? launch_select_compact<4> : launch_select_compact<8>;
-    launch(grid, D * es, norms, T, k, rows, K, V, head_stride * es, kept_idx, Kc, Vc, stream);
+    auto launch = ahead ? (per_lane <= 1 ? launch_select_compact<1, true> : per_lane <= 2 ? launch_select_compact<2, true>
+                           : per_lane <= 4 ? launch_select_compact<4, true> : launch_select_compact<8, true>)
+                        : (per_lane <= 1 ? launch_select_compact<1, false> : per_lane <= 2 ? launch_select_compact<2, false>
+                           : per_lane <= 4 ? launch_select_compact<4, false> : launch_select_compact<8, false>);
+    launch(grid, D * es, norms, T, k, per_share, K, V, head_stride * es, kept_idx, Kc, Vc, stream);
     return launch_status();
 }
 
 l2kv_status compress_short_dispatch(const void* K, const void* V, l2kv_dtype dt, int64_t n_heads, int64_t T, int32_t D,
                                     int64_t head_stride, int64_t k, float* norms, int32_t* kept_idx, void* Kc, void* Vc,
                                     hipStream_t stream) {
-    const int64_t rows = rows_per_share(n_heads, T, k, 64);             // every share reads the whole head
-    const dim3 grid((unsigned)((k + rows - 1) / rows), (unsigned)n_heads);
+    const int64_t tokens = short_tokens(n_heads, T, D * (dt == L2KV_F32 ? 4 : 2)), shares = (T + tokens - 1) / tokens;
+    const dim3 grid((unsigned)((n_heads + kDies - 1) / kDies * kDies * shares));
     auto kernel = dt == L2KV_F32 ? (D == 64 ? compress_short_kernel<F32, 64> : compress_short_kernel<F32, 128>)
                   : D == 256 ? compress_short_kernel<BF16, 256>
                   : D == 64 ? compress_short_kernel<BF16, 64> : compress_short_kernel<BF16, 128>;
-    hipLaunchKernelGGL(kernel, grid, dim3(kSelThreads), 0, stream, static_cast<const char*>(K), static_cast<const char*>(V), T,
-                       (uint32_t)k, (uint32_t)rows, head_stride * (dt == L2KV_F32 ? 4 : 2), norms, kept_idx,
+    hipLaunchKernelGGL(kernel, grid, dim3(kSelThreads), 0, stream, static_cast<const char*>(K), static_cast<const char*>(V),
+                       (uint32_t)n_heads, (uint32_t)shares, T, (uint32_t)k, (uint32_t)tokens, head_stride * (dt == L2KV_F32 ? 4 : 2), norms, kept_idx,
                        static_cast<char*>(Kc), static_cast<char*>(Vc));
     return launch_status();
 }

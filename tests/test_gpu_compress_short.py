@@ -30,7 +30,7 @@ def separate(K, V, k):
     return norms, idx, Kc, Vc
 
 
-# up to 1024 tokens: one launch (while K is at most 2 MB); up to 8192: norms, then selection with compaction; beyond: three
+# up to 1024 tokens: one launch (while a head is at most 128 KB); up to 8192: norms, then selection with compaction; beyond: three
 @pytest.mark.parametrize("dtype,D", [(torch.bfloat16, 64), (torch.bfloat16, 128), (torch.bfloat16, 256),
                                      (torch.float32, 64), (torch.float32, 128)])
 @pytest.mark.parametrize("heads,T,ratio", [(1, 1, 1.0), (3, 2, 0.5), (1, 127, 0.3), (2, 1023, 0.51), (5, 1024, 1.0), (40, 1024, 0.01),
