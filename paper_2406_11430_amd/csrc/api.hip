@@ -220,7 +220,7 @@ l2kv_status l2kv_decode_attn_splits(const void* Q, const void* Kc, const void* V
     if (st != L2KV_OK) return st;
     if (!aligned(workspace, 16)) return L2KV_ERR_ALIGN;
     const float s = scale > 0.f ? scale : 1.0f / std::sqrt(static_cast<float>(D));
-    const DecodePlan plan = decode_plan(B, Hkv, Hq / Hkv, kv_len, n_splits);
+    const DecodePlan plan = decode_plan(B, Hkv, Hq / Hkv, kv_len, D * elem_bytes(dt), n_splits);
     return decode_dispatch(Q, Kc, Vc, dt, B, Hq, Hkv, kv_len, D, kv_head_stride, nullptr, nullptr, nullptr, s,
                            plan, O, workspace, static_cast<hipStream_t>(stream));
 }
@@ -238,7 +238,7 @@ l2kv_status l2kv_decode_attn_out(const void* Q, const void* Kc, const void* Vc, 
     if (st != L2KV_OK) return st;
     if (!aligned(workspace, 16)) return L2KV_ERR_ALIGN;
     const float s = scale > 0.f ? scale : 1.0f / std::sqrt(static_cast<float>(D));
-    DecodePlan plan = decode_plan(B, Hkv, Hq / Hkv, kv_len, 0);
+    DecodePlan plan = decode_plan(B, Hkv, Hq / Hkv, kv_len, D * elem_bytes(dt), 0);
     plan.out_bf16 = out_dt == L2KV_BF16 ? 1 : 0;
     return decode_dispatch(Q, Kc, Vc, dt, B, Hq, Hkv, kv_len, D, kv_head_stride, nullptr, nullptr, nullptr, s,
                            plan, static_cast<float*>(O), workspace, static_cast<hipStream_t>(stream));
@@ -251,7 +251,7 @@ l2kv_status l2kv_decode_attn_static(const void* Q, const void* Kc, const void* V
         st != L2KV_OK)
         return st;
     const float s = scale > 0.f ? scale : 1.0f / std::sqrt(static_cast<float>(D));
-    const DecodePlan plan = decode_plan(B, Hkv, Hq / Hkv, kv_len, 0);
+    const DecodePlan plan = decode_plan(B, Hkv, Hq / Hkv, kv_len, D * elem_bytes(dt), 0);
     // counters + the partials of the workgroups this launch really has
     const size_t need = decode_counter_bytes(B, Hkv) +
                         static_cast<size_t>(B) * static_cast<size_t>(Hq) * static_cast<size_t>(plan.n_splits) *

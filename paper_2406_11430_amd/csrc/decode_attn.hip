@@ -88,7 +88,7 @@ int32_t decode_max_splits(int64_t kv_len) {
     return (int32_t)(by_rows < kDecodeMaxSplits ? by_rows : kDecodeMaxSplits);
 }
 
-DecodePlan decode_plan(int32_t B, int32_t Hkv, int32_t group, int64_t kv_len, int32_t requested_splits) {
+DecodePlan decode_plan(int32_t B, int32_t Hkv, int32_t group, int64_t kv_len, int32_t row_bytes, int32_t requested_splits) {
     const int64_t pairs = (int64_t)B * Hkv;
     int64_t want = requested_splits;
     if (want <= 0) {
@@ -113,6 +113,13 @@ DecodePlan decode_plan(int32_t B, int32_t Hkv, int32_t group, int64_t kv_len, in
         int64_t by_merge = (int64_t)(0.34 * sqrt((double)kv_len));
         if (by_merge < 8) by_merge = 8;
         if (want > by_merge) want = by_merge;
+        // Short heads: up to 8 workgroups merge in registers (kWideMerge), which saves more than longer streams cost while
+        // a head has at most 512 KB of K, and 3072 rows if there is the arithmetic of 5 heads and more to each.  us, split as
+        // above / in 8: bf16 rows of 128 elements, 4 heads of 1673 rows 7.6 / 7.0, 24 of 1146 with 6 query heads each 11.7 /
+        // 10.8, 4 of 3584 with 4 9.7 / 11.7; rows of 64, 16 of 1554 9.5 / 8.4, 16 of 3042 with 6 query heads 11.5 / 10.9, 2 of 3735
+        // with 5 9.5 / 10.0; fp32 rows of 128, 4 of 907 with 8 11.9 / 10.8, 8 of 1419 with 5 10.6 / 10.7.
+        const bool short_head = kv_len * row_bytes <= int64_t{512} << 10 && (group < 5 || kv_len <= 3072);
+        if (want > kDecodeNarrowSplits && short_head) want = kDecodeNarrowSplits;
     }
     const int64_t cap = decode_max_splits(kv_len);
     if (want > cap) want = cap;

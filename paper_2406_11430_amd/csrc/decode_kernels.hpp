@@ -728,7 +728,7 @@ __device__ __forceinline__ void decode_item(const char* __restrict__ Q, const ch
     __syncthreads();
     if (s_ticket != (uint32_t)(n_splits - 1)) return;
 
-    constexpr int kNarrow = 8;
+    constexpr int kNarrow = kDecodeNarrowSplits;
     if constexpr (!kWideMerge) {
         // Launches with at most 8 workgroups per KV head: every lane fetches, for its kVec
         // output elements (one query head, consecutive d), the accumulator elements together
@@ -1039,7 +1039,7 @@ l2kv_status launch_decode(const void* Q, const void* Kc, const void* Vc, int32_t
     float* partial = reinterpret_cast<float*>(static_cast<char*>(workspace) + decode_counter_bytes(B, Hkv));
     // two builds of each kernel: the final merge for at most 8 workgroups per KV head (all in
     // registers) or for more (tables in LDS); keeping both in one kernel slows the short one down
-    const bool wide = plan.n_splits > 8;
+    const bool wide = plan.n_splits > kDecodeNarrowSplits;
     // the work list exists for bf16 heads of 128 elements only (the host plans it for no other)
     constexpr bool kWorkListRows = E::kBytes == 2 && D == 128;
     if constexpr (kWorkListRows) {

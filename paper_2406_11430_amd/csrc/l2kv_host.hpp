@@ -67,6 +67,7 @@ struct DecodePlan {
     int32_t out_bf16;        // 1: O is written as bf16 (16-bit elements behind the float pointer), 0: fp32
 };
 constexpr int kDecodeMaxSplits = 256;
+constexpr int kDecodeNarrowSplits = 8;    // most workgroups of a head whose partials are merged in registers
 constexpr int kDecodeRowTile = 64;   // rows one workgroup consumes per step (4 waves x 16)
 int32_t decode_max_splits(int64_t kv_len);
 // The decode workspace starts with one arrival counter per (sequence, KV head)
@@ -83,7 +84,7 @@ l2kv_status workspace_init_dispatch(void* workspace, size_t bytes, hipStream_t s
 // Device address of the library's own scratch array on the current device (set up on first use,
 // which enqueues one fill kernel on `stream`); nullptr with *status set on failure.
 void* decode_static_scratch(hipStream_t stream, l2kv_status* status);
-DecodePlan decode_plan(int32_t B, int32_t Hkv, int32_t group, int64_t kv_len, int32_t requested_splits);
+DecodePlan decode_plan(int32_t B, int32_t Hkv, int32_t group, int64_t kv_len, int32_t row_bytes, int32_t requested_splits);
 DecodePlan decode_plan_ragged(int32_t n_seq, int32_t Hkv, int64_t max_len, int32_t requested_splits,
                               bool ordered);
 
