@@ -135,9 +135,11 @@ l2kv_status l2kv_compress(const void* K, const void* V, l2kv_dtype dt, int64_t n
         !aligned(kept_idx, 4) || !aligned(workspace, 16))
         return L2KV_ERR_ALIGN;
     const int64_t k = l2kv_keep_count(T, keep_ratio);
-    const int64_t read_again = 3 * k >= T ? kReadAgainBytes : 0;
     const int64_t slab = slab_heads == 0 || slab_heads > n_heads ? n_heads : slab_heads;
     const size_t es = static_cast<size_t>(elem_bytes(dt));
+    const int64_t slab_bytes = slab * T * D * static_cast<int64_t>(es);
+    const bool all_cached = slab_bytes > kReadAgainAllFrom && slab_bytes <= kReadAgainAllTo;
+    const int64_t read_again = 3 * k >= T || all_cached ? kReadAgainBytes : 0;
     hipStream_t s = static_cast<hipStream_t>(stream);
     for (int64_t h0 = 0; h0 < n_heads; h0 += slab) {
         const int64_t nh = n_heads - h0 < slab ? n_heads - h0 : slab;

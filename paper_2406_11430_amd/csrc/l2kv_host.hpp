@@ -27,6 +27,10 @@ l2kv_status norms_dispatch(const void* K, l2kv_dtype dt, int64_t n_heads, int64_
 // 8 heads of 131k, 0.9 kept, 207 against 213, half 146 and 146, 0.3 114 and 115.  From 1 GiB of K on
 // it is left out (120 heads of 32k 485 and 485).  l2kv_norms by itself does without: its caller may not compact.
 constexpr int64_t kReadAgainBytes = int64_t{128} << 20;
+// K of which all stays there is left there however little is kept: 48 heads of 4k, 0.05 kept, 18.4 against 20.8 us, 0.3
+// kept 26.4 and 28.9; 32 heads of 8k (67 MB) 0.15 kept 26.1 and 29.4; 40 heads of 9600 (98 MB) 38.4 and 39.9.  Not much smaller K, 8 heads of
+// 16k (34 MB) 0.2 kept 21.6 and 21.5, nor larger, 8 heads of 64k (134 MB) 0.1 kept 50.5 and 49.8.
+constexpr int64_t kReadAgainAllFrom = int64_t{40} << 20, kReadAgainAllTo = int64_t{96} << 20;
 
 // Scratch memory of a selection in which several workgroups share a head, 16-byte aligned; with less than it takes, or
 // none, every head is selected by one workgroup.

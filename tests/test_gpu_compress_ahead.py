@@ -48,3 +48,16 @@ def test_tokens_of_a_share(dev, dtype, D, heads, T, kept):
     l2kv.l2kv_compress(K, V, ratio, norms, idx, Kc, Vc, ws)
     for got, want in zip((norms, idx, Kc, Vc), separate(K, V, k)):
         assert torch.equal(got, want)
+
+
+# K just within and just outside the sizes of which the norm pass leaves everything in the caches, little kept
+@pytest.mark.parametrize("heads", [40, 41, 96, 97])
+def test_little_kept_of_a_cached_k(dev, heads):
+    g = torch.Generator(device=dev).manual_seed(heads)
+    K, V = (torch.randn((heads, 4096, 128), generator=g, device=dev).bfloat16() for _ in range(2))
+    k = l2kv.l2kv_keep_count(4096, 0.1)
+    norms, idx = torch.empty((heads, 4096), device=dev), torch.empty((heads, k), dtype=torch.int32, device=dev)
+    Kc, Vc = (torch.empty((heads, k, 128), dtype=K.dtype, device=dev) for _ in range(2))
+    l2kv.l2kv_compress(K, V, 0.1, norms, idx, Kc, Vc, torch.zeros(256, dtype=torch.uint8, device=dev))
+    for got, want in zip((norms, idx, Kc, Vc), separate(K, V, k)):
+        assert torch.equal(got, want)
