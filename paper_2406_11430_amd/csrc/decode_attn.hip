@@ -113,12 +113,13 @@ DecodePlan decode_plan(int32_t B, int32_t Hkv, int32_t group, int64_t kv_len, in
         int64_t by_merge = (int64_t)(0.34 * sqrt((double)kv_len));
         if (by_merge < 8) by_merge = 8;
         if (want > by_merge) want = by_merge;
-        // Short heads: up to 8 workgroups merge in registers (kWideMerge), which saves more than longer streams cost while
-        // a head has at most 512 KB of K, and 3072 rows if there is the arithmetic of 5 heads and more to each.  us, split as
-        // above / in 8: bf16 rows of 128 elements, 4 heads of 1673 rows 7.6 / 7.0, 24 of 1146 with 6 query heads each 11.7 /
-        // 10.8, 4 of 3584 with 4 9.7 / 11.7; rows of 64, 16 of 1554 9.5 / 8.4, 16 of 3042 with 6 query heads 11.5 / 10.9, 2 of 3735
-        // with 5 9.5 / 10.0; fp32 rows of 128, 4 of 907 with 8 11.9 / 10.8, 8 of 1419 with 5 10.6 / 10.7.
-        const bool short_head = kv_len * row_bytes <= int64_t{512} << 10 && (group < 5 || kv_len <= 3072);
+        // Short heads: up to 8 workgroups merge in registers (kWideMerge), which saves more than longer streams cost while a
+        // head has at most 384 KB of K.  Groups of 5 heads and more, whose merge of more than 8 goes through LDS: 512 KB and, for
+        // their arithmetic, 3072 rows.  us, split as above / in 8: 16 heads of 1554 rows of 64 elements, 4 query heads each,
+        // 8.7 / 8.2, 4 of 1673 rows of 128 6.5 / 7.0, 3 of 1265 5.7 / 5.6; groups of 5 and more: 24 heads of 1146 rows of 128 11.6 /
+        // 10.9, 16 of 3042 rows of 64 11.5 / 10.9, 2 of 3735 9.5 / 10.0; fp32 rows of 128, 4 of 907 11.9 / 10.8, 8 of 1419 10.6 / 10.7.
+        const int64_t k_bytes = kv_len * row_bytes;
+        const bool short_head = group < 5 ? k_bytes <= int64_t{384} << 10 : k_bytes <= int64_t{512} << 10 && kv_len <= 3072;
         if (want > kDecodeNarrowSplits && short_head) want = kDecodeNarrowSplits;
     }
     const int64_t cap = decode_max_splits(kv_len);

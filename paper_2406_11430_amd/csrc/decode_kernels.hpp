@@ -30,10 +30,10 @@
 // finishes last for its KV head (device-scope counter in the workspace) merges
 // the partials of all workgroups and writes O: one kernel per call.  Two builds
 // of that final merge (template parameter kWideMerge): for at most 8 workgroups
-// per head everything stays in registers; for more, the weights are formed once
-// in LDS and the accumulators arrive as 16-byte device-scope loads.  In both
-// merges a thread forms 1, 2 or 4 consecutive output elements of one head and
-// issues all its reads before the first use: every step of this epilogue is a
+// per head every thread forms its output elements from registers alone; for more,
+// a wave merges a query head, or, for groups of 5 heads and more and beyond 64
+// workgroups, the weights are formed once in LDS.  In all of them every
+// memory request is issued before the first use: every step of this epilogue is a
 // memory or LDS round trip on the critical path of the launch.
 //
 // The same routine (decode_item) runs under two launch shapes: a grid
@@ -81,6 +81,23 @@ __device__ __forceinline__ Words<W> stream_words(const char* p) {
 template <int W>
 __device__ __forceinline__ Words<W> cached_words(const char* p) {
     return load_words<W, Pieces<W>::kStride>(p);
+}
+
+// Largest value and sum over the lanes of a wave, the same in all of them (all must be active): the four DPP rows meet through
+// scalar registers, which is shorter than two trips through the LDS crossbar.
+__device__ __forceinline__ float read_lane(float v, int lane) {
+    return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), lane));
+}
+__device__ __forceinline__ float wave_max(float v) {
+    v = fmaxf(v, dpp_read<kDppXor1>(v));
+    v = fmaxf(v, dpp_read<kDppXor2>(v));
+    v = fmaxf(v, dpp_read<kDppHalfMirror>(v));
+    v = fmaxf(v, dpp_read<kDppMirror>(v));
+    return fmaxf(fmaxf(read_lane(v, 0), read_lane(v, 16)), fmaxf(read_lane(v, 32), read_lane(v, 48)));
+}
+__device__ __forceinline__ float wave_sum(float v) {
+    v = row16_tree_sum(v);
+    return (read_lane(v, 0) + read_lane(v, 16)) + (read_lane(v, 32) + read_lane(v, 48));
 }
 
 // Device-scope (agent) relaxed store of one float.
@@ -787,8 +804,72 @@ __device__ __forceinline__ void decode_item(const char* __restrict__ Q, const ch
             for (int k = 0; k < kVec; ++k)
                 store_out(O, hq0 * D + o0 + k, den > 0.f ? num[k] / den : 0.f, out_bf16);   // 0 for an empty cache
         }
+    } else if (G <= kDecWaves && n_splits <= kWaveSize) {
+    // More than 8 workgroups and at most one for each lane of a wave, query heads for one wave each: every wave merges its head without
+    // LDS or barrier.  Lane s holds (m, l) of workgroup s, so the maximum, the weights and the denominator are one
+    // cross-lane reduction each and one exponential; the accumulators arrive as 16-byte pieces, kRows partial rows to an
+    // instruction, each weighted by the lane that holds its workgroup's weight.  One memory round trip, except for heads of 256
+    // elements in more than 32 workgroups.  us, through the LDS tables below / here: 24 partials of 8 KV heads, 4 query heads each
+    // 16.3 / 15.6, one each 10.7 / 9.4; fp32 rows, 12 partials 19.6 / 18.6; 48 partials of one head 14.9 / 13.2.  (Two query heads
+    // a wave one after the other, groups of 5 to 8: 19.7 / 19.8, 13.3 / 13.6.  At most 8 partials, in the registers above 6.9, here 7.2.)
+    constexpr int kPieces = D / 4;                                      // lanes that share a partial row
+    constexpr int kRows = kWaveSize / kPieces;
+    constexpr int kBatch = D == 64 ? 16 : 32;                           // 16-byte loads per lane requested together
+    constexpr int kTogether = 4;
+    const __amdgpu_buffer_rsrc_t region = __builtin_amdgcn_make_buffer_rsrc(
+        partial + hq0 * n_splits_grid * kRow, 0, G * n_splits_grid * kRow * (int)sizeof(float), kBufferWord3);
+    const int n = __builtin_amdgcn_readfirstlane(n_splits);
+    const int sub = lane / kPieces, piece = lane % kPieces;
+    if (const int g = wave; g < G) {
+        const int head_off = g * n_splits_grid * kRow * (int)sizeof(float);
+        const f32x2 st = fetch2(region, head_off + ((lane < n ? lane : n - 1) * kRow + D) * (int)sizeof(float), 0);
+        f32x4 sum = {0.f, 0.f, 0.f, 0.f};
+        float w = 0.f, den = 0.f;
+        for (int s0 = 0; s0 < n; s0 += kBatch * kRows) {
+            f32x4 v[kBatch];
+#pragma unroll
+            for (int i0 = 0; i0 < kBatch; i0 += kTogether) {
+                if (s0 + i0 * kRows >= n) break;
+#pragma unroll
+                for (int i = i0; i < i0 + kTogether; ++i) {
+                    const int sp = s0 + i * kRows + sub;                 // past the last: its row again, with weight 0
+                    v[i] = fetch4(region, head_off + ((sp < n ? sp : n - 1) * kRow + piece * 4) * (int)sizeof(float));
+                }
+            }
+            __builtin_amdgcn_sched_barrier(0);                           // all requests ahead of the first use
+            if (s0 == 0) {
+                const float m_of = lane < n ? st.x : kNegInf;
+                const float mx = wave_max(m_of);
+                w = m_of == kNegInf ? 0.f : fast_exp2(m_of - mx);        // -inf: a workgroup that saw no row
+                den = wave_sum(w * st.y);
+            }
+#pragma unroll
+            for (int i0 = 0; i0 < kBatch; i0 += kTogether) {
+                if (s0 + i0 * kRows >= n) break;
+#pragma unroll
+                for (int i = i0; i < i0 + kTogether; ++i) {
+                    const int sp = s0 + i * kRows + sub;                 // below 64: s0 < n <= 64 and the steps divide 64
+                    const float wi = __shfl(w, sp);
+                    sum.x = fmaf(wi, v[i].x, sum.x);
+                    sum.y = fmaf(wi, v[i].y, sum.y);
+                    sum.z = fmaf(wi, v[i].z, sum.z);
+                    sum.w = fmaf(wi, v[i].w, sum.w);
+                }
+            }
+        }
+#pragma unroll
+        for (int off = kPieces; off < kWaveSize; off *= 2) {
+#pragma unroll
+            for (int k = 0; k < 4; ++k) sum[k] += __shfl_xor(sum[k], off);
+        }
+        if (sub == 0) {
+            const int64_t o = (hq0 + g) * D + piece * 4;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) store_out(O, o + k, den > 0.f ? sum[k] / den : 0.f, out_bf16);   // 0 for an empty cache
+        }
+    }
     } else {
-    // Launches with more than 8 workgroups per KV head: final merge in one memory round trip
+    // More workgroups than that per KV head: final merge in one memory round trip
     // and four LDS steps.  The weights depend on (m, l) only, the sums on the accumulators
     // only, so both are requested at once.  Entry e = (workgroup, query head) is handled by
     // thread e % 256: (1) an LDS float-max per head (order-free, hence bit-reproducible) gives

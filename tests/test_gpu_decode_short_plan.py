@@ -1,4 +1,5 @@
-"""Decode attention over heads on either side of the size up to which eight workgroups take one."""
+"""Decode attention over heads on either side of the size up to which eight workgroups take one, and the final merge of more than eight
+workgroups: by waves up to 64, through LDS beyond and for groups of 5 heads and more."""
 import math
 
 import pytest
@@ -10,8 +11,8 @@ from paper_2406_11430_amd import binding
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("dtype,D,G,rows", [(torch.bfloat16, 128, 1, 2048), (torch.bfloat16, 64, 4, 4096), (torch.bfloat16, 256, 2, 1024),
-                                            (torch.float32, 128, 4, 1024), (torch.bfloat16, 128, 5, 2048), (torch.bfloat16, 64, 8, 3072), (torch.float32, 128, 6, 1024)])
+@pytest.mark.parametrize("dtype,D,G,rows", [(torch.bfloat16, 128, 1, 1536), (torch.bfloat16, 64, 4, 3072), (torch.bfloat16, 256, 2, 768),
+                                            (torch.float32, 128, 4, 768), (torch.bfloat16, 128, 5, 2048), (torch.bfloat16, 64, 8, 3072), (torch.float32, 128, 6, 1024)])
 def test_either_side_of_the_line(dtype, D, G, rows):
     dev = torch.device("cuda:0")
     g = torch.Generator(device=dev).manual_seed(rows + G)
@@ -31,3 +32,27 @@ def test_either_side_of_the_line(dtype, D, G, rows):
         want = (p[..., None] * v).sum(dim=2)
         # fp32 sums of at most (n / 16 rows + the merges) terms of magnitude max |V| < 6 times weights that add up to 1
         assert (O.cpu().double() - want).abs().max() <= (n / 16 + 64) * 2.0 ** -24 * 6
+
+
+@pytest.mark.parametrize("dtype,D", [(torch.bfloat16, 64), (torch.bfloat16, 128), (torch.bfloat16, 256), (torch.float32, 64), (torch.float32, 128)])
+@pytest.mark.parametrize("G", [1, 3, 4, 5])
+def test_merge_of_many_workgroups(dtype, D, G):
+    if D == 256 and G > 4:
+        pytest.skip("not a supported group")
+    dev = torch.device("cuda:0")
+    n = 4200
+    g = torch.Generator(device=dev).manual_seed(D + G)
+    Q = (2 * torch.randn((1, 3 * G, D), generator=g, device=dev)).to(dtype)
+    K, V = (torch.randn((1, 3, n, D), generator=g, device=dev).to(dtype) for _ in range(2))
+    ws = torch.empty(l2kv.l2kv_decode_workspace_bytes(1, 3 * G, n, D), dtype=torch.uint8, device=dev)
+    binding.l2kv_decode_workspace_init(ws)
+    q, k, v = Q.cpu().double(), K.cpu().double(), V.cpu().double()
+    k, v = (x.repeat_interleave(G, dim=1) for x in (k, v))
+    p = torch.softmax((k @ q[..., None])[..., 0] / math.sqrt(D), dim=-1)
+    want = (p[..., None] * v).sum(dim=2)
+    O = torch.empty((1, 3 * G, D), device=dev)
+    for splits in (8, 9, 15, 16, 17, 31, 32, 33, 47, 63, 64, 65, 66):
+        for _ in range(2):                                  # the counters are left as they were found
+            O.fill_(float("nan"))
+            binding.l2kv_decode_attn_splits(Q, K, V, O, ws, n_splits=splits)
+            assert (O.cpu().double() - want).abs().max() <= (n / 16 + 64) * 2.0 ** -24 * 6, splits
