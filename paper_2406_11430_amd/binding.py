@@ -1,5 +1,5 @@
-"""ctypes binding of libl2kv.so: one Python function per C entry point, same
-names, argument marshalling only.  Tensors are torch CUDA(HIP) tensors used as
+"""Binding of libl2kv.so: one Python function per C entry point, same
+names, argument marshalling only (ctypes; the calls of a decode step and the compression also natively, csrc/calls.cpp).  Tensors are torch CUDA(HIP) tensors used as
 device memory; every step of the path runs inside the library's kernels.
 
 The library must already be built (``python -m paper_2406_11430_amd.build``);
@@ -8,6 +8,7 @@ nothing here falls back to another implementation.
 from __future__ import annotations
 
 import ctypes as C
+import importlib.util
 import os
 from typing import Optional
 
@@ -15,6 +16,7 @@ import torch
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libl2kv.so")
+CALLS_PATH = os.path.join(_HERE, "l2kv_calls.so")
 
 L2KV_F32, L2KV_BF16 = 0, 1
 L2KV_KEEP_LOWEST, L2KV_KEEP_HIGHEST = 0, 1
@@ -91,6 +93,25 @@ class L2KVError(RuntimeError):
 
 
 _lib = None
+_calls = None
+
+
+def calls():
+    """The native calls (csrc/calls.cpp), bound to the loaded library; raises if they have not been built."""
+    global _calls
+    if _calls is None:
+        handle = lib()
+        if not os.path.exists(CALLS_PATH):
+            raise RuntimeError(
+                "l2kv_calls.so is missing at %s: build it with "
+                "`python -m paper_2406_11430_amd.build` (there is no fallback path)" % CALLS_PATH)
+        spec = importlib.util.spec_from_file_location("l2kv_calls", CALLS_PATH)
+        module = importlib.util.module_from_spec(spec)
+        spec.loader.exec_module(module)
+        module.bind(*(C.cast(f, C.c_void_p).value for f in (handle.l2kv_decode_attn, handle.l2kv_decode_attn_out,
+                                                           handle.l2kv_compress)))
+        _calls = module
+    return _calls
 
 
 def lib() -> C.CDLL:
@@ -268,6 +289,9 @@ def l2kv_compress(K: torch.Tensor, V: torch.Tensor, keep_ratio: float, norms: to
                   slab_heads: int = 0, stream=None) -> None:
     """norms -> select -> compact in one call (optionally slab by slab of ``slab_heads`` heads).  The workspace is not
     touched; the outputs are scratch memory before they are filled."""
+    st = (_calls or calls()).compress(K, V, norms, kept_idx, Kc, Vc, workspace, keep_ratio, slab_heads, stream, _stream)
+    if st is not None:
+        return _check("l2kv_compress", st)
     _dev(K, V, norms, kept_idx, Kc, Vc, workspace)
     n, T, D = _heads(K)
     k = kept_idx.shape[-1]
@@ -284,6 +308,9 @@ def l2kv_compress(K: torch.Tensor, V: torch.Tensor, keep_ratio: float, norms: to
 def l2kv_decode_attn(Q: torch.Tensor, Kc: torch.Tensor, Vc: torch.Tensor, O: torch.Tensor,
                      workspace: torch.Tensor, scale: float = 0.0, stream=None) -> None:
     """Q ``[B, Hq, D]``, Kc/Vc ``[B, Hkv, n, D]`` -> O ``[B, Hq, D]`` float32."""
+    st = (_calls or calls()).decode_attn(Q, Kc, Vc, O, workspace, scale, stream, _stream)
+    if st is not None:
+        return _check("l2kv_decode_attn", st)
     l2kv_decode_attn_splits(Q, Kc, Vc, O, workspace, scale=scale, n_splits=None, stream=stream)
 
 
@@ -311,6 +338,9 @@ def l2kv_decode_attn_splits(Q: torch.Tensor, Kc: torch.Tensor, Vc: torch.Tensor,
 def l2kv_decode_attn_out(Q: torch.Tensor, Kc: torch.Tensor, Vc: torch.Tensor, O: torch.Tensor,
                          workspace: torch.Tensor, scale: float = 0.0, stream=None) -> None:
     """l2kv_decode_attn with O ``[B, Hq, D]`` in float32 or bfloat16 (the tensor's dtype decides)."""
+    st = (_calls or calls()).decode_attn_out(Q, Kc, Vc, O, workspace, scale, stream, _stream)
+    if st is not None:
+        return _check("l2kv_decode_attn_out", st)
     _dev(Q, Kc, Vc, O, workspace)
     B, Hq, D = Q.shape
     Bk, Hkv, n, Dk = Kc.shape

@@ -1,4 +1,4 @@
-"""Build libl2kv.so (HIP, gfx950 only) in-tree with hipcc.
+"""Build libl2kv.so (HIP, gfx950 only) in-tree with hipcc, and the native calls of the Python binding with g++.
 
     python -m paper_2406_11430_amd.build          # compile every source, link
 
@@ -67,6 +67,27 @@ def build_library(extra_flags=(), jobs: int = 8, out: str = LIB_PATH, obj_dir: s
     return out
 
 
+CALLS_PATH = os.path.join(HERE, "l2kv_calls.so")
+
+
+def build_calls() -> str:
+    """Compile the binding's native calls (host code, g++) against the installed torch's headers."""
+    import sysconfig
+
+    from torch.utils import cpp_extension
+    include = [*cpp_extension.include_paths(), sysconfig.get_paths()["include"]]
+    libs = cpp_extension.library_paths()
+    tmp = CALLS_PATH + ".tmp.%d" % os.getpid()
+    cmd = ["g++", "-std=c++17", "-O2", "-fPIC", "-shared", "-Wall", *["-isystem" + p for p in include],
+           os.path.join(CSRC, "calls.cpp"), "-o", tmp, *["-L" + p for p in libs], *["-Wl,-rpath," + p for p in libs],
+           "-ltorch_python", "-ltorch_cpu", "-lc10"]
+    res = subprocess.run(cmd, capture_output=True, text=True)
+    if res.returncode != 0:
+        raise RuntimeError("g++ failed for the native calls:\n" + res.stderr)
+    os.replace(tmp, CALLS_PATH)
+    return CALLS_PATH
+
+
 C_DRIVER_SRC = os.path.join(os.path.dirname(HERE), "tests", "abi_c", "l2kv_c_driver.c")
 C_DRIVER_BIN = os.path.join(os.path.dirname(HERE), "tests", "abi_c", "l2kv_c_driver")
 
@@ -87,4 +108,5 @@ def build_c_driver() -> str:
 
 if __name__ == "__main__":
     print(build_library(sys.argv[1:]))
+    print(build_calls())
     print(build_c_driver())

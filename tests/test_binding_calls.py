@@ -1,0 +1,76 @@
+"""The native calls of the binding: what they refuse goes through the Python checks and ends in the same error, and what they
+take reaches the C entry point with the same arguments."""
+import pytest
+import torch
+
+import paper_2406_11430_amd as l2kv
+from paper_2406_11430_amd import binding
+
+
+def tensors(dtype=torch.bfloat16, device="cpu"):
+    Q, O, ws = torch.zeros((1, 4, 64), dtype=dtype), torch.zeros((1, 4, 64)), torch.zeros(1 << 16, dtype=torch.uint8)
+    K, V = (torch.zeros((1, 2, 8, 64), dtype=dtype) for _ in range(2))
+    return [x.to(device) for x in (Q, K, V, O, ws)]
+
+
+def test_host_tensors_are_refused():
+    args = tensors()
+    for call in (l2kv.l2kv_decode_attn, l2kv.l2kv_decode_attn_out):
+        with pytest.raises(ValueError, match="device tensors"):
+            call(*args)
+    Q, K, V, O, ws = args
+    with pytest.raises(ValueError, match="device tensors"):
+        l2kv.l2kv_compress(K, V, 0.5, torch.zeros((1, 2, 8)), torch.zeros((1, 2, 4), dtype=torch.int32), K, V, ws)
+
+
+def test_what_is_not_a_tensor_or_a_number_is_left_to_the_checks():
+    native = binding.calls()
+    assert native.decode_attn(1, 2, 3, 4, 5, 0.0, None, binding._stream) is None
+    assert native.decode_attn(*tensors(), "x", None, binding._stream) is None
+    assert native.decode_attn() is None and native.decode_attn_out() is None and native.compress() is None
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("change", ["none", "stride", "dtype", "shape", "dims", "output", "half", "nan_scale", "workspace", "group"])
+def test_decode_errors(change):
+    Q, K, V, O, ws = tensors(device="cuda")
+    binding.l2kv_decode_workspace_init(ws)
+    scale, expected = 0.0, None
+    if change == "stride":
+        K, expected = torch.zeros((1, 2, 64, 8), dtype=K.dtype, device="cuda").transpose(2, 3), ValueError
+    elif change == "dtype":
+        V, expected = V.float(), AssertionError
+    elif change == "shape":
+        V, expected = V[:, :, :7].contiguous(), AssertionError
+    elif change == "dims":
+        Q, expected = Q[0], ValueError
+    elif change == "output":
+        O, expected = O[:, :3].contiguous(), AssertionError
+    elif change == "half":
+        Q, K, V, expected = Q.half(), K.half(), V.half(), TypeError
+    elif change == "nan_scale":
+        scale, expected = float("nan"), l2kv.L2KVError
+    elif change == "workspace":
+        ws, expected = ws[:16], l2kv.L2KVError
+    elif change == "group":
+        Q, O, expected = Q[:, :3].contiguous(), O[:, :3].contiguous(), l2kv.L2KVError
+    for call in (l2kv.l2kv_decode_attn, l2kv.l2kv_decode_attn_out):
+        if expected is None:
+            call(Q, K, V, O, ws, scale=scale, stream=torch.cuda.current_stream())
+        else:
+            with pytest.raises(expected):
+                call(Q, K, V, O, ws, scale=scale)
+
+
+@pytest.mark.gpu
+def test_subclass_of_tensor_takes_the_python_way():
+    class Named(torch.Tensor):
+        pass
+    Q, K, V, O, ws = tensors(device="cuda")
+    binding.l2kv_decode_workspace_init(ws)
+    V.normal_()
+    sub = O.clone().as_subclass(Named)
+    assert binding.calls().decode_attn(Q, K, V, sub, ws, 0.0, None, binding._stream) is None
+    l2kv.l2kv_decode_attn(Q, K, V, sub, ws)
+    l2kv.l2kv_decode_attn(Q, K, V, O, ws)
+    assert torch.equal(sub.as_subclass(torch.Tensor), O) and O.abs().sum() > 0
