@@ -416,7 +416,7 @@ l2kv_status l2kv_decode_attn_ragged(const void* Q, const void* Kc, const void* V
             return st;
         seq_order = own_order;
     }
-    const DecodePlan plan = decode_plan_ragged(n_seq, Hkv, max_len, n_splits,
+    const DecodePlan plan = decode_plan_ragged(n_seq, Hkv, max_len, total_slots, n_splits,
                                                seq_order != nullptr && work_list_rows(dt, D));
     return decode_dispatch(Q, Kc, Vc, dt, n_seq, Hq, Hkv, max_len, D, total_slots * static_cast<int64_t>(D),
                            lens, slot_offsets, seq_order, s, plan, O, workspace,

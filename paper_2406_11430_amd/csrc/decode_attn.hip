@@ -133,7 +133,7 @@ DecodePlan decode_plan(int32_t B, int32_t Hkv, int32_t group, int64_t kv_len, in
     return plan;
 }
 
-DecodePlan decode_plan_ragged(int32_t n_seq, int32_t Hkv, int64_t max_len, int32_t requested_splits,
+DecodePlan decode_plan_ragged(int32_t n_seq, int32_t Hkv, int64_t max_len, int64_t total_slots, int32_t requested_splits,
                               bool ordered) {
     const int64_t pairs = (int64_t)n_seq * Hkv;
     int64_t want = requested_splits;
@@ -155,6 +155,25 @@ DecodePlan decode_plan_ragged(int32_t n_seq, int32_t Hkv, int64_t max_len, int32
             const int64_t target = 3 * cus / 4;
             const int64_t by_cu = (2 * target + pairs) / (2 * pairs);
             want = by_len > by_cu ? by_len : by_cu;
+            // Sequences much longer than what a workgroup streams in all (`load`, as far as the slots tell) are cut, or the
+            // launch waits for them.  Best into as many pieces as just leave every one a workgroup of its own (each sequence's
+            // last piece is half full on average, and 5 % for chance); where that leaves pieces of more than 1.75 loads and
+            // nothing is cut yet, into three, or two if there are nearly as many pairs as workgroups, unless the sequences
+            // are much alike (192 pairs of 4000 rows 68.3, in three 78.1).  us per layer, whole sequences of 500 to 4400 rows / cut so:
+            // 96 pairs 36.0 / 28.4, 160 (250 to 2260 rows) 35.1 / 23.6, 192 63.5 / 50.8, 240 68.3 / 55.7, 288 57.9 / 53.2,
+            // 320 74.3 / 71.9; 360 pairs, whose longest has 1.3 loads, 47.7, in two 50.1.
+            const int64_t total = total_slots * Hkv, load = (total + cus - 1) / cus;
+            int64_t by_load = 1;
+            if (10 * max_len > 13 * load) {
+                const int64_t room = cus - pairs / 2;
+                by_load = room > 0 ? 20 * max_len * room / (21 * total) : 0;
+                if (by_load < 1 || 4 * max_len > 7 * load * by_load) {
+                    const bool uneven = 2 * max_len * n_seq >= 3 * total_slots;
+                    by_load = want > 1 || !uneven ? want : pairs <= cus - cus / 16 ? 3 : 2;
+                }
+                if (by_load > kDecodeNarrowSplits) by_load = kDecodeNarrowSplits;
+            }
+            if (want < by_load) want = by_load;
         }
         if (want > cap) want = cap;
         if (want < 1) want = 1;

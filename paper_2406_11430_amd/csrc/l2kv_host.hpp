@@ -89,7 +89,7 @@ l2kv_status workspace_init_dispatch(void* workspace, size_t bytes, hipStream_t s
 // which enqueues one fill kernel on `stream`); nullptr with *status set on failure.
 void* decode_static_scratch(hipStream_t stream, l2kv_status* status);
 DecodePlan decode_plan(int32_t B, int32_t Hkv, int32_t group, int64_t kv_len, int32_t row_bytes, int32_t requested_splits);
-DecodePlan decode_plan_ragged(int32_t n_seq, int32_t Hkv, int64_t max_len, int32_t requested_splits,
+DecodePlan decode_plan_ragged(int32_t n_seq, int32_t Hkv, int64_t max_len, int64_t total_slots, int32_t requested_splits,
                               bool ordered);
 
 // lens / slot_off NULL: uniform batch (kv_len rows per slab, slabs kv_head_stride apart).
