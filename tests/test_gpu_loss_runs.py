@@ -78,3 +78,31 @@ def test_logits_that_are_not_finite(dev, T):
     K[0, 1, 5] *= 0.0
     K[0, 1, 5] = -1e4 * Q[0, 1]                                        # a logit far below all others
     assert all(np.allclose(a[0, 1], b[0, 1], rtol=1e-6, atol=0) for a, b in zip(got, losses(dev, K, Q, rank, T // 2)))
+
+
+# Groups of equal logits around what a run takes care of and what is compared.
+@pytest.mark.parametrize("T,Hkv,B", [(8193, 2, 1), (16384, 2, 1), (20481, 2, 1), (32768, 2, 1), (12000, 32, 4), (16384, 32, 8), (19452, 32, 8),
+                                     (32768, 32, 4)])
+@pytest.mark.parametrize("each", [1, 9, 17, 18, 25, 32, 33, 40, 64, 65])
+def test_order(dev, T, Hkv, B, each):
+    """With the ranks of the scores themselves as the order of discarding, both terms of Y are the same sum of the same
+    numbers, and so are both losses: a score out of place shows even where its neighbours are nearly equal."""
+    g = torch.Generator(device=dev).manual_seed(T + each)
+    rows = (T + each - 1) // each
+    K = torch.randn((B, Hkv, rows, 64), generator=g, device=dev) * torch.exp(0.5 * torch.randn((B, Hkv, rows, 1), generator=g, device=dev))
+    K = K.bfloat16()[:, :, torch.randperm(rows * each, generator=g, device=dev)[:T] // each].contiguous()
+    Q = torch.randn((B, Hkv, 64), generator=g, device=dev).bfloat16()
+    rank = torch.zeros((B, Hkv, T), dtype=torch.int32, device=dev)
+    ws = torch.empty(l2kv.l2kv_alr_workspace_bytes(B, Hkv, T), dtype=torch.uint8, device=dev)
+    Y, Lm, Lref = (torch.empty((B, Hkv), dtype=torch.float64, device=dev) for _ in range(3))
+    m = T // 3
+    l2kv.l2kv_alr(Q, K, rank, m, Y, Lm, Lref, ws)
+    logits = ws[:B * Hkv * T * 4].view(torch.float32).view(B, Hkv, T)          # left at its start
+    exact = torch.einsum("bhd,bhtd->bht", Q.cpu().float(), K[:, :, :64].cpu().float()) / 8 * 1.4426950408889634
+    assert (logits[:, :, :64].cpu() - exact).abs().max() <= 1e-4               # these are they; 64 products of up to 1e2 in fp32
+    rank.scatter_(2, torch.argsort(logits, dim=2, stable=True), torch.arange(T, dtype=torch.int32, device=dev).expand(B, Hkv, T).contiguous())
+    l2kv.l2kv_alr(Q, K, rank, m, Y, Lm, Lref, ws)
+    # sums in 64 bits of at most T numbers that add up to 1, times at most T: no term takes part in more than 100 additions (32 by a
+    # lane, the waves', the shares'), in both terms of Y
+    assert Y.abs().max() <= 2 * 128 * 2.0 ** -53 * T
+    assert (Lm - Lref).abs().max() <= 2 * 128 * 2.0 ** -53
