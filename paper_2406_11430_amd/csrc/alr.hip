@@ -615,7 +615,7 @@ __device__ __forceinline__ bool rank_share(const Keys& keys, const Share<typenam
 // more store puts it there, and nothing is gathered or read again.  What is then left to do is order inside the finer bins, of
 // two elements on average: a lane sorts 32 neighbours in registers, which does every bin that does not reach over their end, and
 // merges the upper half of them with the lower half of the next lane's, which does the others, as long as
-// no bin has more than 17.  The lane then holds 32 elements of consecutive ranks and adds them up.
+// no bin has more than 17 (fuller ones are put in order by themselves, sort_bins).  The lane then holds 32 elements of consecutive ranks and adds them up.
 // What bounds it: a key costs 0.2 us per vector instruction and CU (32 keys a lane, four waves a SIMD), and each of its LDS
 // accesses 10 to 15 cycles a wave with its bank conflicts; so a key's way takes a dozen instructions, one atomic and two
 // reads, all lanes doing the same.  128 heads of 32k logits in two shares each, us: fetch and range 6.6, coarse bins 3.9, finer
@@ -653,15 +653,58 @@ template <int kN, int kSpan> __device__ __forceinline__ void merge_runs(float (&
 // that lanes reading the same piece of theirs hit different banks.
 __device__ __forceinline__ uint32_t run_word(uint32_t at) { return at ^ ((at >> 5 & 7u) << 2); }
 
-enum ShareOrder { kInOrder, kTooManyForRuns, kTooManyForBins };
-// kInOrder: run[] holds the elements of ranks kRun * threadIdx.x .. inside the share, as far as they are below s.count.
-// Otherwise nothing.  Called by all lanes; the list is free again after the caller's barrier.
+// The n <= kRun words of the list from `at` on in order.
+__device__ __forceinline__ void sort_words(float* list, uint32_t at, uint32_t n) {
+    float x[kRun];
+#pragma unroll
+    for (uint32_t i = 0; i < kRun; ++i) {
+        x[i] = list[run_word(i < n ? at + i : at)];
+        x[i] = i < n ? x[i] : INFINITY;
+        if (i % 4 == 3) asm volatile("" : "+v"(at));                  // addresses afresh: kept, they would take as many registers again
+    }
+    merge_runs<kRun, 1>(x);
+#pragma unroll
+    for (uint32_t i = 0; i < kRun; ++i) {
+        if (i < n) list[run_word(at + i)] = x[i];
+        if (i % 4 == 3) asm volatile("" : "+v"(at));
+    }
+}
+// Finer bins with more elements than the runs take care of, in pieces of at most kRun that a lane sorts each: first word in the
+// list, length << 16, and for a bin of two, kPaired in both and kSecond in the one that follows.  Two pieces in order, mirrored and
+// compared element by element, leave the smaller ones in front, so that all are in order when each is sorted again.
+constexpr uint32_t kPaired = 1u << 31, kSecond = 1u << 30;
+__device__ __forceinline__ void sort_pieces(const uint32_t* pieces, uint32_t count, uint32_t which, float* list) {
+    for (uint32_t i = threadIdx.x; i < count; i += kSortLanes)
+        if ((pieces[i] & which) == which) sort_words(list, pieces[i] & 0xffffu, pieces[i] >> 16 & (2 * kRun - 1));
+    __syncthreads();
+}
+__device__ __forceinline__ void sort_bins(const uint32_t* pieces, uint32_t count, bool pairs, float* list) {
+    sort_pieces(pieces, count, 0u, list);
+    if (!pairs) return;
+    for (uint32_t i = threadIdx.x; i < count; i += kSortLanes) {
+        if ((pieces[i] & kSecond) == 0) continue;
+        const uint32_t second = pieces[i] & 0xffffu, n = pieces[i] >> 16 & (2 * kRun - 1);
+        for (uint32_t j = 0; j < n; ++j) {                            // past n there is nothing opposite
+            float* const low = list + run_word(second - 1 - j);
+            float* const high = list + run_word(second + j);
+            const float p = *low, q = *high;
+            *low = fminf(p, q);
+            *high = fmaxf(p, q);
+        }
+    }
+    __syncthreads();
+    sort_pieces(pieces, count, kPaired, list);
+}
+
+// True: run[] holds the elements of ranks kRun * threadIdx.x .. inside the share, as far as they are below s.count.
+// False, where some finer bin holds more than kMaxFine: nothing.  Called by all lanes; the list is free again after the caller's barrier.
 template <int E>
-__device__ __forceinline__ ShareOrder order_share(const HeadKeys<E, ValueBins>& keys, const Share<ValueBins>& s, BinShared& sh,
-                                                  float* list, float (&run)[kRun]) {
+__device__ __forceinline__ bool order_share(const HeadKeys<E, ValueBins>& keys, const Share<ValueBins>& s, BinShared& sh,
+                                            float* list, float (&run)[kRun]) {
     const uint32_t lane = threadIdx.x % kWaveSize;
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWaveSize);
     const uint32_t bins = s.end - s.first;
+    if (threadIdx.x == 0) sh.wave[1][0] = sh.wave[1][1] = 0;          // pieces of finer bins with too many for a run, any of two
     for (int i = 0; i < kFinePer / 4; ++i) reinterpret_cast<uint4*>(sh.fine)[i * kSortLanes + threadIdx.x] = make_uint4(0, 0, 0, 0);
     // A bin of the head as a line: the finer bin its first element is expected in, and how many it spans.  Its end does not
     // reach past the start of the next one, whatever the rounding, so the finer bins are in the order of the keys.
@@ -705,11 +748,28 @@ __device__ __forceinline__ ShareOrder order_share(const HeadKeys<E, ValueBins>& 
     Counts<kFinePer> c;
     c.load(sh.fine);
     counts_to_starts(c, sh.fine, sh.wave[0]);
+    static_assert(kListFront + kListWords < 1 << 16 && kMaxFine <= 2 * kRun && kListWords / kMaxRun * 2 <= kRankBins,
+                  "pieces in a word each, in place of the head's bins");
+    uint32_t* const pieces = sh.bin;
+    uint32_t first = c.before + kListFront;
 #pragma unroll
-    for (int i = 0; i < kFinePer; ++i)
-        if (c.v[i] > kMaxRun) atomicOr(&sh.crowded, c.v[i] > kMaxFine ? 2u : 1u);       // 0 so far: the head is not crowded
+    for (int i = 0; i < kFinePer; ++i) {
+        const uint32_t n = c.v[i];
+        if (n > kMaxFine) {
+            sh.crowded = 1;                                           // 0 so far: the head is not crowded
+        } else if (n > kRun) {
+            const uint32_t at = atomicAdd(&sh.wave[1][0], 2u);
+            pieces[at] = first | kRun << 16 | kPaired;
+            pieces[at + 1] = (first + kRun) | (n - kRun) << 16 | kPaired | kSecond;
+            sh.wave[1][1] = 1;
+        } else if (n > kMaxRun) {
+            pieces[atomicAdd(&sh.wave[1][0], 1u)] = first | n << 16;
+        }
+        first += n;
+    }
     __syncthreads();
-    if (sh.crowded != 0) return sh.crowded < 2 ? kTooManyForRuns : kTooManyForBins;
+    if (sh.crowded != 0) return false;
+    const uint32_t full = __builtin_amdgcn_readfirstlane(sh.wave[1][0]), pairs = __builtin_amdgcn_readfirstlane(sh.wave[1][1]);
     constexpr uint32_t kAside = kListFront + kListWords;              // behind the longest share
 #pragma unroll
     for (int e = 0; e < E; ++e) {
@@ -720,6 +780,7 @@ __device__ __forceinline__ ShareOrder order_share(const HeadKeys<E, ValueBins>& 
     }
     if (threadIdx.x < kListFront) list[run_word(threadIdx.x)] = -INFINITY;
     __syncthreads();
+    if (__builtin_expect(full != 0, false)) sort_bins(pieces, full, pairs != 0, list);
     // Lane i: the words 32 i .. 32 i + 31, elements from 16 before its ranks on.
     const uint32_t words = s.count + kListFront;
     float x[kRun];
@@ -752,7 +813,7 @@ __device__ __forceinline__ ShareOrder order_share(const HeadKeys<E, ValueBins>& 
         run[i] = x[kRun / 2 + i];
     }
     merge_step<kRun, kRun / 2, kRun / 2>(run);
-    return kInOrder;
+    return true;
 }
 
 // ---- ranking by an exact cut and a sort ---------------------------------------------------------
@@ -979,8 +1040,7 @@ __device__ __forceinline__ void sort_list(uint32_t* list_key, uint32_t* list_pos
     const uint32_t first = wave * chunk;                              // of this wave; chunk <= kPer * 64
     const uint32_t mine = first >= count ? 0u : (count - first < chunk ? count - first : chunk);
     static_assert(kSortWaves * kBins <= kFineBins && kBins <= kRankBins && kBins % kWaveSize == 0, "counters fit the bins");
-    // of this wave: its elements of every digit so far.  (Read and written for the other lanes to see, not `volatile`: that would
-    // keep the compiler from learning, in a function of its own, that it points into LDS.)
+    // of this wave: its elements of every digit so far, read and written for the other lanes to see
     uint32_t* const counts = sh.fine + wave * kBins;
     auto count_of = [&](uint32_t d) { return __hip_atomic_load(counts + d, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT); };
     auto set_count = [&](uint32_t d, uint32_t v) { __hip_atomic_store(counts + d, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT); };
@@ -1050,9 +1110,11 @@ __device__ __forceinline__ void sort_list(uint32_t* list_key, uint32_t* list_pos
 template <typename KeyOf, bool kWithPos, int kPer, typename Sh>
 __device__ __forceinline__ void sort_head(const uint32_t* src, uint32_t n, uint32_t* list_key, uint32_t* list_pos, Sh& sh) {
     uint32_t least = 0xffffffffu, most = 0u;
+    uint32_t lane_of_all = threadIdx.x;
+    asm volatile("" : "+v"(lane_of_all));                             // positions of earlier passes are not worth registers until here
 #pragma unroll
     for (int u = 0; u < kPer; ++u) {
-        const uint32_t t = u * kSortLanes + threadIdx.x;
+        const uint32_t t = u * kSortLanes + lane_of_all;
         if (t < n) {
             const uint32_t key = KeyOf::of(src[t]);
             list_key[t] = key;
@@ -1346,59 +1408,45 @@ __device__ __forceinline__ void write_losses(const double (&acc)[kRecordSums], i
     if (loss_ref != nullptr) loss_ref[head] = acc[4] / acc[0];
 }
 
-// What the ranking of a head's scores keeps in LDS, one for the kernel and what it calls.
+// What the ranking of a head's scores keeps in LDS.
 struct HeadShared {
     BinShared sh;
     CutShared cut;
     __attribute__((aligned(16))) uint32_t list[kListFront + kListWords + kWaveSize];
     double stage[kSortWaves][kRecordSums];
 };
-__device__ __forceinline__ HeadShared& head_shared() {
-    __shared__ HeadShared all;
-    return all;
-}
 
-// The sums in order of rank of one share, whose bins are known: by comparing inside the finer bins, or, where there are too
-// many elements in one, by an exact cut and a sort.
-template <typename Keys>
-__device__ __forceinline__ RankedSums ranked_sums(const Keys& keys, const Share<ValueBins>& s, const Cut& cut, uint32_t share,
-                                                  bool compare, int64_t m) {
-    HeadShared& lds = head_shared();
+// The sums in order of rank of one share, ranks [r0, r1), by an exact cut and a sort, wherever its elements lie.
+typedef const uint32_t __attribute__((address_space(1)))* GlobalWords;     // of a plain pointer it would not know that it is not LDS
+__device__ __forceinline__ RankedSums sorted_sums(GlobalWords logits, uint32_t n, uint32_t r0, uint32_t r1, float mx, int64_t m, HeadShared& lds) {
     RankedSums ranked;
-    if (compare) {
-        // ranks inside the share, then the sums in order of rank
-        float* const list = reinterpret_cast<float*>(lds.list);
-        Ranked<kListPer, ValueBins> mine;
-        if (rank_share<false, kListPer>(keys, s, lds.sh, list, nullptr, mine)) {
-            __syncthreads();
-#pragma unroll
-            for (int u = 0; u < kListPer; ++u)
-                if (u * kSortLanes + threadIdx.x < s.count) list[mine.rank[u]] = mine.key[u];
-            __syncthreads();
-            for (uint32_t i = threadIdx.x; i < s.count; i += kSortLanes) add_ranked(ranked, score(list[i], s.kmax), s.base + i, m);
-            return ranked;
-        }
-    }
-    const uint32_t r0 = s.crowded ? cut.start(share) : s.base;
-    const uint32_t r1 = s.crowded ? cut.start(share + 1) : s.base + s.count;
-    const uint32_t at = sorted_range<LogitKey, false, kListPer>(keys.src, keys.n, r0, r1, lds.list, nullptr, lds.sh, lds.cut);
+    const uint32_t at = sorted_range<LogitKey, false, kListPer>((const uint32_t*)logits, n, r0, r1, lds.list, nullptr, lds.sh, lds.cut);
     for (uint32_t i = threadIdx.x; i < r1 - r0; i += kSortLanes)
-        add_ranked(ranked, score(float_of_ordered(lds.list[at + i]), s.kmax), r0 + i, m);
+        add_ranked(ranked, score(float_of_ordered(lds.list[at + i]), mx), r0 + i, m);
     return ranked;
 }
-// A function of its own: inlined, its registers made the path that nearly all heads take spill (42 us in place of 33).  Half of the logits
-// equal, 128 heads of 32768: 165 us, 155 inlined.
-typedef const uint32_t __attribute__((address_space(1)))* GlobalWords;     // of a plain pointer it would not know that it is not LDS
-__device__ __attribute__((noinline)) RankedSums ranked_sums_apart(GlobalWords logits, uint32_t n, Share<ValueBins> s, Cut cut,
-                                                                  uint32_t share, bool compare, int64_t m) {
-    return ranked_sums(HeadKeys<0, ValueBins>((const uint32_t*)logits, n), s, cut, share, compare, m);
+// The same by comparing inside the finer bins, as long as these do not hold too many; else false.
+template <typename Keys>
+__device__ __forceinline__ bool compared_sums(const Keys& keys, const Share<ValueBins>& s, int64_t m, RankedSums& ranked, HeadShared& lds) {
+    float* const list = reinterpret_cast<float*>(lds.list);
+    Ranked<kListPer, ValueBins> mine;
+    if (!rank_share<false, kListPer>(keys, s, lds.sh, list, nullptr, mine)) return false;
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < kListPer; ++u)
+        if (u * kSortLanes + threadIdx.x < s.count) list[mine.rank[u]] = mine.key[u];
+    __syncthreads();
+    for (uint32_t i = threadIdx.x; i < s.count; i += kSortLanes) add_ranked(ranked, score(list[i], s.kmax), s.base + i, m);
+    return true;
 }
 
 // Heads of more than 8192 tokens whose keys stay in registers.  us for the losses, compared in the list / in runs: 128 heads of 9000
 // 34.1, 31.9; 12000 39.8, 36.6; 16384 47.3, 43.4; 24000 65.1, 58.7; 32768 85.3, 74.4; 256 heads of 17000 72.6, 59.7; few heads
 // and so small shares the same (32 heads of 9000 23.4, 23.6, of 32768 38.3, 36.3).  Up to 8192 tokens a share is so
 // small that runs of 32 leave most lanes idle: 32 heads of 3000 18.4, 19.7; 128 of 3000 20.9, 22.2.
-// Where the finer bins turn out too full the attempt is lost time: 128 heads of 32768 with 20 equal logits each 148, 157.
+// Full finer bins, 20 equal logits each, list / runs: 128 heads of 32768 148, 95, of 12000 56, 47, 32 of 16384 35.1, 33.2, of 9000
+// 30.5, 30.6; 40 equal: 128 of 32768 153, 142, 32 of 9000 36.3, 31.2.  With more than kMaxFine the attempt is lost time, but less than the
+// list's: 100 equal, 128 of 32768 153, 141, of 12000 75, 70; half of all equal 159, 152.
 template <int E> constexpr bool kInRuns = E > 8;
 
 // Softmax statistics, rank-weighted sums, ranks of the scores by value ranges, and the three
@@ -1412,7 +1460,7 @@ __global__ __launch_bounds__(kSortLanes)
 void alr_head_kernel(uint32_t* __restrict__ scratch, const int32_t* __restrict__ drop_rank, int64_t T,
                      uint32_t n_heads, int32_t G, Cut cut, int64_t m, double* __restrict__ alr,
                      double* __restrict__ loss, double* __restrict__ loss_ref) {
-    HeadShared& lds = head_shared();
+    __shared__ HeadShared lds;
     BinShared& sh = lds.sh;
     uint32_t* const s_list = lds.list;
     double (&stage)[kSortWaves][kRecordSums] = lds.stage;
@@ -1432,21 +1480,25 @@ void alr_head_kernel(uint32_t* __restrict__ scratch, const int32_t* __restrict__
 
     RankedSums ranked;
     if (!equal) {
+        bool done = false;
         if constexpr (kInRuns<E>) {
-            ShareOrder order = kTooManyForBins;
             if (!s.crowded) {
                 float run[kRun];
-                order = order_share<E>(keys, s, sh, reinterpret_cast<float*>(s_list), run);
+                done = order_share<E>(keys, s, sh, reinterpret_cast<float*>(s_list), run);
                 const uint32_t at = threadIdx.x * kRun;
-                if (order == kInOrder && at < s.count) add_run(ranked, run, mx, s.base + at, s.count - at, m);
-            }
-            if (order != kInOrder) {
-                __syncthreads();
-                if (threadIdx.x == 0) sh.crowded = 0;
-                ranked = ranked_sums_apart((GlobalWords)logits, n, s, cut, (uint32_t)part.share, order == kTooManyForRuns, m);
+                if (done && at < s.count) add_run(ranked, run, mx, s.base + at, s.count - at, m);
             }
         } else {
-            ranked = ranked_sums(keys, s, cut, (uint32_t)part.share, !s.crowded, m);
+            if (!s.crowded) done = compared_sums(keys, s, m, ranked, lds);
+        }
+        // Seldom, as the compiler has to know, and with nothing left in registers for it, not even what would only be loaded again:
+        // otherwise the path that nearly all heads take spills (42 us in place of 33 for 128 heads of 32k).
+        if (__builtin_expect(!done, false)) {
+            GlobalWords again = (GlobalWords)logits;
+            uint32_t count = n;
+            asm volatile("" : "+s"(again), "+s"(count));
+            const uint32_t r0 = s.crowded ? p0 : s.base, r1 = s.crowded ? p1 : s.base + s.count;
+            ranked = sorted_sums(again, count, r0, r1, mx, m, lds);
         }
     }
     const PositionSums sums = position_sums<false>(logits, rank, p0, p1, m, mx, equal, ranked);

@@ -1,6 +1,6 @@
 """Losses of heads whose logits stay in registers and are sorted in runs of 32 (more than 8192 tokens, at most 32768):
 lengths at the edges of the register counts and of the runs, one and several shares per head, and clusters of equal
-logits around the 17 that a run takes care of, above which the share is compared or sorted instead."""
+logits around the 17 that a run takes care of, above which a finer bin is put in order by itself or the share is sorted."""
 import numpy as np
 import pytest
 import torch
@@ -80,7 +80,7 @@ def test_logits_that_are_not_finite(dev, T):
     assert all(np.allclose(a[0, 1], b[0, 1], rtol=1e-6, atol=0) for a, b in zip(got, losses(dev, K, Q, rank, T // 2)))
 
 
-# Groups of equal logits around what a run takes care of and what is compared.
+# Groups of equal logits that fill finer bins: up to 17 for a run, 32 for a piece, 64 for two, more for the exact cut.
 @pytest.mark.parametrize("T,Hkv,B", [(8193, 2, 1), (16384, 2, 1), (20481, 2, 1), (32768, 2, 1), (12000, 32, 4), (16384, 32, 8), (19452, 32, 8),
                                      (32768, 32, 4)])
 @pytest.mark.parametrize("each", [1, 9, 17, 18, 25, 32, 33, 40, 64, 65])
