@@ -109,7 +109,7 @@ def calls():
         module = importlib.util.module_from_spec(spec)
         spec.loader.exec_module(module)
         module.bind(*(C.cast(f, C.c_void_p).value for f in (handle.l2kv_decode_attn, handle.l2kv_decode_attn_out,
-                                                           handle.l2kv_compress)))
+                                                           handle.l2kv_compress, handle.l2kv_keep_count)))
         _calls = module
     return _calls
 
@@ -287,8 +287,9 @@ def l2kv_compact(K: torch.Tensor, V: Optional[torch.Tensor], kept_idx: torch.Ten
 def l2kv_compress(K: torch.Tensor, V: torch.Tensor, keep_ratio: float, norms: torch.Tensor,
                   kept_idx: torch.Tensor, Kc: torch.Tensor, Vc: torch.Tensor, workspace: torch.Tensor,
                   slab_heads: int = 0, stream=None) -> None:
-    """norms -> select -> compact in one call (optionally slab by slab of ``slab_heads`` heads).  The workspace is not
-    touched; the outputs are scratch memory before they are filled."""
+    """norms -> select -> compact in one call (optionally slab by slab of ``slab_heads`` heads): kept_idx ``[..., k]``, Kc, Vc
+    ``[..., k, D]`` with k = l2kv_keep_count(T, keep_ratio); one head alone may come with room for more.  The workspace is
+    not touched; the outputs are scratch memory before they are filled."""
     st = (_calls or calls()).compress(K, V, norms, kept_idx, Kc, Vc, workspace, keep_ratio, slab_heads, stream, _stream)
     if st is not None:
         return _check("l2kv_compress", st)
@@ -299,6 +300,9 @@ def l2kv_compress(K: torch.Tensor, V: torch.Tensor, keep_ratio: float, norms: to
     assert norms.dtype == torch.float32 and norms.numel() == n * T
     assert kept_idx.dtype == torch.int32 and kept_idx.numel() == n * k
     assert Kc.numel() == n * k * D and Vc.numel() == n * k * D
+    kept = l2kv_keep_count(T, keep_ratio)
+    if kept > 0 and (k < kept or (k > kept and n > 1)):        # 0: no ratio, which the entry point refuses
+        raise ValueError("l2kv_compress keeps %d of %d tokens, the outputs have %d rows a head" % (kept, T, k))
     _check("l2kv_compress", lib().l2kv_compress(
         _ptr(K), _ptr(V), _dtype_code(K), n, T, D, T * D, float(keep_ratio), int(slab_heads), _ptr(norms),
         _ptr(kept_idx), _ptr(Kc), _ptr(Vc), _ptr(workspace), workspace.numel() * workspace.element_size(),

@@ -15,6 +15,7 @@ namespace {
 decltype(&l2kv_decode_attn) decode_attn_entry = nullptr;
 decltype(&l2kv_decode_attn_out) decode_attn_out_entry = nullptr;
 decltype(&l2kv_compress) compress_entry = nullptr;
+decltype(&l2kv_keep_count) keep_count_entry = nullptr;
 
 // A plain contiguous device tensor, else nullptr.  (Subclasses of torch.Tensor take the way through Python.)
 const at::Tensor* device_tensor(PyObject* o) {
@@ -125,6 +126,9 @@ PyObject* compress_checked(PyObject* const* a, Py_ssize_t n_args) {
         norms.scalar_type() != at::kFloat || norms.numel() != n * T || idx.scalar_type() != at::kInt || idx.numel() != n * k ||
         Kc.numel() != n * k * D || Vc.numel() != n * k * D || D > INT32_MAX)
         Py_RETURN_NONE;
+    // The kernels write as many rows as the ratio says, head after head.  (0: no ratio, which the entry point refuses.)
+    const int64_t kept = keep_count_entry(T, ratio);
+    if (kept > 0 && (k < kept || (k > kept && n > 1))) Py_RETURN_NONE;
     const void *kp = K.data_ptr(), *vp = V.data_ptr();
     float* np = static_cast<float*>(norms.data_ptr());
     int32_t* ip = static_cast<int32_t*>(idx.data_ptr());
@@ -137,11 +141,12 @@ PyObject* compress_checked(PyObject* const* a, Py_ssize_t n_args) {
 PyObject* compress(PyObject*, PyObject* const* a, Py_ssize_t n) { return guarded([&] { return compress_checked(a, n); }); }
 
 PyObject* bind(PyObject*, PyObject* args) {
-    unsigned long long attn, attn_out, comp;
-    if (!PyArg_ParseTuple(args, "KKK", &attn, &attn_out, &comp)) return nullptr;
+    unsigned long long attn, attn_out, comp, count;
+    if (!PyArg_ParseTuple(args, "KKKK", &attn, &attn_out, &comp, &count)) return nullptr;
     decode_attn_entry = reinterpret_cast<decltype(decode_attn_entry)>(attn);
     decode_attn_out_entry = reinterpret_cast<decltype(decode_attn_out_entry)>(attn_out);
     compress_entry = reinterpret_cast<decltype(compress_entry)>(comp);
+    keep_count_entry = reinterpret_cast<decltype(keep_count_entry)>(count);
     Py_RETURN_NONE;
 }
 
