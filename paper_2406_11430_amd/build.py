@@ -75,10 +75,12 @@ def build_calls() -> str:
     import sysconfig
 
     from torch.utils import cpp_extension
+    import torch
     include = [*cpp_extension.include_paths(), sysconfig.get_paths()["include"]]
     libs = cpp_extension.library_paths()
     tmp = CALLS_PATH + ".tmp.%d" % os.getpid()
-    cmd = ["g++", "-std=c++17", "-O2", "-fPIC", "-shared", "-Wall", *["-isystem" + p for p in include],
+    cmd = ["g++", "-std=c++17", "-O2", "-fPIC", "-shared", "-Wall", "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch.compiled_with_cxx11_abi(),
+           '-DL2KV_TORCH="%s"' % torch.__version__, *["-isystem" + p for p in include],
            os.path.join(CSRC, "calls.cpp"), "-o", tmp, *["-L" + p for p in libs], *["-Wl,-rpath," + p for p in libs],
            "-ltorch_python", "-ltorch_cpu", "-lc10"]
     res = subprocess.run(cmd, capture_output=True, text=True)

@@ -159,4 +159,11 @@ PyModuleDef module = {PyModuleDef_HEAD_INIT, "l2kv_calls", nullptr, -1, methods,
 
 }  // namespace
 
-PyMODINIT_FUNC PyInit_l2kv_calls() { return PyModule_Create(&module); }
+PyMODINIT_FUNC PyInit_l2kv_calls() {
+    PyObject* const m = PyModule_Create(&module);
+    if (m != nullptr && PyModule_AddStringConstant(m, "torch_version", L2KV_TORCH) != 0) {
+        Py_DECREF(m);
+        return nullptr;
+    }
+    return m;
+}

@@ -30,6 +30,28 @@ def test_what_is_not_a_tensor_or_a_number_is_left_to_the_checks():
     assert native.decode_attn() is None and native.decode_attn_out() is None and native.compress() is None
 
 
+@pytest.fixture
+def unloaded():
+    before = binding._calls
+    binding._calls = None
+    yield
+    binding._calls = before
+
+
+def test_library_alone(unloaded, monkeypatch, tmp_path):
+    """Without the native calls, or with some for another torch or that do not load, the library is called as well."""
+    broken = tmp_path / "l2kv_calls.so"
+    broken.write_bytes(b"not a library")
+    for path, version, message in ((str(tmp_path / "none.so"), torch.__version__, "missing"), (str(broken), torch.__version__, "l2kv_calls"),
+                                   (binding.CALLS_PATH, "0.0", "built for torch")):
+        binding._calls = None
+        monkeypatch.setattr(binding, "CALLS_PATH", path)
+        monkeypatch.setattr(torch, "__version__", version)
+        with pytest.warns(RuntimeWarning, match=message), pytest.raises(ValueError, match="device tensors"):
+            l2kv.l2kv_decode_attn(*tensors())
+        assert binding.calls().decode_attn(*tensors(), 0.0, None, binding._stream) is None
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("change", ["none", "stride", "dtype", "shape", "dims", "output", "half", "nan_scale", "workspace", "group"])
 def test_decode_errors(change):
