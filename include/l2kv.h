@@ -375,7 +375,8 @@ l2kv_status l2kv_stream_evict(l2kv_dtype dt, int32_t n_planes, int32_t n_seq, in
  *             as a grid in the given order).  It only steers scheduling:
  *             outputs land at the sequence's own rows of O in any case.  An
  *             array that is not a permutation computes some sequences twice
- *             and others not at all (entries are forced into 0..n_seq-1).
+ *             and others not at all (entries are forced into 0..n_seq-1); the
+ *             workspace is left ready for the next call all the same.
  *             The order may be stale (lengths change from step to step).
  *             NULL: batches of 2..512 sequences whose longest has 2048 rows or
  *             more (bf16, D = 128) get a longest-first order worked out inside the call (one

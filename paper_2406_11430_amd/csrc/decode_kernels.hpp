@@ -256,8 +256,10 @@ constexpr int kDecodeMinWaves = kDecodeOnMatrixUnit<E, D, G> ? 2 : 1;
 
 // workspace layout: [counters + work queue: decode_counter_bytes] [partials]
 // partials: [B*Hq][n_splits][D + 4] floats: acc[0..D), m (log2 domain), l, two floats of padding
-// (rows start on 16-byte boundaries; no two workgroups write into the same row).
-//
+// (rows start on 16-byte boundaries; no two workgroups write into the same row).  Counters and
+// partials are those of the position in the launch order, `counter` and `partial` of one KV head's.
+template <int D> constexpr int partial_floats = D + 4;               // decode_partial_floats
+
 // decode_item: the share `split` (of n_splits) of one (sequence, KV head): stream
 // the rows, merge the workgroup's row groups, publish the partial and, if this
 // workgroup is the last of its KV head to finish, merge all partials into O.
@@ -279,7 +281,7 @@ __device__ __forceinline__ void decode_item(const char* __restrict__ Q, const ch
     constexpr int kGroups = Geo::kGroups;
     constexpr bool kBf16 = E::kBytes == 2;
     constexpr float kNegInf = -INFINITY;
-    constexpr int kRow = D + 4;                      // floats per partial row (decode_partial_floats)
+    constexpr int kRow = partial_floats<D>;
     // One LDS array used twice: first the row-group tiles s_acc[16][G][D], s_m[16][G], s_l[16][G]
     // of the workgroup's own merge, then (last workgroup of a KV head only, after two barriers)
     // the tables of the final merge.
@@ -714,7 +716,7 @@ __device__ __forceinline__ void decode_item(const char* __restrict__ Q, const ch
             // Device-scope stores: written through to the level every compute unit
             // of the device reads from, so the merging workgroup below sees them
             // without any bulk cache write-back.
-            float* out = partial + ((hq0 + g) * n_splits_grid + split) * kRow;
+            float* out = partial + (g * n_splits_grid + split) * kRow;
             const __amdgpu_buffer_rsrc_t row = __builtin_amdgcn_make_buffer_rsrc(out, 0, kRow * (int)sizeof(float), kBufferWord3);
             if constexpr (kVec == 4) publish4(row, d * (int)sizeof(float), f32x4{num[0], num[1], num[2], num[3]});
             else if constexpr (kVec == 2) publish2(row, d * (int)sizeof(float), f32x2{num[0], num[1]});
@@ -755,7 +757,7 @@ __device__ __forceinline__ void decode_item(const char* __restrict__ Q, const ch
         // 32-bit offsets into it (per lane: query head and element; uniform: workgroup) keep the
         // address arithmetic off the critical path.
         const __amdgpu_buffer_rsrc_t region = __builtin_amdgcn_make_buffer_rsrc(
-            partial + hq0 * n_splits_grid * kRow, 0, G * n_splits_grid * kRow * (int)sizeof(float), kBufferWord3);
+            partial, 0, G * n_splits_grid * kRow * (int)sizeof(float), kBufferWord3);
         const int last = __builtin_amdgcn_readfirstlane(n_splits - 1);
         const int oo = o0 < G * D ? o0 : 0;                                 // idle lanes re-read element 0
         const int head_off = (oo / D) * n_splits_grid * kRow * (int)sizeof(float);
@@ -817,7 +819,7 @@ __device__ __forceinline__ void decode_item(const char* __restrict__ Q, const ch
     constexpr int kBatch = D == 64 ? 16 : 32;                           // 16-byte loads per lane requested together
     constexpr int kTogether = 4;
     const __amdgpu_buffer_rsrc_t region = __builtin_amdgcn_make_buffer_rsrc(
-        partial + hq0 * n_splits_grid * kRow, 0, G * n_splits_grid * kRow * (int)sizeof(float), kBufferWord3);
+        partial, 0, G * n_splits_grid * kRow * (int)sizeof(float), kBufferWord3);
     const int n = __builtin_amdgcn_readfirstlane(n_splits);
     const int sub = lane / kPieces, piece = lane % kPieces;
     if (const int g = wave; g < G) {
@@ -893,7 +895,7 @@ __device__ __forceinline__ void decode_item(const char* __restrict__ Q, const ch
         const int qg = q / (D / 4);
         // the partials of this KV head's G query heads are one contiguous region
         const __amdgpu_buffer_rsrc_t region = __builtin_amdgcn_make_buffer_rsrc(
-            partial + hq0 * n_splits_grid * kRow, 0, G * n_splits_grid * kRow * (int)sizeof(float), kBufferWord3);
+            partial, 0, G * n_splits_grid * kRow * (int)sizeof(float), kBufferWord3);
         const int q_off = (qg * n_splits_grid * kRow + (q % (D / 4)) * 4) * (int)sizeof(float);
         f32x4 v[kBatch];
 #pragma unroll
@@ -1005,7 +1007,9 @@ void decode_kernel(const char* __restrict__ Q, const char* __restrict__ Kc,
                  "s"(counters), "s"(partial), "s"(O), "s"(out_bf16));
     const int split = blockIdx.x;
     const int hkv = blockIdx.y;
-    const int pair = blockIdx.z * Hkv + hkv;     // b * Hkv + hkv
+    // Counter and partials belong to the position in the launch order, not the sequence: with an order that names a sequence twice,
+    // the workgroups of both would meet at one counter, which could end other than zero, so that a later call merges too early.
+    const int pair = blockIdx.z * Hkv + hkv;
     // Ragged batches may come with a processing order (longest sequence first):
     // the launch index then names a position in that order, not the sequence.
     int b = blockIdx.z;
@@ -1040,7 +1044,8 @@ void decode_kernel(const char* __restrict__ Q, const char* __restrict__ Kc,
     }
     uint32_t unused = 0;
     decode_item<E, D, G, kWideMerge, true>(Q, Kc + slab, Vc + slab, kv_len, hq0, split, n_splits, n_splits_grid,
-                                           scale_log2e, counters + ((int64_t)b * Hkv + hkv), partial, O, out_bf16, nullptr, unused);
+                                           scale_log2e, counters + pair,
+                                           partial + (int64_t)pair * (G * partial_floats<D>) * n_splits_grid, O, out_bf16, nullptr, unused);
 }
 
 // Work-list launch for ragged batches with a known longest-first order.  A
@@ -1094,8 +1099,10 @@ void decode_worklist_kernel(const char* __restrict__ Q, const char* __restrict__
             continue;
         }
         const int64_t hq0 = (int64_t)b * Hq + (int64_t)hkv * G;
+        const int pair = pos * Hkv + hkv;                 // as in the grid launch
         decode_item<E, D, G, kWideMerge, false>(Q, Kc + slab, Vc + slab, kv_len, hq0, split, n_splits, n_splits_grid,
-                                                scale_log2e, counters + ((int64_t)b * Hkv + hkv), partial, O, out_bf16, &queue[0], drawn);
+                                                scale_log2e, counters + pair,
+                                                partial + (int64_t)pair * (G * partial_floats<D>) * n_splits_grid, O, out_bf16, &queue[0], drawn);
     }
     if (threadIdx.x == 0) {
         // every draw of this workgroup has returned (its value was used above), so the workgroup
