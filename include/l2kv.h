@@ -367,8 +367,9 @@ l2kv_status l2kv_stream_evict(l2kv_dtype dt, int32_t n_planes, int32_t n_seq, in
  * to its lens[s] occupied slots (0 slots give a zero output row).
  *   seq_order: a DEVICE int32 [n_seq] permutation of 0..n_seq-1 giving
  *             the order in which the sequences are launched; with the longest
- *             sequence first (l2kv_length_order) the library hands whole
- *             (sequence, KV head) pairs, longest first, to one workgroup per
+ *             sequence first (l2kv_length_order) the library hands
+ *             (sequence, KV head) pairs, longest first and in pieces where the
+ *             first is much longer than a workgroup's share, to one workgroup per
  *             compute unit, whichever is free next (a work list in the
  *             workspace), which is faster on batches of mixed lengths (bf16
  *             caches with heads of 128 elements; other row sizes are launched
@@ -383,8 +384,9 @@ l2kv_status l2kv_stream_evict(l2kv_dtype dt, int32_t n_planes, int32_t n_seq, in
  *             small extra kernel, about 7 us per call on an MI355X); all other
  *             batches are launched in batch order.  Either way the call is
  *             made of plain kernel launches and may be captured into a graph.
- *   max_len : an upper bound of all lens[s] (sizes the decomposition and the
- *             workspace; rows beyond it are still attended to)
+ *   max_len : an upper bound of all lens[s] (sizes the workspace and, but for
+ *             batches with an order, the decomposition; rows beyond it are still
+ *             attended to)
  * A layer that is left uncompressed (Sec. 4 skips the first layers by default)
  * needs no copy at all: pass its prompt tensors as Kc, Vc with slot_offsets =
  * the prompt offsets, total_slots = total_tokens and lens[s] = T_s.  Per-head

@@ -14,7 +14,6 @@ namespace l2kv {
 // of the longest sequence on, the (sequence, KV head) pairs are handed out one by one to a fixed
 // set of workgroups instead of being launched as a grid.
 constexpr int64_t kOrderedMinRows = 2048;
-constexpr int64_t kOrderedMaxRows = 16384;   // rows one workgroup takes before a sequence is split
 
 template <typename E, int D>
 l2kv_status decode_by_group(int G, const void* Q, const void* Kc, const void* Vc, int32_t B, int32_t Hq,
@@ -127,9 +126,6 @@ DecodePlan decode_plan(int32_t B, int32_t Hkv, int32_t group, int64_t kv_len, in
     if (want < 1) want = 1;
     DecodePlan plan;
     plan.n_splits = (int32_t)want;
-    plan.rows_per_wg = 1;
-    plan.worklist_wgs = 0;
-    plan.out_bf16 = 0;
     return plan;
 }
 
@@ -139,45 +135,25 @@ DecodePlan decode_plan_ragged(int32_t n_seq, int32_t Hkv, int64_t max_len, int64
     int64_t want = requested_splits;
     const int64_t cap = decode_max_splits(max_len);
     DecodePlan plan;
-    plan.worklist_wgs = 0;
-    plan.out_bf16 = 0;
     if (ordered && max_len >= kOrderedMinRows) {
-        // A longest-first order is known.  One item of the work list is a whole
-        // (sequence, KV head) -- only sequences beyond 16k rows, or all of them
-        // when the batch has fewer pairs than the uniform rule wants workgroups,
-        // are split -- and one workgroup per compute unit draws items from the
-        // list.  Measured on the 64-sequence streaming batch (512 pairs of
-        // 512..4200 rows): faster than any grid launch of the same batch, whose
+        // A longest-first order is known.  The items of the work list are the (sequence, KV head) pairs, in
+        // pieces where the kernel finds the sequences long (ragged_plan.hpp), and one workgroup per compute unit
+        // draws them from the list.  Measured on the 64-sequence streaming batch (512 pairs of
+        // 512..4200 rows, whole): faster than any grid launch of the same batch, whose
         // best (5 workgroups per pair in batch order) took 108 us per layer.
         const int64_t cus = device_compute_units();
         if (want <= 0) {
-            const int64_t by_len = (max_len + kOrderedMaxRows - 1) / kOrderedMaxRows;
-            const int64_t target = 3 * cus / 4;
-            const int64_t by_cu = (2 * target + pairs) / (2 * pairs);
-            want = by_len > by_cu ? by_len : by_cu;
-            // Sequences much longer than what a workgroup streams in all (`load`, as far as the slots tell) are cut, or the
-            // launch waits for them.  Best into as many pieces as just leave every one a workgroup of its own (each sequence's
-            // last piece is half full on average, and 5 % for chance); where that leaves pieces of more than 1.75 loads and
-            // nothing is cut yet, into three, or two if there are nearly as many pairs as workgroups, unless the sequences
-            // are much alike (192 pairs of 4000 rows 68.3, in three 78.1).  us per layer, whole sequences of 500 to 4400 rows / cut so:
-            // 96 pairs 36.0 / 28.4, 160 (250 to 2260 rows) 35.1 / 23.6, 192 63.5 / 50.8, 240 68.3 / 55.7, 288 57.9 / 53.2,
-            // 320 74.3 / 71.9; 360 pairs, whose longest has 1.3 loads, 47.7, in two 50.1.
-            const int64_t total = total_slots * Hkv, load = (total + cus - 1) / cus;
-            int64_t by_load = 1;
-            if (10 * max_len > 13 * load) {
-                const int64_t room = cus - pairs / 2;
-                by_load = room > 0 ? 20 * max_len * room / (21 * total) : 0;
-                if (by_load < 1 || 4 * max_len > 7 * load * by_load) {
-                    const bool uneven = 2 * max_len * n_seq >= 3 * total_slots;
-                    by_load = want > 1 || !uneven ? want : pairs <= cus - cus / 16 ? 3 : 2;
-                }
-                if (by_load > kDecodeNarrowSplits) by_load = kDecodeNarrowSplits;
+            const RaggedRule rule = ragged_rule(cus, n_seq, Hkv, total_slots, (int32_t)(cap < kRaggedMostPieces ? cap : kRaggedMostPieces));
+            const int32_t bound = (int32_t)(max_len < INT32_MAX ? max_len : INT32_MAX);
+            want = ragged_base(rule, bound);
+            if (want < kRaggedMostPieces) {              // with more, the load has no say
+                plan.rule = rule;
+                plan.pieces = ragged_pieces(rule, bound);
+                want = rule.most;
             }
-            if (want < by_load) want = by_load;
         }
-        if (want > cap) want = cap;
-        if (want < 1) want = 1;
-        const int64_t items = pairs * want;
+        if (plan.rule.most == 0) plan.pieces = (int32_t)(want < cap ? want : cap);
+        const int64_t items = pairs * (want < cap ? want : cap);
         plan.worklist_wgs = (int32_t)(items < cus ? items : cus);
     } else if (want <= 0) {
         // Lengths differ, so the launch relies on the hardware handing out more

@@ -1050,8 +1050,8 @@ void decode_kernel(const char* __restrict__ Q, const char* __restrict__ Kc,
 
 // Work-list launch for ragged batches with a known longest-first order.  A
 // fixed set of workgroups (about one per compute unit) draws items from a
-// device counter: item i is share i % n_splits_grid of KV head
-// (i / n_splits_grid) % Hkv of the sequence at position i / (n_splits_grid * Hkv)
+// device counter: item i is share i % pieces of KV head
+// (i / pieces) % Hkv of the sequence at position i / (pieces * Hkv)
 // of the order, so the longest sequences are handed out first and whichever
 // workgroup becomes free takes the next-longest remaining piece
 // (longest-processing-time-first list scheduling).  The next item is drawn
@@ -1064,45 +1064,72 @@ __global__ __launch_bounds__(kDecThreads)
 void decode_worklist_kernel(const char* __restrict__ Q, const char* __restrict__ Kc,
                             const char* __restrict__ Vc, int Hkv, int n_seq, int64_t plane_stride_bytes,
                             const int32_t* __restrict__ lens, const int64_t* __restrict__ slot_off,
-                            const int32_t* __restrict__ seq_order, int n_splits_grid, int rows_per_wg,
+                            const int32_t* __restrict__ seq_order, int n_splits_grid, int pieces, RaggedRule rule, int rows_per_wg,
                             float scale_log2e, uint32_t* __restrict__ counters, uint32_t* __restrict__ queue,
                             float* __restrict__ partial, float* __restrict__ O, int out_bf16) {
     using S = Slice<E, D>;
     __shared__ uint32_t s_item;
-    const uint32_t n_items = (uint32_t)n_seq * (uint32_t)Hkv * (uint32_t)n_splits_grid;
     const int Hq = Hkv * G;
+    auto sequence_at = [&](int pos) {
+        const int ob = seq_order[pos];
+        return ob < 0 ? 0 : (ob < n_seq ? ob : n_seq - 1);
+    };
+    struct Item { int split, hkv, pos; };
+    auto item_at = [&](uint32_t item) {
+        const uint32_t pair = item / (uint32_t)pieces, pos = pair / (uint32_t)Hkv;
+        return Item{(int)(item - pair * (uint32_t)pieces), (int)(pair - pos * (uint32_t)Hkv), (int)pos};
+    };
     // The first gridDim.x items need no counter: workgroup i starts on item i (a simultaneous
     // draw by every workgroup would queue up behind one memory location); the counter hands
     // out the items from gridDim.x on.
-    uint32_t drawn = blockIdx.x;                          // thread 0 only: the item drawn ahead
-    for (;;) {
-        if (threadIdx.x == 0) s_item = drawn;
-        __syncthreads();
-        const uint32_t item = s_item;
-        __syncthreads();                                  // everyone has read s_item before it is rewritten
-        if (item >= n_items) break;
-        const int split = (int)(item % (uint32_t)n_splits_grid);
-        const int hkv = (int)((item / (uint32_t)n_splits_grid) % (uint32_t)Hkv);
-        const int pos = (int)(item / ((uint32_t)n_splits_grid * (uint32_t)Hkv));
-        const int ob = seq_order[pos];
-        const int b = ob < 0 ? 0 : (ob < n_seq ? ob : n_seq - 1);
-        const int32_t len_b = lens[b];             // requested together with the two offsets below
-        const Range slots = clamped_range(slot_off, b, plane_stride_bytes / S::kRowBytes);
+    uint32_t item = blockIdx.x;
+    Item at = item_at(item);
+    int b = sequence_at(min(at.pos, n_seq - 1));
+    int32_t len_b = lens[b];                              // requested together with the two offsets below
+    Range slots = clamped_range(slot_off, b, plane_stride_bytes / S::kRowBytes);
+    // The length of the first sequence decides on the pieces.  Above, the item was looked up as if the bound that the host knows
+    // were that length; if the pieces come out as many, nothing has waited for them.
+    if (rule.most > 0) {
+        const int32_t first = lens[sequence_at(0)], longest = first > 1 ? first : 1;
+        const int n = ragged_pieces(rule, longest);
+        const int rows = (int)(((uint32_t)longest + (uint32_t)n - 1u) / (uint32_t)n);
+        rows_per_wg = rows < kDecodeRowTile ? kDecodeRowTile : rows;
+        if (n != pieces) {
+            pieces = n;
+            at = item_at(item);
+            b = sequence_at(min(at.pos, n_seq - 1));
+            len_b = lens[b];
+            slots = clamped_range(slot_off, b, plane_stride_bytes / S::kRowBytes);
+        }
+    }
+    const uint32_t n_items = (uint32_t)n_seq * (uint32_t)Hkv * (uint32_t)pieces;
+    uint32_t drawn = 0;                                   // thread 0 only: the item drawn ahead
+    while (item < n_items) {
+        const int split = at.split, hkv = at.hkv;
+        const int pair = at.pos * Hkv + hkv;              // as in the grid launch
         int64_t kv_len = len_b;
         kv_len = kv_len < 0 ? 0 : (kv_len > slots.count ? slots.count : kv_len);
         const int64_t slab = (int64_t)hkv * plane_stride_bytes + slots.first * (int64_t)S::kRowBytes;
         const int need = (int)(((uint32_t)kv_len + (uint32_t)rows_per_wg - 1u) / (uint32_t)rows_per_wg);   // kv_len is a clamped int32 here
-        const int n_splits = need < 1 ? 1 : (need < n_splits_grid ? need : n_splits_grid);
+        const int n_splits = need < 1 ? 1 : (need < pieces ? need : pieces);
         if (split >= n_splits) {                          // uniform: the whole workgroup skips the item
             if (threadIdx.x == 0)
                 drawn = gridDim.x + __hip_atomic_fetch_add(&queue[0], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            continue;
+        } else {
+            const int64_t hq0 = (int64_t)b * Hq + (int64_t)hkv * G;
+            decode_item<E, D, G, kWideMerge, false>(Q, Kc + slab, Vc + slab, kv_len, hq0, split, n_splits, n_splits_grid,
+                                                    scale_log2e, counters + pair,
+                                                    partial + (int64_t)pair * (G * partial_floats<D>) * n_splits_grid, O, out_bf16, &queue[0], drawn);
         }
-        const int64_t hq0 = (int64_t)b * Hq + (int64_t)hkv * G;
-        const int pair = pos * Hkv + hkv;                 // as in the grid launch
-        decode_item<E, D, G, kWideMerge, false>(Q, Kc + slab, Vc + slab, kv_len, hq0, split, n_splits, n_splits_grid,
-                                                scale_log2e, counters + pair,
-                                                partial + (int64_t)pair * (G * partial_floats<D>) * n_splits_grid, O, out_bf16, &queue[0], drawn);
+        if (threadIdx.x == 0) s_item = drawn;
+        __syncthreads();
+        item = s_item;
+        __syncthreads();                                  // everyone has read s_item before it is rewritten
+        if (item >= n_items) break;
+        at = item_at(item);
+        b = sequence_at(at.pos);
+        len_b = lens[b];
+        slots = clamped_range(slot_off, b, plane_stride_bytes / S::kRowBytes);
     }
     if (threadIdx.x == 0) {
         // every draw of this workgroup has returned (its value was used above), so the workgroup
@@ -1138,7 +1165,7 @@ l2kv_status launch_decode(const void* Q, const void* Kc, const void* Vc, int32_t
                                dim3(kDecThreads), 0, stream, static_cast<const char*>(Q),
                                static_cast<const char*>(Kc), static_cast<const char*>(Vc), (int)Hkv, (int)B,
                                kv_head_stride * (int64_t)E::kBytes, lens, slot_off, seq_order,
-                               (int)plan.n_splits, (int)plan.rows_per_wg, scale_log2e, counters, queue, partial, O, (int)plan.out_bf16);
+                               (int)plan.n_splits, (int)plan.pieces, plan.rule, (int)plan.rows_per_wg, scale_log2e, counters, queue, partial, O, (int)plan.out_bf16);
             return launch_status();
         }
     }

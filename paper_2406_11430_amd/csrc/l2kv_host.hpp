@@ -5,6 +5,7 @@
 #include <stdint.h>
 
 #include "../../include/l2kv.h"
+#include "ragged_plan.hpp"
 
 namespace l2kv {
 
@@ -65,10 +66,12 @@ l2kv_status compact_dispatch(const void* K, const void* V, l2kv_dtype dt, const 
 // Decomposition of decode attention over the kv_len rows of a KV head:
 // n_splits workgroups take turns on consecutive 64-row blocks.
 struct DecodePlan {
-    int32_t n_splits;        // workgroups launched per KV head
-    int32_t rows_per_wg;     // ragged batches: a sequence of n rows employs ceil(n / rows_per_wg) of them
-    int32_t worklist_wgs;    // > 0: ordered ragged batch, this many workgroups draw items from a device-side list
-    int32_t out_bf16;        // 1: O is written as bf16 (16-bit elements behind the float pointer), 0: fp32
+    int32_t n_splits = 1;      // workgroups launched per KV head; work list: pieces of a sequence there is room for
+    int32_t rows_per_wg = 1;   // ragged batches: a sequence of n rows employs ceil(n / rows_per_wg) of them
+    int32_t worklist_wgs = 0;  // > 0: ordered ragged batch, this many workgroups draw items from a device-side list
+    int32_t pieces = 1;        // work list: pieces of the longest sequence, as far as the host knows its length
+    RaggedRule rule = {};      // work list: decides them on the device (most > 0)
+    int32_t out_bf16 = 0;      // 1: O is written as bf16 (16-bit elements behind the float pointer), 0: fp32
 };
 constexpr int kDecodeMaxSplits = 256;
 constexpr int kDecodeNarrowSplits = 8;    // most workgroups of a head whose partials are merged in registers
