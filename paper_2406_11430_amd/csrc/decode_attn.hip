@@ -117,8 +117,18 @@ DecodePlan decode_plan(int32_t B, int32_t Hkv, int32_t group, int64_t kv_len, in
         // their arithmetic, 3072 rows.  us, split as above / in 8: 16 heads of 1554 rows of 64 elements, 4 query heads each,
         // 8.7 / 8.2, 4 of 1673 rows of 128 6.5 / 7.0, 3 of 1265 5.7 / 5.6; groups of 5 and more: 24 heads of 1146 rows of 128 11.6 /
         // 10.9, 16 of 3042 rows of 64 11.5 / 10.9, 2 of 3735 9.5 / 10.0; fp32 rows of 128, 4 of 907 11.9 / 10.8, 8 of 1419 10.6 / 10.7.
+        // Fewer than 12 of these heads leave the memory idle, so that a longer stream counts: the longest at most 24 KB longer (64 rows at a
+        // time, so often not at all), for one or two heads not beyond 384 KB.  bf16 rows of 128, 3 heads of 1615 with 5 query heads 8.8 / 9.4, 8 of
+        // 1607 with 6 10.5 / 11.2, 1 of 1804 with 5 6 % slower in 8; fp32 rows of 64, 3 of 1790 with 8 9.3 / 10.3; not longer: fp32 rows of 128, 2 of
+        // 929 with 6 10.0 / 9.1.
         const int64_t k_bytes = kv_len * row_bytes;
-        const bool short_head = group < 5 ? k_bytes <= int64_t{384} << 10 : k_bytes <= int64_t{512} << 10 && kv_len <= 3072;
+        const int64_t blocks = (kv_len + kDecodeRowTile - 1) / kDecodeRowTile;
+        auto longest = [&](int64_t splits) { return (blocks + splits - 1) / splits * kDecodeRowTile * row_bytes; };
+        bool short_head = group < 5 ? k_bytes <= int64_t{384} << 10 : k_bytes <= int64_t{512} << 10 && kv_len <= 3072;
+        if (short_head && group >= 5 && pairs < 12 && want > kDecodeNarrowSplits) {
+            const int64_t longer = longest(kDecodeNarrowSplits) - longest(want);
+            short_head = longer == 0 || (longer <= 24 << 10 && (pairs > 2 || k_bytes <= int64_t{384} << 10));
+        }
         if (want > kDecodeNarrowSplits && short_head) want = kDecodeNarrowSplits;
     }
     const int64_t cap = decode_max_splits(kv_len);

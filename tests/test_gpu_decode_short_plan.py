@@ -56,3 +56,21 @@ def test_merge_of_many_workgroups(dtype, D, G):
             O.fill_(float("nan"))
             binding.l2kv_decode_attn_splits(Q, K, V, O, ws, n_splits=splits)
             assert (O.cpu().double() - want).abs().max() <= (n / 16 + 64) * 2.0 ** -24 * 6, splits
+
+
+@pytest.mark.parametrize("dtype,D,G,heads,n,splits", [(torch.bfloat16, 128, 5, 3, 1615, 13), (torch.float32, 64, 8, 3, 1790, 14), (torch.bfloat16, 128, 5, 1, 1804, 14),
+                                                      (torch.bfloat16, 128, 5, 3, 1804, 8), (torch.float32, 128, 6, 2, 929, 8), (torch.bfloat16, 128, 5, 12, 1615, 8),
+                                                      (torch.bfloat16, 64, 5, 3, 2700, 8)])
+def test_few_heads_of_large_groups(dtype, D, G, heads, n, splits):
+    """Eight workgroups unless the longest of them reads much more than it would in more."""
+    dev = torch.device("cuda:0")
+    g = torch.Generator(device=dev).manual_seed(n)
+    Q = torch.randn((1, heads * G, D), generator=g, device=dev).to(dtype)
+    K, V = (torch.randn((1, heads, n, D), generator=g, device=dev).to(dtype) for _ in range(2))
+    ws = torch.empty(l2kv.l2kv_decode_workspace_bytes(1, heads * G, n, D), dtype=torch.uint8, device=dev)
+    binding.l2kv_decode_workspace_init(ws)
+    O, same, other = (torch.empty((1, heads * G, D), device=dev) for _ in range(3))
+    l2kv.l2kv_decode_attn(Q, K, V, O, ws)
+    binding.l2kv_decode_attn_splits(Q, K, V, same, ws, n_splits=splits)
+    binding.l2kv_decode_attn_splits(Q, K, V, other, ws, n_splits=splits + 1)
+    assert torch.equal(O, same) and not torch.equal(O, other)           # the same plan: the same order of the sums
