@@ -152,7 +152,7 @@ l2kv_status l2kv_compress(const void* K, const void* V, l2kv_dtype dt, int64_t n
         char* Vd = static_cast<char*>(Vc) + dense;
         const int32_t row_bytes = D * static_cast<int32_t>(es);
         l2kv_status st;
-        if (compress_short_applies(nh, T, row_bytes)) {
+        if (compress_short_applies(nh, T, D, dt)) {
             st = compress_short_dispatch(Ks, Vs, dt, nh, T, D, head_stride, k, ns, is, Kd, Vd, s);
         } else {
             st = norms_dispatch(Ks, dt, nh, T, D, head_stride, ns, read_again, s);

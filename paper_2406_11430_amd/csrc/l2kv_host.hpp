@@ -52,7 +52,7 @@ l2kv_status select_compact_dispatch(const float* norms, int64_t n_heads, int64_t
                                     l2kv_dtype dt, int32_t D, int64_t head_stride, int32_t* kept_idx, void* Kc, void* Vc,
                                     hipStream_t stream);
 // The norms as well, for the shortest.
-bool compress_short_applies(int64_t n_heads, int64_t T, int32_t row_bytes);
+bool compress_short_applies(int64_t n_heads, int64_t T, int32_t D, l2kv_dtype dt);
 l2kv_status compress_short_dispatch(const void* K, const void* V, l2kv_dtype dt, int64_t n_heads, int64_t T, int32_t D,
                                     int64_t head_stride, int64_t k, float* norms, int32_t* kept_idx, void* Kc, void* Vc,
                                     hipStream_t stream);

@@ -304,7 +304,8 @@ void select_kernel(const uint32_t* __restrict__ norm_bits, int64_t T, uint32_t k
 constexpr int kFuseMaxTokens = 8 * kSelThreads;
 constexpr int kFuseMaxHeads = 256;
 constexpr int kDies = 8;                               // compute dies, 32 compute units each
-constexpr int64_t kFuseMaxBytes = int64_t{20} << 20, kShortHeadBytes = int64_t{128} << 10;
+constexpr int64_t kFuseMaxBytes = int64_t{20} << 20, kShortHeadBytes = int64_t{128} << 10, kShortHeadBytesF32 = int64_t{192} << 10;
+constexpr int kShortManyHeads = 4;
 constexpr int kFuseRows = 4096;                       // most rows of a share: indices in LDS as 16-bit numbers
 static_assert(kFuseMaxTokens <= 65536, "token indices fit 16 bits");
 
@@ -444,12 +445,13 @@ void select_compact_kernel(const uint32_t* __restrict__ norm_bits, int64_t T, ui
     }
 }
 
-// The whole compression of heads of at most 1024 tokens and 128 KB in one launch: every share also computes all norms of its
+// The whole compression of heads of at most 1024 tokens and 128 KB (fp32, four heads and more: 192 KB) in one launch: every share also computes all norms of its
 // head (out of the L2 for all but the first reader), the first share writes them.  Bound by the chain of load, sums, search
 // and copy of one workgroup.  us, two launches / one: half of 4 heads of 512 tokens 8.2, 7.3, of 64 of 256 9.5, 7.3, of 128 of
 // 512 (16 MB) 13.9, 12.4; of 500 tokens of 17 heads 9.0, 7.7, with the shares of a head on all compute dies 9.6.  Not beyond 128 KB of a head,
 // which one workgroup goes through before anything else: 16 heads of 1024 tokens 9.5, 10.0, one of them 8.0, 9.1, rows of 512 bytes
-// 8.5, 13.8.
+// 8.5, 13.8.  Fp32 has half the elements in a byte to go through: 8 heads of 552 tokens of 64 8.5, 7.8, of 374 of 128 9.5, 8.5, 64 of 365
+// 13.0, 10.3, but 2 of 689 7.7, 7.6, one of 756 6.9, 7.4, and beyond 192 KB 4 of 418 8.0, 8.9.
 template <typename E, int D>
 __global__ __launch_bounds__(kSelThreads)
 void compress_short_kernel(const char* __restrict__ K, const char* __restrict__ V, uint32_t n_heads, uint32_t shares, int64_t T,
@@ -942,12 +944,14 @@ bool select_compact_applies(int64_t n_heads, int64_t T, int64_t k, int32_t row_b
             n_heads * k * row_bytes <= kFuseMaxBytes);
 }
 // Tokens of a share of the one-launch compression: at least 64, and at most one workgroup on a compute unit.  0: not that launch.
-static int64_t short_tokens(int64_t n_heads, int64_t T, int32_t row_bytes) {
-    if (T > kSelThreads || n_heads > kFuseMaxHeads || T * row_bytes > kShortHeadBytes) return 0;
+static int64_t short_tokens(int64_t n_heads, int64_t T, int32_t D, l2kv_dtype dt) {
+    const int32_t row_bytes = D * (dt == L2KV_F32 ? 4 : 2);
+    const int64_t most = dt == L2KV_F32 && n_heads >= kShortManyHeads ? kShortHeadBytesF32 : kShortHeadBytes;
+    if (T > kSelThreads || n_heads > kFuseMaxHeads || T * row_bytes > most) return 0;
     const int64_t shares = kFuseMaxHeads / n_heads, tokens = ((T + shares - 1) / shares + 15) / 16 * 16;
     return tokens <= 64 ? 64 : tokens <= most_ahead(row_bytes) ? tokens : 0;
 }
-bool compress_short_applies(int64_t n_heads, int64_t T, int32_t row_bytes) { return short_tokens(n_heads, T, row_bytes) != 0; }
+bool compress_short_applies(int64_t n_heads, int64_t T, int32_t D, l2kv_dtype dt) { return short_tokens(n_heads, T, D, dt) != 0; }
 
 l2kv_status select_compact_dispatch(const float* norms, int64_t n_heads, int64_t T, int64_t k, const void* K, const void* V,
                                     l2kv_dtype dt, int32_t D, int64_t head_stride, int32_t* kept_idx, void* Kc, void* Vc,
@@ -969,7 +973,7 @@ l2kv_status select_compact_dispatch(const float* norms, int64_t n_heads, int64_t
 l2kv_status compress_short_dispatch(const void* K, const void* V, l2kv_dtype dt, int64_t n_heads, int64_t T, int32_t D,
                                     int64_t head_stride, int64_t k, float* norms, int32_t* kept_idx, void* Kc, void* Vc,
                                     hipStream_t stream) {
-    const int64_t tokens = short_tokens(n_heads, T, D * (dt == L2KV_F32 ? 4 : 2)), shares = (T + tokens - 1) / tokens;
+    const int64_t tokens = short_tokens(n_heads, T, D, dt), shares = (T + tokens - 1) / tokens;
     const dim3 grid((unsigned)((n_heads + kDies - 1) / kDies * kDies * shares));
     auto kernel = dt == L2KV_F32 ? (D == 64 ? compress_short_kernel<F32, 64> : compress_short_kernel<F32, 128>)
                   : D == 256 ? compress_short_kernel<BF16, 256>

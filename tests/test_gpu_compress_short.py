@@ -52,6 +52,20 @@ def test_compress_equals_the_three_calls(dev, dtype, D, heads, T, ratio):
         assert torch.equal(got, want)
 
 
+# fp32 heads on either side of the sizes and numbers that take one launch
+@pytest.mark.parametrize("D,T", [(64, 512), (64, 513), (64, 768), (64, 769), (128, 256), (128, 257), (128, 384), (128, 385)])
+@pytest.mark.parametrize("heads", [1, 3, 4, 9, 64, 86, 256])
+def test_lines_of_fp32(dev, D, T, heads):
+    g = torch.Generator(device=dev).manual_seed(T + heads)
+    K, V = (torch.randn((heads, T, D), generator=g, device=dev) for _ in range(2))
+    for ratio in (0.07, 0.5, 1.0):
+        k = l2kv.l2kv_keep_count(T, ratio)
+        out = [torch.full((heads, T), -1.0, device=dev), torch.full((heads, k), -1, dtype=torch.int32, device=dev),
+               torch.zeros((heads, k, D), device=dev), torch.zeros((heads, k, D), device=dev)]
+        l2kv.l2kv_compress(K, V, ratio, *out, torch.zeros(256, dtype=torch.uint8, device=dev))
+        assert all(torch.equal(got, want) for got, want in zip(out, separate(K, V, k)))
+
+
 def key_sets(rng, T):
     log = (np.exp(rng.standard_normal(T)) * 128).astype(np.float32)
     outliers = log.copy()
