@@ -74,3 +74,25 @@ def test_few_heads_of_large_groups(dtype, D, G, heads, n, splits):
     binding.l2kv_decode_attn_splits(Q, K, V, same, ws, n_splits=splits)
     binding.l2kv_decode_attn_splits(Q, K, V, other, ws, n_splits=splits + 1)
     assert torch.equal(O, same) and not torch.equal(O, other)           # the same plan: the same order of the sums
+
+
+@pytest.mark.parametrize("dtype,D", [(torch.bfloat16, 64), (torch.bfloat16, 128), (torch.bfloat16, 256), (torch.float32, 128)])
+@pytest.mark.parametrize("G", [1, 4])
+def test_merge_of_what_is_not_finite(dtype, D, G):
+    """Values and scores that are not finite come out of the merge by waves as out of that of eight workgroups."""
+    dev, n = torch.device("cuda:0"), 4200
+    g = torch.Generator(device=dev).manual_seed(D + G)
+    Q = (2 * torch.randn((1, 2 * G, D), generator=g, device=dev)).to(dtype)
+    K, V = (torch.randn((1, 2, n, D), generator=g, device=dev).to(dtype) for _ in range(2))
+    V[0, 0, 0, 3], V[0, 0, 2000, 5], V[0, 1, 10, 7] = -torch.inf, torch.nan, torch.inf
+    K[0, 0, 2222] = torch.where(Q[0, 0] > 0, -torch.inf, torch.inf).to(dtype)          # -inf for the first query head, NaN for others
+    ws = torch.empty(l2kv.l2kv_decode_workspace_bytes(1, 2 * G, n, D), dtype=torch.uint8, device=dev)
+    binding.l2kv_decode_workspace_init(ws)
+    want, O = (torch.empty((1, 2 * G, D), device=dev) for _ in range(2))
+    binding.l2kv_decode_attn_splits(Q, K, V, want, ws, n_splits=8)
+    assert want[0, 0, 3] == -torch.inf and want[0, 0, 5].isnan() and (want[0, G:, 7] == torch.inf).all()
+    for splits in (9, 16, 17, 24, 32, 47, 64):
+        binding.l2kv_decode_attn_splits(Q, K, V, O, ws, n_splits=splits)
+        finite = want.isfinite()
+        assert torch.equal(O.isnan(), want.isnan()) and torch.equal(O[~finite & ~want.isnan()], want[~finite & ~want.isnan()])
+        assert (O[finite] - want[finite]).abs().max() <= 2 * (n / 16 + 64) * 2.0 ** -24 * 6       # two orders of the sums
