@@ -18,7 +18,8 @@
 // 4096 bins of equal width between the smallest and the largest key (the few hundred KB of
 // a head come from the L2), takes the bins whose first element falls into its range of
 // ranks, and ranks those few thousand elements in LDS: counted again in 8192 finer bins,
-// put into bin order, each then compared with the one or two others of its bin.
+// put into bin order, each then compared with the one or two others of its bin, or, for the scores of heads of more than
+// 8192 tokens whose keys stay in registers, sorted in runs of 32 (order_share).
 // What bounds it is the passes of every workgroup over all keys of its head (fetch, LDS counting,
 // gathering: two thirds of the time) and the LDS round trips of the comparisons, so the
 // shares are as few as the LDS list allows until they fill the chip.  (One workgroup per

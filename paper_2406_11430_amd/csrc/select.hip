@@ -445,13 +445,15 @@ void select_compact_kernel(const uint32_t* __restrict__ norm_bits, int64_t T, ui
     }
 }
 
-// The whole compression of heads of at most 1024 tokens and 128 KB (fp32, four heads and more: 192 KB) in one launch: every share also computes all norms of its
-// head (out of the L2 for all but the first reader), the first share writes them.  Bound by the chain of load, sums, search
+// The whole compression of heads of at most 1024 tokens and 128 KB (fp32, four heads and more: 192 KB) in one launch: every
+// share also computes all norms of its head (out of the L2 for all but the first reader), the first share writes them.  Bound by the chain of load, sums, search
 // and copy of one workgroup.  us, two launches / one: half of 4 heads of 512 tokens 8.2, 7.3, of 64 of 256 9.5, 7.3, of 128 of
 // 512 (16 MB) 13.9, 12.4; of 500 tokens of 17 heads 9.0, 7.7, with the shares of a head on all compute dies 9.6.  Not beyond 128 KB of a head,
 // which one workgroup goes through before anything else: 16 heads of 1024 tokens 9.5, 10.0, one of them 8.0, 9.1, rows of 512 bytes
 // 8.5, 13.8.  Fp32 has half the elements in a byte to go through: 8 heads of 552 tokens of 64 8.5, 7.8, of 374 of 128 9.5, 8.5, 64 of 365
-// 13.0, 10.3, but 2 of 689 7.7, 7.6, one of 756 6.9, 7.4, and beyond 192 KB 4 of 418 8.0, 8.9.
+// 13.0, 10.3, but 2 of 689 7.7, 7.6, one of 756 6.9, 7.4, and beyond 192 KB 4 of 418 8.0, 8.9.  However little is kept, although all rows of
+// V are loaded: against shares of kept rows in one or two launches, 0.05 kept, 64 heads of 256 8.8, 6.7, 128 of 512 12.7, 12.1; 448
+// calls of 1 to 256 heads of 128 to 1000 tokens, 0.05 to all kept, none slower.
 template <typename E, int D>
 __global__ __launch_bounds__(kSelThreads)
 void compress_short_kernel(const char* __restrict__ K, const char* __restrict__ V, uint32_t n_heads, uint32_t shares, int64_t T,
