@@ -18,13 +18,13 @@
 // 4096 bins of equal width between the smallest and the largest key (the few hundred KB of
 // a head come from the L2), takes the bins whose first element falls into its range of
 // ranks, and ranks those few thousand elements in LDS: counted again in 8192 finer bins,
-// put into bin order, each then compared with the one or two others of its bin, or, for the scores of heads of more than
-// 8192 tokens whose keys stay in registers, sorted in runs of 32 (order_share).
+// put into bin order, each then compared with the one or two others of its bin.  The scores of heads of more than 8192 tokens whose keys
+// stay in registers are counted once, in 20480 bins, and sorted in runs of 32 (order_share).
 // What bounds it is the passes of every workgroup over all keys of its head (fetch, LDS counting,
 // gathering: two thirds of the time) and the LDS round trips of the comparisons, so the
 // shares are as few as the LDS list allows until they fill the chip.  (One workgroup per
 // head and four counting passes of 8 bits over global memory, which this replaces, took
-// 196 us for 32 heads of 32k norms and 221 us for 128 heads of scores; now 22 and 33 us.
+// 196 us for 32 heads of 32k norms and 221 us for 128 heads of scores; now 22 and 30 us.
 // 131k norms of 8 heads: 671 -> 52 us.)
 // Where the bins do not separate the keys -- more than kMaxBin elements in a bin of the head, more than
 // kMaxFine in a finer one: tied or clustered rows, one outlier that stretches the bins of a long head, heads
@@ -48,6 +48,7 @@
 #include "l2kv_device.hpp"
 #include "l2kv_host.hpp"
 
+#include <cstddef>
 #include <type_traits>
 
 namespace l2kv {
@@ -199,10 +200,9 @@ constexpr int kFineBins = kFinePer * kSortLanes;
 
 struct __attribute__((aligned(16))) BinShared {
     uint32_t bin[kRankBins + 4];                     // of the head; one word more than bins
-    uint32_t fine[kFineBins + kWaveSize];            // of the share; a word per lane for keys of other shares
+    uint32_t fine[kFineBins];                        // of the share
     uint32_t wave[2][kSortWaves];
     uint32_t first, end, base, stop, crowded;
-    uint32_t ticket;
 };
 
 // A workgroup's part of a head: `share` of `shares`.
@@ -611,22 +611,23 @@ __device__ __forceinline__ bool rank_share(const Keys& keys, const Share<typenam
 }
 
 // ---- the elements of a share in order, straight from registers ----------------------------------
-// For logits, whose positions do not matter, while the keys of the head stay in registers.  A key of the share is
-// counted in its finer bin as it stands; the number the counter returns is its place in that bin, so that one
-// more store puts it there, and nothing is gathered or read again.  What is then left to do is order inside the finer bins, of
-// two elements on average: a lane sorts 32 neighbours in registers, which does every bin that does not reach over their end, and
+// For logits, whose positions do not matter, while the keys of the head stay in registers.  All keys of the head are counted once, in bins
+// so fine that a few share one (ScoreBins); the number the counter returns is a key's place in its bin, so that, once the bins have their
+// starts, one more store puts the keys of the share in order of the bins, and nothing is gathered or read again.  What is then left
+// to do is order inside the bins: a lane sorts 32 neighbours in registers, which does every bin that does not reach over their end, and
 // merges the upper half of them with the lower half of the next lane's, which does the others, as long as
-// no bin has more than 17 (fuller ones are put in order by themselves, sort_bins).  The lane then holds 32 elements of consecutive ranks and adds them up.
+// no bin has more than 17 (fuller ones are put in order by themselves, sort_full_bins).  The lane then holds 32 elements of consecutive
+// ranks and adds them up.
 // What bounds it: a key costs 0.2 us per vector instruction and CU (32 keys a lane, four waves a SIMD), and each of its LDS
-// accesses 10 to 15 cycles a wave with its bank conflicts; so a key's way takes a dozen instructions, one atomic and two
-// reads, all lanes doing the same.  128 heads of 32k logits in two shares each, us: fetch and range 6.6, coarse bins 3.9, finer
-// bins 4.0, starts 1.4, scatter 3.9, sort 2.7, merge and sums 4.5, position sums 5.1, records 0.9: 33 in place of 45 with
-// the keys fetched three times, gathered into a list, counted and compared there (6.3 + 3.4 + 3.5 + 10.3 + 3.2).
+// accesses 10 to 20 cycles a wave with its bank conflicts; so a key's way takes a dozen and a half instructions, one atomic and two
+// accesses, all lanes doing the same.  128 heads of 32k logits in two shares each, us: fetch and range 6.9, position sums 1.2, bins 4.7,
+// starts 2.1, scatter 3.4, sort 1.4, merge and sums 3.5, records 2.6: 26 in place of 30.5 with the keys counted in 4096 bins of equal width
+// (5.7) and again in 8192 of the share (7.4 with their starts).  Per launch with the logits 76.7 -> 74.4, 32 heads of 9000 24.3 -> 22.4.
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 constexpr int kTogetherKeys = 4;                     // keys whose LDS round trips overlap (8: the same time)
 constexpr int kRun = 32;                             // elements a lane sorts
-constexpr uint32_t kMaxRun = kRun / 2 + 1;           // of one finer bin
+constexpr uint32_t kMaxRun = kRun / 2 + 1;           // of one bin
 constexpr uint32_t kListFront = kRun / 2;            // words of the list in front of the first element
 
 template <int kN, int kSpan, int kStep> __device__ __forceinline__ void merge_step(float (&x)[kN]) {
@@ -654,136 +655,285 @@ template <int kN, int kSpan> __device__ __forceinline__ void merge_runs(float (&
 // that lanes reading the same piece of theirs hit different banks.
 __device__ __forceinline__ uint32_t run_word(uint32_t at) { return at ^ ((at >> 5 & 7u) << 2); }
 
-// The n <= kRun words of the list from `at` on in order.
-__device__ __forceinline__ void sort_words(float* list, uint32_t at, uint32_t n) {
-    float x[kRun];
-#pragma unroll
-    for (uint32_t i = 0; i < kRun; ++i) {
-        x[i] = list[run_word(i < n ? at + i : at)];
-        x[i] = i < n ? x[i] : INFINITY;
-        if (i % 4 == 3) asm volatile("" : "+v"(at));                  // addresses afresh: kept, they would take as many registers again
-    }
-    merge_runs<kRun, 1>(x);
-#pragma unroll
-    for (uint32_t i = 0; i < kRun; ++i) {
-        if (i < n) list[run_word(at + i)] = x[i];
-        if (i % 4 == 3) asm volatile("" : "+v"(at));
-    }
+__device__ __forceinline__ float read_lane(float v, int lane) {
+    return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), lane));
 }
-// Finer bins with more elements than the runs take care of, in pieces of at most kRun that a lane sorts each: first word in the
-// list, length << 16, and for a bin of two, kPaired in both and kSecond in the one that follows.  Two pieces in order, mirrored and
-// compared element by element, leave the smaller ones in front, so that all are in order when each is sorted again.
-constexpr uint32_t kPaired = 1u << 31, kSecond = 1u << 30;
-__device__ __forceinline__ void sort_pieces(const uint32_t* pieces, uint32_t count, uint32_t which, float* list) {
-    for (uint32_t i = threadIdx.x; i < count; i += kSortLanes)
-        if ((pieces[i] & which) == which) sort_words(list, pieces[i] & 0xffffu, pieces[i] >> 16 & (2 * kRun - 1));
-    __syncthreads();
-}
-__device__ __forceinline__ void sort_bins(const uint32_t* pieces, uint32_t count, bool pairs, float* list) {
-    sort_pieces(pieces, count, 0u, list);
-    if (!pairs) return;
-    for (uint32_t i = threadIdx.x; i < count; i += kSortLanes) {
-        if ((pieces[i] & kSecond) == 0) continue;
-        const uint32_t second = pieces[i] & 0xffffu, n = pieces[i] >> 16 & (2 * kRun - 1);
-        for (uint32_t j = 0; j < n; ++j) {                            // past n there is nothing opposite
-            float* const low = list + run_word(second - 1 - j);
-            float* const high = list + run_word(second + j);
-            const float p = *low, q = *high;
-            *low = fminf(p, q);
-            *high = fmaxf(p, q);
+
+// Bins with more elements than the runs take care of: every element finds its place by comparing itself with all others of the bin, a
+// wave to a bin, four from 129 elements on (one bin of 200 among 9000 logits 33 us by one wave).  Bins of equal elements, as copies of a row
+// make them, are left as they are.
+constexpr uint32_t kMaxOfBin = 512;                  // fuller ones: exact cut
+struct FullBin {                                     // in one word
+    uint32_t word;
+    static __device__ __forceinline__ FullBin of(uint32_t start, uint32_t count) { return FullBin{start | count << 16}; }
+    __device__ __forceinline__ uint32_t start() const { return word & 0xffffu; }
+    __device__ __forceinline__ uint32_t count() const { return word >> 16; }
+};
+// A lane's elements lane + 64 * (part + kWaves * k) of a bin, and their places in it; without elements: nothing.
+template <uint32_t kWaves, uint32_t kPer> struct PlacedElements {
+    float x[kPer];
+    uint32_t first, place[kPer];
+    FullBin bin;
+    __device__ __forceinline__ PlacedElements(FullBin b, uint32_t part, const float* list) : first(part * kWaveSize + threadIdx.x % kWaveSize), bin(b) {
+        const uint32_t n = bin.count(), lane = threadIdx.x % kWaveSize;
+#pragma unroll
+        for (uint32_t k = 0; k < kPer; ++k) {
+            const uint32_t i = first + k * kWaves * kWaveSize;
+            x[k] = list[run_word(bin.start() + (i < n ? i : 0u))];
+            place[k] = 0;
+        }
+        for (uint32_t base = 0; base < n; base += kWaveSize) {
+            const float others = list[run_word(bin.start() + (base + lane < n ? base + lane : 0u))];
+            const uint32_t end = n - base < kWaveSize ? n - base : kWaveSize;
+            constexpr uint32_t kTogether = 8;
+            for (uint32_t j0 = 0; j0 < end; j0 += kTogether) {
+#pragma unroll
+                for (uint32_t u = 0; u < kTogether; ++u) {
+                    const uint32_t j = j0 + u;                        // below 64
+                    const float other = read_lane(others, (int)j);    // equal ones in the order in which they stand; no branches
+#pragma unroll
+                    for (uint32_t k = 0; k < kPer; ++k)
+                        place[k] += (((other < x[k]) | ((other == x[k]) & (base + j < first + k * kWaves * kWaveSize))) & (j < end)) ? 1u : 0u;
+                }
+            }
+        }
+    }
+    __device__ __forceinline__ void store(float* list) const {
+#pragma unroll
+        for (uint32_t k = 0; k < kPer; ++k)
+            if (first + k * kWaves * kWaveSize < bin.count()) list[run_word(bin.start() + place[k])] = x[k];
+    }
+};
+struct FullBins { uint32_t listed, few, many; };     // bins in the list; of them, bins whose elements differ, up to 128 and more of them
+// `list_end` words in all: the listed bins, behind them those of few differing elements, from the end downwards those of many.
+__device__ __forceinline__ void sort_full_bins(uint32_t* bins, uint32_t list_end, FullBins& found, float* list) {
+    constexpr uint32_t kAtOnce = kWaveSize / kRowLanes;               // bins that a wave looks over together
+    constexpr uint32_t kWavesOfMany = 4;
+    const uint32_t lane = threadIdx.x % kWaveSize, c = lane % kRowLanes, wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWaveSize);
+    const uint32_t count = __builtin_amdgcn_readfirstlane(found.listed);
+    for (uint32_t i0 = wave * kAtOnce; i0 < count; i0 += kSortWaves * kAtOnce) {
+        const uint32_t i = i0 + lane / kRowLanes;
+        const FullBin bin{bins[i < count ? i : count - 1]};
+        const float first = list[run_word(bin.start())];
+        bool differ = false;
+        for (uint32_t j = c; j < bin.count(); j += kRowLanes) differ |= list[run_word(bin.start() + j)] != first;
+        const uint64_t group = 0xffffull << (lane / kRowLanes * kRowLanes);
+        if ((__ballot(differ) & group) != 0 && c == 0 && i < count) {
+            if (bin.count() <= 2 * kWaveSize) bins[count + atomicAdd(&found.few, 1u)] = bin.word;
+            else bins[list_end - 1 - atomicAdd(&found.many, 1u)] = bin.word;
         }
     }
     __syncthreads();
-    sort_pieces(pieces, count, kPaired, list);
-}
-
-// True: run[] holds the elements of ranks kRun * threadIdx.x .. inside the share, as far as they are below s.count.
-// False, where some finer bin holds more than kMaxFine: nothing.  Called by all lanes; the list is free again after the caller's barrier.
-template <int E>
-__device__ __forceinline__ bool order_share(const HeadKeys<E, ValueBins>& keys, const Share<ValueBins>& s, BinShared& sh,
-                                            float* list, float (&run)[kRun]) {
-    const uint32_t lane = threadIdx.x % kWaveSize;
-    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWaveSize);
-    const uint32_t bins = s.end - s.first;
-    if (threadIdx.x == 0) sh.wave[1][0] = sh.wave[1][1] = 0;          // pieces of finer bins with too many for a run, any of two
-    for (int i = 0; i < kFinePer / 4; ++i) reinterpret_cast<uint4*>(sh.fine)[i * kSortLanes + threadIdx.x] = make_uint4(0, 0, 0, 0);
-    // A bin of the head as a line: the finer bin its first element is expected in, and how many it spans.  Its end does not
-    // reach past the start of the next one, whatever the rounding, so the finer bins are in the order of the keys.
-    f32x2* const line = reinterpret_cast<f32x2*>(list);               // the list is not in use yet
-    const float per_rank = ((float)kFineBins - 0.5f) / (float)(s.count > 0 ? s.count : 1);
-#pragma unroll
-    for (int i = 0; i < kRankBins / kSortLanes; ++i) {
-        const uint32_t b = threadIdx.x + i * kSortLanes;
-        const float here = (float)(int32_t)(sh.bin[b] - s.base) * per_rank, next = (float)(int32_t)(sh.bin[b + 1] - s.base) * per_rank;
-        line[b] = f32x2{here, (next - here) * (1.f - 0x1p-22f)};
+    auto record = [&](uint32_t at) { return FullBin{(uint32_t)__builtin_amdgcn_readfirstlane((int)bins[at])}; };
+    const uint32_t few = __builtin_amdgcn_readfirstlane(found.few), many = __builtin_amdgcn_readfirstlane(found.many);
+    for (uint32_t i = wave; i < few; i += kSortWaves) {
+        const FullBin bin = record(count + i);
+        if (bin.count() <= kWaveSize) PlacedElements<1, 1>(bin, 0, list).store(list);
+        else PlacedElements<1, 2>(bin, 0, list).store(list);
+    }
+    for (uint32_t i0 = 0; i0 < many; i0 += kSortWaves / kWavesOfMany) {
+        const uint32_t i = i0 + wave / kWavesOfMany;
+        const FullBin bin = i < many ? record(list_end - 1 - i) : FullBin{0};
+        const PlacedElements<kWavesOfMany, kMaxOfBin / kWaveSize / kWavesOfMany> mine(bin, wave % kWavesOfMany, list);
+        __syncthreads();                                              // all waves of a bin have read it
+        mine.store(list);
     }
     __syncthreads();
-    // Keys of other shares are counted in a word of the lane instead of being branched around: nothing stands between one
-    // key's LDS round trips and the next one's.
-    static_assert((kMaxFine + 1) * kFineBins * 8 < 0xffffffffu, "number in the bin and offset of its counter in one word");
+}
+
+// Bins of the logits of a head, monotone in the logit: equal widths in the bit pattern of the distance from the mean plus an
+// offset, below the mean and above it alike; 2048 bins to an octave for the first four octaves, 1024 for the fifth and 256 from there on.
+// So they are of one width near the mean, where the logits lie densely, and grow with the distance where they thin out: 32k logits
+// of normal or log-normally scaled rows put 3 elements into a bin on average over the elements and 15 into the fullest, where as many
+// bins of equal width hold 200 of the latter.  (Sums and shifts of rounded floats are monotone whatever their rounding.)
+struct ScoreRange { float lo, hi, mean, deviation; };
+struct ScoreBins {
+    static constexpr uint32_t kHalf = 4u * 10240u;                    // bytes of the counters on one side of the mean
+    static constexpr uint32_t kFourth = 4u * 8192u, kFifth = 4u * (8u * 9216u - 10240u);     // where the lines of 1024 and 256 to an octave meet zero
+    float mean, offset;
+    uint32_t origin;
+    // The offset: a 56th of the largest distance, which is 5 octaves and a bit; where a few logits lie so far out that this is wide for
+    // the others, 0.3 standard deviations, but no less than the nine octaves that there is room for reach.
+    __device__ __forceinline__ explicit ScoreBins(const ScoreRange& r) : mean(r.mean) {
+        const float far = fmaxf(r.hi - r.mean, r.mean - r.lo);
+        offset = fminf(far * (1.f / 56.f), fmaxf(far * (1.f / 511.f), 0.3f * r.deviation));
+        origin = __builtin_bit_cast(uint32_t, offset);
+    }
+    // byte offset of the counter of a logit
+    __device__ __forceinline__ uint32_t operator()(float logit) const {
+        const float x = logit - mean;
+        const uint32_t d = (__builtin_bit_cast(uint32_t, fabsf(x) + offset) - origin) >> 10;
+        const uint32_t away = min(min(min(d, (d + kFourth) >> 1), (d + kFifth) >> 3), kHalf - 1);    // the last for what is not a number
+        const uint32_t side = (uint32_t)(__builtin_bit_cast(int32_t, x) >> 31);
+        return ((away ^ side) + kHalf) & ~3u;                         // below the mean: kHalf - 1 - away
+    }
+};
+constexpr int kScoreBinsPer = 20;                    // per lane
+constexpr uint32_t kScoreBins = kScoreBinsPer * kSortLanes;
+static_assert(ScoreBins::kHalf * 2 == kScoreBins * 4, "a counter per bin");
+constexpr uint32_t kRunWords = (kListFront + 19452 + kMaxOfBin + 31) / 32 * 32;      // a share, and what its last bin brings with it
+struct RunBins {
+    uint32_t bin[kScoreBins + 4];                    // one word more than bins
+    uint32_t aside[kWaveSize];                       // a word per lane for positions past the end
+};
+struct RunShared {
+    float lo[kSortWaves], hi[kSortWaves], sum[kSortWaves], squares[kSortWaves];
+    uint32_t wave[kSortWaves];
+    uint32_t base, stop, crowded, full;
+    FullBins bins;
+};
+
+template <typename Op> __device__ __forceinline__ float row16_all(float v, Op op) {
+    v = op(v, dpp_read<kDppXor1>(v));
+    v = op(v, dpp_read<kDppXor2>(v));
+    v = op(v, dpp_read<kDppHalfMirror>(v));
+    return op(v, dpp_read<kDppMirror>(v));
+}
+template <typename Op> __device__ __forceinline__ float wave_all(float v, Op op) {
+    v = row16_all(v, op);
+    return op(op(read_lane(v, 0), read_lane(v, 16)), op(read_lane(v, 32), read_lane(v, 48)));
+}
+
+// Least and largest logit of the head, their mean and standard deviation, the same in all lanes and shares.  Called by all lanes; one barrier.
+template <int E>
+__device__ __forceinline__ ScoreRange score_range(const HeadKeys<E, ValueBins>& keys, RunShared& sh) {
+    auto least = [](float a, float b) { return fminf(a, b); };
+    auto most = [](float a, float b) { return fmaxf(a, b); };
+    auto plus = [](float a, float b) { return a + b; };
+    float lo = INFINITY, hi = -INFINITY, sum = 0.f, squares = 0.f;
+    keys.each([&](float key, uint32_t) {
+        lo = least(lo, key);
+        hi = most(hi, key);
+        sum += key;
+        squares = fmaf(key, key, squares);
+    });
+    lo = wave_all(lo, least);
+    hi = wave_all(hi, most);
+    sum = wave_all(sum, plus);
+    squares = wave_all(squares, plus);
+    const uint32_t wave = threadIdx.x / kWaveSize;
+    if (threadIdx.x % kWaveSize == 0) {
+        sh.lo[wave] = lo;
+        sh.hi[wave] = hi;
+        sh.sum[wave] = sum;
+        sh.squares[wave] = squares;
+    }
+    if (threadIdx.x == 0) {
+        sh.crowded = sh.full = sh.base = sh.stop = 0;
+        sh.bins = FullBins{0, 0, 0};
+    }
+    __syncthreads();
+    static_assert(kSortWaves == kRowLanes, "a wave's value per lane of a DPP row");
+    const uint32_t i = threadIdx.x % kRowLanes;
+    auto uniform = [](float v) { return read_lane(v, 0); };
+    const float mean = uniform(row16_all(sh.sum[i], plus)) / (float)keys.n, square = uniform(row16_all(sh.squares[i], plus)) / (float)keys.n;
+    return ScoreRange{uniform(row16_all(sh.lo[i], least)), uniform(row16_all(sh.hi[i], most)), mean,
+                      sqrtf(fmaxf(square - mean * mean, 0.f))};
+}
+
+// True: run[] holds the elements of ranks base + kRun * threadIdx.x .., as far as they are among the `count` of the share: the bins
+// that start inside its range of ranks.  False, where some bin of the head holds more than kMaxPieces runs: nothing (all shares alike).
+// The bins are cleared.  Called by all lanes; the list is free again after the caller's barrier.
+template <int E>
+__device__ __forceinline__ bool order_share(const HeadKeys<E, ValueBins>& keys, const ScoreRange& range, uint32_t share, const Cut& cut,
+                                            RunBins& rb, RunShared& sh, float* list, float (&run)[kRun], uint32_t& base, uint32_t& count) {
+    const uint32_t lane = threadIdx.x % kWaveSize;
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWaveSize);
+    const ScoreBins bin_of(range);
+    // One pass for all: the number that the counter returns is the key's place in its bin.
     uint32_t place[E];
     uint32_t left = keys.n - threadIdx.x;                             // negative past the end
     asm volatile("" : "+v"(left));
-    const uint32_t aside = (kFineBins + lane) * 4;
+    constexpr uint32_t kAsideAt = (kScoreBins + 4) * 4, kPlaceShift = 17;
+    static_assert(kAsideAt + 4 * kWaveSize <= 1 << kPlaceShift && E * kSortLanes <= 1 << (32 - kPlaceShift), "counter and place in one word");
 #pragma unroll
     for (int e0 = 0; e0 < E; e0 += kTogetherKeys) {
 #pragma unroll
         for (int u = 0; u < kTogetherKeys; ++u) {
-            const float at = s.bins.position(keys.reg[e0 + u]);
-            const uint32_t b = (uint32_t)at;
-            const f32x2 in_bin = line[b];
-            const uint32_t f = (uint32_t)fmaf(__builtin_amdgcn_fractf(at), in_bin.y, in_bin.x) * 4;
-            const bool mine = ((int32_t)left > (e0 + u) * kSortLanes) & (b - s.first < bins);
-            place[e0 + u] = mine ? f : aside;
+            const uint32_t b = bin_of(keys.reg[e0 + u]);
+            place[e0 + u] = (int32_t)left > (e0 + u) * kSortLanes ? b : kAsideAt + 4 * lane;
         }
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int u = 0; u < kTogetherKeys; ++u) {
-            uint32_t* const counter = reinterpret_cast<uint32_t*>(reinterpret_cast<char*>(sh.fine) + place[e0 + u]);
-            place[e0 + u] |= atomicAdd(counter, 1u) * (kFineBins * 8);
+            uint32_t* const counter = reinterpret_cast<uint32_t*>(reinterpret_cast<char*>(rb.bin) + place[e0 + u]);
+            place[e0 + u] |= atomicAdd(counter, 1u) << kPlaceShift;
         }
 #pragma unroll
         for (int u = 0; u < kTogetherKeys; ++u) asm volatile("" : "+v"(place[e0 + u]));       // one register each, not two
     }
     __syncthreads();
-    Counts<kFinePer> c;
-    c.load(sh.fine);
-    counts_to_starts(c, sh.fine, sh.wave[0]);
-    static_assert(kListFront + kListWords < 1 << 16 && kMaxFine <= 2 * kRun && kListWords / kMaxRun * 2 <= kRankBins,
-                  "pieces in a word each, in place of the head's bins");
-    uint32_t* const pieces = sh.bin;
-    uint32_t first = c.before + kListFront;
+    {
+        Counts<kScoreBinsPer> c;
+        c.load(rb.bin);
+        counts_to_starts(c, rb.bin, sh.wave);
+        if (threadIdx.x < kWaveSize) rb.aside[threadIdx.x] = 1u << 31;         // in no share
+        if (threadIdx.x == 0) rb.bin[kScoreBins] = keys.n;
+        // The share starts behind the bin that holds the rank before its first, and stops behind the bin that holds its last.
+        const uint32_t r0 = cut.start(share), r1 = cut.start(share + 1);
+        uint32_t before = c.before, sum = 0, fullest = 0;
 #pragma unroll
-    for (int i = 0; i < kFinePer; ++i) {
-        const uint32_t n = c.v[i];
-        if (n > kMaxFine) {
-            sh.crowded = 1;                                           // 0 so far: the head is not crowded
-        } else if (n > kRun) {
-            const uint32_t at = atomicAdd(&sh.wave[1][0], 2u);
-            pieces[at] = first | kRun << 16 | kPaired;
-            pieces[at + 1] = (first + kRun) | (n - kRun) << 16 | kPaired | kSecond;
-            sh.wave[1][1] = 1;
-        } else if (n > kMaxRun) {
-            pieces[atomicAdd(&sh.wave[1][0], 1u)] = first | n << 16;
+        for (int i = 0; i < kScoreBinsPer; ++i) {
+            sum += c.v[i];
+            fullest = c.v[i] > fullest ? c.v[i] : fullest;
         }
-        first += n;
+        if (r0 - 1 - before < sum || r1 - 1 - before < sum) {         // r0 == 0: no bin
+#pragma unroll
+            for (int i = 0; i < kScoreBinsPer; ++i) {
+                const uint32_t after = before + c.v[i];
+                if (r0 - 1 - before < c.v[i]) sh.base = after;
+                if (r1 - 1 - before < c.v[i]) sh.stop = after;
+                before = after;
+            }
+        }
+        if (fullest > kMaxRun) {
+            sh.full = 1;
+            if (fullest > kMaxOfBin) sh.crowded = 1;
+        }
     }
     __syncthreads();
     if (sh.crowded != 0) return false;
-    const uint32_t full = __builtin_amdgcn_readfirstlane(sh.wave[1][0]), pairs = __builtin_amdgcn_readfirstlane(sh.wave[1][1]);
-    constexpr uint32_t kAside = kListFront + kListWords;              // behind the longest share
+    base = __builtin_amdgcn_readfirstlane(sh.base);
+    count = __builtin_amdgcn_readfirstlane(sh.stop) - base;
+    const uint32_t full = __builtin_amdgcn_readfirstlane(sh.full);
+    constexpr uint32_t kAside = kRunWords;                            // behind the longest share
 #pragma unroll
     for (int e = 0; e < E; ++e) {
-        const uint32_t f = place[e] % (kFineBins * 8);
-        const uint32_t start = *reinterpret_cast<const uint32_t*>(reinterpret_cast<const char*>(sh.fine) + f);
-        const uint32_t at = run_word(start + place[e] / (kFineBins * 8) + kListFront);
-        list[f < kFineBins * 4 ? at : kAside + lane] = keys.reg[e];
+        constexpr uint32_t kCounter = (1u << kPlaceShift) - 1;
+        const uint32_t start = *reinterpret_cast<const uint32_t*>(reinterpret_cast<const char*>(rb.bin) + (place[e] & kCounter));
+        const uint32_t at = start + (place[e] >> kPlaceShift) - base;
+        list[at < count ? run_word(at + kListFront) : kAside + lane] = keys.reg[e];
     }
     if (threadIdx.x < kListFront) list[run_word(threadIdx.x)] = -INFINITY;
     __syncthreads();
-    if (__builtin_expect(full != 0, false)) sort_bins(pieces, full, pairs != 0, list);
+    if (__builtin_expect(full != 0, false)) {
+        // the starts are not needed any longer: the full bins' records take their place
+        static_assert(kRunWords < 1 << 16 && kRunWords / kMaxRun * 2 <= kScoreBins, "a word each, or two, in place of the bins");
+        Counts<kScoreBinsPer> starts;
+        starts.load(rb.bin);
+        const uint32_t behind = rb.bin[(threadIdx.x + 1) * kScoreBinsPer];
+        auto elements = [&](int i) {
+            const uint32_t n = (i + 1 < kScoreBinsPer ? starts.v[i + 1 < kScoreBinsPer ? i + 1 : 0] : behind) - starts.v[i];
+            return n > kMaxRun && starts.v[i] - base < count ? n : 0u;
+        };
+        uint32_t mine = 0;
+#pragma unroll
+        for (int i = 0; i < kScoreBinsPer; ++i) mine += elements(i) > 0 ? 1u : 0u;
+        const uint32_t incl = wave_inclusive_sum(mine);
+        uint32_t slot = 0;
+        if (lane == kWaveSize - 1) slot = atomicAdd(&sh.bins.listed, incl);
+        slot = (uint32_t)__builtin_amdgcn_readlane((int)slot, kWaveSize - 1) + incl - mine;
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < kScoreBinsPer; ++i) {
+            const uint32_t n = elements(i);
+            if (n > 0) rb.bin[slot++] = FullBin::of(starts.v[i] - base + kListFront, n).word;
+        }
+        __syncthreads();
+        sort_full_bins(rb.bin, kScoreBins, sh.bins, list);
+    }
     // Lane i: the words 32 i .. 32 i + 31, elements from 16 before its ranks on.
-    const uint32_t words = s.count + kListFront;
+    const uint32_t words = count + kListFront;
     float x[kRun];
     if (wave * (kWaveSize * kRun) < words) {
 #pragma unroll
@@ -800,7 +950,7 @@ __device__ __forceinline__ bool order_share(const HeadKeys<E, ValueBins>& keys, 
         for (int i = 0; i < kRun; ++i) x[i] = INFINITY;
     }
     // the lower half of the next lane's; of the next wave's first lane through LDS
-    float* const edge = reinterpret_cast<float*>(sh.fine);
+    float* const edge = reinterpret_cast<float*>(rb.bin);
     if (lane == 0) {
 #pragma unroll
         for (uint32_t i = 0; i < kRun / 2; ++i) edge[wave * (kRun / 2) + i] = x[i];
@@ -1328,22 +1478,40 @@ __device__ __forceinline__ double wave_sum(double v) {
     return (read_lane(v, 0) + read_lane(v, 16)) + (read_lane(v, 32) + read_lane(v, 48));
 }
 
-// Fixed-order sums of N doubles per lane over the workgroup; results valid in thread 0.
-template <int N>
-__device__ __forceinline__ void block_sum(double (&v)[N], double (*stage)[N]) {
-    const int lane = threadIdx.x % kWaveSize;
-    const int wave = threadIdx.x / kWaveSize;
+// Fixed-order sums of doubles over the workgroup, in two steps: every wave leaves its sums of v in stage[wave][kFrom ..]; once all
+// are there, the first wave adds them up (results valid in thread 0; ends with a barrier).
+template <int kFrom, int N, int kAll>
+__device__ __forceinline__ void stage_sums(const double (&v)[N], double (*stage)[kAll]) {
+    static_assert(kFrom + N <= kAll, "columns");
 #pragma unroll
     for (int i = 0; i < N; ++i) {
         const double s = wave_sum(v[i]);
-        if (lane == 0) stage[wave][i] = s;
+        if (threadIdx.x % kWaveSize == 0) stage[threadIdx.x / kWaveSize][kFrom + i] = s;
     }
+}
+template <int N>
+__device__ __forceinline__ void sum_staged(double (&v)[N], double (*stage)[N]) {
     __syncthreads();
-    if (wave == 0) {                      // lane w holds wave w's sum
+    if (threadIdx.x < kWaveSize) {        // the 16 lanes of a row hold the waves' sums of a column, four columns at a time
+        static_assert(kSortWaves == kRowLanes, "a lane per wave");
+        const int row = threadIdx.x / kRowLanes;
 #pragma unroll
-        for (int i = 0; i < N; ++i) v[i] = wave_sum(lane < kSortWaves ? stage[lane][i] : 0.0);
+        for (int i = 0; i < N; i += 4) {
+            double s = stage[threadIdx.x % kRowLanes][i + row < N ? i + row : 0];
+            s += dpp_read<kDppXor1>(s);
+            s += dpp_read<kDppXor2>(s);
+            s += dpp_read<kDppHalfMirror>(s);
+            s += dpp_read<kDppMirror>(s);
+#pragma unroll
+            for (int j = i; j < N && j < i + 4; ++j) v[j] = read_lane(s, (j - i) * kRowLanes);
+        }
     }
     __syncthreads();
+}
+template <int N>
+__device__ __forceinline__ void block_sum(double (&v)[N], double (*stage)[N]) {
+    stage_sums<0>(v, stage);
+    sum_staged(v, stage);
 }
 
 __device__ __forceinline__ double score(float logit, float mx) { return (double)__builtin_amdgcn_exp2f(logit - mx); }
@@ -1385,6 +1553,49 @@ __device__ __forceinline__ PositionSums position_sums(uint32_t* logits, const in
     return sums;
 }
 
+// The same for heads whose logits are in registers, where a share takes whole blocks of 1024 positions: nothing but the ranks is
+// fetched, and those are on their way while the range of the logits is found.
+template <int E> struct RegisterSums {
+    // Block e is in slot e % kSlots.  A share has at most 19452 elements (share_plan), heads of more than 20 blocks at least two shares.
+    static constexpr int kSlots = E <= kListPer ? E : (E + 1) / 2;
+    static_assert(E <= 2 * kListPer, "at most two shares' blocks");
+    __amdgpu_buffer_rsrc_t rank;                                      // reads zero past the end
+    uint32_t n, first, end;                                           // blocks of the share
+    int32_t rk[kSlots];
+    __device__ __forceinline__ RegisterSums(const int32_t* r, uint32_t count, uint32_t share, uint32_t shares) : n(count) {
+        rank = __builtin_amdgcn_make_buffer_rsrc(const_cast<int32_t*>(r), 0, (int)(n * sizeof(int32_t)), kRawBufferWord3);
+        const uint32_t blocks = (n + kSortLanes - 1) / kSortLanes;
+        first = share * blocks / shares;
+        end = (share + 1) * blocks / shares;
+#pragma unroll
+        for (uint32_t j = 0; j < kSlots; ++j) {
+            const uint32_t block = first + (j + kSlots - first % kSlots) % kSlots;
+            rk[j] = __builtin_amdgcn_raw_buffer_load_b32(rank, threadIdx.x * sizeof(int32_t), block * (kSortLanes * sizeof(int32_t)), kBufferPolicyPlain);
+        }
+    }
+    template <typename Keys>
+    __device__ __forceinline__ PositionSums add_up(const Keys& keys, int64_t m, float mx, bool equal, RankedSums& ranked) {
+        PositionSums sums;
+        uint32_t left = n - threadIdx.x;
+        asm volatile("" : "+v"(left));
+        const int32_t dropped = m < INT32_MAX ? (int32_t)m : INT32_MAX;
+#pragma unroll
+        for (uint32_t e = 0; e < (uint32_t)E; ++e) {
+            if (e - first < end - first) {                            // the same for all lanes
+                const double x = (int32_t)left > (int32_t)(e * kSortLanes) ? score(keys.reg[e], mx) : 0.0;
+                const int32_t r = rk[e % kSlots];
+                sums.all += x;
+                sums.weighted += x * (double)r;
+                sums.dropped += r < dropped ? x : 0.0;
+            }
+        }
+        if (equal) {
+            for (uint32_t t = first * kSortLanes + threadIdx.x; t < end * kSortLanes && t < n; t += kSortLanes) add_ranked(ranked, score(mx, mx), t, m);
+        }
+        return sums;
+    }
+};
+
 // The elements of ranks r0 .. r0 + kRun - 1, `count` of which are there.
 __device__ __forceinline__ void add_run(RankedSums& sums, const float (&run)[kRun], float mx, uint32_t r0, uint32_t count, int64_t m) {
     double all = 0.0, above = 0.0;                                    // sum e, sum e * (rank - r0)
@@ -1410,16 +1621,22 @@ __device__ __forceinline__ void write_losses(const double (&acc)[kRecordSums], i
 }
 
 // What the ranking of a head's scores keeps in LDS.
-struct HeadShared {
-    BinShared sh;
+template <bool kRuns> struct HeadShared {
+    union {
+        BinShared sh;
+        std::conditional_t<kRuns, RunBins, uint32_t> bins;
+    };
     CutShared cut;
-    __attribute__((aligned(16))) uint32_t list[kListFront + kListWords + kWaveSize];
+    __attribute__((aligned(16))) uint32_t list[kRuns ? kRunWords + kWaveSize : (uint32_t)kListWords];
     double stage[kSortWaves][kRecordSums];
+    RunShared runs;
+    uint32_t ticket;
 };
 
 // The sums in order of rank of one share, ranks [r0, r1), by an exact cut and a sort, wherever its elements lie.
 typedef const uint32_t __attribute__((address_space(1)))* GlobalWords;     // of a plain pointer it would not know that it is not LDS
-__device__ __forceinline__ RankedSums sorted_sums(GlobalWords logits, uint32_t n, uint32_t r0, uint32_t r1, float mx, int64_t m, HeadShared& lds) {
+template <bool kRuns>
+__device__ __forceinline__ RankedSums sorted_sums(GlobalWords logits, uint32_t n, uint32_t r0, uint32_t r1, float mx, int64_t m, HeadShared<kRuns>& lds) {
     RankedSums ranked;
     const uint32_t at = sorted_range<LogitKey, false, kListPer>((const uint32_t*)logits, n, r0, r1, lds.list, nullptr, lds.sh, lds.cut);
     for (uint32_t i = threadIdx.x; i < r1 - r0; i += kSortLanes)
@@ -1428,7 +1645,7 @@ __device__ __forceinline__ RankedSums sorted_sums(GlobalWords logits, uint32_t n
 }
 // The same by comparing inside the finer bins, as long as these do not hold too many; else false.
 template <typename Keys>
-__device__ __forceinline__ bool compared_sums(const Keys& keys, const Share<ValueBins>& s, int64_t m, RankedSums& ranked, HeadShared& lds) {
+__device__ __forceinline__ bool compared_sums(const Keys& keys, const Share<ValueBins>& s, int64_t m, RankedSums& ranked, HeadShared<false>& lds) {
     float* const list = reinterpret_cast<float*>(lds.list);
     Ranked<kListPer, ValueBins> mine;
     if (!rank_share<false, kListPer>(keys, s, lds.sh, list, nullptr, mine)) return false;
@@ -1441,13 +1658,12 @@ __device__ __forceinline__ bool compared_sums(const Keys& keys, const Share<Valu
     return true;
 }
 
-// Heads of more than 8192 tokens whose keys stay in registers.  us for the losses, compared in the list / in runs: 128 heads of 9000
-// 34.1, 31.9; 12000 39.8, 36.6; 16384 47.3, 43.4; 24000 65.1, 58.7; 32768 85.3, 74.4; 256 heads of 17000 72.6, 59.7; few heads
-// and so small shares the same (32 heads of 9000 23.4, 23.6, of 32768 38.3, 36.3).  Up to 8192 tokens a share is so
-// small that runs of 32 leave most lanes idle: 32 heads of 3000 18.4, 19.7; 128 of 3000 20.9, 22.2.
-// Full finer bins, 20 equal logits each, list / runs: 128 heads of 32768 148, 95, of 12000 56, 47, 32 of 16384 35.1, 33.2, of 9000
-// 30.5, 30.6; 40 equal: 128 of 32768 153, 142, 32 of 9000 36.3, 31.2.  With more than kMaxFine the attempt is lost time, but less than the
-// list's: 100 equal, 128 of 32768 153, 141, of 12000 75, 70; half of all equal 159, 152.
+// Heads of more than 8192 tokens whose keys stay in registers: in runs.  us for the losses, compared in the list / in runs: 128 heads of 9000
+// 34.1, 30.7; 16384 47.3, 43.3; 32768 85.3, 74.4; 256 heads of 18000 72.6, 62.7; 32 heads of 9000 23.4, 22.4, of 32768 38.3, 35.3.  Up to
+// 8192 tokens a share is so small that runs of 32 leave most lanes idle: 32 heads of 3000 18.4, 19.7; 128 of 3000 20.9, 22.2.
+// Equal logits, counted twice in bins of a share with at most 64 in a bin, and the exact cut beyond / here: 20 equal each, 128 heads of 32768
+// 95, 93, of 12000 48, 43, 32 of 9000 30.5, 27.3; 40 equal 142, 90, 68, 47, 31.0, 31.7; 100 equal 141, 116, 68, 57, 54, 44; half of all equal
+// (exact cut) 128 of 12000 70.4, 70.7.  One key row 200 times as long as the others: 135, 78.
 template <int E> constexpr bool kInRuns = E > 8;
 
 // Softmax statistics, rank-weighted sums, ranks of the scores by value ranges, and the three
@@ -1461,8 +1677,8 @@ __global__ __launch_bounds__(kSortLanes)
 void alr_head_kernel(uint32_t* __restrict__ scratch, const int32_t* __restrict__ drop_rank, int64_t T,
                      uint32_t n_heads, int32_t G, Cut cut, int64_t m, double* __restrict__ alr,
                      double* __restrict__ loss, double* __restrict__ loss_ref) {
-    __shared__ HeadShared lds;
-    BinShared& sh = lds.sh;
+    constexpr bool kRuns = kInRuns<E>;
+    __shared__ HeadShared<kRuns> lds;
     uint32_t* const s_list = lds.list;
     double (&stage)[kSortWaves][kRecordSums] = lds.stage;
     const Part part = part_of_block(blockIdx.x, n_heads, cut.shares);     // head = b * Hq + hq
@@ -1475,36 +1691,53 @@ void alr_head_kernel(uint32_t* __restrict__ scratch, const int32_t* __restrict__
 
     const uint32_t p0 = cut.start(part.share), p1 = cut.start(part.share + 1);
     const HeadKeys<E, ValueBins> keys(logits, n);
-    const auto s = find_share(keys, n, part.share, cut, s_list, sh);
-    const float mx = s.kmax;
-    const bool equal = s.kmin == s.kmax;                                  // equal scores: any order
-
+    std::conditional_t<(E > 0), RegisterSums<E>, std::nullptr_t> by_position = [&] {
+        if constexpr (E > 0) return RegisterSums<E>(rank, n, part.share, cut.shares);
+        else return nullptr;
+    }();
+    // equal scores: any order.  mx: the largest.
+    auto sum_positions = [&](float mx, bool equal, RankedSums& ranked) {
+        PositionSums sums;
+        if constexpr (E > 0) sums = by_position.add_up(keys, m, mx, equal, ranked);
+        else sums = position_sums<false>(logits, rank, p0, p1, m, mx, equal, ranked);
+        stage_sums<0>({sums.all, sums.weighted, sums.dropped}, stage);        // not in registers any longer
+    };
     RankedSums ranked;
-    if (!equal) {
-        bool done = false;
-        if constexpr (kInRuns<E>) {
-            if (!s.crowded) {
-                float run[kRun];
-                done = order_share<E>(keys, s, sh, reinterpret_cast<float*>(s_list), run);
-                const uint32_t at = threadIdx.x * kRun;
-                if (done && at < s.count) add_run(ranked, run, mx, s.base + at, s.count - at, m);
-            }
-        } else {
-            if (!s.crowded) done = compared_sums(keys, s, m, ranked, lds);
+    float mx;
+    uint32_t r0 = p0, r1 = p1;                                            // ranks that an exact cut takes
+    bool done = true;
+    if constexpr (kRuns) {
+        for (uint32_t i = threadIdx.x; i < kScoreBins / 4; i += kSortLanes) reinterpret_cast<uint4*>(lds.bins.bin)[i] = make_uint4(0, 0, 0, 0);
+        const ScoreRange range = score_range(keys, lds.runs);
+        mx = range.hi;
+        sum_positions(mx, range.lo == range.hi, ranked);
+        if (range.lo != range.hi) {
+            float run[kRun];
+            uint32_t base, count;
+            done = order_share<E>(keys, range, part.share, cut, lds.bins, lds.runs, reinterpret_cast<float*>(s_list), run, base, count);
+            const uint32_t at = threadIdx.x * kRun;
+            if (done && at < count) add_run(ranked, run, mx, base + at, count - at, m);
         }
-        // Seldom, as the compiler has to know, and with nothing left in registers for it, not even what would only be loaded again:
-        // otherwise the path that nearly all heads take spills (42 us in place of 33 for 128 heads of 32k).
-        if (__builtin_expect(!done, false)) {
-            GlobalWords again = (GlobalWords)logits;
-            uint32_t count = n;
-            asm volatile("" : "+s"(again), "+s"(count));
-            const uint32_t r0 = s.crowded ? p0 : s.base, r1 = s.crowded ? p1 : s.base + s.count;
-            ranked = sorted_sums(again, count, r0, r1, mx, m, lds);
+    } else {
+        const auto s = find_share(keys, n, part.share, cut, s_list, lds.sh);
+        mx = s.kmax;
+        sum_positions(mx, s.kmin == s.kmax, ranked);
+        if (s.kmin != s.kmax) {
+            done = !s.crowded && compared_sums(keys, s, m, ranked, lds);
+            if (!s.crowded) r0 = s.base, r1 = s.base + s.count;
         }
     }
-    const PositionSums sums = position_sums<false>(logits, rank, p0, p1, m, mx, equal, ranked);
-    double acc[kRecordSums] = {sums.all, sums.weighted, sums.dropped, ranked.weighted, ranked.lowest};
-    block_sum<kRecordSums>(acc, stage);                               // valid in thread 0
+    // Seldom, as the compiler has to know, and with nothing left in registers for it, not even what would only be loaded again:
+    // otherwise the path that nearly all heads take spills (42 us in place of 33 for 128 heads of 32k).
+    if (__builtin_expect(!done, false)) {
+        GlobalWords again = (GlobalWords)logits;
+        uint32_t count = n;
+        asm volatile("" : "+s"(again), "+s"(count));
+        ranked = sorted_sums(again, count, r0, r1, mx, m, lds);
+    }
+    stage_sums<3>({ranked.weighted, ranked.lowest}, stage);
+    double acc[kRecordSums];
+    sum_staged(acc, stage);                                           // valid in thread 0
 
     if (cut.shares > 1) {
         uint32_t* counter = record_base(second, head, T);
@@ -1515,10 +1748,10 @@ void alr_head_kernel(uint32_t* __restrict__ scratch, const int32_t* __restrict__
             for (int i = 0; i < kRecordSums; ++i)
                 __hip_atomic_store(out + i, __builtin_bit_cast(unsigned long long, acc[i]), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);
-            sh.ticket = __hip_atomic_fetch_add(counter, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            lds.ticket = __hip_atomic_fetch_add(counter, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
         __syncthreads();
-        if (sh.ticket != cut.shares - 1) return;
+        if (lds.ticket != cut.shares - 1) return;
         // the records into LDS with independent loads, then added in order
         uint32_t* copy = s_list;
         for (uint32_t i = threadIdx.x; i < cut.shares * kRecordWords; i += kSortLanes)
