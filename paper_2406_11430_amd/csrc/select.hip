@@ -164,6 +164,12 @@ template <int E> struct HeadKeys {
 };
 
 constexpr uint32_t kListedKeys = 256;                 // keys of a bin that are compared with each other
+constexpr uint32_t kFewListed = 8;                    // by every wave for itself (35 so: 2 us more than through LDS)
+// Heads of at most 2048 tokens are counted in half as many bins: 32 KB to clear and to sum up, and a bin holds a few keys all the same.  One-launch
+// compressions of 512 tokens 6.85 -> 6.27 us, of 128 5.88 -> 5.25, of 8 heads of 2048 in two launches 9.15 -> 8.80, together with the comparison by
+// every wave.  (In 1024 bins a zero row, which makes the bins wide, costs heads of 1000 more than that gains: 7.74 -> 8.06, here 7.35;
+// for the same reason not up to 4096 tokens: 512 heads 8.2 -> 7.5, with a zero row each 10.0 -> 11.8.)
+constexpr int kFewBits = 11;
 struct SearchShared {
     uint32_t hist[kTopBins * kCopies];                // 64 KB: two workgroups per compute unit
     uint32_t list[kListedKeys];
@@ -176,6 +182,8 @@ struct Threshold { uint32_t tau, need_eq; };          // need_eq >= 1 keys equal
 // The k-th smallest of a head's keys, 1 <= k <= their number.  Called by all 1024 lanes.
 template <int E>
 __device__ __forceinline__ Threshold find_threshold(const HeadKeys<E>& keys, uint32_t k, SearchShared& sh) {
+    constexpr int kBits = E == 1 || E == 2 ? kFewBits : kTopBits;
+    constexpr uint32_t kBins = 1u << kBits;
     const int lane = threadIdx.x % kWaveSize;
     const int wave = threadIdx.x / kWaveSize;
     uint32_t lo = 0xffffffffu, hi = 0u;
@@ -190,35 +198,35 @@ __device__ __forceinline__ Threshold find_threshold(const HeadKeys<E>& keys, uin
         sh.hi[wave] = hi;
     }
     if (threadIdx.x == 0) sh.listed = 0;
-    clear_counts(sh.hist, kTopBins * kCopies);
+    clear_counts(sh.hist, kBins * kCopies);
     __syncthreads();
     lo = __builtin_amdgcn_readfirstlane(row16_min(sh.lo[lane % kRowLanes]));
     hi = ~__builtin_amdgcn_readfirstlane(row16_min(~sh.hi[lane % kRowLanes]));
     // every pass computes the bins afresh: kept from one pass to the next they would not fit the registers
     auto origin = [&] { uint32_t v = lo; asm volatile("" : "+s"(v)); return v; };
     const int bits = hi == lo ? 0 : 32 - __builtin_clz(hi - lo);
-    int shift = bits > kTopBits ? bits - kTopBits : 0;
+    int shift = bits > kBits ? bits - kBits : 0;
     // (the padding falls into the last bin: it comes after all real keys and k is at most their number)
     uint32_t o = origin();
     keys.each([&](uint32_t key, bool) {
         const uint32_t b = (key - o) >> shift;
-        count_digit(sh.hist, b < kTopBins ? b : kTopBins - 1);
+        count_digit(sh.hist, b < kBins ? b : kBins - 1);
     });
     __syncthreads();
-    Found f = find_digit<kTopBins>(sh.hist, k, sh.find);
+    Found f = find_digit<kBins>(sh.hist, k, sh.find);
     uint32_t want = k - f.below;
     uint32_t bin = __builtin_amdgcn_readfirstlane(f.digit);           // (key - lo) >> shift of the wanted key
     uint32_t count = __builtin_amdgcn_readfirstlane(f.count);
     while (shift > 0 && count > kListedKeys) {
-        const int finer = shift > kTopBits ? shift - kTopBits : 0;
-        clear_counts(sh.hist, kTopBins * kCopies);
+        const int finer = shift > kBits ? shift - kBits : 0;
+        clear_counts(sh.hist, kBins * kCopies);
         __syncthreads();
         o = origin();
         keys.each([&](uint32_t key, bool) {
             if ((key - o) >> shift == bin) count_digit(sh.hist, ((key - o) >> finer) - (bin << (shift - finer)));
         });
         __syncthreads();
-        f = find_digit<kTopBins>(sh.hist, want, sh.find);
+        f = find_digit<kBins>(sh.hist, want, sh.find);
         want -= f.below;
         bin = (bin << (shift - finer)) + __builtin_amdgcn_readfirstlane(f.digit);
         count = __builtin_amdgcn_readfirstlane(f.count);
@@ -230,15 +238,32 @@ __device__ __forceinline__ Threshold find_threshold(const HeadKeys<E>& keys, uin
         if ((key - o) >> shift == bin) sh.list[atomicAdd(&sh.listed, 1u)] = key;
     });
     __syncthreads();
-    count = sh.listed;                                                // without padding that was counted with the last bin
-    if (threadIdx.x < count) {
-        const uint32_t key = sh.list[threadIdx.x];
+    count = __builtin_amdgcn_readfirstlane(sh.listed);                // without padding that was counted with the last bin
+    if (count <= kFewListed) {
+        // every wave by itself, lane i with the i-th of them: no barrier, and nothing through LDS
+        const uint32_t key = sh.list[(uint32_t)lane < count ? lane : 0];
         uint32_t less = 0, equal = 0;
         for (uint32_t j = 0; j < count; ++j) {
+            const uint32_t other = __builtin_amdgcn_readlane((int)key, (int)j);
+            less += other < key ? 1u : 0u;
+            equal += other == key ? 1u : 0u;
+        }
+        const uint64_t wanted = __ballot((uint32_t)lane < count && less < want && want <= less + equal);      // and its equals
+        const int at = (int)__builtin_ctzll(wanted | 1ull << (kWaveSize - 1));
+        return Threshold{(uint32_t)__builtin_amdgcn_readlane((int)key, at), want - (uint32_t)__builtin_amdgcn_readlane((int)less, at)};
+    }
+    // four lanes to a key, each for a quarter of the others
+    static_assert(kListedKeys * 4 == kSelThreads, "all of them at once");
+    if (threadIdx.x / 4 < count) {
+        const uint32_t key = sh.list[threadIdx.x / 4];
+        uint32_t less = 0, equal = 0;
+        for (uint32_t j = threadIdx.x % 4; j < count; j += 4) {
             const uint32_t other = sh.list[j];
             less += other < key ? 1u : 0u;
             equal += other == key ? 1u : 0u;
         }
+        less = dpp_add<kDppXor2>(dpp_add<kDppXor1>(less));           // the lanes of a quad are here together
+        equal = dpp_add<kDppXor2>(dpp_add<kDppXor1>(equal));
         if (less < want && want <= less + equal) {                    // the wanted key, and its equals alike
             sh.tau = key;
             sh.need_eq = want - less;
