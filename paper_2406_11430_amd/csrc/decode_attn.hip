@@ -6,6 +6,7 @@
 
 #include <math.h>
 
+#include <algorithm>
 #include <atomic>
 
 namespace l2kv {
@@ -89,6 +90,7 @@ int32_t decode_max_splits(int64_t kv_len) {
 
 DecodePlan decode_plan(int32_t B, int32_t Hkv, int32_t group, int64_t kv_len, int32_t row_bytes, int32_t requested_splits) {
     const int64_t pairs = (int64_t)B * Hkv;
+    const int64_t cap = decode_max_splits(kv_len);
     int64_t want = requested_splits;
     if (want <= 0) {
         // Workgroups (4 waves each) for about three quarters of the compute units,
@@ -130,8 +132,29 @@ DecodePlan decode_plan(int32_t B, int32_t Hkv, int32_t group, int64_t kv_len, in
             short_head = longer == 0 || (longer <= 24 << 10 && (pairs > 2 || k_bytes <= int64_t{384} << 10));
         }
         if (want > kDecodeNarrowSplits && short_head) want = kDecodeNarrowSplits;
+        // Very short heads: a wave has few tiles of 16 rows to read (32 at rows of 128 bytes), and to write, wait for and merge partial
+        // results takes longer than the tiles that the other workgroups would have read.  us, split as above / in 1: bf16 rows of 128, 32
+        // heads of 83 rows 4.6 / 3.2, 8 of 175 4.3 / 3.4; of 64, 128 of 88 with 4 query heads 6.3 / 4.4; fp32 rows of 64, 128 of 184 with 3
+        // 6.7 / 5.7; 4 of 256, 4.2 / 3.3.  Not for more tiles or query heads: bf16 rows of 128, 8 of 189 with 4 5.9 / 6.3; of 256, 8 of 128
+        // with 4 7.1 / 7.3.
+        const int64_t tile_rows = row_bytes <= 128 ? 2 * kDecodeRowTile : kDecodeRowTile;      // of the four waves
+        const int64_t tiles = (kv_len + tile_rows - 1) / tile_rows;
+        const bool long_rows = row_bytes > 256;
+        if (tiles <= 2 ? !long_rows || group <= 3 : !long_rows && (tiles == 3 ? group <= 3 : tiles == 4 && group <= 2)) want = 1;
+        // Few heads of long rows: their streams leave memory idle, so that the splits are counted in the 64-row blocks of the longest.
+        // A block costs 0.9 us and 0.1 for each further query head, a partial result 0.011 to 0.02, twice that past 32 and 2 us
+        // past 64, where the merge goes through LDS.  us, split as above / here: fp32 rows of 128, 3 heads of 1886 with 2 query heads
+        // 7.6 / 6.5, 1 of 9322 10.0 / 8.4, 1 of 53342 with 2 19.7 / 16.0; bf16 rows of 256, 3 of 4121 with 3 12.0 / 10.9.  Four heads beyond
+        // 4 MB of K: 8675 bf16 rows of 256 12.0 / 12.2.
+        if (want > kDecodeNarrowSplits && long_rows && group <= 4 && (pairs <= 3 || (pairs == 4 && k_bytes <= 4 << 20))) {
+            const int64_t most = std::min<int64_t>((2 * target + pairs) / (2 * pairs), cap);
+            double least = 0;
+            for (int64_t each = (blocks + most - 1) / most, splits; (splits = (blocks + each - 1) / each) > kDecodeNarrowSplits; ++each) {
+                const double us = (0.9 + 0.1 * (group - 1)) * each + (0.008 + 0.003 * group) * (splits > 32 ? 2 : 1) * splits + (splits > 64 ? 2 : 0);
+                if (least == 0 || us < least) least = us, want = splits;
+            }
+        }
     }
-    const int64_t cap = decode_max_splits(kv_len);
     if (want > cap) want = cap;
     if (want < 1) want = 1;
     DecodePlan plan;
