@@ -253,11 +253,17 @@ l2kv_status l2kv_decode_attn_static(const void* Q, const void* Kc, const void* V
         st != L2KV_OK)
         return st;
     const float s = scale > 0.f ? scale : 1.0f / std::sqrt(static_cast<float>(D));
-    const DecodePlan plan = decode_plan(B, Hkv, Hq / Hkv, kv_len, D * elem_bytes(dt), 0);
+    DecodePlan plan = decode_plan(B, Hkv, Hq / Hkv, kv_len, D * elem_bytes(dt), 0);
     // counters + the partials of the workgroups this launch really has
-    const size_t need = decode_counter_bytes(B, Hkv) +
-                        static_cast<size_t>(B) * static_cast<size_t>(Hq) * static_cast<size_t>(plan.n_splits) *
-                            decode_partial_floats(D) * sizeof(float);
+    const auto bytes_for = [&](int32_t splits) {
+        return decode_counter_bytes(B, Hkv) + static_cast<size_t>(B) * static_cast<size_t>(Hq) * static_cast<size_t>(splits) *
+                                                  decode_partial_floats(D) * sizeof(float);
+    };
+    size_t need = bytes_for(plan.n_splits);
+    if (need > static_cast<size_t>(L2KV_STATIC_SCRATCH_BYTES) && plan.fewest_splits > 0) {
+        plan.n_splits = plan.fewest_splits;
+        need = bytes_for(plan.n_splits);
+    }
     if (need > static_cast<size_t>(L2KV_STATIC_SCRATCH_BYTES)) return L2KV_ERR_WORKSPACE;
     l2kv_status st = L2KV_OK;
     void* scratch_ptr = decode_static_scratch(static_cast<hipStream_t>(stream), &st);

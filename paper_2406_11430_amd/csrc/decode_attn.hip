@@ -92,6 +92,7 @@ DecodePlan decode_plan(int32_t B, int32_t Hkv, int32_t group, int64_t kv_len, in
     const int64_t pairs = (int64_t)B * Hkv;
     const int64_t cap = decode_max_splits(kv_len);
     int64_t want = requested_splits;
+    DecodePlan plan;
     if (want <= 0) {
         // Workgroups (4 waves each) for about three quarters of the compute units,
         // all resident at once.  Measured over batch sizes 1..16 and cache lengths
@@ -106,6 +107,31 @@ DecodePlan decode_plan(int32_t B, int32_t Hkv, int32_t group, int64_t kv_len, in
         const int64_t target = group >= 5 ? cus : 3 * cus / 4;
         want = (2 * target + pairs) / (2 * pairs);                 // nearest integer to target / pairs
         if (want > 1 && want * pairs > cus) --want;
+        // Two thirds of the compute units or fewer after rounding leave memory idle; one more split each fits.  us, bf16 rows of 128: 80
+        // heads of 9000 rows 64.4 in 2, 60.4 in 3, with 4 query heads 70.3 / 62.6, of 1100 15.4 / 13.3; 56 of 9000 48.7 in 3, 45.1 in 4.
+        if (group < 5 && 3 * want * pairs <= 2 * cus && (want + 1) * pairs <= cus) ++want;
+        // More heads than that: a head in one workgroup means rounds of all compute units, the last of which may have little to do; in
+        // 3 (2, 5) splits the rounds are shorter and fuller.  us, one / three: bf16 rows of 128 of 5000, 136 heads with 8 query
+        // heads 92.7 / 68.5, 288 with 4 166 / 131; 288 of 1500 54.2 / 46.5; fp32 rows of 128, 288 of 5000 with 8 354 / 270; of 64 bf16,
+        // 320 of 5000 78.1 / 66.8; two / five: 88 with 6 52.9 / 46.2.  More partial results and shorter streams cost more than that below these lines:
+        // 136 of 750 rows with 1 query head 0.95 of the speed, of 1500 with 4 0.98; 341 of 512 with 8 0.87; fp32 rows
+        // of 128, 331 of 794 with 7 0.98, 593 of 1311 with 7 0.98, bf16 rows of 256, 593 of 914 0.93.
+        const int64_t k_bytes = kv_len * row_bytes, kb = k_bytes >> 10;
+        const auto rounds = [&](int64_t workgroups) { return (workgroups + cus - 1) / cus; };
+        const bool long_rows = row_bytes > 256;
+        int64_t fuller = want;
+        if (pairs > cus) {
+            if (kb >= (pairs > 2 * cus ? 640 : 384) << (long_rows && group >= 5 ? 1 : 0) && pairs <= 3 * cus && rounds(3 * pairs) <= 3 * rounds(pairs) - 2) fuller = 3;
+            else if (kb >= 384 && 2 * pairs <= 3 * cus && group >= 4 && !long_rows) fuller = 2;
+        } else if (2 * pairs > cus) {
+            if (group >= 5 && !long_rows ? 25 * pairs <= 16 * cus && kb >= 512
+                                         : 7 * pairs <= 4 * cus && kb >= (group >= 7 ? 1024 : 2048))
+                fuller = 3;
+        } else if (group >= 5 && !long_rows && 3 * pairs > cus && 21 * pairs <= 8 * cus && kb >= 1024) {
+            fuller = 5;
+        }
+        if (want == 1 && fuller > 1) plan.fewest_splits = 1;
+        want = fuller;
         // With very few heads that rule asks for so many workgroups per head that
         // the final merge (about 0.2 us per workgroup) outweighs the shorter
         // streams (about 0.025 us per row): the sum is smallest near
@@ -123,7 +149,6 @@ DecodePlan decode_plan(int32_t B, int32_t Hkv, int32_t group, int64_t kv_len, in
         // time, so often not at all), for one or two heads not beyond 384 KB.  bf16 rows of 128, 3 heads of 1615 with 5 query heads 8.8 / 9.4, 8 of
         // 1607 with 6 10.5 / 11.2, 1 of 1804 with 5 6 % slower in 8; fp32 rows of 64, 3 of 1790 with 8 9.3 / 10.3; not longer: fp32 rows of 128, 2 of
         // 929 with 6 10.0 / 9.1.
-        const int64_t k_bytes = kv_len * row_bytes;
         const int64_t blocks = (kv_len + kDecodeRowTile - 1) / kDecodeRowTile;
         auto longest = [&](int64_t splits) { return (blocks + splits - 1) / splits * kDecodeRowTile * row_bytes; };
         bool short_head = group < 5 ? k_bytes <= int64_t{384} << 10 : k_bytes <= int64_t{512} << 10 && kv_len <= 3072;
@@ -139,7 +164,6 @@ DecodePlan decode_plan(int32_t B, int32_t Hkv, int32_t group, int64_t kv_len, in
         // with 4 7.1 / 7.3.
         const int64_t tile_rows = row_bytes <= 128 ? 2 * kDecodeRowTile : kDecodeRowTile;      // of the four waves
         const int64_t tiles = (kv_len + tile_rows - 1) / tile_rows;
-        const bool long_rows = row_bytes > 256;
         if (tiles <= 2 ? !long_rows || group <= 3 : !long_rows && (tiles == 3 ? group <= 3 : tiles == 4 && group <= 2)) want = 1;
         // Few heads of long rows: their streams leave memory idle, so that the splits are counted in the 64-row blocks of the longest.
         // A block costs 0.9 us and 0.1 for each further query head, a partial result 0.011 to 0.02, twice that past 32 and 2 us
@@ -157,7 +181,6 @@ DecodePlan decode_plan(int32_t B, int32_t Hkv, int32_t group, int64_t kv_len, in
     }
     if (want > cap) want = cap;
     if (want < 1) want = 1;
-    DecodePlan plan;
     plan.n_splits = (int32_t)want;
     return plan;
 }

@@ -67,6 +67,7 @@ l2kv_status compact_dispatch(const void* K, const void* V, l2kv_dtype dt, const 
 // n_splits workgroups take turns on consecutive 64-row blocks.
 struct DecodePlan {
     int32_t n_splits = 1;      // workgroups launched per KV head; work list: pieces of a sequence there is room for
+    int32_t fewest_splits = 0; // > 0: what also does, where the partial results of n_splits find no room
     int32_t rows_per_wg = 1;   // ragged batches: a sequence of n rows employs ceil(n / rows_per_wg) of them
     int32_t worklist_wgs = 0;  // > 0: ordered ragged batch, this many workgroups draw items from a device-side list
     int32_t pieces = 1;        // work list: pieces of the longest sequence, as far as the host knows its length
