@@ -165,18 +165,28 @@ DecodePlan decode_plan(int32_t B, int32_t Hkv, int32_t group, int64_t kv_len, in
         const int64_t tile_rows = row_bytes <= 128 ? 2 * kDecodeRowTile : kDecodeRowTile;      // of the four waves
         const int64_t tiles = (kv_len + tile_rows - 1) / tile_rows;
         if (tiles <= 2 ? !long_rows || group <= 3 : !long_rows && (tiles == 3 ? group <= 3 : tiles == 4 && group <= 2)) want = 1;
-        // Few heads of long rows: their streams leave memory idle, so that the splits are counted in the 64-row blocks of the longest.
-        // A block costs 0.9 us and 0.1 for each further query head, a partial result 0.011 to 0.02, twice that past 32 and 2 us
-        // past 64, where the merge goes through LDS.  us, split as above / here: fp32 rows of 128, 3 heads of 1886 with 2 query heads
-        // 7.6 / 6.5, 1 of 9322 10.0 / 8.4, 1 of 53342 with 2 19.7 / 16.0; bf16 rows of 256, 3 of 4121 with 3 12.0 / 10.9.  Four heads beyond
-        // 4 MB of K: 8675 bf16 rows of 256 12.0 / 12.2.
-        if (want > kDecodeNarrowSplits && long_rows && group <= 4 && (pairs <= 3 || (pairs == 4 && k_bytes <= 4 << 20))) {
-            const int64_t most = std::min<int64_t>((2 * target + pairs) / (2 * pairs), cap);
-            double least = 0;
-            for (int64_t each = (blocks + most - 1) / most, splits; (splits = (blocks + each - 1) / each) > kDecodeNarrowSplits; ++each) {
-                const double us = (0.9 + 0.1 * (group - 1)) * each + (0.008 + 0.003 * group) * (splits > 32 ? 2 : 1) * splits + (splits > 64 ? 2 : 0);
-                if (least == 0 || us < least) least = us, want = splits;
-            }
+        // Few heads: their streams leave memory idle, so that the splits are counted in the 64-row steps of the longest: as many as make
+        // its steps and the merge shortest together.  One more partial result costs 0.05 to 0.06 steps of a lone head (0.7 to 1.8 us;
+        // least squares over 16 to 128 splits of 1600 to 32000 rows), more beside others, and with up to 4 query heads a lot past 64,
+        // where it goes through LDS.  us, 0.34 * sqrt(rows) / here: bf16 rows of 128, 1 head of 16000 8.7 / 7.8, 2 of 4096 with 4
+        // query heads 9.1 / 8.2, with 8 13.2 / 11.7; fp32 rows of 128, 1 of 4096 with 8 16.8 / 12.9, 3 with 8 17.5 / 14.0.  Not where less than
+        // 5 % (two heads of 256-byte rows 14 %) is to be gained, nor for more heads (4 of 9404 fp32 rows of 64 9.2 / 9.7) or 128-byte rows (1
+        // of 49352 10.3 / 10.8).
+        // Long rows with up to 4 query heads: a step takes 0.9 us and 0.1 for each further one, a partial result 0.011 to 0.02, twice that
+        // past 32 and 2 us past 64.  fp32 rows of 128, 3 heads of 1886 with 2 query heads 7.6 / 6.5, 1 of 9322 10.0 / 8.4, 1 of 53342 with 2
+        // 19.7 / 16.0; bf16 rows of 256, 3 of 4121 with 3 12.0 / 10.9.  Four heads beyond 4 MB of K: 8675 bf16 rows of 256 12.0 / 12.2.
+        const bool by_long_rows = long_rows && group <= 4;
+        const bool few = by_long_rows ? pairs <= 3 || (pairs == 4 && k_bytes <= 4 << 20)
+                         : row_bytes > 128 && pairs <= (long_rows ? 4 : 2) && k_bytes >= 768 << 10 && kv_len <= (group > 4 && pairs == 1 ? 65536 : 32768);
+        if (want > kDecodeNarrowSplits && few) {
+            const int64_t most = std::min<int64_t>((2 * target + pairs) / (2 * pairs), group <= 4 && !long_rows ? std::min<int64_t>(cap, 64) : cap);
+            const auto cost = [&](int64_t each, int64_t splits) {
+                return by_long_rows ? (0.9 + 0.1 * (group - 1)) * each + (0.008 + 0.003 * group) * (splits > 32 ? 2 : 1) * splits + (splits > 64 ? 2 : 0)
+                                    : each + (0.01 * pairs + (group <= 4 ? 0.06 : 0.05)) * splits;
+            };
+            double least = by_long_rows ? 1e9 : (pairs == 1 || long_rows ? 0.95 : 0.86) * cost((blocks + want - 1) / want, want);
+            for (int64_t each = (blocks + most - 1) / most, splits; (splits = (blocks + each - 1) / each) > kDecodeNarrowSplits; ++each)
+                if (cost(each, splits) < least) least = cost(each, splits), want = splits;
         }
     }
     if (want > cap) want = cap;
