@@ -471,7 +471,9 @@ __device__ __forceinline__ Share<typename Keys::Bins> find_share(const Keys& key
 // fill the finer bins alike (8192 bins for up to 20k elements).  With finer bins of equal width the
 // tails of the logits left a few hundred elements in each of the others: 140 us for 128 heads in two shares
 // against 46.  Hits are gathered with one counter update per wave and batch (a ballot and an update per key:
-// 16k cycles of the 48k of a share, now 7k).  Equal keys rank by position (kWithPos), else in any order.  Called by all lanes; the
+// 16k cycles of the 48k of a share, now 7k).  Keys and positions lie side by side in the list, so that one LDS access moves both: its
+// issue bounds the gather (32 heads of 32k norms 22.4 -> 22.0 us, 20 equal norms each 34.5 -> 33.1; with the lanes that store named by
+// ballots 23.1).  Equal keys rank by position (kWithPos), else in any order.  Called by all lanes; the
 // list is free again after the caller's barrier.
 template <typename Bins> struct FineBins {
     const Share<Bins>& s;
@@ -492,9 +494,23 @@ template <int kPer, typename Bins> struct Ranked {
 };
 template <bool kWithPos, int kPer, typename Keys>
 __device__ __forceinline__ bool rank_share(const Keys& keys, const Share<typename Keys::Bins>& s, BinShared& sh,
-                                           typename Keys::Key* list_key, uint32_t* list_pos,
+                                           typename Keys::Key* list,
                                            Ranked<kPer, typename Keys::Bins>& out) {
     using Key = typename Keys::Key;
+    const auto put = [&](uint32_t at, Key key, uint32_t pos) {
+        if constexpr (kWithPos) reinterpret_cast<uint2*>(list)[at] = make_uint2(key, pos);
+        else list[at] = key;
+    };
+    const auto get = [&](uint32_t at, Key& key, uint32_t& pos) {
+        if constexpr (kWithPos) {
+            const uint2 both = reinterpret_cast<const uint2*>(list)[at];
+            key = both.x;
+            pos = both.y;
+        } else {
+            key = list[at];
+            pos = at;                                                 // ties in the order of the list
+        }
+    };
     const uint32_t bins = s.end - s.first;
     typename Keys::Bins coarse = s.bins;
     if constexpr (std::is_same_v<Key, float>) asm volatile("" : "+v"(coarse.scale));   // computed afresh: the bins of
@@ -515,9 +531,7 @@ __device__ __forceinline__ bool rank_share(const Keys& keys, const Share<typenam
 #pragma unroll
         for (int u = 0; u < kN; ++u) {
             if (hits >> u & 1u) {
-                list_key[at] = key[u];
-                if constexpr (kWithPos) list_pos[at] = pos(u);
-                ++at;
+                put(at++, key[u], pos(u));
             }
         }
     });
@@ -527,8 +541,7 @@ __device__ __forceinline__ bool rank_share(const Keys& keys, const Share<typenam
     for (int u = 0; u < kPer; ++u) {
         const uint32_t i = u * kSortLanes + threadIdx.x;
         if (i < s.count) {
-            out.key[u] = list_key[i];
-            if constexpr (kWithPos) out.pos[u] = list_pos[i];
+            get(i, out.key[u], out.pos[u]);
             out.rank[u] = fine_bin(out.key[u]);
             atomicAdd(&sh.fine[out.rank[u]], 1u);
         }
@@ -545,9 +558,7 @@ __device__ __forceinline__ bool rank_share(const Keys& keys, const Share<typenam
 #pragma unroll
     for (int u = 0; u < kPer; ++u) {
         if (u * kSortLanes + threadIdx.x < s.count) {
-            const uint32_t at = atomicAdd(&sh.fine[out.rank[u]], 1u);
-            list_key[at] = out.key[u];
-            if constexpr (kWithPos) list_pos[at] = out.pos[u];
+            put(atomicAdd(&sh.fine[out.rank[u]], 1u), out.key[u], out.pos[u]);
         }
     }
     __syncthreads();
@@ -566,8 +577,7 @@ __device__ __forceinline__ bool rank_share(const Keys& keys, const Share<typenam
         for (int v = 0; v < kTogether && u0 + v < kPer; ++v) {
             const uint32_t i = (u0 + v) * kSortLanes + lane_of_all;
             const uint32_t at = i < s.count ? i : 0u;
-            out.key[u0 + v] = list_key[at];
-            out.pos[u0 + v] = kWithPos ? list_pos[at] : at;           // ties in the order of the list
+            get(at, out.key[u0 + v], out.pos[u0 + v]);
         }
 #pragma unroll
         for (int v = 0; v < kTogether && u0 + v < kPer; ++v) {
@@ -580,10 +590,7 @@ __device__ __forceinline__ bool rank_share(const Keys& keys, const Share<typenam
 #pragma unroll
         for (int v = 0; v < kTogether && u0 + v < kPer; ++v) {
 #pragma unroll
-            for (int j = 0; j < kListAhead; ++j) {
-                other[v][j] = list_key[start[v] + j];
-                order[v][j] = kWithPos ? list_pos[start[v] + j] : start[v] + j;
-            }
+            for (int j = 0; j < kListAhead; ++j) get(start[v] + j, other[v][j], order[v][j]);
         }
 #pragma unroll
         for (int v = 0; v < kTogether && u0 + v < kPer; ++v) {
@@ -597,10 +604,7 @@ __device__ __forceinline__ bool rank_share(const Keys& keys, const Share<typenam
                 Key o[kListAhead];
                 uint32_t p[kListAhead];
 #pragma unroll
-                for (int j = 0; j < kListAhead; ++j) {
-                    o[j] = list_key[j0 + j];
-                    p[j] = kWithPos ? list_pos[j0 + j] : j0 + j;
-                }
+                for (int j = 0; j < kListAhead; ++j) get(j0 + j, o[j], p[j]);
 #pragma unroll
                 for (int j = 0; j < kListAhead; ++j) r += j0 + j < end[v] && (o[j] < key || (o[j] == key && p[j] < pos)) ? 1u : 0u;
             }
@@ -1327,7 +1331,7 @@ void norm_ranks_kernel(const float* __restrict__ norms, int64_t T, uint32_t n_he
     uint32_t* const list_pos = s_list + kPer * kSortLanes;
     if (!s.crowded) {
         Ranked<kPer, BitBins> mine;
-        if (rank_share<true, kPer>(keys, s, sh, s_list, list_pos, mine)) {
+        if (rank_share<true, kPer>(keys, s, sh, s_list, mine)) {
 #pragma unroll
             for (int u = 0; u < kPer; ++u)
                 if (u * kSortLanes + threadIdx.x < s.count) rank[mine.pos[u]] = n - 1 - (s.base + mine.rank[u]);
@@ -1653,7 +1657,7 @@ template <typename Keys>
 __device__ __forceinline__ bool compared_sums(const Keys& keys, const Share<ValueBins>& s, int64_t m, RankedSums& ranked, HeadShared<false>& lds) {
     float* const list = reinterpret_cast<float*>(lds.list);
     Ranked<kListPer, ValueBins> mine;
-    if (!rank_share<false, kListPer>(keys, s, lds.sh, list, nullptr, mine)) return false;
+    if (!rank_share<false, kListPer>(keys, s, lds.sh, list, mine)) return false;
     __syncthreads();
 #pragma unroll
     for (int u = 0; u < kListPer; ++u)
