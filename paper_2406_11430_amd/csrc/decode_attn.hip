@@ -185,7 +185,9 @@ DecodePlan decode_plan(int32_t B, int32_t Hkv, int32_t group, int64_t kv_len, in
                                     : each + (0.01 * pairs + (group <= 4 ? 0.06 : 0.05)) * splits;
             };
             double least = by_long_rows ? 1e9 : (pairs == 1 || long_rows ? 0.95 : 0.86) * cost((blocks + want - 1) / want, want);
-            for (int64_t each = (blocks + most - 1) / most, splits; (splits = (blocks + each - 1) / each) > kDecodeNarrowSplits; ++each)
+            // all splits together cost less than 32 steps, so that longer streams need not be tried
+            const int64_t shortest = (blocks + most - 1) / most;
+            for (int64_t each = shortest, splits; each < shortest + 32 && (splits = (blocks + each - 1) / each) > kDecodeNarrowSplits; ++each)
                 if (cost(each, splits) < least) least = cost(each, splits), want = splits;
         }
     }
