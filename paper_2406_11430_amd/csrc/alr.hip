@@ -47,6 +47,7 @@
 #include "digit_search.hpp"
 #include "l2kv_device.hpp"
 #include "l2kv_host.hpp"
+#include "position_blocks.hpp"
 
 #include <cstddef>
 #include <type_traits>
@@ -1565,22 +1566,20 @@ __device__ __forceinline__ PositionSums position_sums(uint32_t* logits, const in
 // The same for heads whose logits are in registers, where a share takes whole blocks of 1024 positions: nothing but the ranks is
 // fetched, and those are on their way while the range of the logits is found.
 template <int E> struct RegisterSums {
-    // Block e is in slot e % kSlots.  A share has at most 19452 elements (share_plan), heads of more than 20 blocks at least two shares.
-    static constexpr int kSlots = E <= kListPer ? E : (E + 1) / 2;
+    // A share has at most 19452 elements (share_plan), heads of more than 20 blocks at least two shares.
+    static constexpr uint32_t kSlots = E <= kListPer ? E : (E + 1) / 2;
     static_assert(E <= 2 * kListPer, "at most two shares' blocks");
     __amdgpu_buffer_rsrc_t rank;                                      // reads zero past the end
-    uint32_t n, first, end;                                           // blocks of the share
+    uint32_t n;
+    PositionBlocks<kSlots> blocks;
     int32_t rk[kSlots];
-    __device__ __forceinline__ RegisterSums(const int32_t* r, uint32_t count, uint32_t share, uint32_t shares) : n(count) {
+    __device__ __forceinline__ RegisterSums(const int32_t* r, uint32_t count, uint32_t share, uint32_t shares)
+        : n(count), blocks((count + kSortLanes - 1) / kSortLanes, share, shares) {
         rank = __builtin_amdgcn_make_buffer_rsrc(const_cast<int32_t*>(r), 0, (int)(n * sizeof(int32_t)), kRawBufferWord3);
-        const uint32_t blocks = (n + kSortLanes - 1) / kSortLanes;
-        first = share * blocks / shares;
-        end = (share + 1) * blocks / shares;
+        // all of the offset per lane: that is what is checked against the end of the head
 #pragma unroll
-        for (uint32_t j = 0; j < kSlots; ++j) {
-            const uint32_t block = first + (j + kSlots - first % kSlots) % kSlots;
-            rk[j] = __builtin_amdgcn_raw_buffer_load_b32(rank, threadIdx.x * sizeof(int32_t), block * (kSortLanes * sizeof(int32_t)), kBufferPolicyPlain);
-        }
+        for (uint32_t j = 0; j < kSlots; ++j)
+            rk[j] = __builtin_amdgcn_raw_buffer_load_b32(rank, (blocks.in_slot(j) * kSortLanes + threadIdx.x) * sizeof(int32_t), 0, kBufferPolicyPlain);
     }
     template <typename Keys>
     __device__ __forceinline__ PositionSums add_up(const Keys& keys, int64_t m, float mx, bool equal, RankedSums& ranked) {
@@ -1590,7 +1589,7 @@ template <int E> struct RegisterSums {
         const int32_t dropped = m < INT32_MAX ? (int32_t)m : INT32_MAX;
 #pragma unroll
         for (uint32_t e = 0; e < (uint32_t)E; ++e) {
-            if (e - first < end - first) {                            // the same for all lanes
+            if (blocks.has(e)) {                                      // the same for all lanes
                 const double x = (int32_t)left > (int32_t)(e * kSortLanes) ? score(keys.reg[e], mx) : 0.0;
                 const int32_t r = rk[e % kSlots];
                 sums.all += x;
@@ -1599,7 +1598,7 @@ template <int E> struct RegisterSums {
             }
         }
         if (equal) {
-            for (uint32_t t = first * kSortLanes + threadIdx.x; t < end * kSortLanes && t < n; t += kSortLanes) add_ranked(ranked, score(mx, mx), t, m);
+            for (uint32_t t = blocks.first * kSortLanes + threadIdx.x; t < blocks.end * kSortLanes && t < n; t += kSortLanes) add_ranked(ranked, score(mx, mx), t, m);
         }
         return sums;
     }
