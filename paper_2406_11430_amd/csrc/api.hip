@@ -222,7 +222,7 @@ l2kv_status l2kv_decode_attn_splits(const void* Q, const void* Kc, const void* V
     if (st != L2KV_OK) return st;
     if (!aligned(workspace, 16)) return L2KV_ERR_ALIGN;
     const float s = scale > 0.f ? scale : 1.0f / std::sqrt(static_cast<float>(D));
-    const DecodePlan plan = decode_plan(B, Hkv, Hq / Hkv, kv_len, D * elem_bytes(dt), n_splits);
+    const DecodePlan plan = decode_plan(B, Hkv, Hq / Hkv, kv_len, D, elem_bytes(dt), n_splits);
     return decode_dispatch(Q, Kc, Vc, dt, B, Hq, Hkv, kv_len, D, kv_head_stride, nullptr, nullptr, nullptr, s,
                            plan, O, workspace, static_cast<hipStream_t>(stream));
 }
@@ -240,7 +240,7 @@ l2kv_status l2kv_decode_attn_out(const void* Q, const void* Kc, const void* Vc, 
     if (st != L2KV_OK) return st;
     if (!aligned(workspace, 16)) return L2KV_ERR_ALIGN;
     const float s = scale > 0.f ? scale : 1.0f / std::sqrt(static_cast<float>(D));
-    DecodePlan plan = decode_plan(B, Hkv, Hq / Hkv, kv_len, D * elem_bytes(dt), 0);
+    DecodePlan plan = decode_plan(B, Hkv, Hq / Hkv, kv_len, D, elem_bytes(dt), 0);
     plan.out_bf16 = out_dt == L2KV_BF16 ? 1 : 0;
     return decode_dispatch(Q, Kc, Vc, dt, B, Hq, Hkv, kv_len, D, kv_head_stride, nullptr, nullptr, nullptr, s,
                            plan, static_cast<float*>(O), workspace, static_cast<hipStream_t>(stream));
@@ -253,18 +253,9 @@ l2kv_status l2kv_decode_attn_static(const void* Q, const void* Kc, const void* V
         st != L2KV_OK)
         return st;
     const float s = scale > 0.f ? scale : 1.0f / std::sqrt(static_cast<float>(D));
-    DecodePlan plan = decode_plan(B, Hkv, Hq / Hkv, kv_len, D * elem_bytes(dt), 0);
-    // counters + the partials of the workgroups this launch really has
-    const auto bytes_for = [&](int32_t splits) {
-        return decode_counter_bytes(B, Hkv) + static_cast<size_t>(B) * static_cast<size_t>(Hq) * static_cast<size_t>(splits) *
-                                                  decode_partial_floats(D) * sizeof(float);
-    };
-    size_t need = bytes_for(plan.n_splits);
-    if (need > static_cast<size_t>(L2KV_STATIC_SCRATCH_BYTES) && plan.fewest_splits > 0) {
-        plan.n_splits = plan.fewest_splits;
-        need = bytes_for(plan.n_splits);
-    }
-    if (need > static_cast<size_t>(L2KV_STATIC_SCRATCH_BYTES)) return L2KV_ERR_WORKSPACE;
+    const DecodePlan plan = decode_plan(B, Hkv, Hq / Hkv, kv_len, D, elem_bytes(dt), 0);
+    if (decode_scratch_bytes(B, Hkv, Hq / Hkv, plan.n_splits, D) > static_cast<size_t>(L2KV_STATIC_SCRATCH_BYTES))
+        return L2KV_ERR_WORKSPACE;
     l2kv_status st = L2KV_OK;
     void* scratch_ptr = decode_static_scratch(static_cast<hipStream_t>(stream), &st);
     if (scratch_ptr == nullptr) return st;

@@ -19,8 +19,9 @@ int32_t decode_max_splits(int64_t kv_len) {
     return (int32_t)(by_rows < kDecodeMaxSplits ? by_rows : kDecodeMaxSplits);
 }
 
-DecodePlan decode_plan(int32_t B, int32_t Hkv, int32_t group, int64_t kv_len, int32_t row_bytes, int32_t requested_splits) {
+DecodePlan decode_plan(int32_t B, int32_t Hkv, int32_t group, int64_t kv_len, int32_t D, int32_t elem_bytes, int32_t requested_splits) {
     const int64_t pairs = (int64_t)B * Hkv;
+    const int32_t row_bytes = D * elem_bytes;
     const int64_t cap = decode_max_splits(kv_len);
     int64_t want = requested_splits;
     DecodePlan plan;
@@ -61,7 +62,11 @@ DecodePlan decode_plan(int32_t B, int32_t Hkv, int32_t group, int64_t kv_len, in
         } else if (group >= 5 && !long_rows && 3 * pairs > cus && 21 * pairs <= 8 * cus && kb >= 1024) {
             fuller = 5;
         }
-        if (want == 1 && fuller > 1) plan.fewest_splits = 1;
+        // l2kv_decode_attn_static takes the same splits, so their partial results have to fit its scratch memory.  Those of 513 to 597 heads
+        // with 6 and more query heads (5 from 530 heads on; rows of 256 elements: 3 and more), and of 331 to 341 with 8, do not; one workgroup
+        // each costs them little: bf16 rows of 128, 544 of 4096 with 8 219 in place of 199, 560 of 2600 with 6 151 / 135, 336 of 2048 with 8
+        // 75.9 / 69.8; of 256, 513 of 1500 with 4 147.5 / 148.8.
+        if (fuller > want && decode_scratch_bytes(B, Hkv, group, (int32_t)fuller, D) > L2KV_STATIC_SCRATCH_BYTES) fuller = want;
         want = fuller;
         // With very few heads that rule asks for so many workgroups per head that
         // the final merge (about 0.2 us per workgroup) outweighs the shorter

@@ -67,7 +67,6 @@ l2kv_status compact_dispatch(const void* K, const void* V, l2kv_dtype dt, const 
 // n_splits workgroups take turns on consecutive 64-row blocks.
 struct DecodePlan {
     int32_t n_splits = 1;      // workgroups launched per KV head; work list: pieces of a sequence there is room for
-    int32_t fewest_splits = 0; // > 0: what also does, where the partial results of n_splits find no room
     int32_t rows_per_wg = 1;   // ragged batches: a sequence of n rows employs ceil(n / rows_per_wg) of them
     int32_t worklist_wgs = 0;  // > 0: ordered ragged batch, this many workgroups draw items from a device-side list
     int32_t pieces = 1;        // work list: pieces of the longest sequence, as far as the host knows its length
@@ -88,11 +87,16 @@ inline size_t decode_counter_bytes(int32_t B, int32_t Hkv) {
 // One split partial = D accumulator floats, the running maximum, the denominator and two floats
 // of padding, so that every partial row starts on a 16-byte boundary and belongs to one workgroup.
 inline size_t decode_partial_floats(int32_t D) { return static_cast<size_t>(D) + 4; }
+// Counters, and the partials of the workgroups that a launch of n_splits per KV head has.
+inline size_t decode_scratch_bytes(int32_t B, int32_t Hkv, int32_t group, int32_t n_splits, int32_t D) {
+    return decode_counter_bytes(B, Hkv) + static_cast<size_t>(B) * static_cast<size_t>(Hkv) * static_cast<size_t>(group) *
+                                              static_cast<size_t>(n_splits) * decode_partial_floats(D) * sizeof(float);
+}
 l2kv_status workspace_init_dispatch(void* workspace, size_t bytes, hipStream_t stream);
 // Device address of the library's own scratch array on the current device (set up on first use,
 // which enqueues one fill kernel on `stream`); nullptr with *status set on failure.
 void* decode_static_scratch(hipStream_t stream, l2kv_status* status);
-DecodePlan decode_plan(int32_t B, int32_t Hkv, int32_t group, int64_t kv_len, int32_t row_bytes, int32_t requested_splits);
+DecodePlan decode_plan(int32_t B, int32_t Hkv, int32_t group, int64_t kv_len, int32_t D, int32_t elem_bytes, int32_t requested_splits);
 DecodePlan decode_plan_ragged(int32_t n_seq, int32_t Hkv, int64_t max_len, int64_t total_slots, int32_t requested_splits,
                               bool ordered);
 

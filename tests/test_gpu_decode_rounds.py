@@ -51,3 +51,12 @@ def test_without_a_workspace(G, splits):
     binding.l2kv_decode_attn_static(Q, K, V, O)
     binding.l2kv_decode_attn_splits(Q, K, V, want, ws, n_splits=splits)
     assert torch.equal(O, want)
+
+
+@pytest.mark.parametrize("dtype,D,G,heads,n", [(torch.bfloat16, 128, 8, 544, 4096), (torch.bfloat16, 256, 4, 513, 1500), (torch.float32, 128, 5, 530, 2600), (torch.bfloat16, 128, 8, 331, 2048)])
+def test_same_without_a_workspace(dtype, D, G, heads, n):
+    Q, K, V, ws = operands(dtype, D, G, heads, n)
+    O, want = (torch.full((1, heads * G, D), float("nan"), device=Q.device) for _ in range(2))
+    binding.l2kv_decode_attn_static(Q, K, V, O)
+    l2kv.l2kv_decode_attn(Q, K, V, want, ws)
+    assert torch.equal(O, want)
