@@ -105,6 +105,34 @@ __device__ __forceinline__ void publish(float* p, float v) {
     __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+// Counters in the workspace.  A call of another shape may have left its partial results where this one's counters are, so a count
+// is told from everything else by its bits: kCountFrom + n, a signalling NaN, which no instruction ever returns.  Between the calls
+// a counter is zero.  open_count() makes a count of zero out of anything but a count and the NaNs above them; one workgroup does it at
+// its start, and the answer comes while the rows are streamed.  What is not a count even so (those NaNs, or nobody has opened
+// it yet) is replaced by the first that finds it; the others, whose additions went with it, count again.
+// Sound whatever is found, and nobody waits: an exchange fails only because another workgroup has been there, which happens
+// twice for each of them at most.  us, plain counters / opened so / by every workgroup ahead of its partial results: 24 workgroups for each of
+// 8 heads 14.56 / 14.60 / 15.23, 6 for each of 32 9.78 / 9.83 / 10.1, 12 for each of 16 of fp32 rows 17.11 / 17.13 / 17.94.
+constexpr uint32_t kCountFrom = 0xff800001u;
+static_assert(kCountFrom + kDecodeMostCounted == 0xffbfffffu, "the signalling NaNs with a sign");
+__device__ __forceinline__ bool is_count(uint32_t word) { return word - kCountFrom <= kDecodeMostCounted; }
+__device__ __forceinline__ void open_count(uint32_t* counter) {
+    (void)__hip_atomic_fetch_max(counter, kCountFrom, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ uint32_t add_to_count(uint32_t* counter) {
+    return __hip_atomic_fetch_add(counter, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+// How many were there before; `old`: what add_to_count() returned.
+__device__ __forceinline__ uint32_t counted_before(uint32_t* counter, uint32_t old) {
+    if (__builtin_expect(is_count(old), true)) return old - kCountFrom;
+    uint32_t seen = old + 1u;
+    while (!is_count(seen)) {
+        if (__hip_atomic_compare_exchange_strong(counter, &seen, kCountFrom + 1u, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+            return 0u;
+    }
+    return add_to_count(counter) - kCountFrom;
+}
+
 // Device-scope loads of the published values: buffer loads with the cache policy (sc1) the
 // compiler emits for an agent-scope atomic load of one dword, 16, 8 or 4 bytes wide.  `region`
 // describes the bytes that may be read (the hardware returns zero outside it); offsets are
@@ -295,6 +323,7 @@ __device__ __forceinline__ void decode_item(const char* __restrict__ Q, const ch
     __shared__ uint32_t s_ticket;
     __shared__ float s_max[G];                   // per query head: maximum of the workgroups' m (final merge)
     if (threadIdx.x < G) s_max[threadIdx.x] = -INFINITY;       // ordered before its use by the barriers below
+    if (split != 0 && split == n_splits - 1 && threadIdx.x == 0) open_count(counter);     // it has the fewest rows
     float* const s_acc = s_raw;                                          // [(grp * G + g) * D + d]
     float* const s_m = s_raw + kAccFloats;                               // [grp * G + g]
     float* const s_l = s_m + kGroups * G;
@@ -651,8 +680,7 @@ __device__ __forceinline__ void decode_item(const char* __restrict__ Q, const ch
     // Work-list launches draw the workgroup's next item here, when its rows have been streamed:
     // early enough for the counter's latency to hide behind the merge below, late enough that
     // items are still handed out in the order in which workgroups become free.
-    if (queue != nullptr && threadIdx.x == 0)
-        drawn = gridDim.x + __hip_atomic_fetch_add(queue, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (queue != nullptr && threadIdx.x == 0) drawn = add_to_count(queue);
 
     // ---- merge the 16 row groups of the workgroup through LDS --------------
     if constexpr (kMfma) __syncthreads();          // every wave is done with its buffers in that array
@@ -743,7 +771,7 @@ __device__ __forceinline__ void decode_item(const char* __restrict__ Q, const ch
     __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);
     __syncthreads();
     if (threadIdx.x == 0)
-        s_ticket = __hip_atomic_fetch_add(counter, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        s_ticket = counted_before(counter, add_to_count(counter));
     __syncthreads();
     if (s_ticket != (uint32_t)(n_splits - 1)) return;
 
@@ -1105,7 +1133,12 @@ void decode_worklist_kernel(const char* __restrict__ Q, const char* __restrict__
         }
     }
     const uint32_t n_items = (uint32_t)n_seq * (uint32_t)Hkv * (uint32_t)pieces;
-    uint32_t drawn = 0;                                   // thread 0 only: the item drawn ahead
+    // The queue's words are counts as well, opened by the workgroup whose first item is the shortest (all at once would queue up).
+    if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) {
+        open_count(&queue[0]);
+        open_count(&queue[1]);
+    }
+    uint32_t drawn = 0;                                   // thread 0 only: what the counter was when the next item was drawn ahead
     while (item < n_items) {
         const int split = at.split, hkv = at.hkv;
         const int pair = at.pos * Hkv + hkv;              // as in the grid launch
@@ -1115,15 +1148,14 @@ void decode_worklist_kernel(const char* __restrict__ Q, const char* __restrict__
         const int need = (int)(((uint32_t)kv_len + (uint32_t)rows_per_wg - 1u) / (uint32_t)rows_per_wg);   // kv_len is a clamped int32 here
         const int n_splits = need < 1 ? 1 : (need < pieces ? need : pieces);
         if (split >= n_splits) {                          // uniform: the whole workgroup skips the item
-            if (threadIdx.x == 0)
-                drawn = gridDim.x + __hip_atomic_fetch_add(&queue[0], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (threadIdx.x == 0) drawn = add_to_count(&queue[0]);
         } else {
             const int64_t hq0 = (int64_t)b * Hq + (int64_t)hkv * G;
             decode_item<E, D, G, kWideMerge, false>(Q, Kc + slab, Vc + slab, kv_len, hq0, split, n_splits, n_splits_grid,
                                                     scale_log2e, counters + pair,
                                                     partial + (int64_t)pair * (G * partial_floats<D>) * n_splits_grid, O, out_bf16, &queue[0], drawn);
         }
-        if (threadIdx.x == 0) s_item = drawn;
+        if (threadIdx.x == 0) s_item = gridDim.x + counted_before(&queue[0], drawn);
         __syncthreads();
         item = s_item;
         __syncthreads();                                  // everyone has read s_item before it is rewritten
@@ -1136,7 +1168,8 @@ void decode_worklist_kernel(const char* __restrict__ Q, const char* __restrict__
     if (threadIdx.x == 0) {
         // every draw of this workgroup has returned (its value was used above), so the workgroup
         // that finds all others gone may reset the queue
-        const uint32_t gone = __hip_atomic_fetch_add(&queue[1], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);          // neither is the queue opened any more
+        const uint32_t gone = counted_before(&queue[1], add_to_count(&queue[1]));
         if (gone == gridDim.x - 1) {
             __hip_atomic_store(&queue[0], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             __hip_atomic_store(&queue[1], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);

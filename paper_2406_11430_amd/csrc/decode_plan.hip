@@ -158,7 +158,7 @@ DecodePlan decode_plan_ragged(int32_t n_seq, int32_t Hkv, int64_t max_len, int64
         }
         if (plan.rule.most == 0) plan.pieces = (int32_t)(want < cap ? want : cap);
         const int64_t items = pairs * (want < cap ? want : cap);
-        plan.worklist_wgs = (int32_t)(items < cus ? items : cus);
+        if (items <= kDecodeMostCounted) plan.worklist_wgs = (int32_t)(items < cus ? items : cus);     // more, by the caller's count alone: a grid
     } else if (want <= 0) {
         // Lengths differ, so the launch relies on the hardware handing out more
         // workgroups than fit at once: about 1024 rows per workgroup, and never

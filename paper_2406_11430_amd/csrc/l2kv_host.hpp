@@ -84,6 +84,8 @@ inline size_t decode_counter_bytes(int32_t B, int32_t Hkv) {
     const size_t raw = (static_cast<size_t>(B) * static_cast<size_t>(Hkv) + 2) * sizeof(uint32_t);
     return (raw + 255) / 256 * 256;
 }
+// What a counter can count to (decode_kernels.hpp): the items of a work list.
+constexpr uint32_t kDecodeMostCounted = 0x3ffffe;
 // One split partial = D accumulator floats, the running maximum, the denominator and two floats
 // of padding, so that every partial row starts on a 16-byte boundary and belongs to one workgroup.
 inline size_t decode_partial_floats(int32_t D) { return static_cast<size_t>(D) + 4; }
