@@ -107,12 +107,12 @@ __device__ __forceinline__ void publish(float* p, float v) {
 
 // Counters in the workspace.  A call of another shape may have left its partial results where this one's counters are, so a count
 // is told from everything else by its bits: kCountFrom + n, a signalling NaN, which no instruction ever returns.  Between the calls
-// a counter is zero.  open_count() makes a count of zero out of anything but a count and the NaNs above them; one workgroup does it at
-// its start, and the answer comes while the rows are streamed.  What is not a count even so (those NaNs, or nobody has opened
-// it yet) is replaced by the first that finds it; the others, whose additions went with it, count again.
+// a counter is zero.  open_count() makes a count of zero out of anything but a count and the NaNs above them; one workgroup does it
+// behind its first loads, and the answer comes while the rows are streamed.  What is not a count even so (those NaNs, or nobody has
+// opened it yet) is replaced by the first that finds it; the others, whose additions went with it, count again.
 // Sound whatever is found, and nobody waits: an exchange fails only because another workgroup has been there, which happens
-// twice for each of them at most.  us, plain counters / opened so / by every workgroup ahead of its partial results: 24 workgroups for each of
-// 8 heads 14.56 / 14.60 / 15.23, 6 for each of 32 9.78 / 9.83 / 10.1, 12 for each of 16 of fp32 rows 17.11 / 17.13 / 17.94.
+// twice for each of them at most.  us, plain counters / opened so / ahead of the first loads / by every workgroup ahead of its partial results:
+// 24 workgroups for each of 8 heads 13.29 / 13.36 / 13.38 / 14.0, 6 for each of 32 8.87 / 8.91 / 8.93 / 9.2; never opened 2 to 7 us more.
 constexpr uint32_t kCountFrom = 0xff800001u;
 static_assert(kCountFrom + kDecodeMostCounted == 0xffbfffffu, "the signalling NaNs with a sign");
 __device__ __forceinline__ bool is_count(uint32_t word) { return word - kCountFrom <= kDecodeMostCounted; }
@@ -122,15 +122,17 @@ __device__ __forceinline__ void open_count(uint32_t* counter) {
 __device__ __forceinline__ uint32_t add_to_count(uint32_t* counter) {
     return __hip_atomic_fetch_add(counter, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-// How many were there before; `old`: what add_to_count() returned.
-__device__ __forceinline__ uint32_t counted_before(uint32_t* counter, uint32_t old) {
-    if (__builtin_expect(is_count(old), true)) return old - kCountFrom;
+// The count before this one was added to it, where `old`, which add_to_count() returned, is not a count.
+__device__ __forceinline__ uint32_t count_again(uint32_t* counter, uint32_t old) {
     uint32_t seen = old + 1u;
     while (!is_count(seen)) {
         if (__hip_atomic_compare_exchange_strong(counter, &seen, kCountFrom + 1u, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
-            return 0u;
+            return kCountFrom;
     }
-    return add_to_count(counter) - kCountFrom;
+    return add_to_count(counter);
+}
+__device__ __forceinline__ uint32_t counted_before(uint32_t* counter, uint32_t old) {
+    return (__builtin_expect(is_count(old), true) ? old : count_again(counter, old)) - kCountFrom;
 }
 
 // Device-scope loads of the published values: buffer loads with the cache policy (sc1) the
@@ -323,7 +325,6 @@ __device__ __forceinline__ void decode_item(const char* __restrict__ Q, const ch
     __shared__ uint32_t s_ticket;
     __shared__ float s_max[G];                   // per query head: maximum of the workgroups' m (final merge)
     if (threadIdx.x < G) s_max[threadIdx.x] = -INFINITY;       // ordered before its use by the barriers below
-    if (split != 0 && split == n_splits - 1 && threadIdx.x == 0) open_count(counter);     // it has the fewest rows
     float* const s_acc = s_raw;                                          // [(grp * G + g) * D + d]
     float* const s_m = s_raw + kAccFloats;                               // [grp * G + g]
     float* const s_l = s_m + kGroups * G;
@@ -613,6 +614,7 @@ __device__ __forceinline__ void decode_item(const char* __restrict__ Q, const ch
         int tile = split * kDecWaves + wave;                                     // my next tile
         const int64_t kStride = (int64_t)tile_stride * Geo::kTileRows;          // rows between my tiles
         int64_t row = (int64_t)tile * Geo::kTileRows;
+        const bool opens = split != 0 && split == n_splits - 1 && threadIdx.x == 0;     // the workgroup with the fewest rows
         if (tile < n_full) {
             Tile<E, D> ta, tb;
             // The scheduling barriers pin each batch of loads ahead of the
@@ -620,6 +622,7 @@ __device__ __forceinline__ void decode_item(const char* __restrict__ Q, const ch
             // the loads next to their first use and the prefetch is lost.
             load_tile<E, D>(ta, Kh, Vh, row, lane_off);
             __builtin_amdgcn_sched_barrier(0);
+            if (opens) open_count(counter);
             while (tile + 2 * tile_stride < n_full) {    // ta holds `tile`; at least two more follow
                 load_tile<E, D>(tb, Kh, Vh, row + kStride, lane_off);
                 __builtin_amdgcn_sched_barrier(0);
@@ -642,6 +645,8 @@ __device__ __forceinline__ void decode_item(const char* __restrict__ Q, const ch
                 consume(ta, row, false);
                 tile += tile_stride;
             }
+        } else if (opens) {
+            open_count(counter);
         }
         // `tile` is now the first tile of this wave's sequence at or past the full ones: the
         // ragged last tile of the head, if there is one, belongs to the wave whose sequence hits it
@@ -770,10 +775,16 @@ __device__ __forceinline__ void decode_item(const char* __restrict__ Q, const ch
     // workgroup, so nothing here can hang.
     __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);
     __syncthreads();
-    if (threadIdx.x == 0)
-        s_ticket = counted_before(counter, add_to_count(counter));
+    if (threadIdx.x == 0) s_ticket = add_to_count(counter);
     __syncthreads();
-    if (s_ticket != (uint32_t)(n_splits - 1)) return;
+    const uint32_t last_ticket = kCountFrom + (uint32_t)(n_splits - 1);
+    if (const uint32_t ticket = __builtin_amdgcn_readfirstlane(s_ticket); ticket != last_ticket) {
+        if (__builtin_expect(is_count(ticket), true)) return;
+        __syncthreads();
+        if (threadIdx.x == 0) s_ticket = count_again(counter, ticket);
+        __syncthreads();
+        if (s_ticket != last_ticket) return;
+    }
 
     constexpr int kNarrow = kDecodeNarrowSplits;
     if constexpr (!kWideMerge) {
