@@ -39,9 +39,12 @@ DecodePlan decode_plan(int32_t B, int32_t Hkv, int32_t group, int64_t kv_len, in
         const int64_t target = group >= 5 ? cus : 3 * cus / 4;
         want = (2 * target + pairs) / (2 * pairs);                 // nearest integer to target / pairs
         if (want > 1 && want * pairs > cus) --want;
+        const int64_t blocks = (kv_len + kDecodeRowTile - 1) / kDecodeRowTile;
+        const auto longest_blocks = [&](int64_t splits) { return (blocks + splits - 1) / splits; };
         // Two thirds of the compute units or fewer after rounding leave memory idle; one more split each fits.  us, bf16 rows of 128: 80
-        // heads of 9000 rows 64.4 in 2, 60.4 in 3, with 4 query heads 70.3 / 62.6, of 1100 15.4 / 13.3; 56 of 9000 48.7 in 3, 45.1 in 4.
-        if (group < 5 && 3 * want * pairs <= 2 * cus && (want + 1) * pairs <= cus) ++want;
+        // heads of 9000 rows 64.4 in 2, 60.4 in 3, with 4 query heads 70.3 / 62.6, of 1100 15.4 / 13.3; 56 of 9000 48.7 in 3, 45.1 in 4.  Not
+        // where the longest stream does not get shorter by it: 80 of 248 with 3 7.35 in 2, 7.57 in 3.
+        if (group < 5 && 3 * want * pairs <= 2 * cus && (want + 1) * pairs <= cus && (want == 0 || longest_blocks(want + 1) < longest_blocks(want))) ++want;
         // More heads than that: a head in one workgroup means rounds of all compute units, the last of which may have little to do; in
         // 3 (2, 5) splits the rounds are shorter and fuller.  us, one / three: bf16 rows of 128 of 5000, 136 heads with 8 query
         // heads 92.7 / 68.5, 288 with 4 166 / 131; 288 of 1500 54.2 / 46.5; fp32 rows of 128, 288 of 5000 with 8 354 / 270; of 64 bf16,
@@ -85,8 +88,7 @@ DecodePlan decode_plan(int32_t B, int32_t Hkv, int32_t group, int64_t kv_len, in
         // time, so often not at all), for one or two heads not beyond 384 KB.  bf16 rows of 128, 3 heads of 1615 with 5 query heads 8.8 / 9.4, 8 of
         // 1607 with 6 10.5 / 11.2, 1 of 1804 with 5 6 % slower in 8; fp32 rows of 64, 3 of 1790 with 8 9.3 / 10.3; not longer: fp32 rows of 128, 2 of
         // 929 with 6 10.0 / 9.1.
-        const int64_t blocks = (kv_len + kDecodeRowTile - 1) / kDecodeRowTile;
-        auto longest = [&](int64_t splits) { return (blocks + splits - 1) / splits * kDecodeRowTile * row_bytes; };
+        auto longest = [&](int64_t splits) { return longest_blocks(splits) * kDecodeRowTile * row_bytes; };
         bool short_head = group < 5 ? k_bytes <= int64_t{384} << 10 : k_bytes <= int64_t{512} << 10 && kv_len <= 3072;
         if (short_head && group >= 5 && pairs < 12 && want > kDecodeNarrowSplits) {
             const int64_t longer = longest(kDecodeNarrowSplits) - longest(want);
@@ -97,7 +99,9 @@ DecodePlan decode_plan(int32_t B, int32_t Hkv, int32_t group, int64_t kv_len, in
         // results takes longer than the tiles that the other workgroups would have read.  us, split as above / in 1: bf16 rows of 128, 32
         // heads of 83 rows 4.6 / 3.2, 8 of 175 4.3 / 3.4; of 64, 128 of 88 with 4 query heads 6.3 / 4.4; fp32 rows of 64, 128 of 184 with 3
         // 6.7 / 5.7; 4 of 256, 4.2 / 3.3.  Not for more tiles or query heads: bf16 rows of 128, 8 of 189 with 4 5.9 / 6.3; of 256, 8 of 128
-        // with 4 7.1 / 7.3.
+        // with 4 7.1 / 7.3.  That is with rows in the caches, as after a compression, where three and four tiles gain 2 to 37 %.  From memory,
+        // where every second tile is one more round trip, three whole tiles gain 3 to 18 % for up to 192 heads, four from 9 % less (2 heads) to
+        // 10 % more, and a last tile that is not whole costs 5 %.
         const int64_t tile_rows = row_bytes <= 128 ? 2 * kDecodeRowTile : kDecodeRowTile;      // of the four waves
         const int64_t tiles = (kv_len + tile_rows - 1) / tile_rows;
         if (tiles <= 2 ? !long_rows || group <= 3 : !long_rows && (tiles == 3 ? group <= 3 : tiles == 4 && group <= 2)) want = 1;
@@ -122,7 +126,9 @@ DecodePlan decode_plan(int32_t B, int32_t Hkv, int32_t group, int64_t kv_len, in
             };
             double least = by_long_rows ? 1e9 : (pairs == 1 || long_rows ? 0.95 : 0.86) * cost((blocks + want - 1) / want, want);
             // all splits together cost less than 32 steps, so that longer streams need not be tried
-            const int64_t shortest = (blocks + most - 1) / most;
+            // More than 32 partial results of 256 elements are merged in two round trips, which streams of one block each do not make up
+            // for: bf16, 4 heads of 2826 rows with 2 query heads 45 splits 0.91 of the speed of 18 and 0.85 of that of 23, 3 of 2886 with 2 0.89 of that of 23; 1 of 2155 1.04.
+            const int64_t shortest = std::max<int64_t>(longest_blocks(most), D == 256 && pairs > 2 && blocks > 32 ? 2 : 1);
             for (int64_t each = shortest, splits; each < shortest + 32 && (splits = (blocks + each - 1) / each) > kDecodeNarrowSplits; ++each)
                 if (cost(each, splits) < least) least = cost(each, splits), want = splits;
         }

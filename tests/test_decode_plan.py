@@ -51,6 +51,18 @@ def test_without_a_workspace(lib, D, bytes, most):
 
 
 @pytest.mark.parametrize("heads,group,rows,D,bytes,n", [
+    (80, 3, 256, 128, 2, 2), (80, 3, 257, 128, 2, 3), (56, 1, 384, 128, 2, 3), (56, 1, 385, 128, 2, 4), (56, 4, 576, 128, 4, 3)])
+def test_one_more_split_shortens_the_longest(lib, heads, group, rows, D, bytes, n):
+    assert lib.splits(heads, group, rows, D, bytes) == n
+
+
+@pytest.mark.parametrize("heads,group,rows,D,bytes,n", [
+    (4, 2, 2048, 256, 2, 32), (4, 2, 2049, 256, 2, 17), (4, 2, 2826, 256, 2, 23), (3, 4, 2826, 256, 2, 23), (2, 2, 2826, 256, 2, 45), (4, 2, 2826, 128, 4, 45)])
+def test_streams_behind_two_round_trips(lib, heads, group, rows, D, bytes, n):
+    assert lib.splits(heads, group, rows, D, bytes) == n
+
+
+@pytest.mark.parametrize("heads,group,rows,D,bytes,n", [
     (544, 8, 4096, 128, 2, 1), (513, 6, 2600, 128, 2, 1), (513, 3, 1500, 256, 2, 1), (576, 5, 4096, 128, 2, 1), (529, 5, 4096, 128, 2, 3),
     (530, 5, 4096, 128, 2, 1), (330, 8, 2048, 128, 2, 3), (331, 8, 2048, 128, 2, 1), (597, 4, 4096, 128, 2, 3)])
 def test_three_where_they_fit(lib, heads, group, rows, D, bytes, n):
