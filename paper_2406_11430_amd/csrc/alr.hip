@@ -48,6 +48,7 @@
 #include "l2kv_device.hpp"
 #include "l2kv_host.hpp"
 #include "position_blocks.hpp"
+#include "rank_shares.hpp"
 
 #include <cstddef>
 #include <type_traits>
@@ -55,7 +56,6 @@
 namespace l2kv {
 namespace {
 
-constexpr int kSortLanes = 1024;
 constexpr int kSortWaves = kSortLanes / kWaveSize;
 constexpr int kRadixBits = 8;
 constexpr int kBins = 1 << kRadixBits;
@@ -188,10 +188,6 @@ __device__ void radix_pass(const uint32_t* in_key, const uint32_t* in_val, uint3
 constexpr int kBinBits = 12;
 constexpr int kRankBins = 1 << kBinBits;             // 4 per lane
 static_assert(kRankBins == 4 * kSortLanes, "prefix sums take four bins per lane");
-constexpr int kListPer = 20;                         // 4-byte words of the LDS list per lane
-constexpr int kListWords = kListPer * kSortLanes;    // 80 KB
-constexpr int kListAhead = 4;                        // words read past the last element of a share
-constexpr uint32_t kMaxBin = 1024;                   // elements of one bin of a head that is cut along bins
 constexpr uint32_t kLongHead = 1 << 17;              // keys from which the counters of the bins have copies
 constexpr int kDppWaveShl1 = 0x130;                  // lane i <- lane i + 1; the last lane keeps its own
 constexpr uint32_t kMaxFine = 64;                    // elements of a finer bin that are compared with each other
@@ -776,7 +772,8 @@ struct ScoreBins {
 constexpr int kScoreBinsPer = 20;                    // per lane
 constexpr uint32_t kScoreBins = kScoreBinsPer * kSortLanes;
 static_assert(ScoreBins::kHalf * 2 == kScoreBins * 4, "a counter per bin");
-constexpr uint32_t kRunWords = (kListFront + 19452 + kMaxOfBin + 31) / 32 * 32;      // a share, and what its last bin brings with it
+constexpr uint32_t kRunWords = (kListFront + kLongestShare + kMaxOfBin + 31) / 32 * 32;      // a share, and what its last bin brings with it
+static_assert(kRunWords >= kListFront + kLongestShare + kMaxOfBin && kLongestShare + kMaxOfBin <= kRun * kSortLanes - kRun, "room for the scatter, lanes for the runs");
 struct RunBins {
     uint32_t bin[kScoreBins + 4];                    // one word more than bins
     uint32_t aside[kWaveSize];                       // a word per lane for positions past the end
@@ -837,7 +834,7 @@ __device__ __forceinline__ ScoreRange score_range(const HeadKeys<E, ValueBins>& 
 }
 
 // True: run[] holds the elements of ranks base + kRun * threadIdx.x .., as far as they are among the `count` of the share: the bins
-// that start inside its range of ranks.  False, where some bin of the head holds more than kMaxPieces runs: nothing (all shares alike).
+// that start inside its range of ranks.  False, where some bin of the head holds more than kMaxOfBin elements: nothing (all shares alike).
 // The bins are cleared.  Called by all lanes; the list is free again after the caller's barrier.
 template <int E>
 __device__ __forceinline__ bool order_share(const HeadKeys<E, ValueBins>& keys, const ScoreRange& range, uint32_t share, const Cut& cut,
@@ -1566,9 +1563,7 @@ __device__ __forceinline__ PositionSums position_sums(uint32_t* logits, const in
 // The same for heads whose logits are in registers, where a share takes whole blocks of 1024 positions: nothing but the ranks is
 // fetched, and those are on their way while the range of the logits is found.
 template <int E> struct RegisterSums {
-    // A share has at most 19452 elements (share_plan), heads of more than 20 blocks at least two shares.
-    static constexpr uint32_t kSlots = E <= kListPer ? E : (E + 1) / 2;
-    static_assert(E <= 2 * kListPer, "at most two shares' blocks");
+    static constexpr uint32_t kSlots = position_slots(E);
     __amdgpu_buffer_rsrc_t rank;                                      // reads zero past the end
     uint32_t n;
     PositionBlocks<kSlots> blocks;
@@ -1628,7 +1623,7 @@ __device__ __forceinline__ void write_losses(const double (&acc)[kRecordSums], i
     if (loss_ref != nullptr) loss_ref[head] = acc[4] / acc[0];
 }
 
-// What the ranking of a head's scores keeps in LDS.
+// What the ranking of a head's scores keeps in LDS: with runs 163712 of the 163840 bytes that a compute unit has.
 template <bool kRuns> struct HeadShared {
     union {
         BinShared sh;
@@ -1834,28 +1829,6 @@ void alr_head_passes_kernel(uint32_t* __restrict__ scratch, const int32_t* __res
     if (threadIdx.x == 0) write_losses(acc, head, alr, loss, loss_ref);
 }
 
-// How many workgroups share a head; 0: one workgroup per head and the counting passes.  `list` = elements
-// a share may hold.
-//  - as many as the list needs, less what the last bin of a share may bring with it;
-//  - more while the launch has fewer workgroups than compute units, down to 2048 elements each;
-//  - every share goes over all keys of its head, one head by the passes is one workgroup's, so many long heads
-//    are the passes'.  Norms, ms by shares (distinct norms, 30 % zero) and by the passes: 16 heads of 1M 5.2, 6.4
-//    and 8.4, 7.6; 32 of 1M 9.7, 11.9 and 11.5, 10.0; 64 of 1M 18.2, 23.2 and 16.4, 13.2; 64 of 400k 1.5, 3.9 and 5.9, 4.6;
-//    512 of 131k 1.6, 4.1 and 6.4, 4.7.  Scores: 32 heads of 1M 5.0, 5.9 and 6.0, 6.5; 64 of 1M 10.2, 11.8 and 9.1, 8.7.
-//    Heads of more than kCrowded elements cannot do without the sort of their shares, shorter ones mostly can.
-int64_t share_plan(int64_t n_heads, int64_t T, int64_t list) {
-    constexpr int64_t kLongest = int64_t{1} << 23;     // the records of all shares of a head fit the LDS list
-    constexpr int64_t kCrowded = 3 << 18;
-    if (T > kLongest) return 0;
-    const int64_t full = list - kMaxBin;
-    int64_t shares = (T + full - 1) / full;
-    if (T > kCrowded ? n_heads * shares > 2048 : shares > 64 && n_heads * shares > 4096) return 0;
-    const int64_t fill = (256 + n_heads - 1) / n_heads, most = (T + 2047) / 2048;
-    const int64_t want = fill < most ? fill : most;
-    if (want > shares) shares = want;
-    return n_heads * shares <= 0x7fffffffLL ? shares : 0;      // ceil(T / shares) + kMaxBin <= list
-}
-
 // Heads that are sorted whole in a small workgroup.  Binning takes 100 KB more of LDS, so that half as many run at once, and
 // does not gain on a sort of one or two keys per lane.  Norms, us, by bins / by the counting passes / whole: 16 heads of 300
 // 8.3, 11.0, 6.3 (30 % zero 34.8, 11.1, 6.3); 4096 heads of 300 117, 94, 52; 4096 of 1000 122, 152, 81; 1024 of 2000 37.5,
@@ -1905,7 +1878,7 @@ l2kv_status norm_ranks_dispatch(const float* norms, int64_t n_heads, int64_t T, 
         hipLaunchKernelGGL(kernel, dim3((unsigned)n_heads), dim3(kSortLanes), 0, stream, norms, T, drop_rank);
         return launch_status();
     }
-    const int64_t shares = share_plan(n_heads, T, kListWords / 2 - kListAhead);
+    const int64_t shares = share_plan(n_heads, T, kLongestRankedShare);
     if (shares == 0) {
         hipLaunchKernelGGL(norm_ranks_passes_kernel, dim3((unsigned)n_heads), dim3(kSortLanes), 0, stream, norms, T,
                            static_cast<uint32_t*>(workspace), drop_rank);
@@ -1931,7 +1904,7 @@ l2kv_status alr_dispatch(const void* Q, const void* K, l2kv_dtype dt, const int3
     const float scale_log2e = s * 1.44269504088896340736f;
     float* scores = static_cast<float*>(workspace);
     const int64_t n_heads = (int64_t)B * Hq;
-    const int64_t shares = is_short(n_heads, T) ? 1 : share_plan(n_heads, T, kListWords - kListAhead);
+    const int64_t shares = is_short(n_heads, T) ? 1 : share_plan(n_heads, T, kLongestShare);
     uint32_t* records = shares > 1 ? static_cast<uint32_t*>(workspace) + n_heads * T : nullptr;
     l2kv_status st;
     if (dt == L2KV_BF16 && D == 256)
@@ -1954,13 +1927,13 @@ l2kv_status alr_dispatch(const void* Q, const void* K, l2kv_dtype dt, const int3
                            static_cast<uint32_t*>(workspace), drop_rank, T, G, m, alr, loss, loss_ref);
         return launch_status();
     }
-    // keys per lane: every one costs the same whether it is there or not (12000 tokens at 32: 41.3 us, at 16: 36.6)
-    auto kernel = T <= 8 * kSortLanes    ? alr_head_kernel<8>
-                  : T <= 16 * kSortLanes ? alr_head_kernel<16>
-                  : T <= 20 * kSortLanes ? alr_head_kernel<20>
-                  : T <= 24 * kSortLanes ? alr_head_kernel<24>
-                  : T <= 32 * kSortLanes ? alr_head_kernel<32>
-                                         : alr_head_kernel<0>;
+    const int per = score_keys_per_lane(T);
+    auto kernel = per == 8    ? alr_head_kernel<8>
+                  : per == 16 ? alr_head_kernel<16>
+                  : per == 20 ? alr_head_kernel<20>
+                  : per == 24 ? alr_head_kernel<24>
+                  : per == 32 ? alr_head_kernel<32>
+                              : alr_head_kernel<0>;
     hipLaunchKernelGGL(kernel, dim3((unsigned)(n_heads * shares)), dim3(kSortLanes), 0, stream,
                        static_cast<uint32_t*>(workspace), drop_rank, T, (uint32_t)n_heads, G, Cut((uint32_t)T, (uint32_t)shares), m,
                        alr, loss, loss_ref);
