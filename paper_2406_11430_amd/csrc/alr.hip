@@ -24,10 +24,10 @@
 // gathering: two thirds of the time) and the LDS round trips of the comparisons, so the
 // shares are as few as the LDS list allows until they fill the chip.  (One workgroup per
 // head and four counting passes of 8 bits over global memory, which this replaces, took
-// 196 us for 32 heads of 32k norms and 221 us for 128 heads of scores; now 22 and 30 us.
+// 196 us for 32 heads of 32k norms and 221 us for 128 heads of scores; now 21 and 28 us.
 // 131k norms of 8 heads: 671 -> 52 us.)
 // Where the bins do not separate the keys -- more than kMaxBin elements in a bin of the head, more than
-// kMaxFine in a finer one: tied or clustered rows, one outlier that stretches the bins of a long head, heads
+// kMaxFine in a finer one, more than kMaxOfBin in one of the single count: tied or clustered rows, one outlier that stretches the bins of a long head, heads
 // of a million elements -- a share finds the elements of its ranks exactly and sorts them (sorted_range).
 // Short heads are sorted whole, one small workgroup each (is_short, sort_head).  The counting passes, one workgroup per
 // head, remain for many long heads (share_plan).
@@ -469,8 +469,8 @@ __device__ __forceinline__ Share<typename Keys::Bins> find_share(const Keys& key
 // tails of the logits left a few hundred elements in each of the others: 140 us for 128 heads in two shares
 // against 46.  Hits are gathered with one counter update per wave and batch (a ballot and an update per key:
 // 16k cycles of the 48k of a share, now 7k).  Keys and positions lie side by side in the list, so that one LDS access moves both: its
-// issue bounds the gather (32 heads of 32k norms 22.4 -> 22.0 us, 20 equal norms each 34.5 -> 33.1; with the lanes that store named by
-// ballots 23.1).  Equal keys rank by position (kWithPos), else in any order.  Called by all lanes; the
+// issue bounds the gather (32 heads of 32k norms 20.7 -> 20.5 us, 20 equal norms each 29.0 -> 28.0; with the lanes that store named by
+// ballots 0.7 more).  Equal keys rank by position (kWithPos), else in any order.  Called by all lanes; the
 // list is free again after the caller's barrier.
 template <typename Bins> struct FineBins {
     const Share<Bins>& s;
@@ -621,9 +621,9 @@ __device__ __forceinline__ bool rank_share(const Keys& keys, const Share<typenam
 // ranks and adds them up.
 // What bounds it: a key costs 0.2 us per vector instruction and CU (32 keys a lane, four waves a SIMD), and each of its LDS
 // accesses 10 to 20 cycles a wave with its bank conflicts; so a key's way takes a dozen and a half instructions, one atomic and two
-// accesses, all lanes doing the same.  128 heads of 32k logits in two shares each, us: fetch and range 6.9, position sums 1.2, bins 4.7,
+// accesses, all lanes doing the same.  128 heads of 32k logits in two shares each, us by stamps in the kernel, without its launch: fetch and range 6.9, position sums 1.2, bins 4.7,
 // starts 2.1, scatter 3.4, sort 1.4, merge and sums 3.5, records 2.6: 26 in place of 30.5 with the keys counted in 4096 bins of equal width
-// (5.7) and again in 8192 of the share (7.4 with their starts).  Per launch with the logits 76.7 -> 74.4, 32 heads of 9000 24.3 -> 22.4.
+// (5.7) and again in 8192 of the share (7.4 with their starts).  Both launches, with the logits, 74.9 -> 71.7, 32 heads of 9000 23.4 -> 21.5.
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 constexpr int kTogetherKeys = 4;                     // keys whose LDS round trips overlap (8: the same time)

@@ -5,10 +5,10 @@
 // with ties resolved towards the lower token index.
 //
 // The k-th smallest key tau (key = norm bits, complemented for the keep-highest
-// control) is found exactly: the keys are counted in 4096 LDS bins of equal width between the
+// control) is found exactly: the keys are counted in 4096 LDS bins (2048 for heads of at most 2048 tokens) of equal width between the
 // smallest and the largest of the head, and the prefix sums lead to the bin that holds the k-th.  The bin's
 // keys, a few dozen as a rule, are listed and compared with each other; a fuller bin (tied or
-// clustered norms) is divided into 4096 again, at most twice, until its keys are few or equal.
+// clustered norms) is divided into as many again, at most twice, until its keys are few or equal.
 // Bound by the LDS round trips and barriers of that chain, not by its arithmetic: 512 heads
 // of 4k take 8.8 us, 256 of 32k 15.9, 1024 of 32k 65 (three digits of 12, 10 and 10 bits with a prefix sum for
 // each, in 80 KB of LDS and so one workgroup per compute unit: 11.6, 17.3 and 72; heads with an infinite and a
