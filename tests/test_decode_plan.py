@@ -15,6 +15,7 @@ extern "C" int splits(int heads, int group, long rows, int D, int bytes) {
 }
 extern "C" long scratch(int heads, int group, int n_splits, int D) { return (long)l2kv::decode_scratch_bytes(1, heads, group, n_splits, D); }
 extern "C" long limit() { return L2KV_STATIC_SCRATCH_BYTES; }
+extern "C" int work_list(int n_seq, int hkv, long rows, int n_splits) { return l2kv::decode_plan_ragged(n_seq, hkv, rows, rows, n_splits, true).worklist_wgs; }
 extern "C" int max_splits(long rows) { return l2kv::decode_max_splits(rows); }
 """
 ROWS = [(128, 2, 8), (64, 2, 8), (256, 2, 4), (128, 4, 8), (64, 4, 8)]    # elements, bytes each, largest group
@@ -34,6 +35,7 @@ def lib(tmp_path_factory):
     lib.scratch.argtypes, lib.scratch.restype = [C.c_int] * 4, C.c_long
     lib.limit.restype = C.c_long
     lib.max_splits.argtypes = [C.c_long]
+    lib.work_list.argtypes = [C.c_int, C.c_int, C.c_long, C.c_int]
     return lib
 
 
@@ -67,3 +69,8 @@ def test_streams_behind_two_round_trips(lib, heads, group, rows, D, bytes, n):
     (530, 5, 4096, 128, 2, 1), (330, 8, 2048, 128, 2, 3), (331, 8, 2048, 128, 2, 1), (597, 4, 4096, 128, 2, 3)])
 def test_three_where_they_fit(lib, heads, group, rows, D, bytes, n):
     assert lib.splits(heads, group, rows, D, bytes) == n
+
+
+def test_a_work_list_has_no_more_items_than_its_counter_counts(lib):
+    assert lib.work_list(16384, 1, 20000, 255) == 256 and lib.work_list(2048, 8, 20000, 256) == 0
+    assert lib.work_list(65535, 1, 20000, 63) == 256 and lib.work_list(65535, 1, 20000, 65) == 0 and lib.work_list(65535, 1, 20000, 0) == 256
