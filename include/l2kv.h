@@ -208,7 +208,8 @@ l2kv_status l2kv_compress(const void* K, const void* V, l2kv_dtype dt, int64_t n
  * in place by passing the original cache and kv_len = T.
  * Arithmetic: fp32 accumulation throughout; for bf16 caches q.k is formed with
  * the packed bf16 dot instruction (exact bf16 products, fp32 sum), for fp32
- * caches with fp32 FMAs; softmax and the value sum are fp32.
+ * caches with fp32 FMAs; softmax and the value sum are fp32.  (Where several
+ * workgroups share a head, a partial value sum below 2^-141 counts as zero.)
  * Errors: NULL, SHAPE (Hq % Hkv != 0, Hq/Hkv > 8 -- > 4 for D = 256 --,
  * kv_len <= 0, ...), DTYPE, WORKSPACE, ALIGN, LAUNCH.
  */

@@ -402,19 +402,22 @@ l2kv_status l2kv_decode_attn_ragged(const void* Q, const void* Kc, const void* V
         !aligned(workspace, 16) || !aligned(lens, 4) || !aligned(slot_offsets, 8) || !aligned(seq_order, 4))
         return L2KV_ERR_ALIGN;
     const float s = scale > 0.f ? scale : 1.0f / std::sqrt(static_cast<float>(D));
+    int32_t order_from = 0;
     if (seq_order == nullptr && n_splits == 0 && n_seq > 1 && n_seq <= kSelfOrderMaxSeq &&
         max_len >= kSelfOrderMinRows && work_list_rows(dt, D)) {
         // no order from the caller: a longest-first order is worked out here, per call, into the
         // tail of the workspace (a few microseconds; passing a stored order avoids them)
         int32_t* own_order = reinterpret_cast<int32_t*>(static_cast<char*>(workspace) +
                                                         l2kv_decode_workspace_bytes(n_seq, Hq, max_len, D));
-        if (l2kv_status st = length_order_dispatch(lens, n_seq, own_order, static_cast<hipStream_t>(stream));
+        if (l2kv_status st = length_order_dispatch(lens, n_seq, kOwnOrderFrom, own_order, static_cast<hipStream_t>(stream));
             st != L2KV_OK)
             return st;
         seq_order = own_order;
+        order_from = kOwnOrderFrom;
     }
-    const DecodePlan plan = decode_plan_ragged(n_seq, Hkv, max_len, total_slots, n_splits,
-                                               seq_order != nullptr && work_list_rows(dt, D));
+    DecodePlan plan = decode_plan_ragged(n_seq, Hkv, max_len, total_slots, n_splits,
+                                         seq_order != nullptr && work_list_rows(dt, D));
+    plan.order_from = order_from;
     return decode_dispatch(Q, Kc, Vc, dt, n_seq, Hq, Hkv, max_len, D, total_slots * static_cast<int64_t>(D),
                            lens, slot_offsets, seq_order, s, plan, O, workspace,
                            static_cast<hipStream_t>(stream));
@@ -425,7 +428,7 @@ l2kv_status l2kv_length_order(const int32_t* lens, int32_t n_seq, int32_t* order
     if (n_seq <= 0 || n_seq > 65535) return L2KV_ERR_SHAPE;
     if (lens == order) return L2KV_ERR_SHAPE;
     if (!aligned(lens, 4) || !aligned(order, 4)) return L2KV_ERR_ALIGN;
-    return length_order_dispatch(lens, n_seq, order, static_cast<hipStream_t>(stream));
+    return length_order_dispatch(lens, n_seq, 0, order, static_cast<hipStream_t>(stream));
 }
 
 /* ---- attention-loss analysis ---------------------------------------------- */

@@ -105,14 +105,27 @@ __device__ __forceinline__ void publish(float* p, float v) {
     __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// Counters in the workspace.  A call of another shape may have left its partial results where this one's counters are, so a count
-// is told from everything else by its bits: kCountFrom + n, a signalling NaN, which no instruction ever returns.  Between the calls
-// a counter is zero.  open_count() makes a count of zero out of anything but a count and the NaNs above them; one workgroup does it
-// behind its first loads, and the answer comes while the rows are streamed.  What is not a count even so (those NaNs, or nobody has
-// opened it yet) is replaced by the first that finds it; the others, whose additions went with it, count again.
+// Arrival counters in the workspace.  They are zero between the calls, except that a call of another shape may have left its partial
+// results or its order of sequences where this one's counters are: floats and numbers from kDecodeMaxSplits on, since publishable()
+// and kOwnOrderFrom see to it that nothing else is left.  The counter runs down from n - 1 with the decrement that wraps: of zero and of
+// anything above n - 1 it makes n - 1, so that the first arrival finds either, the others n - 1 to 1, and the n-th leaves zero.
+// us, an addition and a store of zero by the merging workgroup / this: 6 workgroups for each of 32 heads 9.94 / 9.56, 24 for each of 8 15.1 / 14.7,
+// 8 heads of 1000 rows of 64 5.70 / 5.36; 3 for each of 330 110 / 105 (counts told apart by their bits, and opened by an
+// atomic maximum at the start of a head, 112).
+__device__ __forceinline__ bool arrive_last(uint32_t* counter, uint32_t n) {
+    return __builtin_amdgcn_atomic_dec32(counter, n - 1u, __ATOMIC_RELAXED, "agent") == 1u;
+}
+// A partial result as it may lie in the workspace: positive numbers below 2^-141, whose bits are those of a count, are zero.
+__device__ __forceinline__ float publishable(float v) {
+    return __builtin_bit_cast(uint32_t, v) - 1u < (uint32_t)kDecodeMaxSplits - 1u ? 0.f : v;
+}
+
+// The two words of a work list count further than that.  A count there is told from everything else by its bits: kCountFrom + n, a
+// signalling NaN, which no instruction ever returns.  open_count() makes a count of zero out of anything but a count and the NaNs above
+// them; one workgroup does it at its start.  What is not a count even so (those NaNs, or nobody has opened it yet) is replaced
+// by the first that finds it; the others, whose additions went with it, count again.
 // Sound whatever is found, and nobody waits: an exchange fails only because another workgroup has been there, which happens
-// twice for each of them at most.  us, plain counters / opened so / ahead of the first loads / by every workgroup ahead of its partial results:
-// 24 workgroups for each of 8 heads 13.29 / 13.36 / 13.38 / 14.0, 6 for each of 32 8.87 / 8.91 / 8.93 / 9.2; never opened 2 to 7 us more.
+// twice for each of them at most.
 constexpr uint32_t kCountFrom = 0xff800001u;
 static_assert(kCountFrom + kDecodeMostCounted == 0xffbfffffu, "the signalling NaNs with a sign");
 __device__ __forceinline__ bool is_count(uint32_t word) { return word - kCountFrom <= kDecodeMostCounted; }
@@ -279,7 +292,8 @@ __device__ __forceinline__ void load_tile_clamped(Tile<E, D>& t, const char* Kh,
 // ordinary vector registers, and the compiler keeps the accumulators of the matrix instructions
 // in vector registers, where the rescaling of the online softmax reaches them without copies from
 // and to the accumulation registers.
-// (fp32, D = 128, 5 query heads: 258 registers otherwise, and one workgroup per compute unit.)
+// (fp32, D = 128, 5 query heads: 258 registers otherwise, and one workgroup runs on a compute unit in place of two: 1000 heads of 400 rows 68.8 us,
+// 64.6 so.)
 template <typename E, int D, int G>
 constexpr bool kDecodeOnMatrixUnit = E::kBytes == 2 && D == 128 && G >= 6;
 template <typename E, int D, int G>
@@ -323,7 +337,7 @@ __device__ __forceinline__ void decode_item(const char* __restrict__ Q, const ch
     constexpr int kTabFloats = 3 * G * kDecodeMaxSplits + kWays * G * D;
     constexpr int kLdsFloats = kAccFloats + 2 * kGroups * G > kTabFloats ? kAccFloats + 2 * kGroups * G : kTabFloats;
     __shared__ __attribute__((aligned(16))) float s_raw[kLdsFloats];
-    __shared__ uint32_t s_ticket;
+    __shared__ bool s_last;
     __shared__ float s_max[G];                   // per query head: maximum of the workgroups' m (final merge)
     if (threadIdx.x < G) s_max[threadIdx.x] = -INFINITY;       // ordered before its use by the barriers below
     float* const s_acc = s_raw;                                          // [(grp * G + g) * D + d]
@@ -619,7 +633,6 @@ __device__ __forceinline__ void decode_item(const char* __restrict__ Q, const ch
         int tile = split * kDecWaves + wave;                                     // my next tile
         const int64_t kStride = (int64_t)tile_stride * Geo::kTileRows;          // rows between my tiles
         int64_t row = (int64_t)tile * Geo::kTileRows;
-        const bool opens = split != 0 && split == n_splits - 1 && threadIdx.x == 0;     // the workgroup with the fewest rows
         if (tile < n_full) {
             Tile<E, D> ta, tb;
             // The scheduling barriers pin each batch of loads ahead of the
@@ -627,7 +640,6 @@ __device__ __forceinline__ void decode_item(const char* __restrict__ Q, const ch
             // the loads next to their first use and the prefetch is lost.
             load_tile<E, D>(ta, Kh, Vh, row, lane_off);
             __builtin_amdgcn_sched_barrier(0);
-            if (opens) open_count(counter);
             while (tile + 2 * tile_stride < n_full) {    // ta holds `tile`; at least two more follow
                 load_tile<E, D>(tb, Kh, Vh, row + kStride, lane_off);
                 __builtin_amdgcn_sched_barrier(0);
@@ -650,8 +662,6 @@ __device__ __forceinline__ void decode_item(const char* __restrict__ Q, const ch
                 consume(ta, row, false);
                 tile += tile_stride;
             }
-        } else if (opens) {
-            open_count(counter);
         }
         // `tile` is now the first tile of this wave's sequence at or past the full ones: the
         // ragged last tile of the head, if there is one, belongs to the wave whose sequence hits it
@@ -760,10 +770,12 @@ __device__ __forceinline__ void decode_item(const char* __restrict__ Q, const ch
             // without any bulk cache write-back.
             float* out = partial + (g * n_splits_grid + split) * kRow;
             const __amdgpu_buffer_rsrc_t row = __builtin_amdgcn_make_buffer_rsrc(out, 0, kRow * (int)sizeof(float), kBufferWord3);
+#pragma unroll
+            for (int k = 0; k < kVec; ++k) num[k] = publishable(num[k]);
             if constexpr (kVec == 4) publish4(row, d * (int)sizeof(float), f32x4{num[0], num[1], num[2], num[3]});
             else if constexpr (kVec == 2) publish2(row, d * (int)sizeof(float), f32x2{num[0], num[1]});
             else publish(out + d, num[0]);
-            if (d == 0) publish2(row, D * (int)sizeof(float), f32x2{mx, den});
+            if (d == 0) publish2(row, D * (int)sizeof(float), f32x2{publishable(mx), publishable(den)});
         }
     }
     if (n_splits == 1) {
@@ -784,16 +796,9 @@ __device__ __forceinline__ void decode_item(const char* __restrict__ Q, const ch
     // workgroup, so nothing here can hang.
     __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);
     __syncthreads();
-    if (threadIdx.x == 0) s_ticket = add_to_count(counter);
+    if (threadIdx.x == 0) s_last = arrive_last(counter, (uint32_t)n_splits);
     __syncthreads();
-    const uint32_t last_ticket = kCountFrom + (uint32_t)(n_splits - 1);
-    if (const uint32_t ticket = __builtin_amdgcn_readfirstlane(s_ticket); ticket != last_ticket) {
-        if (__builtin_expect(is_count(ticket), true)) return;
-        __syncthreads();
-        if (threadIdx.x == 0) s_ticket = count_again(counter, ticket);
-        __syncthreads();
-        if (s_ticket != last_ticket) return;
-    }
+    if (!s_last) return;
 
     constexpr int kNarrow = kDecodeNarrowSplits;
     if constexpr (!kWideMerge) {
@@ -1023,8 +1028,6 @@ __device__ __forceinline__ void decode_item(const char* __restrict__ Q, const ch
         }
     }
     }
-    // leave the counter ready for the next call on this workspace
-    if (threadIdx.x == 0) __hip_atomic_store(counter, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     __syncthreads();              // the LDS tables may be reused by the caller's next item
 }
 
@@ -1035,7 +1038,7 @@ __global__ __launch_bounds__(kDecThreads) __attribute__((amdgpu_waves_per_eu(kDe
 void decode_kernel(const char* __restrict__ Q, const char* __restrict__ Kc,
                    const char* __restrict__ Vc, int Hkv, int64_t kv_len_uniform,
                    int64_t head_stride_bytes, const int32_t* __restrict__ lens,
-                   const int64_t* __restrict__ slot_off, const int32_t* __restrict__ seq_order,
+                   const int64_t* __restrict__ slot_off, const int32_t* __restrict__ seq_order, int order_from,
                    int n_splits_grid, int rows_per_wg,
                    float scale_log2e, uint32_t* __restrict__ counters,
                    float* __restrict__ partial, float* __restrict__ O, int out_bf16) {
@@ -1048,7 +1051,7 @@ void decode_kernel(const char* __restrict__ Q, const char* __restrict__ Kc,
     // scalar cache; measured, that costs nothing (99.9 against 100.5 us on the ragged
     // streaming batch launched as a grid), and short uniform launches gain about 0.1 us.
     asm volatile("" ::"s"(Q), "s"(Kc), "s"(Vc), "s"(Hkv), "s"(kv_len_uniform), "s"(head_stride_bytes), "s"(lens),
-                 "s"(slot_off), "s"(seq_order), "s"(n_splits_grid), "s"(rows_per_wg), "s"(scale_log2e),
+                 "s"(slot_off), "s"(seq_order), "s"(order_from), "s"(n_splits_grid), "s"(rows_per_wg), "s"(scale_log2e),
                  "s"(counters), "s"(partial), "s"(O), "s"(out_bf16));
     const int split = blockIdx.x;
     const int hkv = blockIdx.y;
@@ -1060,7 +1063,7 @@ void decode_kernel(const char* __restrict__ Q, const char* __restrict__ Kc,
     int b = blockIdx.z;
     if (seq_order != nullptr) {
         const int n_seq = (int)gridDim.z;
-        const int ob = seq_order[b];
+        const int ob = seq_order[b] - order_from;
         b = ob < 0 ? 0 : (ob < n_seq ? ob : n_seq - 1);
     }
     const int Hq = Hkv * G;
@@ -1110,13 +1113,13 @@ void decode_worklist_kernel(const char* __restrict__ Q, const char* __restrict__
                             const char* __restrict__ Vc, int Hkv, int n_seq, int64_t plane_stride_bytes,
                             const int32_t* __restrict__ lens, const int64_t* __restrict__ slot_off,
                             const int32_t* __restrict__ seq_order, int n_splits_grid, int pieces, RaggedRule rule, int rows_per_wg,
-                            float scale_log2e, uint32_t* __restrict__ counters, uint32_t* __restrict__ queue,
+                            float scale_log2e, uint32_t* __restrict__ counters, uint32_t* __restrict__ queue, int order_from,
                             float* __restrict__ partial, float* __restrict__ O, int out_bf16) {
     using S = Slice<E, D>;
     __shared__ uint32_t s_item;
     const int Hq = Hkv * G;
     auto sequence_at = [&](int pos) {
-        const int ob = seq_order[pos];
+        const int ob = seq_order[pos] - order_from;
         return ob < 0 ? 0 : (ob < n_seq ? ob : n_seq - 1);
     };
     struct Item { int split, hkv, pos; };
@@ -1215,7 +1218,7 @@ l2kv_status launch_decode(const void* Q, const void* Kc, const void* Vc, int32_t
                                dim3(kDecThreads), 0, stream, static_cast<const char*>(Q),
                                static_cast<const char*>(Kc), static_cast<const char*>(Vc), (int)Hkv, (int)B,
                                kv_head_stride * (int64_t)E::kBytes, lens, slot_off, seq_order,
-                               (int)plan.n_splits, (int)plan.pieces, plan.rule, (int)plan.rows_per_wg, scale_log2e, counters, queue, partial, O, (int)plan.out_bf16);
+                               (int)plan.n_splits, (int)plan.pieces, plan.rule, (int)plan.rows_per_wg, scale_log2e, counters, queue, (int)plan.order_from, partial, O, (int)plan.out_bf16);
             return launch_status();
         }
     }
@@ -1224,7 +1227,7 @@ l2kv_status launch_decode(const void* Q, const void* Kc, const void* Vc, int32_t
     hipLaunchKernelGGL(kernel, grid, dim3(kDecThreads), 0, stream,
                        static_cast<const char*>(Q), static_cast<const char*>(Kc),
                        static_cast<const char*>(Vc), (int)Hkv, kv_len,
-                       kv_head_stride * (int64_t)E::kBytes, lens, slot_off, seq_order, (int)plan.n_splits,
+                       kv_head_stride * (int64_t)E::kBytes, lens, slot_off, seq_order, (int)plan.order_from, (int)plan.n_splits,
                        (int)plan.rows_per_wg, scale_log2e, counters, partial, O, (int)plan.out_bf16);
     return launch_status();
 }

@@ -71,6 +71,7 @@ struct DecodePlan {
     int32_t worklist_wgs = 0;  // > 0: ordered ragged batch, this many workgroups draw items from a device-side list
     int32_t pieces = 1;        // work list: pieces of the longest sequence, as far as the host knows its length
     RaggedRule rule = {};      // work list: decides them on the device (most > 0)
+    int32_t order_from = 0;    // what the entries of the order count from
     int32_t out_bf16 = 0;      // 1: O is written as bf16 (16-bit elements behind the float pointer), 0: fp32
 };
 constexpr int kDecodeMaxSplits = 256;
@@ -84,7 +85,9 @@ inline size_t decode_counter_bytes(int32_t B, int32_t Hkv) {
     const size_t raw = (static_cast<size_t>(B) * static_cast<size_t>(Hkv) + 2) * sizeof(uint32_t);
     return (raw + 255) / 256 * 256;
 }
-// What a counter can count to (decode_kernels.hpp): the items of a work list.
+// An order that a call works out for itself lies in the workspace, where its numbers must not be taken for counts of workgroups.
+constexpr int32_t kOwnOrderFrom = kDecodeMaxSplits;
+// What the counter of a work list can count to (decode_kernels.hpp).
 constexpr uint32_t kDecodeMostCounted = 0x3ffffe;
 // One split partial = D accumulator floats, the running maximum, the denominator and two floats
 // of padding, so that every partial row starts on a 16-byte boundary and belongs to one workgroup.
@@ -128,7 +131,8 @@ l2kv_status stream_append_dispatch(const void* Knew, const void* Vnew, l2kv_dtyp
                                    const int64_t* slot_off, int64_t total_slots, const int32_t* lens_in,
                                    int32_t* lens_out, void* Kc, void* Vc, float* norms_c, int32_t* pos_c,
                                    hipStream_t stream);
-l2kv_status length_order_dispatch(const int32_t* lens, int32_t n_seq, int32_t* order, hipStream_t stream);
+// Entries count from `from`.
+l2kv_status length_order_dispatch(const int32_t* lens, int32_t n_seq, int32_t from, int32_t* order, hipStream_t stream);
 l2kv_status stream_evict_dispatch(l2kv_dtype dt, int32_t n_planes, int32_t n_seq, int32_t D,
                                   const int64_t* slot_off, int64_t total_slots, const int32_t* lens_in,
                                   const int32_t* budgets, int32_t* lens_out, void* Kc, void* Vc,

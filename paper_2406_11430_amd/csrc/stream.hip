@@ -461,7 +461,7 @@ l2kv_status stream_evict_dispatch(l2kv_dtype dt, int32_t n_planes, int32_t n_seq
 constexpr int kOrderLdsSeqs = 8192;    // batches up to this size are ranked out of LDS
 
 __global__ __launch_bounds__(1024)
-void length_order_kernel(const int32_t* __restrict__ lens, int32_t n_seq, int32_t* __restrict__ order) {
+void length_order_kernel(const int32_t* __restrict__ lens, int32_t n_seq, int32_t from, int32_t* __restrict__ order) {
     __shared__ int32_t s_len[kOrderLdsSeqs];
     const bool in_lds = n_seq <= kOrderLdsSeqs;
     if (in_lds) {
@@ -482,14 +482,14 @@ void length_order_kernel(const int32_t* __restrict__ lens, int32_t n_seq, int32_
                 rank += (other > mine || (other == mine && t < s)) ? 1 : 0;
             }
         }
-        order[rank] = s;
+        order[rank] = from + s;
     }
 }
 
-l2kv_status length_order_dispatch(const int32_t* lens, int32_t n_seq, int32_t* order, hipStream_t stream) {
+l2kv_status length_order_dispatch(const int32_t* lens, int32_t n_seq, int32_t from, int32_t* order, hipStream_t stream) {
     // small batches need only as many lanes as sequences (fewer waves to start and retire)
     const unsigned threads = n_seq <= 64 ? 64u : (n_seq <= 256 ? 256u : 1024u);
-    hipLaunchKernelGGL(length_order_kernel, dim3(1), dim3(threads), 0, stream, lens, n_seq, order);
+    hipLaunchKernelGGL(length_order_kernel, dim3(1), dim3(threads), 0, stream, lens, n_seq, from, order);
     return launch_status();
 }
 

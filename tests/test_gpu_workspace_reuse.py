@@ -82,3 +82,51 @@ def test_after_values_that_are_not_numbers():
         binding.l2kv_decode_attn_static(q, k, v, static)
         assert not want.isnan().any() and torch.equal(here, want) and torch.equal(static, want)
         assert not shared.view(torch.int32)[:heads].any()
+
+
+def test_after_values_whose_bits_are_small_numbers():
+    """Values of a few 2^-149, whose partial sums have the bits of a count of workgroups: those are not left in the workspace, and larger
+    ones are what they were."""
+    g = torch.Generator(device="cuda:0").manual_seed(2)
+    n, G = 9000, 4
+    Q, K = (torch.randn(shape, generator=g, device="cuda:0") for shape in ((1, G, 128), (1, 1, n, 128)))
+    V = (torch.randint(0, 3, (1, 1, n, 128), generator=g, device="cuda:0", dtype=torch.int32) * (torch.rand((1, 1, n, 1), generator=g, device="cuda:0") < 0.02)).to(torch.int32)
+    V[..., 64:] += 1 << 23                                               # normal numbers
+    V = V.view(torch.float32)
+    shared = workspace(max(l2kv.l2kv_decode_workspace_bytes(*x, 128) for x in ((1, G, n), (1, 340 * 4, 1536))))
+    O = torch.empty((1, G, 128), device="cuda:0")
+    l2kv.l2kv_decode_attn(Q, K, V, O, shared)
+    binding.l2kv_decode_attn_static(Q, K, V, O)
+    assert torch.all((O[..., 64:].double() / 2.0 ** -126 - 1).abs() < 1e-3) and torch.all(O[..., :64].abs() <= 2.0 ** -141)
+    for heads, G2, rows in ((70, 4, 900), (128, 1, 2048), (340, 4, 1536)):
+        l2kv.l2kv_decode_attn(Q, K, V, O, shared)
+        binding.l2kv_decode_attn_static(Q, K, V, O)
+        words = shared.view(torch.int32)
+        assert (words[64:heads + 64] >= 1 << 22).any() and not ((words > 0) & (words < 256)).any()
+        q, k, v = operands(heads, G2, rows)
+        want, here, static = (torch.full((1, heads * G2, 128), float("nan"), device="cuda:0") for _ in range(3))
+        l2kv.l2kv_decode_attn(q, k, v, want, workspace(l2kv.l2kv_decode_workspace_bytes(1, heads * G2, rows, 128)))
+        l2kv.l2kv_decode_attn(q, k, v, here, shared)
+        binding.l2kv_decode_attn_static(q, k, v, static)
+        assert not want.isnan().any() and torch.equal(here, want) and torch.equal(static, want)
+
+
+def test_after_an_order_of_its_own():
+    """The order that a ragged call works out for itself stays in the workspace: its numbers are no counts."""
+    n_seq, Hkv, G, rows = 300, 1, 1, 2048
+    ws = workspace(l2kv.l2kv_decode_ragged_workspace_bytes(n_seq, Hkv * G, rows, 128))
+    g = torch.Generator(device="cuda:0").manual_seed(3)
+    lens = torch.randint(1, 40, (n_seq,), generator=g, device="cuda:0", dtype=torch.int32)
+    slots = torch.zeros(n_seq + 1, dtype=torch.int64, device="cuda:0")
+    slots[1:] = torch.cumsum(lens, 0)
+    total = max(rows, int(slots[-1]))
+    Q = torch.randn((n_seq, 1, 128), generator=g, device="cuda:0").to(torch.bfloat16)
+    K, V = (torch.randn((Hkv, total, 128), generator=g, device="cuda:0").to(torch.bfloat16) for _ in range(2))
+    order = torch.empty(n_seq, dtype=torch.int32, device="cuda:0")
+    l2kv.l2kv_length_order(lens, order)
+    want, here = (torch.full((n_seq, 1, 128), float("nan"), device="cuda:0") for _ in range(2))
+    l2kv.l2kv_decode_attn_ragged(Q, K, V, lens, slots, rows, want, ws, seq_order=order)
+    l2kv.l2kv_decode_attn_ragged(Q, K, V, lens, slots, rows, here, ws)
+    assert not want.isnan().any() and torch.equal(here, want) and torch.equal(torch.sort(order).values, torch.arange(n_seq, dtype=torch.int32, device="cuda:0"))
+    words = ws.view(torch.int32)
+    assert not ((words > 0) & (words < 256)).any()
