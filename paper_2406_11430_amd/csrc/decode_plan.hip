@@ -99,9 +99,9 @@ DecodePlan decode_plan(int32_t B, int32_t Hkv, int32_t group, int64_t kv_len, in
         // results takes longer than the tiles that the other workgroups would have read.  us, split as above / in 1: bf16 rows of 128, 32
         // heads of 83 rows 4.6 / 3.2, 8 of 175 4.3 / 3.4; of 64, 128 of 88 with 4 query heads 6.3 / 4.4; fp32 rows of 64, 128 of 184 with 3
         // 6.7 / 5.7; 4 of 256, 4.2 / 3.3.  Not for more tiles or query heads: bf16 rows of 128, 8 of 189 with 4 5.9 / 6.3; of 256, 8 of 128
-        // with 4 7.1 / 7.3.  That is with rows in the caches, as after a compression, where three and four tiles gain 2 to 37 %.  From memory,
-        // where every second tile is one more round trip, three whole tiles gain 3 to 18 % for up to 192 heads, four from 9 % less (2 heads) to
-        // 10 % more, and a last tile that is not whole costs 5 %.
+        // with 4 7.1 / 7.3.  That is with rows in the caches, as after a compression, where three tiles gain 7 to 29 % and four 1 to 17 % in the mean
+        // of 1 to 64 heads (64 heads of 252 rows 0.94 to 0.96).  From memory, where every second tile is one more round trip, three gain 1 to 9 %
+        // and four lose 1 to 3 %; the worst are few heads whose last tile is not whole (4 of 188 rows 0.92 to 0.97, of 252 0.87 to 0.89).
         const int64_t tile_rows = row_bytes <= 128 ? 2 * kDecodeRowTile : kDecodeRowTile;      // of the four waves
         const int64_t tiles = (kv_len + tile_rows - 1) / tile_rows;
         if (tiles <= 2 ? !long_rows || group <= 3 : !long_rows && (tiles == 3 ? group <= 3 : tiles == 4 && group <= 2)) want = 1;
